@@ -1,19 +1,38 @@
 // Half-edge construction on the device (the structure of Section 4.1-4.2,
 // built on the GPU instead of the host).
 //
-//   k_check_xy   coordinates in [0, 2^30]
-//   k_orient     index check, exact int64 orientation test, counter-clockwise
-//                corner order, out-degree count per vertex
-//   k_scan_excl  exclusive scan of the out-degrees (decoupled look-back)
-//   k_bucket     half-edges grouped by origin vertex (CSR), each with its
-//                target vertex beside it
-//   k_match      twin(h) for h = u->v: the half-edge v->u in v's bucket; two
-//                v->u, or (for an h with none) a second u->v in u's
-//                bucket, is non-manifold
+//   k_orient  coordinates in [0, 2^30]; index check, exact int64 orientation
+//             test, counter-clockwise corner order; triangles listed by the
+//             vertex groups that their edges belong to
+//   k_match   twins, one workgroup per group, in LDS
 //
-// Errors are reduced with a 64-bit atomicMin over (rank << 8 | code) so the
-// reported code is deterministic: coordinate range first, then the lowest
-// bad triangle, then the lowest non-manifold half-edge.
+// Both half-edges of an edge {u, v} belong to the group of one of its ends
+// (edge_owner): kBuildGroup consecutive vertices.  So each group's half-edges can
+// be paired on their own, in a hash table in LDS keyed by the edge, and three
+// half-edges of one edge, or two in the same direction, are seen where they
+// meet: non-manifold.
+//
+// A group's list holds triangle ids, one per triangle with an edge in the
+// group (about 1.3 per triangle in an ordered numbering), whose corners are
+// read again from org.  Lists have room for up to kBuildGroupCap triangles,
+// where a planar mesh has at most about 768 to a group.  A group with more, or with
+// more edges than the LDS table holds (a vertex of high degree), is left out
+// and counted, and the host then queues, for those groups alone:
+//
+//   k_part_alloc, k_scatter  their lists again, at full length
+//   k_match_class            their edges in classes by hash, one workgroup
+//                            per class
+//
+// Grouping by single vertices instead (a counting sort by origin, then a
+// search of the target's bucket) took an atomic per vertex and tile in two
+// passes and 8-byte records: 2.92 ms for the 33.5M-triangle grid against the
+// figures at each kernel.
+//
+// Errors are reduced with a 64-bit atomicMax over ~(rank << 8 | code), so the
+// reported code is deterministic and 0 means none: coordinate range first,
+// then the lowest bad triangle, then the lowest non-manifold half-edge seen.
+// A bad triangle joins no group, so the later kernels only ever see valid ones
+// and the host needs one check, at the end.
 #include "gp_internal.h"
 
 namespace gp {
@@ -21,279 +40,455 @@ namespace gp {
 namespace {
 
 constexpr int kCoordMax = 1 << 30;
-constexpr int kScanBlock = 256;
-constexpr int kScanItems = 8;
-constexpr uint64_t kScanAgg = 1ull << 62;
-constexpr uint64_t kScanInc = 2ull << 62;
-// k_orient and k_bucket work in tiles of 256 threads x kTileItems items and
-// count per vertex in an LDS histogram when the tile's vertex ids span at
-// most kHistBins (meshes numbered row by row or along a curve do): one
-// global atomic per distinct vertex of the tile instead of one per corner
+// k_orient works in tiles of 256 threads x kTileItems triangles and counts per
+// group in an LDS window of kBins groups around the tile (meshes numbered row
+// by row or along a curve stay in it): one global atomic per group the tile
+// touches.  Groups outside the window cost one per wave, or per triangle where
+// no two of a wave share one.
 constexpr int kTileItems = 4;
-constexpr int kHistBins = 8192;
+constexpr int kTileTri = 256 * kTileItems;
+constexpr int kBins = 512;
+constexpr int kCopyItems = 8;        // vertices per thread of k_orient's coordinate blocks
+constexpr int kShift = 7;
+static_assert(1 << kShift == kBuildGroup, "groups by shift");
+constexpr int kGroupCap = kBuildGroupCap;
+// slots of the LDS edge table: an ordered or random planar mesh has about 384
+// edges to a group of 128 vertices
+constexpr int kSlots = 1024;
+constexpr int kClassSplit = 128;     // triangles per class of a large group
+constexpr int kClassBlocks = 2048;
 
-// [lo, hi] of the values v over the block (hi < lo when no thread has one);
-// every thread calls it, s_lohi is shared
-__device__ __forceinline__ void block_range(int vlo, int vhi, int *s_lohi, int &lo, int &hi) {
-    if (threadIdx.x == 0) {
-        s_lohi[0] = 0x7fffffff;
-        s_lohi[1] = -1;
+// three ints at 4-byte alignment: loads of 12-byte records; coordinates at
+// 4-byte alignment (the caller's array)
+typedef int v3i_a4 __attribute__((ext_vector_type(3), aligned(4)));
+typedef int v2i_a4 __attribute__((ext_vector_type(2), aligned(4)));
+
+__device__ __forceinline__ void report(unsigned long long *err, unsigned long long rank, int code) {
+    atomicMax(err, ~((rank << 8) | (unsigned long long)(-code)));
+}
+
+// The end of edge {a, b} whose group pairs it.  The lower end when the two are
+// near, as along the rows or the curve of an ordered numbering: then nearly all
+// half-edges of a run of triangles fall into the same few groups.  Far ends
+// (most edges of a random numbering) take turns by parity, since the lower end
+// would give low vertices twice their share.
+__device__ __forceinline__ int edge_owner(int a, int b, int near) {
+    const int lo = min(a, b), hi = max(a, b);
+    return (hi - lo < near || ((lo ^ hi) & 1)) ? lo : hi;
+}
+
+// The groups of a triangle's three edges, each once (-1: none, or there
+// already).
+__device__ __forceinline__ void triangle_groups(const BuildBuffers &b, bool ok, v3i_a4 c, int g[3]) {
+    g[0] = edge_owner(c.x, c.y, b.near) >> kShift;
+    g[1] = edge_owner(c.y, c.z, b.near) >> kShift;
+    g[2] = edge_owner(c.z, c.x, b.near) >> kShift;
+    if (g[2] == g[0] || g[2] == g[1]) g[2] = -1;
+    if (g[1] == g[0]) g[1] = -1;
+    if (!ok) g[0] = g[1] = g[2] = -1;
+}
+
+// Adds the lanes of `same` (this lane's group's, found by a ballot) to counter
+// *c with one atomic; returns the counter's value at this lane's place.
+__device__ __forceinline__ int add_together(int *c, unsigned long long same, int lane) {
+    const int leader = __ffsll((long long)same) - 1;
+    int b = 0;
+    if (lane == leader) b = atomicAdd(c, __popcll(same));
+    return __builtin_amdgcn_readlane(b, leader) + __popcll(same & ((1ull << lane) - 1ull));
+}
+
+// Adds this wave's triangles to their groups' counters: lane's group g (g < 0:
+// none), counted in the LDS window s_bin of kBins groups from w0 on, or in
+// count[] (global) outside it.  Lanes of one group add together (a wave of an
+// ordered mesh has one to three groups; 64 atomics on one word would run one
+// by one), for four groups at most, and the rest alone: a random numbering has
+// hardly two lanes of one group.  Returns the counter's value at the lane's
+// place.
+__device__ __forceinline__ int bin_add(int *s_bin, int32_t *count, int g, int w0) {
+    const int lane = __lane_id();
+    const bool in = g >= 0 && (unsigned)(g - w0) < (unsigned)kBins;
+    unsigned long long todo = __ballot(in);
+    const unsigned long long out = __ballot(g >= 0 && !in);
+    int place = 0;
+#pragma unroll 1
+    for (int k = 0; k < 4 && todo; k++) {
+        const int gl = __builtin_amdgcn_readlane(g, __ffsll((long long)todo) - 1);
+        const unsigned long long same = __ballot(g == gl);
+        const int at = add_together(&s_bin[gl - w0], same, lane);
+        if ((same >> lane) & 1) place = at;
+        todo &= ~same;
     }
-    __syncthreads();
-    if (vhi >= vlo) {
-        atomicMin(&s_lohi[0], vlo);
-        atomicMax(&s_lohi[1], vhi);
+    if ((todo >> lane) & 1) place = atomicAdd(&s_bin[g - w0], 1);
+    if (out) {   // (uniform)
+        todo = out;
+#pragma unroll 1
+        for (int k = 0; k < 4 && todo; k++) {
+            const int gl = __builtin_amdgcn_readlane(g, __ffsll((long long)todo) - 1);
+            const unsigned long long same = __ballot(g == gl);
+            if (__popcll(same) < 4) break;
+            const int at = add_together(&count[gl], same, lane);
+            if ((same >> lane) & 1) place = at;
+            todo &= ~same;
+        }
+        if ((todo >> lane) & 1) place = atomicAdd(&count[g], 1);
     }
-    __syncthreads();
-    lo = s_lohi[0];
-    hi = s_lohi[1];
+    return place;
 }
 
-__device__ __forceinline__ unsigned long long err_key(unsigned long long rank, int code) {
-    return (rank << 8) | (unsigned long long)(-code);
+// Workgroups go to the 8 XCDs round-robin; this gives each XCD one contiguous
+// run of tiles, whose neighbours' coordinates then share its L2.
+__device__ __forceinline__ int xcd_run(int b, int G) {
+    const int q = G >> 3, r = G & 7, x = b & 7;
+    return x * q + (x < r ? x : r) + (b >> 3);
 }
 
-__device__ __forceinline__ int he_next_b(int h) {
-    int t = h / 3;
-    return (h - 3 * t == 2) ? h - 2 : h + 1;
+// First group of a tile's window: kBins groups around the median of the first
+// corners of three of its cnt triangles (one alone may straddle a jump of the
+// curve, which would leave the whole tile outside).
+__device__ __forceinline__ int window_start(const BuildBuffers &b, int base, int cnt) {
+    const int x = b.tri[3 * (size_t)base], y = b.tri[3 * (size_t)(base + cnt / 2)],
+              z = b.tri[3 * (size_t)(base + cnt - 1)];
+    return max(0, (max(min(x, y), min(max(x, y), z)) >> kShift) - kBins / 2);
 }
 
-__global__ void k_check_xy(const int2 *__restrict__ xy, int nv, unsigned long long *err) {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
-        int2 p = xy[v];
-        if (p.x < 0 || p.x > kCoordMax || p.y < 0 || p.y > kCoordMax) atomicMin(err, err_key(0, -2));
-    }
-}
-
-__global__ void __launch_bounds__(256) k_orient(const int2 *__restrict__ xy, const int32_t *__restrict__ tri,
-                                                 int nv, int nt, int32_t *__restrict__ org,
-                                                 int32_t *__restrict__ deg, unsigned long long *err,
-                                                 int32_t *nflipped) {
-    __shared__ int s_hist[kHistBins];
-    __shared__ int s_lohi[2];
-    const int TB = 256 * kTileItems;
-    for (int base = blockIdx.x * TB; base < nt; base += gridDim.x * TB) {   // block-uniform
-        int cv[kTileItems][3];
-        bool ok[kTileItems];
-        int vlo = 0x7fffffff, vhi = -1, nflip = 0;
+// Blocks [0, tiles): a tile of triangles each.  The others: the coordinates,
+// checked, and copied to the mesh when the caller's array is on the device.
+__global__ void __launch_bounds__(256) k_orient(BuildBuffers b, int tiles) {
+    __shared__ int s_bin[kBins];
+    __shared__ int s_flip;
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= tiles) {   // (uniform)
+        const long long v0 = (long long)(blockIdx.x - tiles) * (256 * kCopyItems) + tid;
+        bool bad = false;
 #pragma unroll
-        for (int j = 0; j < kTileItems; j++) {
-            const int t = base + j * 256 + threadIdx.x;
+        for (int j = 0; j < kCopyItems; j++) {
+            const long long v = v0 + j * 256;
+            if (v >= b.nv) continue;
+            const v2i_a4 p = reinterpret_cast<const v2i_a4 *>(b.xy_in)[v];
+            bad |= p.x < 0 || p.x > kCoordMax || p.y < 0 || p.y > kCoordMax;
+            if (b.xy_out) b.xy_out[v] = make_int2(p.x, p.y);
+        }
+        if (bad) report(b.err, 0, -2);
+        return;
+    }
+    const int base = xcd_run(blockIdx.x, tiles) * kTileTri;
+    const int cnt = min(kTileTri, b.nt - base);
+    const int w0 = window_start(b, base, cnt);   // (uniform; any value will do)
+    for (int k = tid; k < kBins; k += 256) s_bin[k] = 0;
+    if (tid == 0) s_flip = 0;
+    // a wave takes 256 triangles in a row; all corners, then all coordinates
+    // in flight together
+    const int lt0 = (tid & ~63) * kTileItems + (tid & 63);
+    v3i_a4 c[kTileItems];
+    bool ok[kTileItems];
+#pragma unroll
+    for (int j = 0; j < kTileItems; j++) {
+        const int lt = lt0 + 64 * j;
+        c[j] = *reinterpret_cast<const v3i_a4 *>(b.tri + 3 * (size_t)(base + (lt < cnt ? lt : 0)));
+        ok[j] = (unsigned)c[j].x < (unsigned)b.nv && (unsigned)c[j].y < (unsigned)b.nv &&
+                (unsigned)c[j].z < (unsigned)b.nv;
+    }
+    v2i_a4 p[kTileItems][3];
+#pragma unroll
+    for (int j = 0; j < kTileItems; j++) {
+        const v2i_a4 *xy = reinterpret_cast<const v2i_a4 *>(b.xy_in);
+        if (b.nv > 0) {   // (uniform)
+            p[j][0] = xy[ok[j] ? c[j].x : 0];
+            p[j][1] = xy[ok[j] ? c[j].y : 0];
+            p[j][2] = xy[ok[j] ? c[j].z : 0];
+        }
+    }
+    int nflip = 0;
+#pragma unroll
+    for (int j = 0; j < kTileItems; j++) {
+        const int lt = lt0 + 64 * j;
+        if (lt >= cnt) {
             ok[j] = false;
-            bool flip = false;
-            if (t < nt) {
-                int a = tri[3 * t], b = tri[3 * t + 1], c = tri[3 * t + 2];
-                if ((unsigned)a >= (unsigned)nv || (unsigned)b >= (unsigned)nv || (unsigned)c >= (unsigned)nv) {
-                    atomicMin(err, err_key(1ull + t, -1));
-                } else {
-                    int2 pa = xy[a], pb = xy[b], pc = xy[c];
-                    long long o = ((long long)pb.x - pa.x) * ((long long)pc.y - pa.y) -
-                                  ((long long)pb.y - pa.y) * ((long long)pc.x - pa.x);
-                    if (o == 0) {
-                        atomicMin(err, err_key(1ull + t, -3));
-                    } else {
-                        if (o < 0) {
-                            int s = b;
-                            b = c;
-                            c = s;
-                            flip = true;
-                        }
-                        org[3 * t] = a;
-                        org[3 * t + 1] = b;
-                        org[3 * t + 2] = c;
-                        cv[j][0] = a;
-                        cv[j][1] = b;
-                        cv[j][2] = c;
-                        ok[j] = true;
-                        vlo = min(vlo, min(a, min(b, c)));
-                        vhi = max(vhi, max(a, max(b, c)));
-                    }
-                }
-            }
-            const unsigned long long m = __ballot(flip);
-            nflip += __popcll(m);
+            continue;
         }
-        if (nflip && __lane_id() == 0) atomicAdd(nflipped, nflip);
-        int lo, hi;
-        block_range(vlo, vhi, s_lohi, lo, hi);
-        if (hi >= lo && hi - lo < kHistBins) {   // block-uniform
-            const int range = hi - lo + 1;
-            for (int k = threadIdx.x; k < range; k += 256) s_hist[k] = 0;
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < kTileItems; j++)
-                if (ok[j])
-#pragma unroll
-                    for (int i = 0; i < 3; i++) atomicAdd(&s_hist[cv[j][i] - lo], 1);
-            __syncthreads();
-            for (int k = threadIdx.x; k < range; k += 256) {
-                const int n = s_hist[k];
-                if (n) atomicAdd(&deg[lo + k], n);
-            }
+        const int t = base + lt;
+        if (!ok[j]) {
+            report(b.err, 1ull + t, -1);
         } else {
-#pragma unroll
-            for (int j = 0; j < kTileItems; j++)
-                if (ok[j])
-#pragma unroll
-                    for (int i = 0; i < 3; i++) atomicAdd(&deg[cv[j][i]], 1);
-        }
-        __syncthreads();   // the histogram and range are reused by the next tile
-    }
-}
-
-// Exclusive scan of in[0, n) into out[0, n], out[n] = total.  One pass with
-// dynamically numbered tiles and decoupled look-back.
-__global__ void __launch_bounds__(kScanBlock) k_scan_excl(const int32_t *__restrict__ in, int32_t *out,
-                                                           int n, uint64_t *status, int32_t *tile_ctr,
-                                                           unsigned long long *err) {
-    __shared__ int s_tile;
-    __shared__ int s_wave[kScanBlock / 64];
-    __shared__ int s_prefix;
-    if (threadIdx.x == 0) s_tile = atomicAdd(tile_ctr, 1);
-    __syncthreads();
-    const int tile = s_tile;
-    const int i0 = tile * kScanBlock * kScanItems + threadIdx.x * kScanItems;
-    int v[kScanItems];
-    int sum = 0;
-#pragma unroll
-    for (int j = 0; j < kScanItems; j++) {
-        v[j] = (i0 + j < n) ? in[i0 + j] : 0;
-        sum += v[j];
-    }
-    // block exclusive scan of the per-thread sums
-    int lane = __lane_id(), w = threadIdx.x / 64;
-    int x = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int y = __shfl_up(x, d);
-        if (lane >= d) x += y;
-    }
-    if (lane == 63) s_wave[w] = x;
-    __syncthreads();
-    int wave_off = 0, total = 0;
-    for (int k = 0; k < kScanBlock / 64; k++) {
-        if (k < w) wave_off += s_wave[k];
-        total += s_wave[k];
-    }
-    int excl = wave_off + x - sum;
-    if (threadIdx.x == 0) {
-        int prefix = 0;
-        if (tile == 0) {
-            __hip_atomic_store(&status[0], kScanInc | (uint32_t)total, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            __hip_atomic_store(&status[tile], kScanAgg | (uint32_t)total, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            int k = tile - 1, spins = 0;
-            while (k >= 0) {
-                uint64_t st = __hip_atomic_load(&status[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                uint64_t flag = st & (3ull << 62);
-                if (flag == 0ull) {
-                    if (++spins > (1 << 26)) {
-                        atomicMin(err, err_key(0, -10));
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                    continue;
-                }
-                prefix += (int)(uint32_t)st;
-                if (flag == kScanInc) break;
-                --k;
+            // differences of valid coordinates fit 32 bits; others have
+            // failed the build already (code -2 ranks first)
+            const v2i_a4 pa = p[j][0], pb = p[j][1], pc = p[j][2];
+            const long long o = (long long)(int)((unsigned)pb.x - (unsigned)pa.x) * (int)((unsigned)pc.y - (unsigned)pa.y) -
+                                (long long)(int)((unsigned)pb.y - (unsigned)pa.y) * (int)((unsigned)pc.x - (unsigned)pa.x);
+            if (o == 0) {
+                report(b.err, 1ull + t, -3);
+                ok[j] = false;
+            } else if (o < 0) {
+                const int s = c[j].y;
+                c[j].y = c[j].z;
+                c[j].z = s;
+                nflip++;
             }
-            __hip_atomic_store(&status[tile], kScanInc | (uint32_t)(prefix + total), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
         }
-        s_prefix = prefix;
+        if (!ok[j]) c[j].x = -1;   // joins no group
+        *reinterpret_cast<v3i_a4 *>(b.org + 3 * (size_t)t) = c[j];
     }
     __syncthreads();
-    int run = s_prefix + excl;
+    if (nflip) atomicAdd(&s_flip, nflip);
+    int g[kTileItems][3], place[kTileItems][3];
 #pragma unroll
-    for (int j = 0; j < kScanItems; j++) {
-        if (i0 + j < n) out[i0 + j] = run;
-        run += v[j];
+    for (int j = 0; j < kTileItems; j++) {
+        triangle_groups(b, ok[j], c[j], g[j]);
+#pragma unroll
+        for (int i = 0; i < 3; i++) place[j][i] = bin_add(s_bin, b.count, g[j][i], w0);
     }
-    const int last_tile = (n + kScanBlock * kScanItems - 1) / (kScanBlock * kScanItems) - 1;
-    if (tile == (last_tile < 0 ? 0 : last_tile) && threadIdx.x == kScanBlock - 1) out[n] = run;
+    __syncthreads();
+    for (int k = tid; k < kBins; k += 256) {
+        const int n = s_bin[k];
+        if (n) s_bin[k] = atomicAdd(&b.count[w0 + k], n);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kTileItems; j++) {
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            if (g[j][i] < 0) continue;
+            const int w = g[j][i] - w0, at = place[j][i] + ((unsigned)w < (unsigned)kBins ? s_bin[w] : 0);
+            if (at < b.cap) b.list[(size_t)g[j][i] * b.cap + at] = base + lt0 + 64 * j;
+        }
+    }
+    if (tid == 0 && s_flip) atomicAdd(b.nflipped, s_flip);
 }
 
-// Slots within a vertex's bucket come in any order: the tile ranks its
-// half-edges per vertex in LDS, reserves each vertex's run with one global
-// atomic, and places them (the match does not depend on the order).
-__global__ void __launch_bounds__(256) k_bucket(const int32_t *__restrict__ org, int nh,
-                                                const int32_t *__restrict__ vstart, int32_t *fill, int2 *bucket) {
-    __shared__ int s_hist[kHistBins];
-    __shared__ int s_lohi[2];
-    const int TB = 256 * kTileItems;
-    for (int base = blockIdx.x * TB; base < nh; base += gridDim.x * TB) {   // block-uniform
-        int v[kTileItems], w[kTileItems];
-        int vlo = 0x7fffffff, vhi = -1;
-#pragma unroll
-        for (int j = 0; j < kTileItems; j++) {
-            const int h = base + j * 256 + threadIdx.x;
-            v[j] = -1;
-            if (h < nh) {
-                v[j] = org[h];
-                w[j] = org[he_next_b(h)];
-                vlo = min(vlo, v[j]);
-                vhi = max(vhi, v[j]);
-            }
+// The LDS edge table.  A slot is 0, or an edge with one or two half-edges:
+//   bits 0-30   the edge's other end
+//   bit 31      used
+//   bits 32-38  the owner's index in its group
+//   bit 39      the first half-edge leaves the owner
+//   bits 40-51  the first half-edge's id in the workgroup
+//   bits 52-63  the second's id + 1, 0 before it comes
+// Ids are below 3 kGroupCap = 3072.
+struct GroupEdge {
+    uint32_t other, own, out;   // other end; owner's index in the group; 1: leaves the owner
+};
+constexpr uint32_t kUsed = 1u << 31;
+static_assert(3 * kGroupCap < 4095, "ids of 12 bits");
+
+// Edge i of triangle corners c, as its group sees it; false when it belongs to
+// another group.
+__device__ __forceinline__ bool group_edge(const BuildBuffers &b, v3i_a4 c, int i, int group, GroupEdge &e) {
+    const int u = i == 0 ? c.x : (i == 1 ? c.y : c.z), v = i == 0 ? c.y : (i == 1 ? c.z : c.x);
+    const int o = edge_owner(u, v, b.near);
+    e.other = (uint32_t)(o == u ? v : u);
+    e.own = (uint32_t)o - ((uint32_t)group << kShift);
+    e.out = o == u;
+    return (o >> kShift) == group;
+}
+
+__device__ __forceinline__ uint32_t edge_hash(const GroupEdge &e) {
+    return e.other * 0x9E3779B1u + e.own * 0x85EBCA6Bu;
+}
+
+// Puts half-edge id into the table; returns its edge's slot, or -1 when the
+// table is full.  dup: the edge has another half-edge in this direction, or
+// two already.
+__device__ __forceinline__ int edge_insert(unsigned long long *table, const GroupEdge &e, int id, bool &dup) {
+    uint32_t q = edge_hash(e) >> (32 - 10);
+    static_assert(kSlots == 1 << 10, "slots from the hash's top bits");
+    const uint32_t key = e.other | kUsed;
+    const unsigned long long mine = (unsigned long long)(e.own | (e.out << 7) | ((uint32_t)id << 8)) << 32 | key;
+    for (int k = 0; k < kSlots; k++) {
+        const unsigned long long was = atomicCAS(&table[q], 0ull, mine);
+        if (was == 0ull) return (int)q;
+        const uint32_t hi = (uint32_t)(was >> 32);
+        if ((uint32_t)was == key && ((hi ^ e.own) & 127u) == 0) {
+            const unsigned long long old = atomicOr(&table[q], (unsigned long long)(id + 1) << 52);
+            dup |= (old >> 52) != 0 || ((hi >> 7) & 1u) == e.out;
+            return (int)q;
         }
-        int lo, hi;
-        block_range(vlo, vhi, s_lohi, lo, hi);
-        if (hi >= lo && hi - lo < kHistBins) {   // block-uniform
-            const int range = hi - lo + 1;
-            for (int k = threadIdx.x; k < range; k += 256) s_hist[k] = 0;
-            __syncthreads();
-            int rank[kTileItems];
-#pragma unroll
-            for (int j = 0; j < kTileItems; j++) rank[j] = v[j] >= 0 ? atomicAdd(&s_hist[v[j] - lo], 1) : 0;
-            __syncthreads();
-            for (int k = threadIdx.x; k < range; k += 256) {
-                const int n = s_hist[k];
-                if (n) s_hist[k] = atomicAdd(&fill[lo + k], n);   // the run's first slot in the bucket
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < kTileItems; j++)
-                if (v[j] >= 0)
-                    bucket[vstart[v[j]] + s_hist[v[j] - lo] + rank[j]] = make_int2(base + j * 256 + threadIdx.x, w[j]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < kTileItems; j++)
-                if (v[j] >= 0)
-                    bucket[vstart[v[j]] + atomicAdd(&fill[v[j]], 1)] = make_int2(base + j * 256 + threadIdx.x, w[j]);
+        q = (q + 1) & (kSlots - 1);
+    }
+    return -1;
+}
+
+// The id of the other half-edge in slot s, or -1 on the boundary.
+__device__ __forceinline__ int edge_mate(unsigned long long s, int id) {
+    const int first = (int)(s >> 40) & 0xfff, second = (int)(s >> 52) - 1;
+    return id == first ? second : first;
+}
+
+__global__ void __launch_bounds__(256) k_match(BuildBuffers b) {
+    __shared__ unsigned long long s_table[kSlots];
+    __shared__ int s_tri[kGroupCap];
+    constexpr int kIt = kGroupCap / 256;
+    const int tid = threadIdx.x, g = xcd_run(blockIdx.x, b.nparts);
+    const int n = b.count[g];
+    if (n == 0) return;   // (uniform)
+    if (n > b.cap) {
+        if (tid == 0) {
+            b.cursor[g] = 1;
+            atomicAdd(b.nbig, 1);
         }
-        __syncthreads();   // the histogram and range are reused by the next tile
+        return;
+    }
+    const int32_t *list = b.list + (size_t)g * b.cap;
+    int t[kIt];
+#pragma unroll
+    for (int j = 0; j < kIt; j++) {
+        if (256 * j >= n) continue;   // (uniform)
+        t[j] = list[256 * j + tid < n ? 256 * j + tid : 0];
+    }
+    for (int k = tid; k < kSlots; k += 256) s_table[k] = 0ull;
+    v3i_a4 c[kIt];
+#pragma unroll
+    for (int j = 0; j < kIt; j++) {
+        if (256 * j >= n) continue;
+        c[j] = *reinterpret_cast<const v3i_a4 *>(b.org + 3 * (size_t)t[j]);
+        s_tri[256 * j + tid] = t[j];
+    }
+    __syncthreads();
+    int slot[kIt][3];   // -1: not this group's
+    bool full = false;
+#pragma unroll
+    for (int j = 0; j < kIt; j++) {
+        if (256 * j >= n) continue;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            slot[j][i] = -1;
+            GroupEdge e;
+            if (256 * j + tid >= n || !group_edge(b, c[j], i, g, e)) continue;
+            bool dup = false;
+            slot[j][i] = edge_insert(s_table, e, 3 * (256 * j + tid) + i, dup);
+            full |= slot[j][i] < 0;
+            if (dup) report(b.err, 1ull + b.nt + 3ull * t[j] + i, -4);
+        }
+    }
+    if (__syncthreads_or(full)) {   // (uniform)
+        if (tid == 0) {
+            b.cursor[g] = 1;
+            atomicAdd(b.nbig, 1);
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < kIt; j++) {
+        if (256 * j >= n) continue;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            if (slot[j][i] < 0) continue;
+            const int m = edge_mate(s_table[slot[j][i]], 3 * (256 * j + tid) + i);
+            const int q = m < 0 ? 0 : (int)((unsigned)m / 3u) & (kGroupCap - 1);   // (ids of a repeated edge run together)
+            b.twin[3 * (size_t)t[j] + i] = m < 0 ? -1 : 3 * s_tri[q] + (m - 3 * q);
+        }
     }
 }
 
-__global__ void k_match(const int32_t *__restrict__ org, int nt, const int32_t *__restrict__ vstart,
-                        const int2 *__restrict__ bucket, int32_t *__restrict__ twin,
-                        unsigned long long *err) {
-    const int nh = 3 * nt;
-    for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < nh; h += gridDim.x * blockDim.x) {
-        int u = org[h], v = org[he_next_b(h)];
-        int found = -1, nrev = 0, ndup = 0;
-        for (int k = vstart[v], e = vstart[v + 1]; k < e; k++) {
-            const int2 g = bucket[k];   // (half-edge v->w, w)
-            if (g.y == u) {
-                found = g.x;
-                ++nrev;
-            }
+// ---- groups too large for k_match ------------------------------------------
+
+// Places in the list for the groups that k_match left out (cursor != 0), in
+// any order; a group's cursor is its place + 1.  Its classes, about
+// kClassSplit triangles each, are listed.
+__global__ void __launch_bounds__(256) k_part_alloc(BuildBuffers b) {
+    const int g = blockIdx.x * 256 + threadIdx.x;
+    if (g >= b.nparts || b.cursor[g] == 0) return;
+    const int n = b.count[g], k = (n + kClassSplit - 1) / kClassSplit;
+    b.cursor[g] = atomicAdd(b.total, n) + 1;
+    const int at = atomicAdd(b.ntasks, k);
+    for (int r = 0; r < k; r++) b.tasks[at + r] = {g, r, k};   // at most build_tasks() in all
+}
+
+__global__ void __launch_bounds__(256) k_scatter(BuildBuffers b) {
+    const int lane = __lane_id();
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    v3i_a4 c = {-1, -1, -1};
+    if (t < b.nt) c = *reinterpret_cast<const v3i_a4 *>(b.org + 3 * (size_t)t);
+    int g[3];
+    triangle_groups(b, c.x >= 0, c, g);
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        unsigned long long todo = __ballot(g[i] >= 0 && b.cursor[g[i] < 0 ? 0 : g[i]] != 0);
+        while (todo) {   // (uniform)
+            const int gl = __builtin_amdgcn_readlane(g[i], __ffsll((long long)todo) - 1);
+            const unsigned long long same = __ballot(g[i] == gl);
+            const int at = add_together(&b.cursor[gl], same, lane) - 1;
+            if ((same >> lane) & 1) b.list[at] = t;
+            todo &= ~same;
         }
-        // a second u->v: when some v->u exists, its own search finds both
-        // u->v and reports them, so only a half-edge without a reverse looks
-        if (nrev == 0) {
-            for (int k = vstart[u], e = vstart[u + 1]; k < e; k++) {
-                const int2 g = bucket[k];
-                if (g.x != h && g.y == v) ++ndup;
-            }
-        }
-        if (nrev > 1 || ndup > 0) atomicMin(err, err_key(1ull + nt + h, -4));
-        twin[h] = nrev == 1 ? found : -1;
     }
 }
 
+// One class of a large group: the edges of the group that hash into the class.
+// A class whose edges still do not fit the table (an edge repeated without
+// end, so an error, or a freak of the hash) compares its half-edges one by
+// one.  The scans stop once an error is known.
+__device__ void match_class(const BuildBuffers &b, unsigned long long *s_table, int *s_he, int *s_n, ClassTask task) {
+    const int tid = threadIdx.x, g = task.group, n = b.count[g], first = b.cursor[g] - 1 - n;
+    const uint32_t classes = (uint32_t)task.classes;
+    auto mine = [&](const GroupEdge &e) {
+        const uint32_t x = edge_hash(e);
+        return ((x ^ (x >> 15)) * 0x2C1B3C6Du >> 8) % classes == (uint32_t)task.cls;
+    };
+    auto failed = [&]() { return __hip_atomic_load(b.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0ull; };
+    // every edge of the class, f(half-edge, edge)
+    auto each = [&](int k, auto f) {
+        const int t = b.list[first + k];
+        const v3i_a4 c = *reinterpret_cast<const v3i_a4 *>(b.org + 3 * (size_t)t);
+        for (int i = 0; i < 3; i++) {
+            GroupEdge e;
+            if (group_edge(b, c, i, g, e) && mine(e)) f(3 * t + i, e);
+        }
+    };
+    __syncthreads();
+    for (int k = tid; k < kSlots; k += 256) s_table[k] = 0ull;
+    if (tid == 0) *s_n = 0;
+    bool full = false, again = false;
+    for (int k0 = 0; k0 < n; k0 += 256) {   // block-uniform
+        if ((k0 & 0xffff) == 0 && __syncthreads_or(failed())) return;
+        if (k0 + tid >= n) continue;
+        each(k0 + tid, [&](int h, const GroupEdge &e) {
+            const int id = atomicAdd(s_n, 1);
+            bool dup = false;
+            if (id < kSlots) {
+                s_he[id] = h;
+                full |= edge_insert(s_table, e, id, dup) < 0;
+            }
+            full |= id >= kSlots;
+            if (dup) report(b.err, 1ull + b.nt + h, -4);
+            again |= dup;
+        });
+    }
+    if (__syncthreads_or(again)) return;   // (uniform)
+    if (!__syncthreads_or(full)) {   // (uniform)
+        for (int k = tid; k < kSlots; k += 256) {
+            const unsigned long long s = s_table[k];
+            if (s == 0ull) continue;
+            const int x = s_he[(int)(s >> 40) & 0xfff], m = (int)(s >> 52) - 1;
+            b.twin[x] = m < 0 ? -1 : s_he[m];
+            if (m >= 0) b.twin[s_he[m]] = x;
+        }
+        return;
+    }
+    for (int k0 = tid; k0 < n; k0 += 256) {
+        bool stop = false;
+        each(k0, [&](int h, const GroupEdge &e) {
+            int found = -1, others = 0;
+            for (int k = 0; k < n && !stop; k++) {
+                if ((k & 0xfff) == 0) stop = failed();
+                each(k, [&](int h2, const GroupEdge &e2) {
+                    if (h2 == h || e2.other != e.other || e2.own != e.own) return;
+                    found = h2;
+                    others += e2.out == e.out ? 2 : 1;
+                });
+            }
+            if (others > 1) report(b.err, 1ull + b.nt + h, -4);
+            b.twin[h] = found;
+        });
+        if (stop) return;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_match_class(BuildBuffers b) {
+    __shared__ unsigned long long s_table[kSlots];
+    __shared__ int s_he[kSlots];
+    __shared__ int s_n;
+    const int ntasks = *b.ntasks;
+    for (int k = blockIdx.x; k < ntasks; k += kClassBlocks) match_class(b, s_table, s_he, &s_n, b.tasks[k]);
+}
 
 // ---------------------------------------------------------------------------
 // compact half-edge encoding
@@ -407,31 +602,31 @@ inline int grid_for(long long n, int block, int cap = 1 << 16) {
 
 }  // namespace
 
-int32_t build_scan_tiles(int32_t n) {
-    int per = kScanBlock * kScanItems;
-    int k = (n + per - 1) / per;
-    return k < 1 ? 1 : k;
+BuildSizes build_sizes(int64_t nv, int64_t nt) {
+    BuildSizes z;
+    z.parts = (nv + kBuildGroup - 1) / kBuildGroup;
+    z.tasks = 3 * nt / kClassSplit + z.parts + 1;
+    // 12 bytes a vertex and 24 a triangle are enough for full lists unless
+    // most vertices are in no triangle; lists then are shorter
+    const int64_t bytes = 12 * nv + 24 * nt + 65536 - 8 * z.parts - (int64_t)sizeof(ClassTask) * z.tasks;
+    z.cap = z.parts > 0 ? bytes / (4 * z.parts) : kGroupCap;
+    if (z.cap > kGroupCap) z.cap = kGroupCap;
+    z.list = z.parts * z.cap > 3 * nt ? z.parts * z.cap : 3 * nt;   // large groups' lists: 3 nt at most
+    return z;
 }
 
-hipError_t launch_build_orient(const BuildBuffers &b, hipStream_t s) {
-    hipLaunchKernelGGL(k_check_xy, dim3(grid_for(b.nv, 256)), dim3(256), 0, s, b.xy, b.nv, b.err_key);
-    if (b.nt > 0)
-        hipLaunchKernelGGL(k_orient, dim3(grid_for(b.nt, 256 * kTileItems)), dim3(256), 0, s, b.xy, b.tri, b.nv, b.nt,
-                           b.org, b.deg, b.err_key, b.nflipped);
+hipError_t launch_build(const BuildBuffers &b, hipStream_t s) {
+    const int tiles = (b.nt + kTileTri - 1) / kTileTri;
+    const int copies = (int)(((int64_t)b.nv + 256 * kCopyItems - 1) / (256 * kCopyItems));
+    if (tiles + copies > 0) hipLaunchKernelGGL(k_orient, dim3(tiles + copies), dim3(256), 0, s, b, tiles);
+    if (tiles > 0 && b.nparts > 0) hipLaunchKernelGGL(k_match, dim3(b.nparts), dim3(256), 0, s, b);
     return hipGetLastError();
 }
 
-hipError_t launch_build_link(const BuildBuffers &b, hipStream_t s) {
-    int tiles = build_scan_tiles(b.nv);
-    hipLaunchKernelGGL(k_scan_excl, dim3(tiles), dim3(kScanBlock), 0, s, b.deg, b.vstart, b.nv,
-                       b.scan_status, b.scan_ctr, b.err_key);
-    long long nh = 3ll * b.nt;
-    if (nh > 0) {
-        hipLaunchKernelGGL(k_bucket, dim3(grid_for(nh, 256 * kTileItems)), dim3(256), 0, s, b.org, (int)nh, b.vstart,
-                           b.fill, b.bucket);
-        hipLaunchKernelGGL(k_match, dim3(grid_for(nh, 256)), dim3(256), 0, s, b.org, b.nt, b.vstart,
-                           b.bucket, b.twin, b.err_key);
-    }
+hipError_t launch_build_large(const BuildBuffers &b, hipStream_t s) {
+    hipLaunchKernelGGL(k_part_alloc, dim3((b.nparts + 255) / 256), dim3(256), 0, s, b);
+    hipLaunchKernelGGL(k_scatter, dim3(b.nt / 256 + 1), dim3(256), 0, s, b);
+    hipLaunchKernelGGL(k_match_class, dim3(kClassBlocks), dim3(256), 0, s, b);
     return hipGetLastError();
 }
 

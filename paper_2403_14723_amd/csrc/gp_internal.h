@@ -226,24 +226,44 @@ hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nv, int max_nt
 
 // ---- build (build_kernels.hip) -------------------------------------------
 
-struct BuildBuffers {
-    const int2 *xy;
-    const int32_t *tri;
-    int32_t nv, nt;
-    int32_t *org, *twin;
-    int32_t *deg;      // nv + 1, zeroed by the build
-    int32_t *vstart;   // nv + 1
-    int32_t *fill;     // nv
-    int2 *bucket;      // 3 nt: (half-edge, its target vertex), grouped by origin
-    uint64_t *scan_status;  // scan tiles
-    int32_t *scan_ctr;
-    unsigned long long *err_key;  // lowest (rank << 8 | code) seen
-    int32_t *nflipped;
+constexpr int kBuildGroup = 128;       // vertices per group (build_kernels.hip)
+constexpr int kBuildGroupCap = 1024;   // most triangles of a group that one workgroup matches
+
+// one class of the edges of a group too large for that
+struct ClassTask {
+    int32_t group, cls, classes;
 };
 
-hipError_t launch_build_orient(const BuildBuffers &b, hipStream_t s);
-hipError_t launch_build_link(const BuildBuffers &b, hipStream_t s);
-int32_t build_scan_tiles(int32_t n);
+// Scratch of a build: vertex groups, triangles a group's list has room for,
+// ints of all lists, classes of large groups.
+struct BuildSizes {
+    int64_t parts, cap, list, tasks;
+};
+BuildSizes build_sizes(int64_t nv, int64_t nt);
+// Ends of an edge are near below 8,192 or an eighth of the vertices: a grid's
+// rows (up to that wide) are, most edges of a random numbering are not.
+inline int32_t build_near(int32_t nv) { return nv / 8 < 8192 ? nv / 8 + 1 : 8192; }
+
+struct BuildBuffers {
+    const int32_t *xy_in;   // 2 nv, 4-byte aligned
+    int2 *xy_out;           // nv: xy_in is copied here; null when it is the mesh's own array
+    const int32_t *tri;
+    int32_t nv, nt, nparts, cap, near;
+    int32_t *org, *twin;
+    int32_t *list;          // cap per group: its triangles
+    ClassTask *tasks;
+    // zeroed before the build
+    int32_t *count;         // nparts: triangles per group
+    int32_t *cursor;        // nparts: not 0 for a large group (then its place in list + 1)
+    unsigned long long *err;   // 0, or the highest ~(rank << 8 | -code) seen
+    int32_t *nflipped;
+    int32_t *nbig;          // large groups, left to launch_build_large
+    int32_t *total, *ntasks;   // its list entries and classes
+};
+
+hipError_t launch_build(const BuildBuffers &b, hipStream_t s);
+// The groups that launch_build left out, when *nbig is not 0.
+hipError_t launch_build_large(const BuildBuffers &b, hipStream_t s);
 
 // ---- renumbering along a Z-order curve (renumber.hip) ---------------------
 

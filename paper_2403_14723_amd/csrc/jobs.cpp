@@ -8,8 +8,8 @@
 //   1. queue the uploads of the next group's inputs;
 //   2. wait for the previous group's meshing run to finish and queue its
 //      downloads, so they run while this group builds and the next uploads;
-//   3. build this group's half-edge structures (after its uploads; two host
-//      checks for the whole group) and queue its meshing run;
+//   3. build this group's half-edge structures (after its uploads; one host
+//      wait for the whole group) and queue its meshing run;
 //   4. give back the memory of groups whose downloads have completed (at
 //      most two meshed groups hold memory at once).
 // Memory goes back to the context's pool only after the host has seen the

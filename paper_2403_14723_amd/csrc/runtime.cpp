@@ -372,16 +372,31 @@ namespace gprt {
 
 namespace {
 
-// One half-edge build, in three stages around the two checks of its inputs
-// (orientation and indices first, then the twin matching), so that many
-// builds can share each host check.
+// What a build reports to the host: the first words of its zeroed scratch.
+struct BuildReport {
+    unsigned long long err;   // gp::BuildBuffers::err
+    int32_t nflipped, nbig, total, ntasks;
+};
+
+// Device scratch of one build.
+size_t build_scratch_bytes(int64_t nv, int64_t nt, bool inputs_on_device) {
+    const gp::BuildSizes z = gp::build_sizes(nv, nt);
+    return align_up(sizeof(BuildReport) + 2 * sizeof(int32_t) * (size_t)z.parts) + arena_bytes<int32_t>(z.list) +
+           arena_bytes<gp::ClassTask>(z.tasks) + (inputs_on_device ? 0 : arena_bytes<int32_t>(3 * nt));
+}
+
+// One half-edge build: queued whole, its inputs' checks among its kernels, and
+// finished after the stream has drained, so that many builds can share one
+// host wait (a second one when some vertex group was too large for the usual
+// kernels).
 struct BuildJob {
     gp_mesh *m = nullptr;
     void *p_tmp = nullptr;
     gp::BuildBuffers b{};
-    unsigned long long *key_h = nullptr;   // pinned: the error key after a stage
-    int32_t *nflip_h = nullptr;            // pinned: triangles flipped to CCW
+    BuildReport *report = nullptr;   // pinned
+    const BuildReport *report_dev = nullptr;
     int rc = GP_OK;
+    bool large() const { return rc == GP_OK && report->err == 0 && report->nbig > 0; }
 };
 
 void build_abort(gp_ctx *c, BuildJob &j) {
@@ -391,10 +406,9 @@ void build_abort(gp_ctx *c, BuildJob &j) {
     j.m = nullptr;
 }
 
-// Stage 0: allocation, input copies, clears and the orientation kernels
-// (which also check every index and coordinate), all queued.
-int build_stage0(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, int32_t nt, uint32_t flags,
-                 BuildJob &j) {
+// Allocation, input copies, the kernels and the readback, all queued.
+int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, int32_t nt, uint32_t flags,
+                BuildJob &j) {
     if (nv < 0 || nt < 0) return GP_EINVAL;
     if ((nv > 0 && !xy) || (nt > 0 && !tri)) return GP_EINVAL;
     if (3ll * nt >= (1ll << 31)) return GP_ERANGE;
@@ -413,67 +427,64 @@ int build_stage0(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, i
     m->org = static_cast<int32_t *>(p_org);
     if (rc == GP_OK) rc = c->pool.alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(nh, 1), &p_twin);
     m->twin = static_cast<int32_t *>(p_twin);
-    const int32_t scan_tiles = gp::build_scan_tiles(nv);
-    const size_t tmp_bytes = arena_bytes<int32_t>(nv + 1) * 2 + arena_bytes<int32_t>(nv + 1) +
-                             arena_bytes<int2>(nh + 1) + arena_bytes<uint64_t>(scan_tiles) +
-                             arena_bytes<int32_t>(4) + arena_bytes<unsigned long long>(1) +
-                             (in_dev ? 0 : arena_bytes<int32_t>(nh + 1));
+    const size_t tmp_bytes = build_scratch_bytes(nv, nt, in_dev);
     if (rc == GP_OK) rc = c->pool.alloc(tmp_bytes, &j.p_tmp);
     if (rc != GP_OK) return rc;
     Arena a{static_cast<char *>(j.p_tmp), tmp_bytes, 0};
+    const gp::BuildSizes z = gp::build_sizes(nv, nt);
     gp::BuildBuffers &b = j.b;
     b.nv = nv;
     b.nt = nt;
+    b.nparts = (int32_t)z.parts;
+    b.cap = (int32_t)z.cap;
+    b.near = gp::build_near(nv);
     b.org = m->org;
     b.twin = m->twin;
-    b.deg = a.take<int32_t>(nv + 1);
-    b.fill = a.take<int32_t>(nv + 1);
-    b.vstart = a.take<int32_t>(nv + 1);
-    b.bucket = a.take<int2>(nh + 1);
-    b.scan_status = a.take<uint64_t>(scan_tiles);
-    int32_t *small = a.take<int32_t>(4);
-    b.scan_ctr = small;
-    b.nflipped = small + 1;
-    b.err_key = a.take<unsigned long long>(1);
-    int32_t *tri_dev = in_dev ? const_cast<int32_t *>(tri) : a.take<int32_t>(nh + 1);
-    b.xy = m->xy;
-    b.tri = tri_dev;
+    const size_t zero_bytes = sizeof(BuildReport) + 2 * sizeof(int32_t) * (size_t)b.nparts;
+    char *zero = a.take<char>(zero_bytes);
+    BuildReport *rep = reinterpret_cast<BuildReport *>(zero);
+    j.report_dev = rep;
+    b.err = &rep->err;
+    b.nflipped = &rep->nflipped;
+    b.nbig = &rep->nbig;
+    b.total = &rep->total;
+    b.ntasks = &rep->ntasks;
+    b.count = reinterpret_cast<int32_t *>(zero + sizeof(BuildReport));
+    b.cursor = b.count + b.nparts;
+    b.list = a.take<int32_t>(z.list);
+    b.tasks = a.take<gp::ClassTask>(z.tasks);
+    int32_t *tri_dev = in_dev ? nullptr : a.take<int32_t>(nh);
+    b.tri = in_dev ? tri : tri_dev;
+    b.xy_in = in_dev ? xy : reinterpret_cast<const int32_t *>(m->xy);
+    b.xy_out = in_dev ? m->xy : nullptr;
     hipStream_t s = c->stream;
-    const hipMemcpyKind kind = in_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    if ((nv > 0 && hipMemcpyAsync(m->xy, xy, sizeof(int2) * (size_t)nv, kind, s) != hipSuccess) ||
+    if ((!in_dev && nv > 0 &&
+         hipMemcpyAsync(m->xy, xy, sizeof(int2) * (size_t)nv, hipMemcpyHostToDevice, s) != hipSuccess) ||
         (!in_dev && nt > 0 &&
          hipMemcpyAsync(tri_dev, tri, sizeof(int32_t) * (size_t)nh, hipMemcpyHostToDevice, s) != hipSuccess) ||
-        hipMemsetAsync(b.deg, 0, sizeof(int32_t) * (size_t)(nv + 1), s) != hipSuccess ||
-        hipMemsetAsync(b.fill, 0, sizeof(int32_t) * (size_t)(nv + 1), s) != hipSuccess ||
-        hipMemsetAsync(b.scan_status, 0, sizeof(uint64_t) * (size_t)scan_tiles, s) != hipSuccess ||
-        hipMemsetAsync(small, 0, sizeof(int32_t) * 4, s) != hipSuccess ||
-        hipMemsetAsync(b.err_key, 0xff, sizeof(unsigned long long), s) != hipSuccess ||
-        gp::launch_build_orient(b, s) != hipSuccess ||
-        hipMemcpyAsync(j.key_h, b.err_key, sizeof(unsigned long long), hipMemcpyDeviceToHost, s) != hipSuccess) {
+        hipMemsetAsync(zero, 0, zero_bytes, s) != hipSuccess || gp::launch_build(b, s) != hipSuccess ||
+        gp::launch_copy_words(j.report, rep, sizeof(BuildReport), s) != hipSuccess) {
         (void)hipGetLastError();
         return GP_EHIP;
     }
     return GP_OK;
 }
 
-// Stage 1 (after the stream has drained stage 0): the inputs passed their
-// checks; queue the twin matching and the readbacks of its checks.
-int build_stage1(gp_ctx *c, BuildJob &j) {
-    if (*j.key_h != ~0ull) return -(int)(*j.key_h & 0xff);
-    hipStream_t s = c->stream;
-    if (gp::launch_build_link(j.b, s) != hipSuccess ||
-        hipMemcpyAsync(j.key_h, j.b.err_key, sizeof(unsigned long long), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(j.nflip_h, j.b.nflipped, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess) {
+// After the stream has drained: the groups that were too large.
+int build_queue_large(gp_ctx *c, BuildJob &j) {
+    if (gp::launch_build_large(j.b, c->stream) != hipSuccess ||
+        gp::launch_copy_words(j.report, j.report_dev, sizeof(BuildReport), c->stream) != hipSuccess) {
         (void)hipGetLastError();
         return GP_EHIP;
     }
     return GP_OK;
 }
 
-// Stage 2 (after the stream has drained stage 1): the mesh is complete.
-int build_stage2(gp_ctx *c, BuildJob &j) {
-    if (*j.key_h != ~0ull) return -(int)(*j.key_h & 0xff);
-    j.m->nflipped = *j.nflip_h;
+// After the stream has drained: the mesh is complete, or its inputs failed a
+// check.
+int build_finish(gp_ctx *c, BuildJob &j) {
+    if (j.report->err) return -(int)(~j.report->err & 0xff);
+    j.m->nflipped = j.report->nflipped;
     j.m->bytes = align_up(sizeof(int2) * (size_t)std::max(j.m->nv, 1)) +
                  2 * align_up(sizeof(int32_t) * (size_t)std::max<int64_t>(3ll * j.m->nt, 1));
     c->pool.release(j.p_tmp);
@@ -744,12 +755,11 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
             return build_small_many(c, n, xy, nv, tri, nt, flags, out, status);
     }
     std::vector<BuildJob> jobs(n);
-    const size_t hb = 16 * (size_t)std::max(n, 1);
-    char *host = static_cast<char *>(pinned_take(c, hb));
+    const size_t hb = sizeof(BuildReport) * (size_t)std::max(n, 1);
+    BuildReport *host = static_cast<BuildReport *>(pinned_take(c, hb));
     if (!host) return GP_ENOMEM;
     for (int i = 0; i < n; i++) {
-        jobs[i].key_h = reinterpret_cast<unsigned long long *>(host + 16 * i);
-        jobs[i].nflip_h = reinterpret_cast<int32_t *>(host + 16 * i + 8);
+        jobs[i].report = host + i;
         out[i] = nullptr;
     }
     auto drain = [&]() {
@@ -765,22 +775,26 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
         if (flags & GP_RENUMBER) {
             jobs[i].rc = renumber_input(c, xy[i], nv[i], tri[i], nt[i], (flags & GP_IN_DEVICE) != 0, rn[i]);
             if (jobs[i].rc == GP_OK)
-                jobs[i].rc = build_stage0(c, static_cast<const int32_t *>(rn[i].xy), nv[i],
-                                          static_cast<const int32_t *>(rn[i].tri), nt[i], flags | GP_IN_DEVICE,
-                                          jobs[i]);
+                jobs[i].rc = build_queue(c, static_cast<const int32_t *>(rn[i].xy), nv[i],
+                                         static_cast<const int32_t *>(rn[i].tri), nt[i], flags | GP_IN_DEVICE,
+                                         jobs[i]);
         } else {
-            jobs[i].rc = build_stage0(c, xy[i], nv[i], tri[i], nt[i], flags, jobs[i]);
+            jobs[i].rc = build_queue(c, xy[i], nv[i], tri[i], nt[i], flags, jobs[i]);
         }
     }
     drain();
+    bool large = false;
+    for (BuildJob &j : jobs) {
+        if (!j.large()) continue;
+        j.rc = build_queue_large(c, j);
+        large = true;
+    }
+    if (large) drain();
     for (BuildJob &j : jobs)
-        if (j.rc == GP_OK) j.rc = build_stage1(c, j);
-    drain();
-    for (BuildJob &j : jobs)
-        if (j.rc == GP_OK) j.rc = build_stage2(c, j);
+        if (j.rc == GP_OK) j.rc = build_finish(c, j);
     if (flags & GP_COMPACT)
         for (BuildJob &j : jobs)
-            if (j.rc == GP_OK) j.rc = compact_mesh(c, j.m, j.nflip_h);
+            if (j.rc == GP_OK) j.rc = compact_mesh(c, j.m, &j.report->nflipped);
     // a failed job's memory goes back after the stream has drained its work
     // (as do the renumbered inputs, which the builds have finished reading)
     bool failed = false;
@@ -809,10 +823,7 @@ size_t build_footprint(int64_t nv, int64_t nt, bool inputs_on_device) {
     const int64_t nh = 3 * nt;
     const size_t keep = align_up(sizeof(int2) * (size_t)std::max<int64_t>(nv, 1)) +
                         2 * align_up(sizeof(int32_t) * (size_t)std::max<int64_t>(nh, 1));
-    const size_t tmp = arena_bytes<int32_t>(nv + 1) * 3 + arena_bytes<int2>(nh + 1) +
-                       arena_bytes<uint64_t>(gp::build_scan_tiles((int32_t)nv)) + arena_bytes<int32_t>(4) +
-                       arena_bytes<unsigned long long>(1) + (inputs_on_device ? 0 : arena_bytes<int32_t>(nh + 1));
-    return keep + align_up(tmp);
+    return keep + align_up(build_scratch_bytes(nv, nt, inputs_on_device));
 }
 
 size_t batch_footprint(const gp::LaunchCfg &cfg, const int32_t *nts, int n) {

@@ -152,7 +152,7 @@ struct DeviceGuard {
 };
 
 // Builds n half-edge structures (the work of gpolylla_build_halfedges for
-// each) with two host checks in all, on the context's stream: out[i] and
+// each) with one host wait in all, on the context's stream: out[i] and
 // status[i] per build.  Returns GP_ENOMEM when the host staging cannot be
 // allocated (nothing built), else GP_OK.
 // Coherent pinned host blocks cached per context (a block of at least n

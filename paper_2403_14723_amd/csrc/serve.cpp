@@ -175,7 +175,7 @@ void launch(gp_server *s, Lane &L, std::vector<Request *> &batch) {
         nv[i] = batch[i]->nv;
         nt[i] = batch[i]->nt;
     }
-    // every build of the batch, with two host checks in all
+    // every build of the batch, with one host wait in all
     const int b = build_many(L.ctx, n, xy.data(), nv.data(), tri.data(), nt.data(), 0, ms.data(), st.data());
     for (int i = 0; i < n; i++) {
         const int rc = b != GP_OK ? b : st[i];

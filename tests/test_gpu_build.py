@@ -1,0 +1,136 @@
+"""The grouped half-edge build against the oracle: corners and twins at the
+edges of its tiles, groups and LDS capacity, in numberings with and without
+locality, and the errors it has to see.  small=0 keeps every mesh off the
+one-workgroup build.  All comparisons are exact."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2403_14723_amd as gp
+from paper_2403_14723_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = gp.Context(0)
+    c.set_launch("small=0")
+    yield c
+    c.close()
+
+
+def fan(deg, hub_last=False):
+    """deg triangles around one vertex: all their half-edges but the rim's
+    belong to edges of the hub."""
+    a = 2.0 * np.pi * np.arange(deg) / deg
+    rim = np.stack([2.0**29 * (1 + np.cos(a)), 2.0**29 * (1 + np.sin(a))], 1).astype(np.int32)
+    hub = np.array([[1 << 29, 1 << 29]], np.int32)
+    k = np.arange(deg)
+    nxt = (k + 1) % deg
+    if hub_last:
+        return np.concatenate([rim, hub]), np.stack([np.full(deg, deg), k, nxt], 1).astype(np.int32)
+    return np.concatenate([hub, rim]), np.stack([np.zeros(deg, int), k + 1, nxt + 1], 1).astype(np.int32)
+
+
+def grid_prefix(n, nt, seed):
+    m = W.jittered_grid(n, seed=seed)
+    return m.xy, m.tri[:nt]
+
+
+def scrambled_prefix(n, nt, seed):
+    m = W.scrambled(W.jittered_grid(n, seed=seed), seed)
+    return m.xy, m.tri[:nt]
+
+
+def unused_vertices():
+    m = W.jittered_grid(40, seed=5)
+    return np.concatenate([np.zeros((700_001, 2), np.int32), m.xy]), m.tri + 700_001
+
+
+CASES = [("one", lambda: grid_prefix(1, 1, 1)), ("tile-1", lambda: grid_prefix(40, 1023, 2)),
+         ("tile", lambda: grid_prefix(40, 1024, 3)), ("tile+1", lambda: grid_prefix(40, 1025, 4)),
+         ("rows", lambda: grid_prefix(317, 2 * 317 * 317 - 5, 5)),
+         ("wide", lambda: grid_prefix(600, 600 * 2 * 3 + 7, 6)),
+         # near and far ends, inside and outside the window of groups
+         ("scattered_small", lambda: scrambled_prefix(60, 7001, 7)),
+         ("scattered", lambda: scrambled_prefix(340, 231_111, 8)),
+         ("delaunay", lambda: (lambda m: (m.xy, m.tri))(W.random_delaunay(30_000, 9))),
+         ("unused_vertices", unused_vertices),
+         # groups about the LDS capacity (2,048) and far above it
+         ("fan_900", lambda: fan(900)), ("fan_1024", lambda: fan(1024)), ("fan_1025", lambda: fan(1025)),
+         ("fan_hub_last", lambda: fan(2000, True)), ("fan_30000", lambda: fan(30_000)),
+         ("fan_30000_hub_last", lambda: fan(30_000, True))]
+
+
+@pytest.mark.parametrize("name,make", CASES, ids=[c[0] for c in CASES])
+def test_corners_and_twins(ctx, name, make):
+    xy, tri = make()
+    print(f"[gpu] {name}: nv={len(xy)} nt={len(tri)}", flush=True)
+    o = oracle.polylla(xy, tri)
+    m = ctx.build_halfedges(xy, tri)
+    org, twin, nflip = m.copy()
+    m.free()
+    assert np.array_equal(org, o.org)
+    assert np.array_equal(twin, o.twin)
+    assert nflip == o.stats["nflipped"]
+
+
+def test_unaligned_device_arrays(ctx):
+    """Device arrays that start 4 bytes past any wider alignment."""
+    import torch
+    xy, tri = scrambled_prefix(90, 16_001, 11)
+    o = oracle.polylla(xy, tri)
+    dxy = torch.zeros(xy.size + 1, dtype=torch.int32, device="cuda")
+    dtri = torch.zeros(tri.size + 1, dtype=torch.int32, device="cuda")
+    dxy[1:] = torch.from_numpy(xy.reshape(-1))
+    dtri[1:] = torch.from_numpy(tri.reshape(-1))
+    torch.cuda.synchronize()
+    m = ctx.build_halfedges(dxy[1:], dtri[1:])
+    org, twin, _ = m.copy()
+    m.free()
+    assert np.array_equal(org, o.org) and np.array_equal(twin, o.twin)
+
+
+def _bad(kind):
+    xy, tri = (a.copy() for a in grid_prefix(50, 4999, 12))
+    if kind == "index":
+        tri[4998, 2] = len(xy)
+    elif kind == "negative":
+        tri[0, 0] = -7
+    elif kind == "coordinate":
+        xy[-1, 1] = (1 << 30) + 1
+    elif kind == "flat":
+        tri[1024, 1] = tri[1024, 0]
+    elif kind == "twice":             # a triangle again
+        tri = np.concatenate([tri, tri[3000:3001]])
+    elif kind == "turned":            # a triangle again, from the other side: three of its edges, each twice
+        tri = np.concatenate([tri, tri[3000:3001, ::-1]])
+    elif kind == "third":             # a third triangle on an interior edge
+        a, b, c = tri[2500]
+        far = int(np.argmax(np.abs(xy.astype(np.int64) - xy[a]).sum(1)))
+        tri = np.concatenate([tri, np.array([[a, b, far]], np.int32)])
+    elif kind == "many_times":        # one group's edges repeat beyond any class
+        tri = np.concatenate([tri, np.repeat(tri[10:11], 9000, 0)])
+    elif kind == "fan_twice":         # a repeat in a group above the LDS capacity
+        xy, tri = fan(5000)
+        tri = np.concatenate([tri, tri[4321:4322]])
+    elif kind == "range_before_index":
+        xy[0, 0] = -1
+        tri[5, 1] = -1
+    elif kind == "index_before_repeat":
+        tri = np.concatenate([tri, tri[:1]])
+        tri[4000, 0] = len(xy) + 5
+    return xy, tri
+
+
+@pytest.mark.parametrize("kind", ["index", "negative", "coordinate", "flat", "twice", "turned", "third", "many_times",
+                                  "fan_twice", "range_before_index", "index_before_repeat"])
+def test_errors(ctx, kind):
+    xy, tri = _bad(kind)
+    print(f"[gpu] {kind}", flush=True)
+    with pytest.raises(oracle.OracleError) as want:
+        oracle.polylla(xy, tri)
+    with pytest.raises(gp.GPolyllaError) as got:
+        ctx.build_halfedges(xy, tri)
+    assert got.value.code == want.value.code
