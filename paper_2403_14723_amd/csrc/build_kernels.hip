@@ -40,14 +40,10 @@ namespace gp {
 namespace {
 
 constexpr int kCoordMax = 1 << 30;
-// k_orient works in tiles of 256 threads x kTileItems triangles and counts per
-// group in an LDS window of kBins groups around the tile (meshes numbered row
-// by row or along a curve stay in it): one global atomic per group the tile
-// touches.  Groups outside the window cost one per wave, or per triangle where
-// no two of a wave share one.
+// k_orient gives each wave kTileItems x 64 triangles in a row
 constexpr int kTileItems = 4;
 constexpr int kTileTri = 256 * kTileItems;
-constexpr int kBins = 512;
+constexpr int kMaxRounds = 48;       // groups a wave of k_orient places together
 constexpr int kCopyItems = 8;        // vertices per thread of k_orient's coordinate blocks
 constexpr int kShift = 7;
 static_assert(1 << kShift == kBuildGroup, "groups by shift");
@@ -88,53 +84,6 @@ __device__ __forceinline__ void triangle_groups(const BuildBuffers &b, bool ok, 
     if (!ok) g[0] = g[1] = g[2] = -1;
 }
 
-// Adds the lanes of `same` (this lane's group's, found by a ballot) to counter
-// *c with one atomic; returns the counter's value at this lane's place.
-__device__ __forceinline__ int add_together(int *c, unsigned long long same, int lane) {
-    const int leader = __ffsll((long long)same) - 1;
-    int b = 0;
-    if (lane == leader) b = atomicAdd(c, __popcll(same));
-    return __builtin_amdgcn_readlane(b, leader) + __popcll(same & ((1ull << lane) - 1ull));
-}
-
-// Adds this wave's triangles to their groups' counters: lane's group g (g < 0:
-// none), counted in the LDS window s_bin of kBins groups from w0 on, or in
-// count[] (global) outside it.  Lanes of one group add together (a wave of an
-// ordered mesh has one to three groups; 64 atomics on one word would run one
-// by one), for four groups at most, and the rest alone: a random numbering has
-// hardly two lanes of one group.  Returns the counter's value at the lane's
-// place.
-__device__ __forceinline__ int bin_add(int *s_bin, int32_t *count, int g, int w0) {
-    const int lane = __lane_id();
-    const bool in = g >= 0 && (unsigned)(g - w0) < (unsigned)kBins;
-    unsigned long long todo = __ballot(in);
-    const unsigned long long out = __ballot(g >= 0 && !in);
-    int place = 0;
-#pragma unroll 1
-    for (int k = 0; k < 4 && todo; k++) {
-        const int gl = __builtin_amdgcn_readlane(g, __ffsll((long long)todo) - 1);
-        const unsigned long long same = __ballot(g == gl);
-        const int at = add_together(&s_bin[gl - w0], same, lane);
-        if ((same >> lane) & 1) place = at;
-        todo &= ~same;
-    }
-    if ((todo >> lane) & 1) place = atomicAdd(&s_bin[g - w0], 1);
-    if (out) {   // (uniform)
-        todo = out;
-#pragma unroll 1
-        for (int k = 0; k < 4 && todo; k++) {
-            const int gl = __builtin_amdgcn_readlane(g, __ffsll((long long)todo) - 1);
-            const unsigned long long same = __ballot(g == gl);
-            if (__popcll(same) < 4) break;
-            const int at = add_together(&count[gl], same, lane);
-            if ((same >> lane) & 1) place = at;
-            todo &= ~same;
-        }
-        if ((todo >> lane) & 1) place = atomicAdd(&count[g], 1);
-    }
-    return place;
-}
-
 // Workgroups go to the 8 XCDs round-robin; this gives each XCD one contiguous
 // run of tiles, whose neighbours' coordinates then share its L2.
 __device__ __forceinline__ int xcd_run(int b, int G) {
@@ -142,181 +91,276 @@ __device__ __forceinline__ int xcd_run(int b, int G) {
     return x * q + (x < r ? x : r) + (b >> 3);
 }
 
-// First group of a tile's window: kBins groups around the median of the first
-// corners of three of its cnt triangles (one alone may straddle a jump of the
-// curve, which would leave the whole tile outside).
-__device__ __forceinline__ int window_start(const BuildBuffers &b, int base, int cnt) {
-    const int x = b.tri[3 * (size_t)base], y = b.tri[3 * (size_t)(base + cnt / 2)],
-              z = b.tri[3 * (size_t)(base + cnt - 1)];
-    return max(0, (max(min(x, y), min(max(x, y), z)) >> kShift) - kBins / 2);
+// A list entry: a triangle and which of its edges are the group's (bits 0-2).
+// WIDE (2^28 triangles or 2^25 vertices and more): arrays past the reach of
+// 32-bit byte offsets; entries are then triangle ids alone.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t list_entry(int t, int edges) {
+    return WIDE ? (uint32_t)t : ((uint32_t)t << 3) | (uint32_t)edges;
 }
 
-// Blocks [0, tiles): a tile of triangles each.  The others: the coordinates,
+// The T at STRIDE-byte element i of an array, by a 32-bit byte offset from a
+// uniform base unless WIDE.
+template <bool WIDE, int STRIDE, class T>
+__device__ __forceinline__ T &at(const void *base, uint32_t i) {
+    const char *p = static_cast<const char *>(base);
+    return *reinterpret_cast<T *>(const_cast<char *>(WIDE ? p + (size_t)i * STRIDE : p + i * (uint32_t)STRIDE));
+}
+
+// What a wave of k_orient has found of its triangles' groups: lane r holds the
+// r-th group and how many triangles go to its list.
+struct WaveGroups {
+    int group = 0, n = 0, rounds = 0, thin = 0;
+};
+
+// Places one entry per item (group e[j], -1: none) of the wave: item j's round
+// and rank in it as place[j] = round << 16 | rank, or -1 for the entries left
+// in e when the groups have grown too many or too thin (a random numbering).
+__device__ __forceinline__ void place_items(WaveGroups &w, int e[kTileItems], int place[kTileItems], int lane) {
+#pragma unroll
+    for (int j = 0; j < kTileItems; j++) place[j] = -1;
+    while (w.rounds < kMaxRounds && w.thin < 4) {   // (uniform)
+        int cand = -1;
+#pragma unroll
+        for (int j = 0; j < kTileItems; j++) cand = max(cand, e[j]);
+        const unsigned long long any = __ballot(cand >= 0);
+        if (!any) break;
+        const int g = __builtin_amdgcn_readlane(cand, __ffsll((long long)any) - 1);
+        int n = 0;
+#pragma unroll
+        for (int j = 0; j < kTileItems; j++) {
+            const bool is = e[j] == g;
+            const unsigned long long m = __ballot(is);
+            const int rank = (w.rounds << 16) + n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            place[j] = is ? rank : place[j];
+            e[j] = is ? -1 : e[j];
+            n += __popcll(m);
+        }
+        const bool mine = lane == w.rounds;
+        w.group = mine ? g : w.group;
+        w.n = mine ? n : w.n;
+        w.thin += n < 4;
+        w.rounds++;
+    }
+}
+
+// Blocks [0, tiles): 256 triangles per wave.  The others: the coordinates,
 // checked, and copied to the mesh when the caller's array is on the device.
+//
+// Every wave works alone: it finds the groups of its triangles (three to five
+// in an ordered numbering), takes their places in the groups' lists with one
+// atomic instruction, a lane to a group, and writes the entries, consecutive
+// lanes to consecutive places.  33.5M-triangle grid: 0.325 ms for 1.24 GB
+// (12 bytes a triangle in and out, 8 a vertex in and out, 1.3 entries of 4
+// bytes), 3.8 TB/s of the 4.7 a large copy reaches; 647 vector instructions a
+// wave, which take half of that time.  With a tile's counts in LDS, two
+// barriers and an atomic per workgroup and group it took 0.39 ms and 1,043.
+template <bool WIDE>
 __global__ void __launch_bounds__(256) k_orient(BuildBuffers b, int tiles) {
-    __shared__ int s_bin[kBins];
-    __shared__ int s_flip;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = __lane_id();
     if ((int)blockIdx.x >= tiles) {   // (uniform)
         const long long v0 = (long long)(blockIdx.x - tiles) * (256 * kCopyItems) + tid;
+        v2i_a4 p[kCopyItems];
+#pragma unroll
+        for (int j = 0; j < kCopyItems; j++)
+            p[j] = reinterpret_cast<const v2i_a4 *>(b.xy_in)[min(v0 + j * 256, (long long)b.nv - 1)];
         bool bad = false;
 #pragma unroll
         for (int j = 0; j < kCopyItems; j++) {
-            const long long v = v0 + j * 256;
-            if (v >= b.nv) continue;
-            const v2i_a4 p = reinterpret_cast<const v2i_a4 *>(b.xy_in)[v];
-            bad |= p.x < 0 || p.x > kCoordMax || p.y < 0 || p.y > kCoordMax;
-            if (b.xy_out) b.xy_out[v] = make_int2(p.x, p.y);
+            bad |= (unsigned)p[j].x > (unsigned)kCoordMax || (unsigned)p[j].y > (unsigned)kCoordMax;
+            if (b.xy_out && v0 + j * 256 < b.nv) b.xy_out[v0 + j * 256] = make_int2(p[j].x, p[j].y);
         }
         if (bad) report(b.err, 0, -2);
         return;
     }
-    const int base = xcd_run(blockIdx.x, tiles) * kTileTri;
-    const int cnt = min(kTileTri, b.nt - base);
-    const int w0 = window_start(b, base, cnt);   // (uniform; any value will do)
-    for (int k = tid; k < kBins; k += 256) s_bin[k] = 0;
-    if (tid == 0) s_flip = 0;
-    // a wave takes 256 triangles in a row; all corners, then all coordinates
-    // in flight together
-    const int lt0 = (tid & ~63) * kTileItems + (tid & 63);
+    const int base = xcd_run(blockIdx.x, tiles) * kTileTri + __builtin_amdgcn_readfirstlane(tid >> 6) * (64 * kTileItems);
+    const int cnt = b.nt - base;
+    if (cnt <= 0) return;   // (the whole wave)
+    if (b.nv <= 0) {        // (uniform) no valid index
+        if (lane == 0) report(b.err, 1ull + base, -1);
+        return;
+    }
+    // all corners, then all coordinates in flight together (lanes past the
+    // end take the last triangle, and drop it)
+    const int32_t *tri = b.tri + 3 * (size_t)base;
     v3i_a4 c[kTileItems];
-    bool ok[kTileItems];
 #pragma unroll
-    for (int j = 0; j < kTileItems; j++) {
-        const int lt = lt0 + 64 * j;
-        c[j] = *reinterpret_cast<const v3i_a4 *>(b.tri + 3 * (size_t)(base + (lt < cnt ? lt : 0)));
-        ok[j] = (unsigned)c[j].x < (unsigned)b.nv && (unsigned)c[j].y < (unsigned)b.nv &&
-                (unsigned)c[j].z < (unsigned)b.nv;
-    }
+    for (int j = 0; j < kTileItems; j++) c[j] = at<false, 12, const v3i_a4>(tri, (uint32_t)min(lane + 64 * j, cnt - 1));
     v2i_a4 p[kTileItems][3];
+    const uint32_t vmax = (uint32_t)b.nv - 1u;
 #pragma unroll
     for (int j = 0; j < kTileItems; j++) {
-        const v2i_a4 *xy = reinterpret_cast<const v2i_a4 *>(b.xy_in);
-        if (b.nv > 0) {   // (uniform)
-            p[j][0] = xy[ok[j] ? c[j].x : 0];
-            p[j][1] = xy[ok[j] ? c[j].y : 0];
-            p[j][2] = xy[ok[j] ? c[j].z : 0];
+        p[j][0] = at<WIDE, 8, const v2i_a4>(b.xy_in, min((uint32_t)c[j].x, vmax));
+        p[j][1] = at<WIDE, 8, const v2i_a4>(b.xy_in, min((uint32_t)c[j].y, vmax));
+        p[j][2] = at<WIDE, 8, const v2i_a4>(b.xy_in, min((uint32_t)c[j].z, vmax));
+    }
+    int32_t *org = b.org + 3 * (size_t)base;
+    int nflip = 0;
+    bool bad = false;
+    int ga[kTileItems], gb[kTileItems], gc[kTileItems];   // the triangle's groups, -1: no more
+    uint32_t edges = 0;   // 9 bits per item, at 9 j: the edges of ga, gb, gc
+    uint32_t edges3 = 0;  // item 3's
+#pragma unroll
+    for (int j = 0; j < kTileItems; j++) {
+        const bool live = lane + 64 * j < cnt;
+        const bool index = max(max((uint32_t)c[j].x, (uint32_t)c[j].y), (uint32_t)c[j].z) <= vmax;
+        // differences of valid coordinates fit 32 bits; others have failed
+        // the build already (code -2 ranks first)
+        const v2i_a4 pa = p[j][0], pb = p[j][1], pc = p[j][2];
+        const int ux = (int)((unsigned)pb.x - (unsigned)pa.x), uy = (int)((unsigned)pb.y - (unsigned)pa.y),
+                  vx = (int)((unsigned)pc.x - (unsigned)pa.x), vy = (int)((unsigned)pc.y - (unsigned)pa.y);
+        const long long l = (long long)ux * vy, r = (long long)uy * vx;
+        const bool flip = l < r, ok = index && l != r;
+        bad |= live && !ok;
+        const int cy = flip ? c[j].z : c[j].y, cz = flip ? c[j].y : c[j].z, cx = ok ? c[j].x : -1;   // -1: joins no group
+        nflip += __popcll(__ballot(flip && ok && live));
+        const v3i_a4 o = {cx, cy, cz};
+        if (live) at<false, 12, v3i_a4>(org, (uint32_t)(lane + 64 * j)) = o;
+        const int g0 = edge_owner(cx, cy, b.near) >> kShift, g1 = edge_owner(cy, cz, b.near) >> kShift,
+                  g2 = edge_owner(cz, cx, b.near) >> kShift;
+        // the groups in ga, gb, gc, each once, from the front
+        const bool s01 = g0 == g1, s02 = g0 == g2, s12 = g1 == g2, in = ok && live;
+        ga[j] = in ? g0 : -1;
+        gb[j] = !in ? -1 : (!s01 ? g1 : (!s02 ? g2 : -1));
+        gc[j] = in && !s01 && !s02 && !s12 ? g2 : -1;
+        const uint32_t ea = 1u | (s01 ? 2u : 0u) | (s02 ? 4u : 0u), eb = s01 ? 4u : (s12 ? 6u : 2u);
+        const uint32_t all = ea | (eb << 3) | (4u << 6);
+        if (j < 3)
+            edges |= all << (9 * j);
+        else
+            edges3 = all;
+    }
+    if (__any(bad)) {   // (uniform, rare)
+#pragma unroll
+        for (int j = 0; j < kTileItems; j++) {
+            if (lane + 64 * j >= cnt) continue;
+            const bool index = max(max((uint32_t)c[j].x, (uint32_t)c[j].y), (uint32_t)c[j].z) <= vmax;
+            const unsigned long long t = (unsigned long long)base + lane + 64 * j;
+            if (!index)
+                report(b.err, 1ull + t, -1);
+            else if (ga[j] < 0)
+                report(b.err, 1ull + t, -3);
         }
     }
-    int nflip = 0;
+    if (nflip && lane == 0) atomicAdd(&b.flips[kFlipPad * (blockIdx.x % kFlipStripes)], nflip);
+    WaveGroups w;
+    int pa[kTileItems], pb[kTileItems], pc[kTileItems];
+    place_items(w, ga, pa, lane);
+    place_items(w, gb, pb, lane);
+    place_items(w, gc, pc, lane);
+    // the places, one lane per group; entries past a list's end are dropped
+    // (the group's count says so)
+    int first = 0;
+    if (lane < w.rounds) first = atomicAdd(&b.count[w.group], w.n);
+    const int room = b.cap - first;
+    const size_t slot = (size_t)w.group * (uint32_t)b.cap + (uint32_t)first;
+    auto put = [&](const int rest[kTileItems], const int place[kTileItems], int which) {
 #pragma unroll
-    for (int j = 0; j < kTileItems; j++) {
-        const int lt = lt0 + 64 * j;
-        if (lt >= cnt) {
-            ok[j] = false;
-            continue;
-        }
-        const int t = base + lt;
-        if (!ok[j]) {
-            report(b.err, 1ull + t, -1);
-        } else {
-            // differences of valid coordinates fit 32 bits; others have
-            // failed the build already (code -2 ranks first)
-            const v2i_a4 pa = p[j][0], pb = p[j][1], pc = p[j][2];
-            const long long o = (long long)(int)((unsigned)pb.x - (unsigned)pa.x) * (int)((unsigned)pc.y - (unsigned)pa.y) -
-                                (long long)(int)((unsigned)pb.y - (unsigned)pa.y) * (int)((unsigned)pc.x - (unsigned)pa.x);
-            if (o == 0) {
-                report(b.err, 1ull + t, -3);
-                ok[j] = false;
-            } else if (o < 0) {
-                const int s = c[j].y;
-                c[j].y = c[j].z;
-                c[j].z = s;
-                nflip++;
+        for (int j = 0; j < kTileItems; j++) {
+            const int r = place[j] >> 16, rank = place[j] & 0xffff;   // (-1: lane 63's, unused)
+            const int lim = __shfl(room, r);
+            const int t = base + lane + 64 * j;
+            const uint32_t entry = list_entry<WIDE>(t, (int)(((j < 3 ? edges >> (9 * j) : edges3) >> (3 * which)) & 7u));
+            if (WIDE) {
+                const size_t to = (size_t)__shfl((unsigned long long)slot, r);
+                if (place[j] >= 0 && rank < lim) b.list[to + rank] = entry;
+            } else {
+                const uint32_t to = (uint32_t)__shfl((int)(uint32_t)slot, r) + (uint32_t)rank;
+                if (place[j] >= 0 && rank < lim) at<false, 4, uint32_t>(b.list, to) = entry;
+            }
+            if (rest[j] >= 0) {
+                const int k = atomicAdd(&b.count[rest[j]], 1);
+                if (k < b.cap) b.list[(size_t)rest[j] * (uint32_t)b.cap + k] = entry;
             }
         }
-        if (!ok[j]) c[j].x = -1;   // joins no group
-        *reinterpret_cast<v3i_a4 *>(b.org + 3 * (size_t)t) = c[j];
-    }
-    __syncthreads();
-    if (nflip) atomicAdd(&s_flip, nflip);
-    int g[kTileItems][3], place[kTileItems][3];
+    };
+    put(ga, pa, 0);
+    put(gb, pb, 1);
+    bool third = false;
 #pragma unroll
-    for (int j = 0; j < kTileItems; j++) {
-        triangle_groups(b, ok[j], c[j], g[j]);
-#pragma unroll
-        for (int i = 0; i < 3; i++) place[j][i] = bin_add(s_bin, b.count, g[j][i], w0);
-    }
-    __syncthreads();
-    for (int k = tid; k < kBins; k += 256) {
-        const int n = s_bin[k];
-        if (n) s_bin[k] = atomicAdd(&b.count[w0 + k], n);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kTileItems; j++) {
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            if (g[j][i] < 0) continue;
-            const int w = g[j][i] - w0, at = place[j][i] + ((unsigned)w < (unsigned)kBins ? s_bin[w] : 0);
-            if (at < b.cap) b.list[(size_t)g[j][i] * b.cap + at] = base + lt0 + 64 * j;
-        }
-    }
-    if (tid == 0 && s_flip) atomicAdd(b.nflipped, s_flip);
+    for (int j = 0; j < kTileItems; j++) third |= pc[j] >= 0 || gc[j] >= 0;
+    if (__any(third)) put(gc, pc, 2);
 }
 
 // The LDS edge table.  A slot is 0, or an edge with one or two half-edges:
-//   bits 0-30   the edge's other end
-//   bit 31      used
-//   bits 32-38  the owner's index in its group
-//   bit 39      the first half-edge leaves the owner
-//   bits 40-51  the first half-edge's id in the workgroup
-//   bits 52-63  the second's id + 1, 0 before it comes
-// Ids are below 3 kGroupCap = 3072.
+//   low word    the edge's other end (25 bits) and the owner's index in its
+//               group; WIDE: the other end and, in bit 31, a 1
+//   high word   bits 0-11   the first half-edge's id in the workgroup
+//               bit 12      it leaves the owner
+//               bits 13-19  a 1; WIDE: the owner's index
+//               bits 20-31  the second half-edge's id + 1, 0 before it comes
+// Ids are 4 x the entry's place in the list + the edge's index: at most
+// 4 kGroupCap - 2.
 struct GroupEdge {
     uint32_t other, own, out;   // other end; owner's index in the group; 1: leaves the owner
 };
-constexpr uint32_t kUsed = 1u << 31;
-static_assert(3 * kGroupCap < 4095, "ids of 12 bits");
+constexpr int kNarrowVerts = 1 << 25;
+static_assert(4 * kGroupCap <= 4096, "ids of 12 bits");
 
-// Edge i of triangle corners c, as its group sees it; false when it belongs to
-// another group.
-__device__ __forceinline__ bool group_edge(const BuildBuffers &b, v3i_a4 c, int i, int group, GroupEdge &e) {
-    const int u = i == 0 ? c.x : (i == 1 ? c.y : c.z), v = i == 0 ? c.y : (i == 1 ? c.z : c.x);
+template <bool WIDE>
+__device__ __forceinline__ unsigned long long edge_word(const GroupEdge &e, int id) {
+    const uint32_t hi = (uint32_t)id | (e.out << 12) | (WIDE ? e.own << 13 : 1u << 13);
+    return (unsigned long long)hi << 32 | (WIDE ? e.other | (1u << 31) : e.other | (e.own << 25));
+}
+template <bool WIDE>
+__device__ __forceinline__ bool slot_empty(unsigned long long s) {
+    return WIDE ? (uint32_t)s == 0u : (uint32_t)(s >> 32) == 0u;
+}
+// Whether slot s holds the edge of word w.
+template <bool WIDE>
+__device__ __forceinline__ bool same_edge(unsigned long long s, unsigned long long w) {
+    return (uint32_t)s == (uint32_t)w && (!WIDE || (((uint32_t)(s >> 32) ^ (uint32_t)(w >> 32)) >> 13 & 127u) == 0);
+}
+__device__ __forceinline__ bool same_direction(unsigned long long s, unsigned long long w) {
+    return (((uint32_t)(s >> 32) ^ (uint32_t)(w >> 32)) & (1u << 12)) == 0;
+}
+// Adds half-edge id as the second of a slot's edge.
+__device__ __forceinline__ unsigned add_second(unsigned long long *slot, int id) {
+    return atomicOr(reinterpret_cast<unsigned *>(slot) + 1, (unsigned)(id + 1) << 20);
+}
+
+// Edge u -> v as group sees it; false when it belongs to another group.
+__device__ __forceinline__ bool group_edge(const BuildBuffers &b, int u, int v, int group, GroupEdge &e) {
     const int o = edge_owner(u, v, b.near);
-    e.other = (uint32_t)(o == u ? v : u);
-    e.own = (uint32_t)o - ((uint32_t)group << kShift);
+    e.other = (uint32_t)(u ^ v ^ o);
+    e.own = (uint32_t)(o - (group << kShift));
     e.out = o == u;
     return (o >> kShift) == group;
 }
 
-__device__ __forceinline__ uint32_t edge_hash(const GroupEdge &e) {
-    return e.other * 0x9E3779B1u + e.own * 0x85EBCA6Bu;
+// Eight slots to an owner, which has about three edges; one that finds them
+// taken goes on into the next owner's.  By the distance d to the other end: a
+// grid's rows give each of an owner's edges a slot of its own (one neighbour in
+// the row, three consecutive ones in the next), other numberings spread over
+// the eight (0.17 further tries per edge on a Delaunay mesh along a Z-order
+// curve).  A hash of the other end, which lets the owners of a grid share
+// slots, cost 100 us more on the 33.5M grid.  Every fourth owner's slots are
+// turned by one, or the like edges of a row's owners would meet in four LDS
+// banks.
+__device__ __forceinline__ uint32_t edge_slot(uint32_t own, uint32_t d) {
+    static_assert(kSlots == 8 * kBuildGroup, "eight slots to an owner");
+    return 8u * own | ((((d & 3u) | (d > 8u ? 4u : 0u)) + (own >> 2)) & 7u);
 }
 
-// Puts half-edge id into the table; returns its edge's slot, or -1 when the
-// table is full.  dup: the edge has another half-edge in this direction, or
-// two already.
-__device__ __forceinline__ int edge_insert(unsigned long long *table, const GroupEdge &e, int id, bool &dup) {
-    uint32_t q = edge_hash(e) >> (32 - 10);
-    static_assert(kSlots == 1 << 10, "slots from the hash's top bits");
-    const uint32_t key = e.other | kUsed;
-    const unsigned long long mine = (unsigned long long)(e.own | (e.out << 7) | ((uint32_t)id << 8)) << 32 | key;
-    for (int k = 0; k < kSlots; k++) {
-        const unsigned long long was = atomicCAS(&table[q], 0ull, mine);
-        if (was == 0ull) return (int)q;
-        const uint32_t hi = (uint32_t)(was >> 32);
-        if ((uint32_t)was == key && ((hi ^ e.own) & 127u) == 0) {
-            const unsigned long long old = atomicOr(&table[q], (unsigned long long)(id + 1) << 52);
-            dup |= (old >> 52) != 0 || ((hi >> 7) & 1u) == e.out;
-            return (int)q;
-        }
-        q = (q + 1) & (kSlots - 1);
-    }
-    return -1;
-}
-
-// The id of the other half-edge in slot s, or -1 on the boundary.
-__device__ __forceinline__ int edge_mate(unsigned long long s, int id) {
-    const int first = (int)(s >> 40) & 0xfff, second = (int)(s >> 52) - 1;
-    return id == first ? second : first;
-}
-
+// One workgroup per group: the triangles of its list, their edges into the
+// table, then each half-edge's twin from its slot.  33.5M-triangle grid: 0.39
+// ms for 1.0 GB (the list, 1.2 x 12 bytes a triangle of corners, 12 of twins);
+// bound by its 367 vector instructions a wave (three quarters of the time).
+// The three edges' first tries go out together, without branches: one loop per
+// edge took 0.53 ms, 430 vector and 474 scalar instructions.
+template <bool WIDE>
 __global__ void __launch_bounds__(256) k_match(BuildBuffers b) {
-    __shared__ unsigned long long s_table[kSlots];
-    __shared__ int s_tri[kGroupCap];
+    __shared__ unsigned long long s_table[kSlots + 64];   // 64 for lanes with nothing to add
+    __shared__ int s_tri[kGroupCap];   // a list entry's first half-edge
     constexpr int kIt = kGroupCap / 256;
     const int tid = threadIdx.x, g = xcd_run(blockIdx.x, b.nparts);
+    if (blockIdx.x == 0 && tid < 64) {   // (a whole wave) k_orient's counts of flipped triangles
+        static_assert(kFlipStripes == 64, "one lane per stripe");
+        int f = b.flips[kFlipPad * tid];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) f += __shfl_xor(f, d);
+        if (tid == 0) *b.nflipped = f;
+    }
     const int n = b.count[g];
     if (n == 0) return;   // (uniform)
     if (n > b.cap) {
@@ -326,37 +370,89 @@ __global__ void __launch_bounds__(256) k_match(BuildBuffers b) {
         }
         return;
     }
-    const int32_t *list = b.list + (size_t)g * b.cap;
-    int t[kIt];
+    const uint32_t *list = b.list + (size_t)g * (uint32_t)b.cap;
+    uint32_t rec[kIt];
 #pragma unroll
-    for (int j = 0; j < kIt; j++) {
-        if (256 * j >= n) continue;   // (uniform)
-        t[j] = list[256 * j + tid < n ? 256 * j + tid : 0];
-    }
-    for (int k = tid; k < kSlots; k += 256) s_table[k] = 0ull;
+    for (int j = 0; j < kIt; j++)
+        if (256 * j < n) rec[j] = list[min(256 * j + tid, n - 1)];   // (uniform)
+    for (int k = tid; k < (kSlots + 64) / 2; k += 256) reinterpret_cast<ulonglong2 *>(s_table)[k] = ulonglong2{0ull, 0ull};
     v3i_a4 c[kIt];
 #pragma unroll
     for (int j = 0; j < kIt; j++) {
         if (256 * j >= n) continue;
-        c[j] = *reinterpret_cast<const v3i_a4 *>(b.org + 3 * (size_t)t[j]);
-        s_tri[256 * j + tid] = t[j];
+        const uint32_t t = WIDE ? rec[j] : rec[j] >> 3;
+        c[j] = at<WIDE, 12, const v3i_a4>(b.org, t);
+        s_tri[256 * j + tid] = 3 * (int)t;
     }
     __syncthreads();
-    int slot[kIt][3];   // -1: not this group's
-    bool full = false;
+    const uint32_t v0 = (uint32_t)g << kShift;
+    uint32_t slots[kIt];   // eleven bits per edge
+    uint32_t mine[kIt];    // bit i: edge i is the group's
+    bool full = false, dup = false;
 #pragma unroll
     for (int j = 0; j < kIt; j++) {
+        slots[j] = mine[j] = 0;
         if (256 * j >= n) continue;
+        const uint32_t v[4] = {(uint32_t)c[j].x, (uint32_t)c[j].y, (uint32_t)c[j].z, (uint32_t)c[j].x};
+        const int id = 4 * (256 * j + tid);
+        unsigned long long word[3], was[3];
+        uint32_t q[3], in;
+        if (!WIDE)
+            in = 256 * j + tid < n ? rec[j] & 7u : 0u;
+        else
+            in = 0;
 #pragma unroll
         for (int i = 0; i < 3; i++) {
-            slot[j][i] = -1;
             GroupEdge e;
-            if (256 * j + tid >= n || !group_edge(b, c[j], i, g, e)) continue;
-            bool dup = false;
-            slot[j][i] = edge_insert(s_table, e, 3 * (256 * j + tid) + i, dup);
-            full |= slot[j][i] < 0;
-            if (dup) report(b.err, 1ull + b.nt + 3ull * t[j] + i, -4);
+            if (!WIDE) {
+                // an edge of this group with both ends in it belongs to the
+                // lower (near ends); else its owner is the end that is: the
+                // lower index from the group's first vertex, either way
+                const uint32_t x = v[i] - v0, y = v[i + 1] - v0;
+                e.own = min(x, y);
+                e.out = e.own == x;
+                e.other = max(x, y) + v0;
+            } else {
+                const bool is = group_edge(b, (int)v[i], (int)v[i + 1], g, e);
+                in |= is && 256 * j + tid < n ? 1u << i : 0u;
+            }
+            word[i] = edge_word<WIDE>(e, id + i);
+            q[i] = (in >> i) & 1u ? edge_slot(e.own, e.other - v0 - e.own) : (uint32_t)kSlots + (tid & 63);
         }
+        // first tries of the three edges in flight together
+#pragma unroll
+        for (int i = 0; i < 3; i++) was[i] = atomicCAS(&s_table[q[i]], 0ull, word[i]);
+        uint32_t miss = 0;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const bool taken = !slot_empty<WIDE>(was[i]) && ((in >> i) & 1u), same = same_edge<WIDE>(was[i], word[i]);
+            if (taken && same) {
+                add_second(&s_table[q[i]], id + i);
+                dup |= same_direction(was[i], word[i]);
+            }
+            miss |= taken && !same ? 1u << i : 0u;
+        }
+        for (int k = 0; miss; k++) {
+            const int i = __ffs((int)miss) - 1;
+            const unsigned long long x = i == 0 ? word[0] : (i == 1 ? word[1] : word[2]);
+            const uint32_t to = ((i == 0 ? q[0] : (i == 1 ? q[1] : q[2])) + 1) & (kSlots - 1);
+            q[0] = i == 0 ? to : q[0];
+            q[1] = i == 1 ? to : q[1];
+            q[2] = i == 2 ? to : q[2];
+            const unsigned long long y = atomicCAS(&s_table[to], 0ull, x);
+            const bool taken = !slot_empty<WIDE>(y), same = same_edge<WIDE>(y, x);
+            if (taken && same) {
+                add_second(&s_table[to], id + i);
+                dup |= same_direction(y, x);
+            }
+            if (!taken || same) miss &= miss - 1;
+            if (k >= 3 * kSlots) {   // no slot left
+                full = true;
+                break;
+            }
+        }
+        slots[j] = q[0] | (q[1] << 11) | (q[2] << 22);   // (of the third the low ten bits: an edge's)
+        mine[j] = in;
     }
     if (__syncthreads_or(full)) {   // (uniform)
         if (tid == 0) {
@@ -368,14 +464,23 @@ __global__ void __launch_bounds__(256) k_match(BuildBuffers b) {
 #pragma unroll
     for (int j = 0; j < kIt; j++) {
         if (256 * j >= n) continue;
+        const uint32_t t = WIDE ? rec[j] : rec[j] >> 3;
+        const uint32_t id = 4u * (uint32_t)(256 * j + tid);
 #pragma unroll
         for (int i = 0; i < 3; i++) {
-            if (slot[j][i] < 0) continue;
-            const int m = edge_mate(s_table[slot[j][i]], 3 * (256 * j + tid) + i);
-            const int q = m < 0 ? 0 : (int)((unsigned)m / 3u) & (kGroupCap - 1);   // (ids of a repeated edge run together)
-            b.twin[3 * (size_t)t[j] + i] = m < 0 ? -1 : 3 * s_tri[q] + (m - 3 * q);
+            if (!((mine[j] >> i) & 1u)) continue;
+            const uint32_t s = reinterpret_cast<const uint32_t *>(s_table)[2 * ((slots[j] >> (11 * i)) & (kSlots - 1)) + 1];
+            const uint32_t first = s & 0xfffu, second = s >> 20;
+            const bool lead = first == id + i;
+            // a third half-edge's id has run together with the second's: one
+            // of the two at least does not find its own
+            dup |= !lead && second != id + i + 1;
+            const uint32_t m = lead ? second - 1u : first;
+            const int tw = s_tri[(m >> 2) & (kGroupCap - 1)] + (int)(m & 3u);
+            at<WIDE, 4, int32_t>(b.twin, 3u * t + i) = second == 0u ? -1 : tw;
         }
     }
+    if (dup) report(b.err, 1ull + b.nt, -4);
 }
 
 // ---- groups too large for k_match ------------------------------------------
@@ -403,10 +508,12 @@ __global__ void __launch_bounds__(256) k_scatter(BuildBuffers b) {
     for (int i = 0; i < 3; i++) {
         unsigned long long todo = __ballot(g[i] >= 0 && b.cursor[g[i] < 0 ? 0 : g[i]] != 0);
         while (todo) {   // (uniform)
-            const int gl = __builtin_amdgcn_readlane(g[i], __ffsll((long long)todo) - 1);
+            const int leader = __ffsll((long long)todo) - 1, gl = __builtin_amdgcn_readlane(g[i], leader);
             const unsigned long long same = __ballot(g[i] == gl);
-            const int at = add_together(&b.cursor[gl], same, lane) - 1;
-            if ((same >> lane) & 1) b.list[at] = t;
+            int k = 0;
+            if (lane == leader) k = atomicAdd(&b.cursor[gl], __popcll(same)) - 1;
+            k = __builtin_amdgcn_readlane(k, leader) + __popcll(same & ((1ull << lane) - 1ull));
+            if ((same >> lane) & 1) b.list[k] = (uint32_t)t;
             todo &= ~same;
         }
     }
@@ -419,18 +526,19 @@ __global__ void __launch_bounds__(256) k_scatter(BuildBuffers b) {
 __device__ void match_class(const BuildBuffers &b, unsigned long long *s_table, int *s_he, int *s_n, ClassTask task) {
     const int tid = threadIdx.x, g = task.group, n = b.count[g], first = b.cursor[g] - 1 - n;
     const uint32_t classes = (uint32_t)task.classes;
-    auto mine = [&](const GroupEdge &e) {
-        const uint32_t x = edge_hash(e);
-        return ((x ^ (x >> 15)) * 0x2C1B3C6Du >> 8) % classes == (uint32_t)task.cls;
+    auto hash = [](const GroupEdge &e) {
+        const uint32_t x = e.other * 0x9E3779B1u + e.own * 0x85EBCA6Bu;
+        return (x ^ (x >> 15)) * 0x2C1B3C6Du;
     };
     auto failed = [&]() { return __hip_atomic_load(b.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0ull; };
     // every edge of the class, f(half-edge, edge)
     auto each = [&](int k, auto f) {
-        const int t = b.list[first + k];
+        const int t = (int)b.list[first + k];
         const v3i_a4 c = *reinterpret_cast<const v3i_a4 *>(b.org + 3 * (size_t)t);
         for (int i = 0; i < 3; i++) {
+            const int u = i == 0 ? c.x : (i == 1 ? c.y : c.z), v = i == 0 ? c.y : (i == 1 ? c.z : c.x);
             GroupEdge e;
-            if (group_edge(b, c, i, g, e) && mine(e)) f(3 * t + i, e);
+            if (group_edge(b, u, v, g, e) && (hash(e) >> 8) % classes == (uint32_t)task.cls) f(3 * t + i, e);
         }
     };
     __syncthreads();
@@ -442,14 +550,21 @@ __device__ void match_class(const BuildBuffers &b, unsigned long long *s_table, 
         if (k0 + tid >= n) continue;
         each(k0 + tid, [&](int h, const GroupEdge &e) {
             const int id = atomicAdd(s_n, 1);
-            bool dup = false;
-            if (id < kSlots) {
-                s_he[id] = h;
-                full |= edge_insert(s_table, e, id, dup) < 0;
-            }
             full |= id >= kSlots;
-            if (dup) report(b.err, 1ull + b.nt + h, -4);
-            again |= dup;
+            if (id >= kSlots) return;
+            s_he[id] = h;
+            const unsigned long long x = edge_word<true>(e, id);
+            uint32_t q = hash(e) >> 22;
+            for (int k = 0; k < kSlots; k++, q = (q + 1) & (kSlots - 1)) {   // room for all of the ids
+                const unsigned long long was = atomicCAS(&s_table[q], 0ull, x);
+                if (was == 0ull) break;
+                if (!same_edge<true>(was, x)) continue;
+                if ((add_second(&s_table[q], id) >> 20) != 0 || same_direction(was, x)) {
+                    report(b.err, 1ull + b.nt + h, -4);
+                    again = true;
+                }
+                break;
+            }
         });
     }
     if (__syncthreads_or(again)) return;   // (uniform)
@@ -457,7 +572,7 @@ __device__ void match_class(const BuildBuffers &b, unsigned long long *s_table, 
         for (int k = tid; k < kSlots; k += 256) {
             const unsigned long long s = s_table[k];
             if (s == 0ull) continue;
-            const int x = s_he[(int)(s >> 40) & 0xfff], m = (int)(s >> 52) - 1;
+            const int x = s_he[(int)(s >> 32) & 0xfff], m = (int)(s >> 52) - 1;
             b.twin[x] = m < 0 ? -1 : s_he[m];
             if (m >= 0) b.twin[s_he[m]] = x;
         }
@@ -618,8 +733,14 @@ BuildSizes build_sizes(int64_t nv, int64_t nt) {
 hipError_t launch_build(const BuildBuffers &b, hipStream_t s) {
     const int tiles = (b.nt + kTileTri - 1) / kTileTri;
     const int copies = (int)(((int64_t)b.nv + 256 * kCopyItems - 1) / (256 * kCopyItems));
-    if (tiles + copies > 0) hipLaunchKernelGGL(k_orient, dim3(tiles + copies), dim3(256), 0, s, b, tiles);
-    if (tiles > 0 && b.nparts > 0) hipLaunchKernelGGL(k_match, dim3(b.nparts), dim3(256), 0, s, b);
+    // not wide: arrays within the reach of 32-bit byte offsets, entries with
+    // their edges, and an edge in one word of the table
+    const bool wide = b.nt >= 1 << 28 || b.nv >= kNarrowVerts;
+    static_assert((long long)kNarrowVerts / kBuildGroup * kBuildGroupCap * 4 < 1ll << 32, "lists in reach");
+    if (tiles + copies > 0)
+        hipLaunchKernelGGL(wide ? k_orient<true> : k_orient<false>, dim3(tiles + copies), dim3(256), 0, s, b, tiles);
+    if (tiles > 0 && b.nparts > 0)
+        hipLaunchKernelGGL(wide ? k_match<true> : k_match<false>, dim3(b.nparts), dim3(256), 0, s, b);
     return hipGetLastError();
 }
 

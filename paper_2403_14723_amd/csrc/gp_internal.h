@@ -241,8 +241,14 @@ struct BuildSizes {
 };
 BuildSizes build_sizes(int64_t nv, int64_t nt);
 // Ends of an edge are near below 8,192 or an eighth of the vertices: a grid's
-// rows (up to that wide) are, most edges of a random numbering are not.
-inline int32_t build_near(int32_t nv) { return nv / 8 < 8192 ? nv / 8 + 1 : 8192; }
+// rows (up to that wide) are, most edges of a random numbering are not.  Two
+// ends in one group always are.
+inline int32_t build_near(int32_t nv) {
+    return nv / 8 < kBuildGroup ? kBuildGroup : (nv / 8 < 8192 ? nv / 8 : 8192);
+}
+// triangles flipped, counted in stripes a cache line apart
+constexpr int kFlipStripes = 64;
+constexpr int kFlipPad = 32;
 
 struct BuildBuffers {
     const int32_t *xy_in;   // 2 nv, 4-byte aligned
@@ -250,9 +256,10 @@ struct BuildBuffers {
     const int32_t *tri;
     int32_t nv, nt, nparts, cap, near;
     int32_t *org, *twin;
-    int32_t *list;          // cap per group: its triangles
+    uint32_t *list;         // cap per group: its triangles
     ClassTask *tasks;
     // zeroed before the build
+    int32_t *flips;         // kFlipStripes, kFlipPad apart
     int32_t *count;         // nparts: triangles per group
     int32_t *cursor;        // nparts: not 0 for a large group (then its place in list + 1)
     unsigned long long *err;   // 0, or the highest ~(rank << 8 | -code) seen

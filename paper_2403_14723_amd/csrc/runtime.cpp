@@ -378,10 +378,14 @@ struct BuildReport {
     int32_t nflipped, nbig, total, ntasks;
 };
 
+// the report, then the flip counters; each vertex group's two counters follow
+constexpr size_t kBuildFlipsAt = 256;
+constexpr size_t kBuildZeroBytes = kBuildFlipsAt + sizeof(int32_t) * gp::kFlipStripes * gp::kFlipPad;
+
 // Device scratch of one build.
 size_t build_scratch_bytes(int64_t nv, int64_t nt, bool inputs_on_device) {
     const gp::BuildSizes z = gp::build_sizes(nv, nt);
-    return align_up(sizeof(BuildReport) + 2 * sizeof(int32_t) * (size_t)z.parts) + arena_bytes<int32_t>(z.list) +
+    return align_up(kBuildZeroBytes + 2 * sizeof(int32_t) * (size_t)z.parts) + arena_bytes<uint32_t>(z.list) +
            arena_bytes<gp::ClassTask>(z.tasks) + (inputs_on_device ? 0 : arena_bytes<int32_t>(3 * nt));
 }
 
@@ -440,7 +444,7 @@ int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, in
     b.near = gp::build_near(nv);
     b.org = m->org;
     b.twin = m->twin;
-    const size_t zero_bytes = sizeof(BuildReport) + 2 * sizeof(int32_t) * (size_t)b.nparts;
+    const size_t zero_bytes = kBuildZeroBytes + 2 * sizeof(int32_t) * (size_t)b.nparts;
     char *zero = a.take<char>(zero_bytes);
     BuildReport *rep = reinterpret_cast<BuildReport *>(zero);
     j.report_dev = rep;
@@ -449,9 +453,10 @@ int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, in
     b.nbig = &rep->nbig;
     b.total = &rep->total;
     b.ntasks = &rep->ntasks;
-    b.count = reinterpret_cast<int32_t *>(zero + sizeof(BuildReport));
+    b.flips = reinterpret_cast<int32_t *>(zero + kBuildFlipsAt);
+    b.count = reinterpret_cast<int32_t *>(zero + kBuildZeroBytes);
     b.cursor = b.count + b.nparts;
-    b.list = a.take<int32_t>(z.list);
+    b.list = a.take<uint32_t>(z.list);
     b.tasks = a.take<gp::ClassTask>(z.tasks);
     int32_t *tri_dev = in_dev ? nullptr : a.take<int32_t>(nh);
     b.tri = in_dev ? tri : tri_dev;

@@ -48,6 +48,20 @@ def unused_vertices():
     return np.concatenate([np.zeros((700_001, 2), np.int32), m.xy]), m.tri + 700_001
 
 
+def spread_vertices():
+    """2^25 and more vertices: a mesh's own lie far apart, in no order."""
+    m = W.scrambled(W.jittered_grid(100, seed=13), 13)
+    step = (1 << 25) // m.nv + 1
+    xy = np.zeros((m.nv * step, 2), np.int32)
+    xy[::step] = m.xy
+    return xy, (m.tri.astype(np.int64) * step).astype(np.int32)
+
+
+def many_vertices():
+    m = W.jittered_grid(70, seed=14)
+    return np.concatenate([np.zeros((1 << 25, 2), np.int32), m.xy]), m.tri + (1 << 25)
+
+
 CASES = [("one", lambda: grid_prefix(1, 1, 1)), ("tile-1", lambda: grid_prefix(40, 1023, 2)),
          ("tile", lambda: grid_prefix(40, 1024, 3)), ("tile+1", lambda: grid_prefix(40, 1025, 4)),
          ("rows", lambda: grid_prefix(317, 2 * 317 * 317 - 5, 5)),
@@ -56,7 +70,7 @@ CASES = [("one", lambda: grid_prefix(1, 1, 1)), ("tile-1", lambda: grid_prefix(4
          ("scattered_small", lambda: scrambled_prefix(60, 7001, 7)),
          ("scattered", lambda: scrambled_prefix(340, 231_111, 8)),
          ("delaunay", lambda: (lambda m: (m.xy, m.tri))(W.random_delaunay(30_000, 9))),
-         ("unused_vertices", unused_vertices),
+         ("unused_vertices", unused_vertices), ("spread_vertices", spread_vertices), ("many_vertices", many_vertices),
          # groups about the LDS capacity (2,048) and far above it
          ("fan_900", lambda: fan(900)), ("fan_1024", lambda: fan(1024)), ("fan_1025", lambda: fan(1025)),
          ("fan_hub_last", lambda: fan(2000, True)), ("fan_30000", lambda: fan(30_000)),
