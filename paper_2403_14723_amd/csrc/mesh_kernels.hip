@@ -381,14 +381,20 @@ __global__ void __launch_bounds__(1024) k_label(const MeshDesc *__restrict__ des
 //
 // One thread per triangle.  Phase 1 derives each triangle's frontier bits
 // and seed bit from its own longest-edge label and its neighbours' (Section
-// 6.2-6.3) and keeps the byte in LDS.  Phase 2 turns around the ends of every
+// 6.2-6.3) and keeps them in LDS.  Phase 2 turns around the ends of every
 // frontier half-edge (Section 6.5): a candidate in the tile reads its
 // frontier bit from LDS; one outside derives it from the longest-edge labels,
 // which no kernel changes during this pass (the tile's label bytes are
 // written back with their longest-edge bits unchanged).  Each thread loads
 // its triangles' twins and stores their next'/prev' itself (12 contiguous
-// bytes per triangle); the label and loop bytes go out through LDS in whole
-// words.
+// bytes per triangle).
+//
+// Vector instructions bound this kernel, so half-edges are slots 4t + i in it
+// (the triangle and the local index are a shift and a mask), choices among a
+// triangle's edges come from tables of its three frontier bits, and counts
+// from ballots: 536 vector instructions per wave of 128 triangles, where half-
+// edge ids (a division by 3 for each), masks and a block scan took 772.  33.5M
+// grid: 0.415 -> 0.350 ms for 1.32 GB; 2.1M grid 32 -> 25 us.
 // ---------------------------------------------------------------------------
 
 // Loop byte of the minimum's triangle: (min(len, kPlMax) << 2) | local
@@ -427,69 +433,65 @@ __device__ __forceinline__ bool claim_won(const MeshDesc &d, uint32_t old, int m
 // with the bit clear.
 constexpr uint32_t kStoredBit = 1u << 6;
 
-// Copies n bytes from LDS src to global dst; both 4-byte aligned.
-__device__ __forceinline__ void store_bytes_from_lds(gu8 dst, const uint8_t *src, int n) {
-    const int B = blockDim.x, tid = threadIdx.x;
-    const uint32_t *s4 = reinterpret_cast<const uint32_t *>(src);
-    GLOBAL uint32_t *d4 = reinterpret_cast<GLOBAL uint32_t *>(dst);
-    for (int k = tid; k < n / 4; k += B) d4[k] = s4[k];
-    for (int k = (n & ~3) + tid; k < n; k += B) dst[k] = src[k];
+// Slots: half-edge 3t + i as 4t + i; a boundary twin (-1) is kNoSlot, the only
+// slot of local index 3.
+constexpr uint32_t kNoSlot = ~0u;
+__device__ __forceinline__ uint32_t he_slot(int h) {   // h >= -1
+    return ((uint32_t)h + (uint32_t)h / 3u) | (uint32_t)(h >> 31);
 }
+__device__ __forceinline__ int he_of_slot(uint32_t s) { return (int)(s - (s >> 2)); }
+__device__ __forceinline__ uint32_t next_slot(uint32_t s) { return (s & 2u) ? s - 2u : s + 1u; }
+__device__ __forceinline__ uint32_t prev_slot(uint32_t s) { return (s & 3u) ? s - 1u : s + 2u; }
 
-// Frontier test of half-edge c during k_relink.  Lc is the longest-edge label
-// of c's triangle, or -1 when it has not been loaded.
+// What a turn in k_relink reads.
 struct TileLabels {
     TwinView twin;
-    gcu8 tflag;                          // longest-edge bits (0-1) only are read
-    const int *s_tw;                     // the tile's twins
-    const uint8_t *s_f;                  // the tile's label bytes, frontier bits set
-    int base, cnt;                       // the tile's triangles [base, base + cnt)
+    gcu8 tflag;               // longest-edge bits (0-1) only are read
+    const uint32_t *s_slot;   // the tile's half-edges by slot: their twins' slots
+    const uint32_t *s_lab;    // its triangles' label bytes
+    uint32_t base, cnt;       // the tile's triangles [base, base + cnt)
 };
 
-// One step of a turn around a vertex at candidate c (Lc: the longest-edge
+// One step of a turn around a vertex at candidate slot c (Lc: the longest-edge
 // label of c's triangle, or -1 when not loaded).  Returns 1 when c is a
 // frontier half-edge (the turn ends there), 0 after moving c to the next
 // candidate (next: c <- next(twin(c)), else c <- prev(twin(c))), -1 when the
 // mesh is inconsistent.
-__device__ __forceinline__ int turn_step(const TileLabels &T, int &c, int &Lc, bool next) {
-    const int tc = tri_of(c), lc = c - 3 * tc, kk = tc - T.base;
-    int g, Lg = -1;
-    if ((unsigned)kk < (unsigned)T.cnt) {
-        if (fbit(T.s_f[kk], lc)) return 1;
-        g = T.s_tw[3 * kk + lc];
-        if (g < 0) return -1;   // a non-frontier edge is interior
+__device__ __forceinline__ int turn_step(const TileLabels &T, uint32_t &c, int &Lc, bool next) {
+    const uint32_t tc = c >> 2, lc = c & 3u, kk = tc - T.base;
+    uint32_t g;
+    int Lg = -1;
+    if (kk < T.cnt) {
+        if (fbit(T.s_lab[kk], (int)lc)) return 1;
+        g = T.s_slot[4 * kk + lc];
+        if (g == kNoSlot) return -1;   // a non-frontier edge is interior
     } else {
-        g = T.twin[c];
+        g = he_slot(T.twin[he_of_slot(c)]);
         const uint32_t fc = Lc < 0 ? T.tflag[tc] : 0u;   // in flight with the twin
-        if (g < 0) return 1;   // boundary
+        if (g == kNoSlot) return 1;   // boundary
         if (Lc < 0) Lc = (int)(fc & 3u);
-        if (Lc != lc) {   // c is not its triangle's longest edge
+        if (Lc != (int)lc) {   // c is not its triangle's longest edge
             // twin(c)'s triangle is often back in the tile, whose label
             // bytes (longest-edge bits unchanged) are in LDS
-            const int tg = tri_of(g), kg = tg - T.base;
-            Lg = (int)(((unsigned)kg < (unsigned)T.cnt ? (uint32_t)T.s_f[kg] : (uint32_t)T.tflag[tg]) & 3u);
-            if (Lg != g - 3 * tg) return 1;   // nor is twin(c)
+            const uint32_t tg = g >> 2, kg = tg - T.base;
+            Lg = (int)((kg < T.cnt ? T.s_lab[kg] : (uint32_t)T.tflag[tg]) & 3u);
+            if (Lg != (int)(g & 3u)) return 1;   // nor is twin(c)
         }
     }
-    c = next ? he_next(g) : he_prev(g);
+    c = next ? next_slot(g) : prev_slot(g);
     Lc = Lg;
     return 0;
 }
 
-// The whole turn from candidate c: the frontier half-edge it ends at, or -1.
-__device__ __forceinline__ int run_turn(const TileLabels &T, int c, int Lc, bool next) {
+// The whole turn from candidate c: the frontier slot it ends at, or kNoSlot.
+__device__ __forceinline__ uint32_t run_turn(const TileLabels &T, uint32_t c, bool next) {
+    int Lc = -1;
     for (int k = 0; k < kRotGuard; k++) {
         const int r = turn_step(T, c, Lc, next);
-        if (r != 0) return r > 0 ? c : -1;
+        if (r != 0) return r > 0 ? c : kNoSlot;
     }
-    return -1;
+    return kNoSlot;
 }
-
-// Records a barrier tip found in a k_relink tile in the tile's LDS list
-// (appended to the global list once per block); straight to the global list
-// when the LDS list is full.
-__device__ __forceinline__ void tile_tip(int *s_tip, int *s_ntip, int tcap, int local_he, int base, RunCounters *rc,
-                                         ListEntry *tips, int cap_tips, const MeshDesc &d, int mi, bool &err);
 
 // Appends barrier tip he of mesh mi to the tip list.
 __device__ __forceinline__ void push_tip(RunCounters *rc, ListEntry *tips, int cap_tips, const MeshDesc &d, int mi,
@@ -504,24 +506,41 @@ __device__ __forceinline__ void push_tip(RunCounters *rc, ListEntry *tips, int c
     }
 }
 
-__device__ __forceinline__ void tile_tip(int *s_tip, int *s_ntip, int tcap, int local_he, int base, RunCounters *rc,
-                                         ListEntry *tips, int cap_tips, const MeshDesc &d, int mi, bool &err) {
-    const int i = atomicAdd(s_ntip, 1);
-    if (i < tcap)
-        s_tip[i] = local_he;
-    else
-        push_tip(rc, tips, cap_tips, d, mi, 3 * base + local_he, err);
+// Frontier bit of slot c of a triangle outside the tile whose longest-edge
+// label is Lc.
+__device__ __forceinline__ bool outside_fbit(const TileLabels &T, uint32_t c, uint32_t Lc) {
+    if (Lc == (c & 3u)) return false;
+    const uint32_t g = he_slot(T.twin[he_of_slot(c)]);
+    return g == kNoSlot || (T.tflag[g >> 2] & 3u) != (g & 3u);
 }
 
-// Frontier bit of half-edge c of a triangle outside the tile whose
-// longest-edge label is Lc.
-__device__ __forceinline__ bool outside_fbit(const TileLabels &T, int c, int Lc) {
-    const int tc = c / 3, lc = c - 3 * tc;
-    if (Lc == lc) return false;
-    const int g = T.twin[c];
-    if (g < 0) return true;
-    const int tg = g / 3;
-    return (int)(T.tflag[tg] & 3u) != g - 3 * tg;
+// Tables of a triangle's frontier bits F (edge i: bit i), two bits each.  A
+// triangle has at most one frontier edge followed by an edge that is not, and
+// at most one preceded by one.
+//   kCrossNext  that following edge: next' of the frontier edge before it turns
+//               across it (3: there is none)
+//   kCrossPrev  that preceding edge: prev' of the frontier edge after it turns
+//               across it
+constexpr uint32_t cross_table(bool next) {
+    uint32_t t = 0;
+    for (uint32_t F = 0; F < 8; F++) {
+        uint32_t e = 3;
+        for (uint32_t i = 0; i < 3; i++) {
+            const uint32_t x = next ? (i + 1) % 3 : (i + 2) % 3;
+            if (((F >> i) & 1u) && !((F >> x) & 1u)) e = x;
+        }
+        t |= e << (2 * F);
+    }
+    return t;
+}
+constexpr uint32_t kCrossNext = cross_table(true), kCrossPrev = cross_table(false);
+
+__device__ __forceinline__ uint32_t pick3(uint32_t i, uint32_t a, uint32_t b, uint32_t c) {
+    return i == 0 ? a : (i == 1 ? b : c);
+}
+
+__host__ __device__ inline size_t relink_lds_bytes(int tile) {
+    return sizeof(int) * (4 * (size_t)tile + 4 * (size_t)tile + (size_t)tile + 4 + (size_t)tile / 4);
 }
 
 // CM: some mesh of the run is compact (else the int32 twins are read
@@ -533,25 +552,26 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
                                                   ListEntry *walk, int32_t *walk_counts, int walk_cap,
                                                   uint64_t *agg, int cmp_tb) {
     extern __shared__ int4 lds_raw[];
-    int *lds = reinterpret_cast<int *>(lds_raw);
-    const int B = blockDim.x, tid = threadIdx.x, TB = B * ITEMS;
-    int *s_tw = lds;                                            // the tile's twins
-    uint8_t *s_f = reinterpret_cast<uint8_t *>(lds + 3 * TB);   // label bytes
-    uint8_t *s_pl = s_f + TB;                                   // loop bytes
-    int *s_q = reinterpret_cast<int *>(s_pl + TB);              // queued turns, 2 ints each
-    const int qcap = TB / 2;
-    int *s_tip = s_q + 2 * qcap;                                // barrier tips found here
+    const int B = blockDim.x, tid = threadIdx.x, TB = B * ITEMS, lane = __lane_id();
+    uint32_t *s_slot = reinterpret_cast<uint32_t *>(lds_raw);   // by slot in the tile: the twin's slot
+    uint2 *s_q = reinterpret_cast<uint2 *>(s_slot + 4 * TB);    // queued turns (at most two per triangle)
+    uint32_t *s_lab = reinterpret_cast<uint32_t *>(s_q + 2 * TB);   // label bytes; after them one without frontier edges
+    int *s_tip = reinterpret_cast<int *>(s_lab + TB + 4);           // barrier tips found here
     const int tcap = TB / 4;
-    __shared__ int s_ntip;
+    // queued turns; open seeds; settled loops << 16 | their half-edges; tips; the open seeds' place in the walk list
+    __shared__ int s_nq, s_nopen, s_tot, s_ntip, s_wbase;
     // loops settled here, per compaction tile, when the tile's triangles
     // span several of them (a relink tile of <= 1024 triangles, compaction
     // tiles of >= 64: at most 17)
     constexpr int kSpan = 1024 / 64 + 1;
     __shared__ int s_aggc[kSpan], s_aggl[kSpan];
-    if (threadIdx.x == 0) s_ntip = 0;
-    if (threadIdx.x < kSpan) {
-        s_aggc[threadIdx.x] = 0;
-        s_aggl[threadIdx.x] = 0;
+    if (tid == 0) {
+        s_nq = s_nopen = s_tot = s_ntip = 0;
+        s_lab[TB] = 0;
+    }
+    if (tid < kSpan) {
+        s_aggc[tid] = 0;
+        s_aggl[tid] = 0;
     }
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int mi = find_mesh<1>(descs, nmesh, tile);
@@ -568,137 +588,89 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     // Each thread loads its triangles' twins itself (12 contiguous bytes per
     // triangle, so a wave's loads are contiguous) and issues the label
     // gathers as soon as they arrive; the twins go to LDS for the turns of
-    // phase 2, published by the barrier after the label bytes.  Every load is
-    // issued unconditionally (indices clamped to 0, results masked after) so
-    // that all of them are in flight together.
-    int tw[ITEMS][3];
-    uint32_t f[ITEMS], fn[ITEMS][3];
+    // phase 2.  Every load is issued unconditionally (indices clamped,
+    // results masked after) so that all of them are in flight together.
+    uint32_t s[ITEMS][3], own[ITEMS], fn[ITEMS][3];
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
         const int lt = j * B + tid;
-        const bool ok = lt < cnt;
-        const int hj = 3 * (base + (ok ? lt : 0));
+        const int t = base + (lt < cnt ? lt : 0);
         v3i_a4 g;
         if (!twin.t16) {   // (uniform) one 12-byte load
-            g = *(GLOBAL const v3i_a4 *)(twin.t32 + hj);
+            g = *(GLOBAL const v3i_a4 *)(twin.t32 + 3 * t);
         } else {
-            g.x = twin[hj];
-            g.y = twin[hj + 1];
-            g.z = twin[hj + 2];
+            g.x = twin[3 * t];
+            g.y = twin[3 * t + 1];
+            g.z = twin[3 * t + 2];
         }
-        tw[j][0] = ok ? g.x : -1;
-        tw[j][1] = ok ? g.y : -1;
-        tw[j][2] = ok ? g.z : -1;
-        f[j] = tflag[base + (ok ? lt : 0)];
+        s[j][0] = he_slot(g.x);
+        s[j][1] = he_slot(g.y);
+        s[j][2] = he_slot(g.z);
+        own[j] = tflag[t];
 #pragma unroll
-        for (int i = 0; i < 3; i++) fn[j][i] = tflag[tri_of(tw[j][i] < 0 ? 0 : tw[j][i])];
+        for (int i = 0; i < 3; i++) fn[j][i] = tflag[min(s[j][i] >> 2, (uint32_t)nt - 1u)];
     }
+    uint32_t F[ITEMS], lab[ITEMS];   // frontier bits; the label byte
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
         const int lt = j * B + tid;
-        if (lt < cnt) {
+        const bool in = lt < cnt;
+        const uint32_t L = own[j] & 3u, lbit = 1u << L, sL = pick3(L, s[j][0], s[j][1], s[j][2]);
+        // bit i: the twin of edge i is not its triangle's longest edge
+        // (a boundary twin's local index, 3, equals no label)
+        const uint32_t E = min((fn[j][0] ^ s[j][0]) & 3u, 1u) | (min((fn[j][1] ^ s[j][1]) & 3u, 1u) << 1) |
+                           (min((fn[j][2] ^ s[j][2]) & 3u, 1u) << 2);
+        // frontier: the longest edge of neither triangle
+        uint32_t f = E & ~lbit;
+        // terminal edge: longest on both sides (the lower half-edge holds the seed)
+        bool seed = !(E & lbit) && 4u * (uint32_t)(base + lt) + L < sL;
+        if (__any(max(max(s[j][0], s[j][1]), s[j][2]) == kNoSlot)) {   // (uniform)
+            // boundary edges are frontier edges; the longest one is terminal
+            uint32_t bnd = 0;
 #pragma unroll
-            for (int i = 0; i < 3; i++) s_tw[3 * lt + i] = tw[j][i];
+            for (int i = 0; i < 3; i++) bnd |= s[j][i] == kNoSlot ? 1u << i : 0u;
+            f |= bnd;
+            seed |= (bnd & lbit) != 0;
         }
-    }
-    int ties = 0;
-#pragma unroll
-    for (int j = 0; j < ITEMS; j++) {
-        const int lt = j * B + tid;
-        const int t = base + lt;
-        const uint32_t L = f[j] & 3u;
-        ties += (lt < cnt && (f[j] & kTieBit)) ? 1 : 0;
-        uint32_t out = L;
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            const int g = tw[j][i];
-            fn[j][i] = g >= 0 ? fn[j][i] & 3u : 0u;
-            const bool twin_long = g >= 0 && (int)fn[j][i] == g - 3 * tri_of(g);
-            // frontier: boundary, or the longest edge of neither triangle
-            out |= (g < 0 || ((int)L != i && !twin_long)) ? 1u << (2 + i) : 0u;
-            // terminal edge: longest on both sides (the lower half-edge holds
-            // the seed), or longest and on the boundary
-            out |= ((int)L == i && (g < 0 || (twin_long && 3 * t + i < g))) ? kSeedBit : 0u;
+        F[j] = in ? f : 0u;
+        lab[j] = in ? L | (f << 2) | (seed ? kSeedBit : 0u) : 0u;
+        if (__any(in && (own[j] & kTieBit))) {   // (uniform, rare)
+            const int n = __popcll(__ballot(in && (own[j] & kTieBit)));
+            if (lane == 0) atomicAdd(&d.ctr->nties, n);
         }
-        f[j] = lt < cnt ? out : 0u;
-        if (lt < cnt) s_f[lt] = (uint8_t)out;
+        reinterpret_cast<uint4 *>(s_slot)[lt] = make_uint4(s[j][0], s[j][1], s[j][2], 0u);
+        s_lab[lt] = lab[j];
     }
-    if (ties) atomicAdd(&d.ctr->nties, ties);   // (rare)
     __syncthreads();
     // phase 2: next'/prev' of every frontier half-edge.  The next (previous)
     // edge in the triangle is taken when it is frontier itself; otherwise the
-    // turn continues in the neighbour across it.  A triangle has at most one
-    // frontier half-edge followed by a non-frontier one and at most one
-    // preceded by one, so each item has at most two turns; nearly all of
-    // them end at their first candidate.  The common path is straight-line
-    // code; only turns that go on, and candidates outside the tile, branch.
-    const TileLabels T = {twin, tflag, s_tw, s_f, base, cnt};
+    // turn continues in the neighbour across it.  Nearly all turns end at
+    // their first candidate (96% on the grids), read from LDS; the others are
+    // queued.  (The first candidate is never the twin of the turn's own
+    // half-edge: two triangles of a valid mesh share one edge.)
+    const TileLabels T = {twin, tflag, s_slot, s_lab, (uint32_t)base, (uint32_t)cnt};
     bool err = false;
-    int openmask = 0;   // bit j: item j holds a seed whose loop k_walk must walk
-    int scnt = 0, slen = 0;   // loops settled here: count, half-edges
+    uint32_t cn[ITEMS], cp[ITEMS];       // the turns' candidates: next', prev'
+    uint32_t xy[ITEMS];                  // edges crossed: x | y << 2
+    int qn[ITEMS], qp[ITEMS];            // their places in the queue, -1: ended here
+    int open[ITEMS];                     // place of an open seed among the tile's, -1: none
     uint8_t codes[ITEMS];
-    uint32_t pend = 0;  // bit 2j (2j+1): the next' (prev') turn of item j goes on
-    int cur[2 * ITEMS], lab[2 * ITEMS], src[2 * ITEMS];   // turn state; src: the
-                                                          // local index of the half-edge
-    int nv3[ITEMS][3], pv3[ITEMS][3];                     // this lane's next'/prev'
-    int qslot[2 * ITEMS];                                 // LDS queue slot of turn k, or -1
+    unsigned long long mn[ITEMS], mp[ITEMS], mo[ITEMS];   // ballots: queued next', prev'; open seeds
+    int wq = 0, wo = 0, wtot = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
-        const int lt = j * B + tid;   // lt >= cnt: f[j] == 0, so nothing is queued
-        const int h0 = 3 * (base + lt);
-        const uint32_t F3 = (f[j] >> 2) & 7u;
-        const uint32_t rn = ((F3 >> 1) | (F3 << 2)) & 7u;   // bit i: edge i+1 frontier
-        const uint32_t rp = ((F3 << 1) | (F3 >> 2)) & 7u;   // bit i: edge i-1 frontier
-        const uint32_t mn = F3 & ~rn, mp = F3 & ~rp;        // at most one bit each
-        // in-triangle values (the turn's slot gets its value when the turn ends)
-        int nxv[3], pvv[3];
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            nxv[i] = ((F3 & rn) >> i) & 1u ? h0 + (i == 2 ? 0 : i + 1) : -1;
-            pvv[i] = ((F3 & rp) >> i) & 1u ? h0 + (i == 0 ? 2 : i - 1) : -1;
-        }
-        // next' turn: from the frontier half-edge na, across x = next(na)
-        const int na = mn ? __builtin_ctz(mn) : 0, x = na == 2 ? 0 : na + 1;
-        const int ux = x == 0 ? tw[j][0] : (x == 1 ? tw[j][1] : tw[j][2]);
-        src[2 * j] = 3 * lt + na;
-        cur[2 * j] = he_next(ux < 0 ? 0 : ux);
-        lab[2 * j] = (int)(x == 0 ? fn[j][0] : (x == 1 ? fn[j][1] : fn[j][2]));
-        // prev' turn: from the frontier half-edge pa, across y = prev(pa)
-        const int pa = mp ? __builtin_ctz(mp) : 0, y = pa == 0 ? 2 : pa - 1;
-        const int uy = y == 0 ? tw[j][0] : (y == 1 ? tw[j][1] : tw[j][2]);
-        src[2 * j + 1] = 3 * lt + pa;
-        cur[2 * j + 1] = he_prev(uy < 0 ? 0 : uy);
-        lab[2 * j + 1] = (int)(y == 0 ? fn[j][0] : (y == 1 ? fn[j][1] : fn[j][2]));
-        // a non-frontier edge is interior: ux, uy >= 0 whenever the turn exists
-        err |= (mn && ux < 0) || (mp && uy < 0);
-        // first candidates: most are frontier half-edges of a triangle in the
-        // tile, which ends the turn at once
-        const int cn = cur[2 * j], tn = tri_of(cn), kn = tn - base;
-        const int cp = cur[2 * j + 1], tq = tri_of(cp), kq = tq - base;
-        const bool inn = (unsigned)kn < (unsigned)cnt, inq = (unsigned)kq < (unsigned)cnt;
-        const uint32_t fbn = s_f[inn ? kn : 0], fbq = s_f[inq ? kq : 0];
-        const bool hitn = mn && inn && fbit(fbn, cn - 3 * tn);
-        const bool hitq = mp && inq && fbit(fbq, cp - 3 * tq);
-        if (hitn) {
-            // next'(h) == twin(h): the target of h is a barrier tip
-            if (cn == (na == 0 ? tw[j][0] : (na == 1 ? tw[j][1] : tw[j][2])))
-                tile_tip(s_tip, &s_ntip, tcap, 3 * lt + na, base, rc, tips, cap_tips, d, mi, err);
-        }
-        const bool pn = mn && !hitn, pp = mp && !hitq;   // turns that go on
-        pend |= (pn ? 1u : 0u) << (2 * j) | (pp ? 1u : 0u) << (2 * j + 1);
-        // this triangle's next'/prev' stay in registers until the tile is done
-        // (a turn that goes on fills its slot later), then go out as one
-        // 12-byte store each, so every line is written once and whole
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            nv3[j][i] = (mn && i == na) ? cn : nxv[i];
-            pv3[j][i] = (mp && i == pa) ? cp : pvv[i];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < ITEMS; j++) {
-        const int lt = j * B + tid;
-        const int t = base + lt, h0 = 3 * t;
+        const uint32_t t = (uint32_t)(base + j * B + tid);   // past cnt: F == 0, so nothing happens
+        const uint32_t x = (kCrossNext >> (2 * F[j])) & 3u, y = (kCrossPrev >> (2 * F[j])) & 3u;
+        const uint32_t sx = pick3(x, s[j][0], s[j][1], s[j][2]), sy = pick3(y, s[j][0], s[j][1], s[j][2]);
+        // a neighbour outside the tile reads the entry past it: no frontier edges
+        const uint32_t fx = s_lab[min((sx >> 2) - (uint32_t)base, (uint32_t)TB)],
+                       fy = s_lab[min((sy >> 2) - (uint32_t)base, (uint32_t)TB)];
+        cn[j] = next_slot(sx);
+        cp[j] = prev_slot(sy);
+        xy[j] = x | (y << 2);
+        mn[j] = __ballot(x != 3u && !fbit(fx, (int)(cn[j] & 3u)));
+        mp[j] = __ballot(y != 3u && !fbit(fy, (int)(cp[j] & 3u)));
+        wq += __popcll(mn[j]) + __popcll(mp[j]);
         // A seed whose polygon is one triangle (boundary terminal edge, both
         // other edges frontier) or two (interior terminal edge, the four
         // other edges frontier) is settled here: its loop is those 3 or 4
@@ -706,149 +678,114 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
         // tip and no repair touches them.  The seed is the lower half-edge of
         // its terminal edge, so the loop's minimum lies in this triangle and
         // its byte is written here with the rest of the tile.
-        const int L = (int)(f[j] & 3u), a = L == 2 ? 0 : L + 1, b = L == 0 ? 2 : L - 1;
-        const bool cand = (f[j] & kSeedBit) && fbit(f[j], a) && fbit(f[j], b);
-        const int g = L == 0 ? tw[j][0] : (L == 1 ? tw[j][1] : tw[j][2]);
-        const int tp = tri_of(g < 0 ? 0 : g), Lp = g - 3 * tp;
-        const int ap = Lp == 2 ? 0 : Lp + 1, bp = Lp == 0 ? 2 : Lp - 1;
-        const int kp = tp - base;
-        const bool inp = (unsigned)kp < (unsigned)cnt;
-        const uint32_t fp = s_f[inp ? kp : 0];
-        bool quad = fbit(fp, ap) && fbit(fp, bp);
-        if (cand && g >= 0 && !inp)   // partner outside the tile (rare on ordered meshes)
-            quad = outside_fbit(T, 3 * tp + ap, Lp) && outside_fbit(T, 3 * tp + bp, Lp);
-        const uint8_t code = !cand ? (uint8_t)0
-                             : g < 0 ? loop_code(h0, 3)
-                             : !quad ? (uint8_t)0
-                             : tp == t + 1 ? (uint8_t)((kPlQuadNext << 2) | Lp)
-                                           : loop_code(h0 + min(a, b), 4);
-        openmask |= ((f[j] & kSeedBit) && !code) ? 1 << j : 0;
-        s_pl[lt] = code;   // entries past cnt are never stored
-        codes[j] = code;
-        scnt += code ? 1 : 0;
-        slen += !code ? 0 : (code >> 2) == kPlQuadNext ? 4 : (code >> 2);
+        const uint32_t L = lab[j] & 3u, lbit = 1u << L;
+        const bool seed = lab[j] & kSeedBit;
+        const bool cand = seed && F[j] == (7u ^ lbit);   // then x == y == L
+        bool quad = cand && ((fx >> 2) & 7u) == (7u ^ (1u << (sx & 3u)));
+        if (cand && (sx >> 2) - (uint32_t)base >= (uint32_t)TB) {   // partner outside the tile (rare on ordered meshes)
+            const uint32_t Lp = sx & 3u;
+            quad = outside_fbit(T, cn[j], Lp) && outside_fbit(T, prev_slot(sx), Lp);
+        }
+        const bool one = seed && F[j] == 7u;
+        codes[j] = quad ? (uint8_t)((sx >> 2) == t + 1 ? (kPlQuadNext << 2) | (sx & 3u) : (4u << 2) | (L == 0 ? 1u : 0u))
+                        : (one ? (uint8_t)(3u << 2) : (uint8_t)0);
+        const unsigned long long mq = __ballot(quad), m1 = __ballot(one);
+        mo[j] = __ballot(seed && !quad && !one);
+        wo += __popcll(mo[j]);
+        const int nq = __popcll(mq), n1 = __popcll(m1);
+        wtot += ((nq + n1) << 16) | (4 * nq + 3 * n1);
     }
-    // One block scan places the turns still open in the LDS queue and the
-    // open seeds in the walk list (stripe by tile, one atomic per block), and
-    // totals the loops settled here for their compaction tile.  Each count
-    // fits in 16 bits (at most 2 per triangle, lengths at most 4 per
-    // triangle, tiles of at most 1024 triangles), so two ride in one int.
-    {
-        __shared__ int s_scan[72];
-        __shared__ int s_wbase;
-        int ea, eb, ta, tb;
-        block_excl_scan2((__popc(pend) << 16) | __popc(openmask), (scnt << 16) | slen, ea, eb, ta, tb, s_scan);
-        int eq = ea >> 16;
-        const int eo = ea & 0xffff, tq = ta >> 16, to = ta & 0xffff;
-        const int stripe = tile % kStripes;
-        // the block's triangles lie in one compaction tile unless that tile is
-        // smaller than this one or not aligned with it
-        const bool one = base / cmp_tb == (base + cnt - 1) / cmp_tb;
-        if (tid == 0) {
-            s_wbase = to > 0 ? atomicAdd(&walk_counts[stripe * kStripePad], to) : 0;
-            if (one && tb != 0)
-                atomicAdd(reinterpret_cast<unsigned long long *>(agg + d.cmp_tile0 + base / cmp_tb),
-                          ((unsigned long long)(uint32_t)(tb >> 16) << 32) | (unsigned long long)(tb & 0xffff));
-        }
-        const int ct0 = base / cmp_tb;   // first compaction tile of this tile
-        if (!one) {   // totals per compaction tile in LDS, one global atomic each below
-#pragma unroll
-            for (int j = 0; j < ITEMS; j++) {
-                if (!codes[j]) continue;
-                const int k = (base + j * B + tid) / cmp_tb - ct0;
-                const int len = (codes[j] >> 2) == kPlQuadNext ? 4 : (codes[j] >> 2);
-                atomicAdd(&s_aggc[k], 1);
-                atomicAdd(&s_aggl[k], len);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 2 * ITEMS; k++) {
-            qslot[k] = -1;
-            if (!((pend >> k) & 1u)) continue;
-            if (eq < qcap) {
-                s_q[2 * eq] = cur[k];
-                s_q[2 * eq + 1] = (src[k] << 3) | ((k & 1) == 0 ? 4 : 0) | (lab[k] + 1);
-                qslot[k] = eq;
-                pend &= ~(1u << k);
-            }
-            ++eq;
-        }
-        __syncthreads();
-        if (!one && tid <= (base + cnt - 1) / cmp_tb - ct0 && s_aggc[tid] != 0)
-            atomicAdd(reinterpret_cast<unsigned long long *>(agg + d.cmp_tile0 + ct0 + tid),
-                      ((unsigned long long)(uint32_t)s_aggc[tid] << 32) | (unsigned long long)(uint32_t)s_aggl[tid]);
-        const int wbase = s_wbase;
-        err |= wbase + to > walk_cap;
-        int e = stripe * walk_cap + wbase + eo;
-        const int lim = (stripe + 1) * walk_cap;
-#pragma unroll
-        for (int j = 0; j < ITEMS; j++) {
-            if (!((openmask >> j) & 1)) continue;
-            if (e < lim) {
-                const int t = base + j * B + tid;
-                walk[e].mesh = mi;
-                walk[e].he = 3 * t + (int)(f[j] & 3u);
-            }
-            ++e;
-        }
-        // the queued turns, one per thread: only the first lanes of the block work
-        const int nq = min(tq, qcap);
-        for (int q = tid; q < nq; q += B) {
-            const int w = s_q[2 * q + 1], sh = w >> 3;
-            const bool nxt = (w & 4) != 0;
-            const int res = run_turn(T, s_q[2 * q], (w & 3) - 1, nxt);
-            err |= res < 0;
-            s_q[2 * q] = res;   // the owner picks it up after the barrier
-            if (nxt && res >= 0 && res == s_tw[sh])
-                tile_tip(s_tip, &s_ntip, tcap, sh, base, rc, tips, cap_tips, d, mi, err);
-        }
+    // the block's triangles lie in one compaction tile unless that tile is
+    // smaller than this one or not aligned with it
+    const int ct0 = base / cmp_tb;   // first compaction tile of this tile
+    const bool one_tile = ct0 == (base + cnt - 1) / cmp_tb;
+    // the wave's places in the queue and among the open seeds; its settled loops
+    int q0 = 0, o0 = 0;
+    if (lane == 0) {
+        if (wq) q0 = atomicAdd(&s_nq, wq);
+        if (wo) o0 = atomicAdd(&s_nopen, wo);
+        if (one_tile && wtot) atomicAdd(&s_tot, wtot);
     }
-    // turns beyond the queue (meshes whose polygons are mostly large), in registers
-    for (int step = 0; pend; step++) {
+    q0 = __builtin_amdgcn_readfirstlane(q0);
+    o0 = __builtin_amdgcn_readfirstlane(o0);
 #pragma unroll
-        for (int k = 0; k < 2 * ITEMS; k++) {
-            if (!((pend >> k) & 1u)) continue;
-            const int r = step < kRotGuard ? turn_step(T, cur[k], lab[k], (k & 1) == 0) : -1;
-            if (r == 0) continue;
-            const int res = r > 0 ? cur[k] : -1;
-            err |= r < 0;
-            const int li = src[k] % 3;
-            if ((k & 1) == 0) {
-#pragma unroll
-                for (int i = 0; i < 3; i++)
-                    if (i == li) nv3[k >> 1][i] = res;
-                if (res >= 0 && res == s_tw[src[k]])
-                    tile_tip(s_tip, &s_ntip, tcap, src[k], base, rc, tips, cap_tips, d, mi, err);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 3; i++)
-                    if (i == li) pv3[k >> 1][i] = res;
-            }
-            pend &= ~(1u << k);
+    for (int j = 0; j < ITEMS; j++) {
+        const uint32_t src = 4u * (uint32_t)(j * B + tid), x = xy[j] & 3u, y = xy[j] >> 2;
+        const auto before = [](unsigned long long m) {
+            return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        };
+        qn[j] = qp[j] = open[j] = -1;
+        if ((mn[j] >> lane) & 1) {   // from the frontier edge before x
+            qn[j] = q0 + before(mn[j]);
+            s_q[qn[j]] = make_uint2(cn[j], (src | (x == 0 ? 2u : x - 1u)) << 1 | 1u);
+        }
+        q0 += __popcll(mn[j]);
+        if ((mp[j] >> lane) & 1) {   // from the frontier edge after y
+            qp[j] = q0 + before(mp[j]);
+            s_q[qp[j]] = make_uint2(cp[j], (src | (y == 2 ? 0u : y + 1u)) << 1);
+        }
+        q0 += __popcll(mp[j]);
+        if ((mo[j] >> lane) & 1) open[j] = o0 + before(mo[j]);
+        o0 += __popcll(mo[j]);
+        if (!one_tile && codes[j]) {   // totals per compaction tile in LDS, one global atomic each below
+            const int k = (base + j * B + tid) / cmp_tb - ct0;
+            atomicAdd(&s_aggc[k], 1);
+            atomicAdd(&s_aggl[k], (codes[j] >> 2) == kPlQuadNext ? 4 : (codes[j] >> 2));
         }
     }
     __syncthreads();
-    // next'/prev' of this lane's triangles, with the queued turns' results
+    const int stripe = tile % kStripes;
+    if (tid == B - kWave) {   // (in the last wave: the first ones have the turns)
+        s_wbase = s_nopen > 0 ? atomicAdd(&walk_counts[stripe * kStripePad], s_nopen) : 0;
+        if (one_tile && s_tot != 0)
+            atomicAdd(reinterpret_cast<unsigned long long *>(agg + d.cmp_tile0 + ct0),
+                      ((unsigned long long)(uint32_t)(s_tot >> 16) << 32) | (unsigned long long)(s_tot & 0xffff));
+    }
+    if (!one_tile && tid <= (base + cnt - 1) / cmp_tb - ct0 && s_aggc[tid] != 0)
+        atomicAdd(reinterpret_cast<unsigned long long *>(agg + d.cmp_tile0 + ct0 + tid),
+                  ((unsigned long long)(uint32_t)s_aggc[tid] << 32) | (unsigned long long)(uint32_t)s_aggl[tid]);
+    // the queued turns, one per thread: only the first lanes of the block work
+    const int nq = s_nq;
+    for (int q = tid; q < nq; q += B) {
+        const uint2 w = s_q[q];
+        const uint32_t src = w.y >> 1;
+        const bool nxt = w.y & 1u;
+        const uint32_t res = run_turn(T, w.x, nxt);
+        err |= res == kNoSlot;
+        s_q[q].x = res;   // the owner picks it up after the barrier
+        // next'(h) == twin(h): the target of h is a barrier tip
+        if (nxt && res != kNoSlot && res == s_slot[src]) {
+            const int he = 3 * base + he_of_slot(src), i = atomicAdd(&s_ntip, 1);
+            if (i < tcap)
+                s_tip[i] = he;
+            else
+                push_tip(rc, tips, cap_tips, d, mi, he, err);
+        }
+    }
+    __syncthreads();
+    const int wbase = s_wbase;
+    err |= wbase + s_nopen > walk_cap;
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
-        const int lt = j * B + tid;
-        if (lt >= cnt) continue;
-#pragma unroll
-        for (int kk = 0; kk < 2; kk++) {
-            const int k = 2 * j + kk;
-            if (qslot[k] < 0) continue;
-            const int res = s_q[2 * qslot[k]], li = src[k] - 3 * lt;
-#pragma unroll
-            for (int i = 0; i < 3; i++) {
-                if (i != li) continue;
-                if (kk == 0)
-                    nv3[j][i] = res;
-                else
-                    pv3[j][i] = res;
-            }
+        const int lt = j * B + tid, t = base + lt, h0 = 3 * t;
+        if (open[j] >= 0 && wbase + open[j] < walk_cap) {
+            ListEntry &e = walk[stripe * walk_cap + wbase + open[j]];
+            e.mesh = mi;
+            e.he = h0 + (int)(lab[j] & 3u);
         }
-        const int h0 = 3 * (base + lt);
-        const v3i nv = v3i{nv3[j][0], nv3[j][1], nv3[j][2]}, pv = v3i{pv3[j][0], pv3[j][1], pv3[j][2]};
+        if (lt >= cnt) continue;
+        // next'/prev' of the triangle's edges, the queued turns' results in
+        // place, as one 12-byte store each, so every line is written once
+        // and whole (kNoSlot becomes -1 or thereabouts: an error was set)
+        if (qn[j] >= 0) cn[j] = s_q[qn[j]].x;
+        if (qp[j] >= 0) cp[j] = s_q[qp[j]].x;
+        const int hn = he_of_slot(cn[j]), hp = he_of_slot(cp[j]);
+        const uint32_t x = xy[j] & 3u, y = xy[j] >> 2;
+        const int none[3] = {(F[j] & 1u) ? 0 : -1, (F[j] & 2u) ? 0 : -1, (F[j] & 4u) ? 0 : -1};
+        const v3i nv = v3i{x == 1u ? hn : (h0 + 1) | none[0], x == 2u ? hn : (h0 + 2) | none[1],
+                           x == 0u ? hn : h0 | none[2]};
+        const v3i pv = v3i{y == 2u ? hp : (h0 + 2) | none[0], y == 0u ? hp : h0 | none[1],
+                           y == 1u ? hp : (h0 + 1) | none[2]};
         if (NT) {
             __builtin_nontemporal_store(nv, reinterpret_cast<GLOBAL v3i *>(nxo + h0));
             __builtin_nontemporal_store(pv, reinterpret_cast<GLOBAL v3i *>(pvo + h0));
@@ -856,11 +793,11 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
             *reinterpret_cast<GLOBAL v3i *>(nxo + h0) = nv;
             *reinterpret_cast<GLOBAL v3i *>(pvo + h0) = pv;
         }
+        // the label byte keeps its longest-edge bits, which other tiles may
+        // be reading
+        tflag[t] = (uint8_t)lab[j];
+        ((gu8)d.pl)[t] = codes[j];
     }
-    // the tile's label and loop bytes in whole words (the label bytes keep
-    // their longest-edge bits, which other tiles may be reading)
-    store_bytes_from_lds((gu8)(d.pl) + base, s_pl, cnt);
-    store_bytes_from_lds(tflag + base, s_f, cnt);
     if (tid == 0) {   // the tile's tips: one append
         const int n = min(s_ntip, tcap);
         if (n > 0) {
@@ -869,7 +806,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
             for (int i = 0; i < n; i++) {
                 if (at + i < cap_tips) {
                     tips[at + i].mesh = mi;
-                    tips[at + i].he = 3 * base + s_tip[i];
+                    tips[at + i].he = s_tip[i];
                 } else {
                     err = true;
                 }
@@ -2474,7 +2411,7 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
 
     H(K_RELINK, 0);
     {
-        const size_t lds = (sizeof(int) * 3 + 2 + 4 + 1) * (size_t)cfg.block_relink * cfg.items_relink;
+        const size_t lds = relink_lds_bytes(cfg.block_relink * cfg.items_relink);
         const hipError_t e = rb.compact ? launch_relink<true>(cfg, rb, s, lds, cmp_tb)
                                         : launch_relink<false>(cfg, rb, s, lds, cmp_tb);
         if (e != hipSuccess) return e;
