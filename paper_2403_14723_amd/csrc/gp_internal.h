@@ -35,16 +35,6 @@ struct MeshCounters {
     int32_t chunks_done;   // k_tile_scan blocks finished (the last one scans the chunk totals)
 };
 
-// list sizes and the dynamic tile counter of one run
-struct RunCounters {
-    int32_t ntips;
-    int32_t unused;
-    int32_t nfix;
-    int32_t tile_ctr;
-    int32_t err;
-    int32_t pad[3];
-};
-
 struct MeshDesc {
     const int2 *xy;
     const int32_t *org;
@@ -92,6 +82,11 @@ struct EmitEntry {
 // holds entries [s*cap, s*cap + min(count[s], cap)).
 constexpr int kStripes = 64;
 constexpr int kStripePad = 32;   // counters 128 bytes apart: one cache line each
+// The tip list has fewer: one append per tile with a tip, and its readers take
+// all the counters in uniform loads.  With one counter for all (and another per
+// mesh) the 3,867 tiles of a 1M-point Delaunay mesh, nearly all with a tip, cost
+// k_relink 20 of 62 us.
+constexpr int kTipStripes = 8;
 
 // ---- launch plumbing (host side, defined in mesh_kernels.hip) ------------
 
@@ -122,10 +117,11 @@ struct RunBuffers {
     int32_t tri_tiles;       // total triangle tiles (label)
     int32_t he_tiles;        // total relink tiles
     int32_t cmp_tiles;       // total compaction tiles
-    RunCounters *rc;         // device
-    ListEntry *tips;         // capacity cap_tips
-    ListEntry *fixes;        // capacity cap_fix
-    int32_t cap_tips, cap_fix;
+    ListEntry *tips;         // striped: barrier tips
+    int32_t *tip_counts;     // kTipStripes counters, kStripePad ints apart
+    int32_t tip_cap;         // per stripe
+    int32_t cap_tips;        // most tips in all
+    ListEntry *fixes;        // 2 cap_tips
     uint64_t *status;        // per compaction tile: (loops << 32 | half-edges), then its prefix within its chunk
     uint64_t *cpre;          // per compaction tile; at each chunk's first tile: the chunk's prefix
     int32_t max_chunks;      // most chunks (of kScanChunk tiles) in one mesh

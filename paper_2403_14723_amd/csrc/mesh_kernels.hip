@@ -225,13 +225,7 @@ __device__ __forceinline__ int striped_prefix(const int32_t *counts, int cap, in
     if (threadIdx.x < kWave) {
         int c = counts[threadIdx.x * kStripePad];
         c = c < 0 ? 0 : (c > cap ? cap : c);
-        int x = c;
-#pragma unroll
-        for (int dd = 1; dd < kWave; dd <<= 1) {
-            const int y = __shfl_up(x, dd);
-            if ((int)threadIdx.x >= dd) x += y;
-        }
-        s_pref[threadIdx.x + 1] = x;
+        s_pref[threadIdx.x + 1] = wave_incl_scan(c);
         if (threadIdx.x == 0) s_pref[0] = 0;
     }
     __syncthreads();
@@ -250,6 +244,24 @@ __device__ __forceinline__ int striped_index(const int *s_pref, int cap, int g) 
     }
     return lo * cap + (g - s_pref[lo]);
 }
+
+// The tip list's stripes: how many tips come before each (uniform loads).
+struct TipStripes {
+    int first[kTipStripes + 1];
+    __device__ __forceinline__ TipStripes(const int32_t *counts, int cap) {
+        first[0] = 0;
+#pragma unroll
+        for (int s = 0; s < kTipStripes; s++) first[s + 1] = first[s] + max(0, min(counts[s * kStripePad], cap));
+    }
+    __device__ __forceinline__ int total() const { return first[kTipStripes]; }
+    // place in the list of the g-th tip
+    __device__ __forceinline__ int index(int g, int cap) const {
+        int at = g;
+#pragma unroll
+        for (int s = 1; s < kTipStripes; s++) at = g >= first[s] ? s * cap + g - first[s] : at;
+        return at;
+    }
+};
 
 // Copies n ints from global src to LDS dst; src and dst 16-byte aligned.
 // PER: 16-byte loads per thread that cover n (n <= 4 * PER * blockDim.x); all
@@ -279,11 +291,10 @@ __device__ __forceinline__ void load_to_lds(int *dst, gcint src, int n) {
 
 // What a run clears before its kernels count into it.
 struct ClearArgs {
-    RunCounters *rc;
     MeshCounters *ctrs;
     uint64_t *status;   // per compaction tile
     int nstatus;
-    int32_t *walk_counts, *emit_counts, *wbuf_counts;
+    int32_t *tip_counts, *walk_counts, *emit_counts, *wbuf_counts;
 };
 
 // Label byte bit 7: the maximum edge length of the triangle is tied (k_label
@@ -298,12 +309,12 @@ __global__ void __launch_bounds__(1024) k_label(const MeshDesc *__restrict__ des
         const int gid = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
         for (int k = gid; k < ca.nstatus; k += stride) ca.status[k] = 0ull;
         for (int k = gid; k < nmesh; k += stride) ca.ctrs[k] = MeshCounters{};
+        if (gid < kTipStripes) ca.tip_counts[gid * kStripePad] = 0;
         if (gid < kStripes) {
             ca.walk_counts[gid * kStripePad] = 0;
             ca.emit_counts[gid * kStripePad] = 0;
             ca.wbuf_counts[gid * kStripePad] = 0;
         }
-        if (gid == 0) *ca.rc = RunCounters{};
     }
     extern __shared__ int4 lds_raw[];
     int *s_org = reinterpret_cast<int *>(lds_raw);
@@ -493,19 +504,6 @@ __device__ __forceinline__ uint32_t run_turn(const TileLabels &T, uint32_t c, bo
     return kNoSlot;
 }
 
-// Appends barrier tip he of mesh mi to the tip list.
-__device__ __forceinline__ void push_tip(RunCounters *rc, ListEntry *tips, int cap_tips, const MeshDesc &d, int mi,
-                                         int he, bool &err) {
-    const int slot = atomicAdd(&rc->ntips, 1);
-    if (slot < cap_tips) {
-        tips[slot].mesh = mi;
-        tips[slot].he = he;
-        atomicAdd(&d.ctr->ntips, 1);
-    } else {
-        err = true;
-    }
-}
-
 // Frontier bit of slot c of a triangle outside the tile whose longest-edge
 // label is Lc.
 __device__ __forceinline__ bool outside_fbit(const TileLabels &T, uint32_t c, uint32_t Lc) {
@@ -540,7 +538,7 @@ __device__ __forceinline__ uint32_t pick3(uint32_t i, uint32_t a, uint32_t b, ui
 }
 
 __host__ __device__ inline size_t relink_lds_bytes(int tile) {
-    return sizeof(int) * (4 * (size_t)tile + 4 * (size_t)tile + (size_t)tile + 4 + (size_t)tile / 4);
+    return sizeof(int) * (4 * (size_t)tile + 4 * (size_t)tile + (size_t)tile + 4);
 }
 
 // CM: some mesh of the run is compact (else the int32 twins are read
@@ -548,7 +546,7 @@ __host__ __device__ inline size_t relink_lds_bytes(int tile) {
 // (nontemporal) stores.
 template <int ITEMS, bool CM, bool NT>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) k_relink(const MeshDesc *__restrict__ descs, int nmesh,
-                                                  RunCounters *rc, ListEntry *tips, int cap_tips,
+                                                  ListEntry *tips, int32_t *tip_counts, int tip_cap,
                                                   ListEntry *walk, int32_t *walk_counts, int walk_cap,
                                                   uint64_t *agg, int cmp_tb) {
     extern __shared__ int4 lds_raw[];
@@ -556,10 +554,9 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     uint32_t *s_slot = reinterpret_cast<uint32_t *>(lds_raw);   // by slot in the tile: the twin's slot
     uint2 *s_q = reinterpret_cast<uint2 *>(s_slot + 4 * TB);    // queued turns (at most two per triangle)
     uint32_t *s_lab = reinterpret_cast<uint32_t *>(s_q + 2 * TB);   // label bytes; after them one without frontier edges
-    int *s_tip = reinterpret_cast<int *>(s_lab + TB + 4);           // barrier tips found here
-    const int tcap = TB / 4;
-    // queued turns; open seeds; settled loops << 16 | their half-edges; tips; the open seeds' place in the walk list
-    __shared__ int s_nq, s_nopen, s_tot, s_ntip, s_wbase;
+    // queued turns; open seeds; settled loops << 16 | their half-edges; barrier
+    // tips; the open seeds' and the tips' places in their lists
+    __shared__ int s_nq, s_nopen, s_tot, s_ntip, s_wbase, s_tbase;
     // loops settled here, per compaction tile, when the tile's triangles
     // span several of them (a relink tile of <= 1024 triangles, compaction
     // tiles of >= 64: at most 17)
@@ -753,16 +750,16 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
         const uint32_t res = run_turn(T, w.x, nxt);
         err |= res == kNoSlot;
         s_q[q].x = res;   // the owner picks it up after the barrier
-        // next'(h) == twin(h): the target of h is a barrier tip
-        if (nxt && res != kNoSlot && res == s_slot[src]) {
-            const int he = 3 * base + he_of_slot(src), i = atomicAdd(&s_ntip, 1);
-            if (i < tcap)
-                s_tip[i] = he;
-            else
-                push_tip(rc, tips, cap_tips, d, mi, he, err);
-        }
+        // next'(h) == twin(h): the target of h is a barrier tip (its place
+        // among the tile's in the entry's other word)
+        if (nxt) s_q[q].y = res != kNoSlot && res == s_slot[src] ? (uint32_t)atomicAdd(&s_ntip, 1) : kNoSlot;
     }
     __syncthreads();
+    const int ntip = s_ntip;
+    if (ntip > 0) {   // (uniform)
+        if (tid == 0) s_tbase = atomicAdd(&tip_counts[tile % kTipStripes * kStripePad], ntip);
+        __syncthreads();
+    }
     const int wbase = s_wbase;
     err |= wbase + s_nopen > walk_cap;
 #pragma unroll
@@ -777,7 +774,17 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
         // next'/prev' of the triangle's edges, the queued turns' results in
         // place, as one 12-byte store each, so every line is written once
         // and whole (kNoSlot becomes -1 or thereabouts: an error was set)
-        if (qn[j] >= 0) cn[j] = s_q[qn[j]].x;
+        if (qn[j] >= 0) {
+            const uint2 w = s_q[qn[j]];
+            cn[j] = w.x;
+            if (w.y != kNoSlot) {
+                const int k = s_tbase + (int)w.y, x = (int)(xy[j] & 3u);
+                if (k < tip_cap)
+                    tips[tile % kTipStripes * tip_cap + k] = {mi, h0 + (x == 0 ? 2 : x - 1)};
+                else
+                    err = true;
+            }
+        }
         if (qp[j] >= 0) cp[j] = s_q[qp[j]].x;
         const int hn = he_of_slot(cn[j]), hp = he_of_slot(cp[j]);
         const uint32_t x = xy[j] & 3u, y = xy[j] >> 2;
@@ -797,21 +804,6 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
         // be reading
         tflag[t] = (uint8_t)lab[j];
         ((gu8)d.pl)[t] = codes[j];
-    }
-    if (tid == 0) {   // the tile's tips: one append
-        const int n = min(s_ntip, tcap);
-        if (n > 0) {
-            const int at = atomicAdd(&rc->ntips, n);
-            atomicAdd(&d.ctr->ntips, n);
-            for (int i = 0; i < n; i++) {
-                if (at + i < cap_tips) {
-                    tips[at + i].mesh = mi;
-                    tips[at + i].he = s_tip[i];
-                } else {
-                    err = true;
-                }
-            }
-        }
     }
     if (err) atomicOr(&d.ctr->err, kErrCorrupt);
 }
@@ -842,20 +834,26 @@ __device__ __forceinline__ int wave_reserve2(int32_t *counter, bool pred) {
 
 // Middle edge of every barrier tip.  Whole waves take consecutive tips, so the
 // list appends and counters cost one atomic per wave (tips are many on
-// general-position meshes, and atomics on one address serialize).
-__global__ void k_repair(const MeshDesc *__restrict__ descs, RunCounters *rc, const ListEntry *tips,
-                         int cap_tips, ListEntry *walk, int32_t *walk_counts, int walk_cap, ListEntry *fixes,
-                         int cap_fix) {
-    const int ntips = min(rc->ntips, cap_tips);
+// general-position meshes, and atomics on one address serialize).  Tip k's two
+// anchors for k_fixup go to entries 2k and 2k + 1 (half-edge -1: none).
+__global__ void k_repair(const MeshDesc *__restrict__ descs, int nmesh, const ListEntry *tips, const int32_t *tip_counts,
+                         int tip_cap, int cap_tips, ListEntry *walk, int32_t *walk_counts, int walk_cap,
+                         ListEntry *fixes) {
+    const TipStripes stripes(tip_counts, tip_cap);
+    const int all = stripes.total(), ntips = min(all, cap_tips);
     const int lane = __lane_id();
     const int stride = gridDim.x * blockDim.x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (all > cap_tips) atomicOr(&descs[0].ctr->err, kErrCorrupt);
+        if (nmesh == 1) descs[0].ctr->ntips = ntips;
+    }
     for (int wbase = blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); wbase < ntips; wbase += stride) {
         const int k = wbase + lane;
         bool ok = k < ntips;
         int mesh = 0, a = -1, m = -1, mt = -1;
         bool newmid = false;
         if (ok) {
-            const ListEntry e = tips[k];
+            const ListEntry e = tips[stripes.index(k, tip_cap)];
             mesh = e.mesh;
             const MeshDesc &d = descs[e.mesh];
             const TwinView twin = twin_view(d);
@@ -904,34 +902,30 @@ __global__ void k_repair(const MeshDesc *__restrict__ descs, RunCounters *rc, co
         // both halves of the middle edge seed the polygons on either side
         const int stripe = (wbase / kWave) % kStripes;
         const int c = wave_reserve2(&walk_counts[stripe * kStripePad], ok);
-        const int f = wave_reserve2(&rc->nfix, ok);
+        if (k < ntips) {
+            fixes[2 * k] = {mesh, ok ? a : -1};        // leaves the tip
+            fixes[2 * k + 1] = {mesh, ok ? mt : -1};   // leaves the other end of the middle edge
+        }
         if (ok) {
-            bool full = false;
             if (c + 1 < walk_cap) {
                 walk[stripe * walk_cap + c].mesh = mesh;
                 walk[stripe * walk_cap + c].he = m;
                 walk[stripe * walk_cap + c + 1].mesh = mesh;
                 walk[stripe * walk_cap + c + 1].he = mt;
             } else {
-                full = true;
+                atomicOr(&descs[mesh].ctr->err, kErrCorrupt);
             }
-            if (f + 1 < cap_fix) {
-                fixes[f].mesh = mesh;
-                fixes[f].he = a;        // leaves the tip
-                fixes[f + 1].mesh = mesh;
-                fixes[f + 1].he = mt;   // leaves the other end of the middle edge
-            } else {
-                full = true;
-            }
-            if (full) atomicOr(&descs[mesh].ctr->err, kErrCorrupt);
         }
-        // new middle edges, counted per mesh: one atomic per mesh in the wave
-        unsigned long long pending = __ballot(ok && newmid);
+        // tips (of a batch) and new middle edges, counted per mesh: one atomic each per mesh in the wave
+        unsigned long long pending = __ballot(k < ntips);
         while (pending) {
             const int leader = __ffsll((long long)pending) - 1;
             const int lm = __shfl(mesh, leader);
-            const unsigned long long same = __ballot(ok && newmid && mesh == lm);
-            if (lane == leader) atomicAdd(&descs[lm].ctr->nmiddle, __popcll(same));
+            const unsigned long long same = __ballot(k < ntips && mesh == lm), mid = __ballot(ok && newmid && mesh == lm);
+            if (lane == leader) {
+                if (nmesh > 1) atomicAdd(&descs[lm].ctr->ntips, __popcll(same));
+                if (mid) atomicAdd(&descs[lm].ctr->nmiddle, __popcll(mid));
+            }
             pending &= ~same;
         }
     }
@@ -962,12 +956,13 @@ __device__ __forceinline__ void sweep_step(gcu8 tfl, gint nxo, gint pvo, int o, 
     }
 }
 
-__global__ void __launch_bounds__(256) k_fixup(const MeshDesc *__restrict__ descs, RunCounters *rc,
-                                               const ListEntry *fixes, int cap_fix) {
-    const int nfix = min(rc->nfix, cap_fix);
+__global__ void __launch_bounds__(256) k_fixup(const MeshDesc *__restrict__ descs, const int32_t *tip_counts,
+                                               int tip_cap, int cap_tips, const ListEntry *fixes) {
+    const int nfix = 2 * min(TipStripes(tip_counts, tip_cap).total(), cap_tips);
     const int stride = gridDim.x * blockDim.x;
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < nfix; q += stride) {
         const ListEntry en = fixes[q];
+        if (en.he < 0) continue;
         const MeshDesc &d = descs[en.mesh];
         const TwinView twin = twin_view(d);
         const gcu8 tfl = (gcu8)d.tflag;
@@ -2305,7 +2300,7 @@ hipError_t launch_export_counts(const MeshCounters *c, int32_t *out, hipStream_t
 template <bool CM, bool NT>
 hipError_t launch_relink_nt(const LaunchCfg &cfg, const RunBuffers &rb, hipStream_t s, size_t lds, int cmp_tb) {
     const dim3 grid(rb.he_tiles), block(cfg.block_relink);
-#define GP_RELINK_ARGS rb.descs, rb.nmesh, rb.rc, rb.tips, rb.cap_tips, rb.walk, rb.walk_counts, rb.walk_cap, \
+#define GP_RELINK_ARGS rb.descs, rb.nmesh, rb.tips, rb.tip_counts, rb.tip_cap, rb.walk, rb.walk_counts, rb.walk_cap, \
                        rb.status, cmp_tb
     switch (cfg.items_relink) {
         case 1: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_relink<1, CM, NT>), grid, block, lds, s, GP_RELINK_ARGS); break;
@@ -2397,12 +2392,14 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
         H(K_SMALL, 1);
         return hipGetLastError();
     }
-    const int pb = cfg.persistent_blocks, pt = cfg.block_persistent;
+    // tips are at most half the triangles and rarely many: a quarter of the
+    // blocks for them, for the time that idle ones take to start and end
+    const int pb = cfg.persistent_blocks, pt = cfg.block_persistent, pq = (pb + 3) / 4;
     const int cmp_tb = cfg.block_compact * cfg.items_compact;   // triangles per compaction tile
 
     H(K_LABEL, 0);
     {
-        const ClearArgs ca = {rb.rc, rb.ctrs, rb.status, rb.cmp_tiles, rb.walk_counts, rb.emit_counts,
+        const ClearArgs ca = {rb.ctrs, rb.status, rb.cmp_tiles, rb.tip_counts, rb.walk_counts, rb.emit_counts,
                               rb.wbuf_counts};
         GP_LAUNCH_ITEMS(k_label, cfg.items_label, dim3(rb.tri_tiles), dim3(cfg.block_label),
                         sizeof(int) * 3 * (size_t)cfg.block_label * cfg.items_label, s, rb.descs, rb.nmesh, ca);
@@ -2419,12 +2416,12 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
     H(K_RELINK, 1);
 
     H(K_REPAIR, 0);
-    hipLaunchKernelGGL(k_repair, dim3(pb), dim3(pt), 0, s, rb.descs, rb.rc, rb.tips, rb.cap_tips, rb.walk,
-                       rb.walk_counts, rb.walk_cap, rb.fixes, rb.cap_fix);
+    hipLaunchKernelGGL(k_repair, dim3(pq), dim3(pt), 0, s, rb.descs, rb.nmesh, rb.tips, rb.tip_counts, rb.tip_cap, rb.cap_tips,
+                       rb.walk, rb.walk_counts, rb.walk_cap, rb.fixes);
     H(K_REPAIR, 1);
 
     H(K_FIXUP, 0);
-    hipLaunchKernelGGL(k_fixup, dim3(pb), dim3(256), 0, s, rb.descs, rb.rc, rb.fixes, rb.cap_fix);
+    hipLaunchKernelGGL(k_fixup, dim3(pq), dim3(256), 0, s, rb.descs, rb.tip_counts, rb.tip_cap, rb.cap_tips, rb.fixes);
     H(K_FIXUP, 1);
 
     H(K_WALK, 0);

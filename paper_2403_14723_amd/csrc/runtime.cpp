@@ -106,9 +106,10 @@ void debug_hook(void *user, int kernel, int after) {
                 (void)hipMemcpyAsync(h->d->prev_relink[i], x->prev_o, 4 * nh, hipMemcpyDeviceToDevice, s);
             }
         }
-        (void)hipMemcpyAsync(h->d->tips, h->rb->tips, sizeof(gp::ListEntry) * (size_t)h->d->cap_tips,
+        (void)hipMemcpyAsync(h->d->tips, h->rb->tips, sizeof(gp::ListEntry) * (size_t)h->d->tip_cap * gp::kTipStripes,
                              hipMemcpyDeviceToDevice, s);
-        (void)hipMemcpyAsync(h->d->ntips, &h->rb->rc->ntips, sizeof(int32_t), hipMemcpyDeviceToDevice, s);
+        (void)hipMemcpyAsync(h->d->tip_counts, h->rb->tip_counts, sizeof(int32_t) * gp::kTipStripes * gp::kStripePad,
+                             hipMemcpyDeviceToDevice, s);
     } else if (kernel == gp::K_EMIT) {
         for (int i = 0; i < n; i++) {
             const size_t nt = (size_t)(*h->res)[i]->nt;
@@ -246,7 +247,7 @@ namespace {
 // Sizes of one run over meshes of nts[0..n) triangles.  No allocation: the
 // no-allocation entry point plans its single mesh with this directly.
 struct PlanSizes {
-    int64_t tri_tiles = 0, he_tiles = 0, cmp_tiles = 0, cap_tips = 0, cap_fix = 0;
+    int64_t tri_tiles = 0, he_tiles = 0, cmp_tiles = 0, cap_tips = 0, tip_cap = 0;
     int64_t walk_cap = 0, emit_cap = 0, wbuf_cap = 0;
     size_t out_bytes = 0, tmp_bytes = 0, tmp_mesh = 0;
 };
@@ -279,22 +280,24 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
         total_nt += nt;
         if (p->tri_tiles > 0x7fffffff || p->he_tiles > 0x7fffffff || p->cap_tips > (1ll << 30)) return GP_ERANGE;
     }
-    p->cap_fix = 2 * p->cap_tips;
     // striped lists, sized for the worst case: every triangle of a tile holds
-    // a seed (walk) or a loop minimum (emit); repair seeds spread evenly
+    // a tip, a seed (walk) or a loop minimum (emit); repair seeds spread evenly
     const int64_t S = gp::kStripes;
+    p->tip_cap = (p->he_tiles + gp::kTipStripes - 1) / gp::kTipStripes * th;
     p->walk_cap = (p->he_tiles + S - 1) / S * th + (2 * p->cap_tips + S - 1) / S + 2;
     p->emit_cap = (p->cmp_tiles + S - 1) / S * tc;
-    // walked loops: at most 3T half-edges in all (each loop is stored once)
-    // plus one rotation index per loop; slack for uneven stripes
-    p->wbuf_cap = align_up((4 * total_nt + S - 1) / S + 4096, 4);
+    // walked loops: a general-position mesh takes about 1.7 ints a triangle
+    // (a stripe that fills up leaves its loops to k_emit); slack for uneven
+    // stripes
+    p->wbuf_cap = align_up((3 * total_nt + S - 1) / S + 2048, 4);
     if (p->walk_cap * S > 0x7fffffff || p->emit_cap * S > 0x7fffffff || p->wbuf_cap * S > 0x7fffffff)
         return GP_ERANGE;
-    p->tmp_bytes = p->tmp_mesh + arena_bytes<gp::MeshDesc>(n) + arena_bytes<gp::RunCounters>(1) +
-                   arena_bytes<gp::MeshCounters>(n) + arena_bytes<gp::ListEntry>(p->cap_tips) +
-                   arena_bytes<gp::ListEntry>(p->cap_fix) + 2 * arena_bytes<uint64_t>(p->cmp_tiles) +
+    p->tmp_bytes = p->tmp_mesh + arena_bytes<gp::MeshDesc>(n) +
+                   arena_bytes<gp::MeshCounters>(n) + arena_bytes<gp::ListEntry>(p->tip_cap * gp::kTipStripes) +
+                   arena_bytes<gp::ListEntry>(2 * p->cap_tips) + 2 * arena_bytes<uint64_t>(p->cmp_tiles) +
                    arena_bytes<gp::ListEntry>(p->walk_cap * S) + arena_bytes<gp::EmitEntry>(p->emit_cap * S) +
-                   arena_bytes<int32_t>(p->wbuf_cap * S + 32) + 3 * arena_bytes<int32_t>(S * gp::kStripePad);
+                   arena_bytes<int32_t>(p->wbuf_cap * S + 32) + 3 * arena_bytes<int32_t>(S * gp::kStripePad) +
+                   arena_bytes<int32_t>(gp::kTipStripes * gp::kStripePad);
     return GP_OK;
 }
 
@@ -330,12 +333,12 @@ void layout_scratch(const PlanSizes &p, const gp::MeshDesc *descs, int n, void *
     rb->tri_tiles = (int32_t)p.tri_tiles;
     rb->he_tiles = (int32_t)p.he_tiles;
     rb->cmp_tiles = (int32_t)p.cmp_tiles;
-    rb->rc = at.take<gp::RunCounters>(1);
     rb->ctrs = at.take<gp::MeshCounters>(n);
-    rb->tips = at.take<gp::ListEntry>(p.cap_tips);
-    rb->fixes = at.take<gp::ListEntry>(p.cap_fix);
+    rb->tips = at.take<gp::ListEntry>(p.tip_cap * gp::kTipStripes);
+    rb->tip_counts = at.take<int32_t>(gp::kTipStripes * gp::kStripePad);
+    rb->tip_cap = (int32_t)p.tip_cap;
     rb->cap_tips = (int32_t)p.cap_tips;
-    rb->cap_fix = (int32_t)p.cap_fix;
+    rb->fixes = at.take<gp::ListEntry>(2 * p.cap_tips);
     rb->status = at.take<uint64_t>(p.cmp_tiles);
     rb->cpre = at.take<uint64_t>(p.cmp_tiles);
     {
@@ -1054,7 +1057,7 @@ int parse_launch_spec(const char *spec, gp::LaunchCfg *cfg) {
         }
     }
     // LDS per tile: k_label stages 12 bytes per triangle (tile <= 4096),
-    // k_relink 37 bytes (tile <= 1024), k_compact 19 bytes (tile <= 2048)
+    // k_relink 36 bytes (tile <= 1024), k_compact 19 bytes (tile <= 2048)
     while ((int64_t)g.block_label * g.items_label > 4096 && g.items_label > 1) g.items_label /= 2;
     while ((int64_t)g.block_relink * g.items_relink > 1024 && g.items_relink > 1) g.items_relink /= 2;
     while ((int64_t)g.block_compact * g.items_compact > 2048 && g.items_compact > 1) g.items_compact /= 2;
@@ -1204,16 +1207,20 @@ int gpolylla_result_debug(gp_result *x, gp_result_debug *out) {
     if (nt && out->tflag_final) HIP_OK(hipMemcpy(out->tflag_final, d.tflag_final[i], nt, hipMemcpyDeviceToHost));
     if (nh && out->next_relink) HIP_OK(hipMemcpy(out->next_relink, d.next_relink[i], 4 * nh, hipMemcpyDeviceToHost));
     if (nh && out->prev_relink) HIP_OK(hipMemcpy(out->prev_relink, d.prev_relink[i], 4 * nh, hipMemcpyDeviceToHost));
-    int32_t total = 0;
-    HIP_OK(hipMemcpy(&total, d.ntips, sizeof total, hipMemcpyDeviceToHost));
-    total = std::max(0, std::min(total, d.cap_tips));
-    std::vector<gp::ListEntry> all((size_t)total);
-    if (total) HIP_OK(hipMemcpy(all.data(), d.tips, sizeof(gp::ListEntry) * (size_t)total, hipMemcpyDeviceToHost));
+    std::vector<int32_t> counts(gp::kTipStripes * gp::kStripePad);
+    HIP_OK(hipMemcpy(counts.data(), d.tip_counts, sizeof(int32_t) * counts.size(), hipMemcpyDeviceToHost));
+    std::vector<gp::ListEntry> part;
     int32_t k = 0;
-    for (const gp::ListEntry &e : all) {
-        if (e.mesh != i) continue;
-        if (out->tips && k < out->tips_cap) out->tips[k] = e.he;
-        k++;
+    for (int s = 0; s < gp::kTipStripes; s++) {
+        part.resize((size_t)std::max(0, std::min(counts[s * gp::kStripePad], d.tip_cap)));
+        if (!part.empty())
+            HIP_OK(hipMemcpy(part.data(), d.tips + (size_t)s * d.tip_cap, sizeof(gp::ListEntry) * part.size(),
+                             hipMemcpyDeviceToHost));
+        for (const gp::ListEntry &e : part) {
+            if (e.mesh != i) continue;
+            if (out->tips && k < out->tips_cap) out->tips[k] = e.he;
+            k++;
+        }
     }
     out->ntips = k;
     return st;
@@ -1467,7 +1474,9 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
     if (err == GP_OK && c->debug) {
         // the snapshots' memory: per mesh two label arrays and next', prev'
         DebugSnap *d = new (std::nothrow) DebugSnap();
-        size_t bytes = align_up(sizeof(gp::ListEntry) * (size_t)std::max(rb.cap_tips, 1)) + kAlign;
+        const size_t ntips = (size_t)rb.tip_cap * gp::kTipStripes,
+                     ncounts = (size_t)gp::kTipStripes * gp::kStripePad;
+        size_t bytes = arena_bytes<gp::ListEntry>(ntips) + arena_bytes<int32_t>(ncounts);
         for (int i = 0; i < n; i++)
             bytes += 2 * align_up((size_t)std::max(res[i]->nt, 1)) +
                      2 * align_up(sizeof(int32_t) * 3 * (size_t)std::max(res[i]->nt, 1));
@@ -1476,9 +1485,9 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
             err = GP_ENOMEM;
         } else {
             Arena ad{static_cast<char *>(d->block), bytes, 0};
-            d->cap_tips = rb.cap_tips;
-            d->tips = ad.take<gp::ListEntry>((size_t)std::max(rb.cap_tips, 1));
-            d->ntips = ad.take<int32_t>(1);
+            d->tip_cap = rb.tip_cap;
+            d->tips = ad.take<gp::ListEntry>(ntips);
+            d->tip_counts = ad.take<int32_t>(ncounts);
             for (int i = 0; i < n; i++) {
                 const size_t nt = (size_t)std::max(res[i]->nt, 1);
                 d->tflag_relink.push_back(ad.take<uint8_t>(nt));

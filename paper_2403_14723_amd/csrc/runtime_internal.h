@@ -241,9 +241,9 @@ struct DebugSnap {
     void *block = nullptr;
     std::vector<uint8_t *> tflag_relink, tflag_final;
     std::vector<int32_t *> next_relink, prev_relink;
-    gp::ListEntry *tips = nullptr;    // cap_tips entries
-    int32_t *ntips = nullptr;         // the run's tip count
-    int32_t cap_tips = 0;
+    gp::ListEntry *tips = nullptr;    // the striped list: tip_cap entries per stripe
+    int32_t *tip_counts = nullptr;    // its counters
+    int32_t tip_cap = 0;
 };
 
 struct RunState {
