@@ -5,7 +5,8 @@
 //   org[3T]     origin vertex of each half-edge (counter-clockwise corners)
 //   twin[3T]    opposite half-edge, -1 on the boundary
 //   tflag[T]    uint8 per triangle: bits 0-1 local index of the longest edge,
-//               bits 2-4 frontier bit of local edges 0..2, bit 5 seed
+//               bits 2-4 frontier bit of local edges 0..2, bit 5 seed, bits 6-7
+//               marks of the repair and the walk (mesh_kernels.hip)
 //   pl[T]       uint8 per triangle: 0, or (min(L,63) << 2 | i) when half-edge
 //               3t+i is the minimum of a loop of length L
 //   next_o/prev_o[3T], seeds[<=T], loop_off[<=T+1], loop_he[<=3T] (outputs)
@@ -46,8 +47,8 @@ struct MeshDesc {
     int32_t *seeds;
     int32_t *loop_off;
     int32_t *loop_he;
-    int32_t *lpos;       // per triangle: where k_walk stored the loop whose minimum it holds
-                         // (or that loop's length, when it is kPlMax or longer)
+    int32_t *lpos;       // per triangle: where k_walk stored the loop whose minimum it holds (-1: nowhere;
+                         // or that loop's length, when it is kPlMax or longer)
     MeshCounters *ctr;
     int32_t nt;
     int32_t nv;
@@ -143,7 +144,6 @@ struct RunBuffers {
 // loops are left to k_emit
 constexpr int kWalkBuf = 16;
 constexpr long long kStreamOutBytes = 256ll << 20;   // MI355X's last-level cache (Infinity Cache)
-constexpr int kWalkItems = 1;   // chains per k_walk thread
 constexpr int kTileScanItems = 4;                   // compaction tiles per k_tile_scan thread
 constexpr int kScanChunk = 1024 * kTileScanItems;   // compaction tiles per k_tile_scan block
 // k_compact's LDS holds up to this many loop half-edges per 4 triangles of

@@ -33,8 +33,9 @@
 //   bits 2-4  frontier bit of local edges 0..2 (the repair sets more of them)
 //   bit  5    the longest edge is a terminal edge and this triangle holds its
 //             seed half-edge
-//   bit  6    k_walk stored the loop whose minimum lies in this triangle
-//   bit  7    (from k_label to k_relink only) the longest edge is tied
+//   bit  6    the repair split the polygon whose seed this triangle holds
+//   bit  7    from k_label to k_relink: the longest edge is tied; in k_walk: a
+//             loop of a split polygon whose minimum lies here has been counted
 #include "gp_internal.h"
 
 namespace gp {
@@ -418,31 +419,20 @@ __device__ __forceinline__ uint8_t loop_code(int mn, int len) {
 }
 constexpr int kPlQuadNext = 1;
 
-// Records a walked loop (minimum mn, length len) once: the walker that sets
-// the byte of the minimum's triangle adds the loop to the totals of that
-// triangle's compaction tile.  After a repair several seeds of one polygon
-// walk the same loop; only the first counts it.  claim_issue ORs the code in
-// and returns the word as it was (every walker of the loop writes the same
-// code, so OR-ing is safe); claim_won reads the verdict from it, so other
-// memory operations can be issued while the atomic is in flight.
-__device__ __forceinline__ uint32_t claim_issue(const MeshDesc &d, int mn, int len) {
-    const int tm = tri_of(mn);
-    uint32_t *w = reinterpret_cast<uint32_t *>(d.pl) + (tm >> 2);
-    return atomicOr(w, (uint32_t)loop_code(mn, len) << (8 * (tm & 3)));
-}
-__device__ __forceinline__ bool claim_won(const MeshDesc &d, uint32_t old, int mn, int len, uint64_t *agg,
-                                          int cmp_tb) {
-    const int tm = tri_of(mn);
-    if ((old >> (8 * (tm & 3))) & 0xffu) return false;
-    atomicAdd(reinterpret_cast<unsigned long long *>(agg + d.cmp_tile0 + tm / cmp_tb),
-              (1ull << 32) | (unsigned long long)(uint32_t)len);
-    return true;
-}
+// Label bits 6 and 7 (k_relink writes the label bytes with both clear).  The
+// repair splits a polygon along middle edges, both sides of which then seed a
+// walk, so every part has such a seed, some several, and the polygon's own seed
+// is not needed: its triangle is marked and its walk left out.  Of the walks
+// that a part still has several of, the first to set bit 7 at the minimum's
+// triangle counts the loop; no other loop is walked twice.
+constexpr uint32_t kSplitBit = 1u << 6;
+constexpr uint32_t kCountedBit = 1u << 7;
 
-// Label bit 6 of a loop's minimum triangle: k_walk stored the loop in the
-// scratch pool (at lpos of that triangle); k_relink writes the label bytes
-// with the bit clear.
-constexpr uint32_t kStoredBit = 1u << 6;
+// Sets a bit of triangle t's label byte; returns whether it was set before.
+__device__ __forceinline__ bool set_label_bit(const MeshDesc &d, int t, uint32_t bit) {
+    const uint32_t b = bit << (8 * (t & 3));
+    return atomicOr(reinterpret_cast<uint32_t *>(d.tflag) + (t >> 2), b) & b;
+}
 
 // Slots: half-edge 3t + i as 4t + i; a boundary twin (-1) is kNoSlot, the only
 // slot of local index 3.
@@ -836,7 +826,8 @@ __device__ __forceinline__ int wave_reserve2(int32_t *counter, bool pred) {
 // list appends and counters cost one atomic per wave (tips are many on
 // general-position meshes, and atomics on one address serialize).  Tip k's two
 // anchors for k_fixup go to entries 2k and 2k + 1 (half-edge -1: none).
-__global__ void k_repair(const MeshDesc *__restrict__ descs, int nmesh, const ListEntry *tips, const int32_t *tip_counts,
+template <bool ONE>
+__global__ void k_repair(const MeshDesc *__restrict__ descs, const ListEntry *tips, const int32_t *tip_counts,
                          int tip_cap, int cap_tips, ListEntry *walk, int32_t *walk_counts, int walk_cap,
                          ListEntry *fixes) {
     const TipStripes stripes(tip_counts, tip_cap);
@@ -845,7 +836,7 @@ __global__ void k_repair(const MeshDesc *__restrict__ descs, int nmesh, const Li
     const int stride = gridDim.x * blockDim.x;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (all > cap_tips) atomicOr(&descs[0].ctr->err, kErrCorrupt);
-        if (nmesh == 1) descs[0].ctr->ntips = ntips;
+        if (ONE) descs[0].ctr->ntips = ntips;
     }
     for (int wbase = blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); wbase < ntips; wbase += stride) {
         const int k = wbase + lane;
@@ -854,8 +845,8 @@ __global__ void k_repair(const MeshDesc *__restrict__ descs, int nmesh, const Li
         bool newmid = false;
         if (ok) {
             const ListEntry e = tips[stripes.index(k, tip_cap)];
-            mesh = e.mesh;
-            const MeshDesc &d = descs[e.mesh];
+            mesh = ONE ? 0 : e.mesh;
+            const MeshDesc &d = descs[ONE ? 0 : mesh];
             const TwinView twin = twin_view(d);
             // a: the only frontier edge at the tip v = target(e.he), leaving v.
             // The middle edge is the outgoing half-edge floor(deg / 2)
@@ -909,11 +900,11 @@ __global__ void k_repair(const MeshDesc *__restrict__ descs, int nmesh, const Li
         if (ok) {
             if (c + 1 < walk_cap) {
                 walk[stripe * walk_cap + c].mesh = mesh;
-                walk[stripe * walk_cap + c].he = m;
+                walk[stripe * walk_cap + c].he = ~m;
                 walk[stripe * walk_cap + c + 1].mesh = mesh;
-                walk[stripe * walk_cap + c + 1].he = mt;
+                walk[stripe * walk_cap + c + 1].he = ~mt;
             } else {
-                atomicOr(&descs[mesh].ctr->err, kErrCorrupt);
+                atomicOr(&descs[ONE ? 0 : mesh].ctr->err, kErrCorrupt);
             }
         }
         // tips (of a batch) and new middle edges, counted per mesh: one atomic each per mesh in the wave
@@ -923,8 +914,8 @@ __global__ void k_repair(const MeshDesc *__restrict__ descs, int nmesh, const Li
             const int lm = __shfl(mesh, leader);
             const unsigned long long same = __ballot(k < ntips && mesh == lm), mid = __ballot(ok && newmid && mesh == lm);
             if (lane == leader) {
-                if (nmesh > 1) atomicAdd(&descs[lm].ctr->ntips, __popcll(same));
-                if (mid) atomicAdd(&descs[lm].ctr->nmiddle, __popcll(mid));
+                if (!ONE) atomicAdd(&descs[ONE ? 0 : lm].ctr->ntips, __popcll(same));
+                if (mid) atomicAdd(&descs[ONE ? 0 : lm].ctr->nmiddle, __popcll(mid));
             }
             pending &= ~same;
         }
@@ -956,14 +947,54 @@ __device__ __forceinline__ void sweep_step(gcu8 tfl, gint nxo, gint pvo, int o, 
     }
 }
 
-__global__ void __launch_bounds__(256) k_fixup(const MeshDesc *__restrict__ descs, const int32_t *tip_counts,
-                                               int tip_cap, int cap_tips, const ListEntry *fixes) {
-    const int nfix = 2 * min(TipStripes(tip_counts, tip_cap).total(), cap_tips);
+// Marks the seed of triangle t's polygon as split: up the longest edges from t
+// (Lepp, Definition 1) to the terminal edge, whose lower half-edge is the seed.
+// A triangle's label and its three twins are loaded together, so a step is one
+// dependent load.  Returns false when the structure is inconsistent.
+__device__ __forceinline__ bool mark_split(const MeshDesc &d, int t) {
+    const TwinView twin = twin_view(d);
+    const gcu8 tfl = (gcu8)d.tflag;
+    int L = (int)(tfl[t] & 3u), g0 = twin[3 * t], g1 = twin[3 * t + 1], g2 = twin[3 * t + 2];
+    for (int k = 0; k < kRotGuard; k++) {   // (a longer edge each time)
+        const int g = L == 0 ? g0 : (L == 1 ? g1 : g2);
+        if (g < 0) {   // a boundary terminal edge
+            set_label_bit(d, t, kSplitBit);
+            return true;
+        }
+        const int u = tri_of(g), Lu = (int)(tfl[u] & 3u);
+        g0 = twin[3 * u];
+        g1 = twin[3 * u + 1];
+        g2 = twin[3 * u + 2];
+        if (Lu == g - 3 * u) {
+            set_label_bit(d, 3 * t + L < g ? t : u, kSplitBit);
+            return true;
+        }
+        t = u;
+        L = Lu;
+    }
+    return false;
+}
+
+// The anchors of every tip, and its polygon's mark: in waves of its own, beside
+// those of the anchors, since both are chains of dependent loads.
+template <bool ONE>
+__global__ void __launch_bounds__(256) k_fixup(const MeshDesc *__restrict__ descs, const ListEntry *tips,
+                                               const int32_t *tip_counts, int tip_cap, int cap_tips,
+                                               const ListEntry *fixes) {
+    const TipStripes stripes(tip_counts, tip_cap);
+    const int ntips = min(stripes.total(), cap_tips), nfix = 2 * ntips, mark0 = (nfix + kWave - 1) & ~(kWave - 1);
     const int stride = gridDim.x * blockDim.x;
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < nfix; q += stride) {
+    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < mark0 + ntips; q += stride) {
+        if (q >= nfix) {
+            if (q < mark0) continue;
+            const ListEntry tip = tips[stripes.index(q - mark0, tip_cap)];
+            const MeshDesc &d = descs[ONE ? 0 : tip.mesh];
+            if (!mark_split(d, tri_of(tip.he))) atomicOr(&d.ctr->err, kErrCorrupt);
+            continue;
+        }
         const ListEntry en = fixes[q];
         if (en.he < 0) continue;
-        const MeshDesc &d = descs[en.mesh];
+        const MeshDesc &d = descs[ONE ? 0 : en.mesh];
         const TwinView twin = twin_view(d);
         const gcu8 tfl = (gcu8)d.tflag;
         const gint nxo = (gint)d.next_o, pvo = (gint)d.prev_o;
@@ -1045,34 +1076,38 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 }
 
 
-// Every entry of the walk list: from the seed to a frontier half-edge of its
-// polygon (a frontier half-edge of the seed's own triangle if it has one),
-// around the loop, and the loop recorded.  A loop still open after
-// kWalkBoth steps (or after the first, when the loops are few and so
-// latency decides) is walked from both ends from then on:
-// forward along next' and backward along prev' from the start, the two
-// loads of a step in flight together, until the ends meet, so a long loop
-// of len half-edges takes about len / 2 dependent steps (short loops, the
-// most, read no prev').  Each
-// thread keeps ITEMS loops in flight and advances them in lock-step.  Every
-// chain also writes the half-edges it visits to an LDS buffer (forward ones
-// from the front, backward ones from the back), so the walker that claims a
-// loop of at most BUF half-edges copies it to the scratch pool (rotation
-// index of the minimum, then the half-edges in loop order from the first
-// backward one) and k_compact places it without walking it again.  Whole
-// waves iterate together: the pool is reserved once per wave and step, for
-// every loop that closed in that step and fits the buffer, while the claims
-// are still in flight (a walker that loses the claim leaves its space
-// unused).
+// Every entry of the walk list (a repair seed's half-edge complemented): from
+// the seed to a frontier half-edge of its polygon (a frontier half-edge of the
+// seed's own triangle if it has one), around the loop, and the loop recorded:
+// its code at the minimum's triangle, one more loop for that triangle's
+// compaction tile.  A loop still open after kWalkBoth steps (or after the
+// first, when the loops are few and so latency decides) is walked from both
+// ends from then on: forward along next' and backward along prev' from the
+// start, the two loads of a step in flight together, until the ends meet, so
+// a long loop of len half-edges takes about len / 2 dependent steps (short
+// loops, the most, read no prev').  Each chain also writes the half-edges it
+// visits to an LDS buffer (forward ones from the front, backward ones from
+// the back), so a loop of at most BUF half-edges is copied to the scratch pool
+// (rotation index of the minimum, then the half-edges in loop order from the
+// first backward one) and k_compact places it without walking it again.
+//
+// Whole waves iterate together, with nothing but the two loads in a step.  What
+// bounds the kernel is its device-scope atomics: one per wave for the pool, one
+// per wave and compaction tile for the totals (a wave's loops end in a few
+// tiles), one per repair seed.  With a claim, a total and a mark per loop,
+// settled in the step in which it closed, the 1M-point Delaunay mesh (280,000
+// loops) took 61 us.
 constexpr int kWalkBoth = 8;
 
-template <int ITEMS, int BUF>
+// ONE (here and in the other list-driven kernels): a run of one mesh, whose
+// descriptor is read once, uniformly, and not per entry.
+template <int BUF, bool ONE>
 __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs, const ListEntry *walk,
                                               const int32_t *walk_counts, int walk_cap, uint64_t *agg,
                                               int cmp_tb, int32_t *wbuf, int32_t *wbuf_counts, int wbuf_cap) {
-    constexpr int kSlots = 256 * ITEMS;
+    constexpr int kSlots = 256;
     __shared__ int s_pref[kStripes + 1];
-    __shared__ int s_buf[BUF * kSlots];   // element k of chain slot q at k * kSlots + q
+    __shared__ int s_buf[BUF * kSlots];   // element k of thread q's chain at k * kSlots + q
     const int total = striped_prefix(walk_counts, walk_cap, s_pref);
     const int nthreads = gridDim.x * blockDim.x;
     const int lane = __lane_id(), tid = threadIdx.x;
@@ -1081,130 +1116,110 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
     // critical path, so all go both ways from the first step; otherwise only
     // the long ones
     const int both = total <= nthreads / 4 ? 1 : kWalkBoth;
-    for (int b0 = blockIdx.x * blockDim.x; b0 < total; b0 += nthreads * ITEMS) {   // block-uniform
-        gcint nx[ITEMS], pv[ITEMS];
+    for (int b0 = blockIdx.x * blockDim.x; b0 < total; b0 += nthreads) {   // block-uniform
+        gcint nx = nullptr, pv = nullptr;
         // forward end fc (fa half-edges taken, from the start on), backward
         // end bc (bb taken before the start; the start itself while bb == 0);
         // the minimum so far and where: forward index, or ~backward index
-        int mesh[ITEMS], fc[ITEMS], bc[ITEMS], fa[ITEMS], bb[ITEMS], mn[ITEMS], mpos[ITEMS], lim[ITEMS];
-        bool live[ITEMS];
-#pragma unroll
-        for (int j = 0; j < ITEMS; j++) {
-            fc[j] = bc[j] = mn[j] = -1;
-            fa[j] = bb[j] = mpos[j] = lim[j] = 0;
-            mesh[j] = 0;
-            live[j] = false;
-            nx[j] = pv[j] = nullptr;
-            const int g = b0 + tid + j * nthreads;
-            if (g >= total) continue;
-            const ListEntry e = walk[striped_index(s_pref, walk_cap, g)];
-            const MeshDesc &d = descs[e.mesh];
-            mesh[j] = e.mesh;
-            nx[j] = (gcint)d.next_o;
-            pv[j] = (gcint)d.prev_o;
-            lim[j] = 3 * d.nt;
-            const int t = tri_of(e.he);
+        int mesh = 0, fc = -1, bc = -1, fa = 0, bb = 0, mn = -1, mpos = 0, lim = 0;
+        bool live = false, closed = false, repair = false;
+        if (b0 + tid < total) {
+            const ListEntry e = walk[striped_index(s_pref, walk_cap, b0 + tid)];
+            mesh = ONE ? 0 : e.mesh;
+            const MeshDesc &d = descs[mesh];
+            repair = e.he < 0;
+            const int he = repair ? ~e.he : e.he, t = tri_of(he);
+            nx = (gcint)d.next_o;
+            pv = (gcint)d.prev_o;
+            lim = 3 * d.nt;
             const uint32_t f = ((gcu8)d.tflag)[t];
-            int st = fbit(f, e.he - 3 * t) ? e.he : -1;
+            if (repair || !(f & kSplitBit)) {
+                int st = fbit(f, he - 3 * t) ? he : -1;
 #pragma unroll
-            for (int i = 0; i < 3; i++)
-                if (st < 0 && fbit(f, i)) st = 3 * t + i;
-            if (st < 0) st = seek_frontier(d, e.he);
-            if (st < 0) {
-                atomicOr(&d.ctr->err, kErrCorrupt);
-                continue;
+                for (int i = 0; i < 3; i++)
+                    if (st < 0 && fbit(f, i)) st = 3 * t + i;
+                if (st < 0) st = seek_frontier(d, he);
+                if (st < 0) atomicOr(&d.ctr->err, kErrCorrupt);
+                live = st >= 0;
+                fc = bc = mn = st;
+                fa = 1;
+                s_buf[tid] = st;
             }
-            fc[j] = bc[j] = mn[j] = st;
-            fa[j] = 1;
-            live[j] = true;
-            s_buf[j * 256 + tid] = st;
         }
-        while (true) {
-            bool active = false;
-            int need[ITEMS], len[ITEMS], rot[ITEMS];
-            bool closed[ITEMS];
-            uint32_t claim[ITEMS];
-#pragma unroll
-            for (int j = 0; j < ITEMS; j++) {
-                need[j] = len[j] = rot[j] = 0;
-                closed[j] = false;
-                claim[j] = 0;
-                if (!live[j]) continue;
-                const bool two = fa[j] >= both;
-                const int nf = nx[j][fc[j]], nb = two ? pv[j][bc[j]] : 0;
-                bool done = nf == bc[j];   // the forward end reached the backward one
-                if (!done && nf >= 0) {
-                    fc[j] = nf;
-                    if (fa[j] < BUF) s_buf[fa[j] * kSlots + j * 256 + tid] = nf;
-                    if (nf < mn[j]) {
-                        mn[j] = nf;
-                        mpos[j] = fa[j];
+        while (__any(live)) {
+            if (!live) continue;
+            const bool two = fa >= both;
+            const int nf = nx[fc], nb = two ? pv[bc] : 0;
+            bool done = nf == bc;   // the forward end reached the backward one
+            if (!done && nf >= 0) {
+                fc = nf;
+                if (fa < BUF) s_buf[fa * kSlots + tid] = nf;
+                if (nf < mn) {
+                    mn = nf;
+                    mpos = fa;
+                }
+                ++fa;
+                done = two && nb == nf;   // the backward end reached the forward one
+                if (two && !done && nb >= 0) {
+                    bc = nb;
+                    if (bb < BUF) s_buf[(BUF - 1 - bb) * kSlots + tid] = nb;
+                    if (nb < mn) {
+                        mn = nb;
+                        mpos = ~bb;
                     }
-                    ++fa[j];
-                    done = two && nb == nf;   // the backward end reached the forward one
-                    if (two && !done && nb >= 0) {
-                        bc[j] = nb;
-                        if (bb[j] < BUF) s_buf[(BUF - 1 - bb[j]) * kSlots + j * 256 + tid] = nb;
-                        if (nb < mn[j]) {
-                            mn[j] = nb;
-                            mpos[j] = ~bb[j];
-                        }
-                        ++bb[j];
-                    }
+                    ++bb;
                 }
-                len[j] = fa[j] + bb[j];
-                if (nf < 0 || nb < 0 || len[j] > lim[j]) {
-                    atomicOr(&descs[mesh[j]].ctr->err, kErrCorrupt);
-                    live[j] = false;
-                    continue;
-                }
-                if (done) {
-                    closed[j] = true;
-                    // position of the minimum in loop order from the first backward half-edge
-                    rot[j] = mpos[j] >= 0 ? bb[j] + mpos[j] : bb[j] - 1 - ~mpos[j];
-                    claim[j] = claim_issue(descs[mesh[j]], mn[j], len[j]);
-                    // whole 16-byte groups, so k_compact reads a loop with vector loads
-                    need[j] = len[j] <= BUF ? (len[j] + 4) & ~3 : 0;
-                    live[j] = false;
-                    continue;
-                }
-                active = true;
             }
-            // pool space for the loops claimed in this step: one atomic per wave
-            int mine = 0;
-#pragma unroll
-            for (int j = 0; j < ITEMS; j++) mine += need[j];
-            const int incl = wave_incl_scan(mine);   // the loop's exit is wave-uniform: all lanes here
-            const int wtot = __builtin_amdgcn_readlane(incl, kWave - 1);
-            int wbase = 0;
-            if (lane == 0 && wtot > 0) wbase = atomicAdd(&wbuf_counts[wstripe * kStripePad], wtot);
-            wbase = __builtin_amdgcn_readlane(wbase, 0);
-            const bool room = wbase + wtot <= wbuf_cap;
-            int pos = wstripe * wbuf_cap + wbase + incl - mine;
-#pragma unroll
-            for (int j = 0; j < ITEMS; j++) {
-                if (!closed[j]) continue;
-                const MeshDesc &d = descs[mesh[j]];
-                const bool won = claim_won(d, claim[j], mn[j], len[j], agg, cmp_tb);
-                // a loop too long for its length code is never stored, so its
-                // minimum's lpos slot is free: its length goes there for k_compact
-                if (won && len[j] >= kPlMax) ((gint)d.lpos)[tri_of(mn[j])] = len[j];
-                if (won && need[j] && room) {
-                    const gint out = (gint)wbuf + pos;
-                    out[0] = rot[j];
-                    // the backward half-edges (from the back of the buffer), then the forward ones
-                    for (int k = 0; k < len[j]; k++) {
-                        const int at = k < bb[j] ? BUF - bb[j] + k : k - bb[j];
-                        out[1 + k] = s_buf[at * kSlots + j * 256 + tid];
-                    }
-                    const int tm = tri_of(mn[j]);
-                    ((gint)d.lpos)[tm] = pos;
-                    atomicOr(reinterpret_cast<uint32_t *>(d.tflag) + (tm >> 2), kStoredBit << (8 * (tm & 3)));
-                }
-                pos += need[j];
-            }
-            if (!__any(active)) break;
+            const bool bad = nf < 0 || nb < 0 || fa + bb > lim;
+            if (bad) atomicOr(&descs[ONE ? 0 : mesh].ctr->err, kErrCorrupt);
+            closed = done && !bad;
+            live = !done && !bad;
         }
+        // every loop of the wave has closed: the claims of the repair seeds,
+        // in flight with one atomic for the wave's pool space (a walker that
+        // loses its claim leaves its space unused)
+        const MeshDesc &d = descs[ONE ? 0 : mesh];
+        const int len = fa + bb, tm = closed ? tri_of(mn) : 0;
+        const bool taken = closed && repair && set_label_bit(d, tm, kCountedBit);
+        // whole 16-byte groups, so k_compact reads a loop with vector loads
+        const int need = closed && len <= BUF ? (len + 4) & ~3 : 0;
+        const int incl = wave_incl_scan(need), wtot = __builtin_amdgcn_readlane(incl, kWave - 1);
+        int wbase = 0;
+        if (lane == 0 && wtot > 0) wbase = atomicAdd(&wbuf_counts[wstripe * kStripePad], wtot);
+        wbase = __builtin_amdgcn_readlane(wbase, 0);
+        const int pos = wbase + wtot <= wbuf_cap ? wstripe * wbuf_cap + wbase + incl - need : -1;
+        const bool won = closed && !taken;
+        const int key = won ? d.cmp_tile0 + tm / cmp_tb : -1;
+        if (won) {
+            ((gu8)d.pl)[tm] = loop_code(mn, len);
+            // where the loop is stored (-1: nowhere), or its length when the
+            // code does not hold it
+            if (len <= BUF || len >= kPlMax) ((gint)d.lpos)[tm] = len >= kPlMax ? len : pos;
+            if (need && pos >= 0) {
+                // position of the minimum in loop order from the first backward
+                // half-edge; then the backward half-edges (from the back of the
+                // buffer) and the forward ones, in 16-byte groups
+                GLOBAL v4i *out = (GLOBAL v4i *)((gint)wbuf + pos);
+                const int rot = mpos >= 0 ? bb + mpos : bb - 1 - ~mpos;
+                const int back = (BUF - bb) * kSlots + tid, fore = -bb * kSlots + tid;
+                const auto at = [&](int k) { return s_buf[(k < bb ? back : fore) + min(k, len - 1) * kSlots]; };
+                for (int k = -1; k < len; k += 4) *out++ = v4i{k < 0 ? rot : at(k), at(k + 1), at(k + 2), at(k + 3)};
+            }
+        }
+        // the loops into their compaction tiles' totals, tile by tile for up
+        // to four tiles, then one by one
+        unsigned long long todo = __ballot(won);
+        for (int k = 0; k < 4 && todo; k++) {
+            const int leader = __ffsll((long long)todo) - 1, kt = __builtin_amdgcn_readlane(key, leader);
+            const unsigned long long same = __ballot(key == kt);
+            const int sum = __builtin_amdgcn_readlane(wave_incl_scan(key == kt ? len : 0), kWave - 1);
+            if (lane == leader)
+                atomicAdd(reinterpret_cast<unsigned long long *>(agg + kt),
+                          ((unsigned long long)(uint32_t)__popcll(same) << 32) | (unsigned long long)(uint32_t)sum);
+            todo &= ~same;
+        }
+        if ((todo >> lane) & 1)
+            atomicAdd(reinterpret_cast<unsigned long long *>(agg + key), (1ull << 32) | (unsigned long long)(uint32_t)len);
     }
 }
 
@@ -1212,7 +1227,7 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
 // from both ends at once: position s forward along next' and position len - s
 // backward along prev', so the two loads of a step are in flight together and
 // a loop of len half-edges takes about len / 2 dependent steps.
-template <int ITEMS>
+template <int ITEMS, bool ONE>
 __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs, const EmitEntry *emit,
                                               const int32_t *emit_counts, int emit_cap) {
     __shared__ int s_pref[kStripes + 1];
@@ -1232,8 +1247,8 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
             const int g = g0 + j * nthreads;
             if (g >= total) continue;
             const EmitEntry e = emit[striped_index(s_pref, emit_cap, g)];
-            const MeshDesc &d = descs[e.mesh];
-            mesh[j] = e.mesh;
+            const MeshDesc &d = descs[ONE ? 0 : e.mesh];
+            mesh[j] = ONE ? 0 : e.mesh;
             // k_compact left the loop's length in its first slot
             const int L = (e.off >= 0 && e.off < 3 * d.nt) ? ((gcint)d.loop_he)[e.off] : -1;
             if (L < 1 || (long long)e.off + L > 3ll * d.nt) {
@@ -1260,7 +1275,7 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
                 }
                 const int nf = nx[j][f[j]], nb = pv[j][b[j]];   // both in flight together
                 if (nf < 0 || nb < 0) {
-                    atomicOr(&descs[mesh[j]].ctr->err, kErrCorrupt);
+                    atomicOr(&descs[ONE ? 0 : mesh[j]].ctr->err, kErrCorrupt);
                     live[j] = false;
                     continue;
                 }
@@ -1423,13 +1438,13 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
         }
     }
     int lens[ITEMS];
-    bool defer[ITEMS];
+    bool defer[ITEMS], stored[ITEMS];
     int cnt = 0, sum = 0, nd = 0;
     bool bad = false;
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
         lens[j] = 0;
-        defer[j] = false;
+        defer[j] = stored[j] = false;
         if (!code[j]) continue;
         int len = code[j] >> 2;
         if (len == kPlQuadNext) len = 4;
@@ -1444,7 +1459,8 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
         defer[j] = len > 0 && len != 3 && !(len == 4 && __popc((fl[j] >> 2) & 7u) == 2);
         cnt += 1;
         sum += len;
-        nd += defer[j] && !(fl[j] & kStoredBit);
+        stored[j] = defer[j] && len <= kWalkBuf && lp[j] >= 0;
+        nd += defer[j] && !stored[j];
     }
     // 2. block scan: tile-local loop index and offset, emit-list slot
     int ecn, esum, tcn, tsum;
@@ -1519,7 +1535,7 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
                     he_out[off + 2] = he_next(p1);
                     he_out[off + 3] = aa;
                 }
-            } else if (defer[j] && (fl[j] & kStoredBit)) {
+            } else if (stored[j]) {
                 // stored by k_walk in walk order from some start; rotate so
                 // the loop begins at its minimum (loads first, all in flight)
                 static_assert(kWalkBuf % 4 == 0, "stored loops are read in 16-byte groups");
@@ -2396,6 +2412,7 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
     // blocks for them, for the time that idle ones take to start and end
     const int pb = cfg.persistent_blocks, pt = cfg.block_persistent, pq = (pb + 3) / 4;
     const int cmp_tb = cfg.block_compact * cfg.items_compact;   // triangles per compaction tile
+    const bool one = rb.nmesh == 1;
 
     H(K_LABEL, 0);
     {
@@ -2416,16 +2433,17 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
     H(K_RELINK, 1);
 
     H(K_REPAIR, 0);
-    hipLaunchKernelGGL(k_repair, dim3(pq), dim3(pt), 0, s, rb.descs, rb.nmesh, rb.tips, rb.tip_counts, rb.tip_cap, rb.cap_tips,
+    hipLaunchKernelGGL(one ? k_repair<true> : k_repair<false>, dim3(pq), dim3(pt), 0, s, rb.descs, rb.tips, rb.tip_counts, rb.tip_cap, rb.cap_tips,
                        rb.walk, rb.walk_counts, rb.walk_cap, rb.fixes);
     H(K_REPAIR, 1);
 
     H(K_FIXUP, 0);
-    hipLaunchKernelGGL(k_fixup, dim3(pq), dim3(256), 0, s, rb.descs, rb.tip_counts, rb.tip_cap, rb.cap_tips, rb.fixes);
+    hipLaunchKernelGGL(one ? k_fixup<true> : k_fixup<false>, dim3(pq), dim3(256), 0, s, rb.descs, rb.tips, rb.tip_counts,
+                       rb.tip_cap, rb.cap_tips, rb.fixes);
     H(K_FIXUP, 1);
 
     H(K_WALK, 0);
-    hipLaunchKernelGGL((k_walk<kWalkItems, kWalkBuf>), dim3(pb), dim3(256), 0, s, rb.descs, rb.walk,
+    hipLaunchKernelGGL((one ? k_walk<kWalkBuf, true> : k_walk<kWalkBuf, false>), dim3(pb), dim3(256), 0, s, rb.descs, rb.walk,
                        rb.walk_counts, rb.walk_cap, rb.status, cmp_tb, rb.wbuf, rb.wbuf_counts, rb.wbuf_cap);
     H(K_WALK, 1);
 
@@ -2441,7 +2459,7 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
     H(K_COMPACT, 1);
 
     H(K_EMIT, 0);
-    hipLaunchKernelGGL(k_emit<4>, dim3(pb), dim3(256), 0, s, rb.descs, rb.emit, rb.emit_counts, rb.emit_cap);
+    hipLaunchKernelGGL((one ? k_emit<4, true> : k_emit<4, false>), dim3(pb), dim3(256), 0, s, rb.descs, rb.emit, rb.emit_counts, rb.emit_cap);
     H(K_EMIT, 1);
     return hipGetLastError();
 }
