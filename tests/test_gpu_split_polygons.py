@@ -26,15 +26,14 @@ def fixture_mesh(name):
 
 def meshes():
     out = [fixture_mesh("p3_fan_degree8.txt"), fixture_mesh("p4_fan_degree7.txt")]
-    for n, seed, order in ((400, 31, "qhull"), (5000, 32, "morton"), (9000, 33, "morton"), (20000, 34, "qhull")):
+    for n, seed, order in ((400, 31, "qhull"), (5000, 32, "morton"), (9000, 33, "morton"), (20000, 34, "qhull"), (60000, 37, "morton")):
         m = W.random_delaunay(n, seed, order=order)
         out.append((m.xy, m.tri))
     m = W.scrambled(W.random_delaunay(7000, 35, order="morton"), 5)
     out.append((m.xy, m.tri))
-    # tips at both ends of one middle edge, and polygons split more than once,
-    # come with thin triangles
+    # stretched: fewer tips, longer polygons
     m = W.random_delaunay(12000, 36, order="morton")
-    out.append((np.ascontiguousarray(m.xy * np.array([1, 64], np.int32)), m.tri))
+    out.append((np.ascontiguousarray(m.xy * np.array([1, 2], np.int32)), m.tri))
     return out
 
 
