@@ -95,11 +95,10 @@ constexpr int kTipStripes = 8;
 // of kSmallBlock threads with every intermediate array in LDS
 constexpr int kSmallMaxTri = 4096;
 constexpr int kSmallBlock = 1024;
-// LDS of k_small for a mesh of nt triangles: per triangle four slots (one
-// unused) of two 16-bit arrays and a 32-bit one, and a label byte
-__host__ __device__ inline size_t small_a16_bytes(int nt) { return (8 * (size_t)nt + 15) / 16 * 16; }
-__host__ __device__ inline size_t small_lab_bytes(int nt) { return ((size_t)nt + 15) / 16 * 16; }
-inline size_t small_lds_bytes(int nt) { return 4 * small_a16_bytes(nt) + small_lab_bytes(nt); }
+// LDS of k_small for a mesh of nt triangles: per triangle four slots (one for
+// the triangle itself) of three 16-bit arrays, and two seeds (at most one per
+// triangle and two per tip, of which there are at most nt / 2 + 1)
+inline size_t small_lds_bytes(int nt) { return 28 * (size_t)nt + 16; }
 
 struct LaunchCfg {
     int block_label = 128, items_label = 4;
@@ -201,7 +200,8 @@ inline int32_t tiles_for(int64_t n, int64_t tile) {
 // inputs already on the device: one workgroup checks and orients it, matches
 // its twins in LDS, then meshes it as k_small does.  counts receives the
 // mesh counters (kJobCounts ints: the 8 of MeshCounters, the build's error
-// key as two words (~0 when the build passed), the triangles it flipped).
+// key as two words (~0 when the build passed), the triangles it flipped).  org
+// and twin are written by a build on its own only.
 constexpr int kJobSmallTri = kSmallMaxTri;
 constexpr int kJobSmallV = 4096;
 constexpr int kJobCounts = 12;
@@ -219,6 +219,8 @@ struct SmallJob {
 // dynamic LDS of one such workgroup
 size_t small_job_lds_bytes(int max_nv, int max_nt);
 hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nv, int max_nt, hipStream_t s);
+// one such job; counts may be coherent host memory
+hipError_t launch_small_job_one(const SmallJob &job, hipStream_t s);
 
 // ---- build (build_kernels.hip) -------------------------------------------
 

@@ -1622,44 +1622,68 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
 // most kSmallMaxTri triangles keeps every intermediate array in LDS, and one
 // workgroup runs the steps with block barriers between them:
 //   1. longest edge of every triangle (Section 6.1, Algorithm 8);
-//   2. frontier half-edges (Section 6.2, Algorithm 9);
-//   3. next' of every frontier half-edge by turning clockwise around its
-//      target (Section 6.5, Algorithm 12).  The same turns find the barrier
-//      tips (Section 6.4, Algorithm 11): a turn from next(h) that comes all
-//      the way round to twin(h) met no other frontier edge, so the target of
-//      h is a tip whose degree is the turn's length; its middle edge lies
-//      half the degree further round from twin(h).  The turns around both
-//      ends of every middle edge are then taken again with the repaired
-//      frontier;
-//   4. prev' as the inverse of next';
-//   5. every half-edge's loop minimum and its distance to it along next', by
-//      pointer doubling (Section 6.6, Algorithm 14): after a round with
-//      window w, a half-edge holds the minimum of the w half-edges from it on
-//      and how far ahead that minimum first occurs; a round that lowers no
-//      minimum has reached each loop's minimum everywhere (the windows that
-//      start w apart cover a loop and all hold the same minimum);
-//   6. seeds, loop offsets and loops in half-edge order from a block scan
-//      over the loop minima (Section 6.7).
+//   2. frontier bits and the seeds of terminal edges (Sections 6.2-6.3);
+//   3. next' of every frontier half-edge, as in k_relink: the turn across the
+//      edge that its triangle's frontier bits name (Section 6.5, Algorithm
+//      12).  The same turns find the barrier tips (Section 6.4, Algorithm 11):
+//      one that comes all the way round to the twin of its half-edge met no
+//      other frontier edge, so that target is a tip whose degree is the turn's
+//      length; its middle edge lies half the degree further round.  The turns
+//      around both ends of every middle edge are then taken again with the
+//      repaired frontier;
+//   4. prev' as the inverse of next'; every seed's loop walked once for its
+//      minimum and length (Section 6.6, Algorithm 14; the first walker of a
+//      loop that several seeds reach records it);
+//   5. seeds and loop offsets from a block scan over the triangles that hold a
+//      minimum (Section 6.7);
+//   6. every loop walked again from its minimum into its place.
 // In LDS a half-edge 3t + i is slot 4t + i, so next and the triangle of a
 // slot are bit operations (the order of slots is the order of half-edges),
-// and a slot's 16-bit entry holds its twin's slot with both frontier bits.
-// Each thread owns a few triangles and half-edges, and the turns of its
-// items step together so that their LDS reads overlap.  The outputs equal
-// the tiled chain's element by element.  One workgroup per mesh: a batch
-// whose meshes are all small is one launch.
+// and slot 4t + 3 holds what belongs to the triangle.  The vector instructions
+// of a single CU bound the kernel: a thread handles whole triangles, most with
+// one turn that ends at its first candidate, and a thread per loop walks it.
+// (One item per half-edge, and loop minima by pointer doubling over all of
+// them, took 22 us for 2,048 triangles.)  The outputs equal the tiled chain's
+// element by element.  One workgroup per mesh: a batch whose meshes are all
+// small is one launch.
 // ---------------------------------------------------------------------------
 
-constexpr uint32_t kSlotNone = 0x3fff;   // no twin (4t + 3 is never a half-edge's slot)
-constexpr uint32_t kSlotF1 = 1u << 14;   // frontier (label phase)
-constexpr uint32_t kSlotF2 = 1u << 15;   // frontier after the repair
-constexpr uint32_t kNone16 = 0xffff;     // no minimum (not on a loop)
+constexpr uint32_t kNo16 = 0xffff;   // no slot (boundary), in 16 bits
+// The word of slot 4t + 3: bits 0-1 the longest edge, bits 2-4 the label
+// phase's frontier bits, bits 5-7 the edges the repair adds, bit 8 the loop
+// whose minimum lies in t has been recorded.
+constexpr uint32_t kRecorded = 1u << 8;
+__device__ __forceinline__ uint32_t repaired_bits(uint32_t lab) { return ((lab >> 2) | (lab >> 5)) & 7u; }
 
-__device__ __forceinline__ int slot_next(int q) { return (q & 3) == 2 ? q - 2 : q + 1; }
-__device__ __forceinline__ int slot_prev(int q) { return (q & 3) == 0 ? q + 2 : q - 1; }
-__device__ __forceinline__ int slot_he(int q) { return 3 * (q >> 2) + (q & 3); }
+// The corners and twin slots of a thread's triangles t = tid + j * kSmallBlock.
+template <int TI>
+struct SmallTris {
+    int v[TI][3];
+    uint32_t s[TI][3];
+};
 
-// IT: half-edges per thread (3, 6 or 12; meshes of up to IT * kSmallBlock / 3
-// triangles), IT / 3 triangles per thread
+template <int TI>
+__device__ __forceinline__ void small_load(const MeshDesc &d, SmallTris<TI> &tr) {
+    const TwinView twin = twin_view(d);
+#pragma unroll
+    for (int j = 0; j < TI; j++) {
+        const int t = threadIdx.x + j * kSmallBlock, tt = t < d.nt ? t : 0;
+        if (!d.org8) {
+            const gcint org = (gcint)(d.org);
+#pragma unroll
+            for (int i = 0; i < 3; i++) tr.v[j][i] = org[3 * tt + i];
+        } else {
+            const v2i r = ((GLOBAL const v2i *)d.org8)[tt];
+            const int d1 = (int)(int16_t)(r.y & 0xffff), d2 = r.y >> 16;
+            tr.v[j][0] = r.x;
+            tr.v[j][1] = d1 != kEsc16 ? r.x + d1 : esc_lookup(d.esc, d.esc_mask, ~(3 * tt + 1));
+            tr.v[j][2] = d2 != kEsc16 ? r.x + d2 : esc_lookup(d.esc, d.esc_mask, ~(3 * tt + 2));
+        }
+#pragma unroll
+        for (int i = 0; i < 3; i++) tr.s[j][i] = he_slot(max(twin[3 * tt + i], -1));
+    }
+}
+
 // The counts of a run go to the mesh's device counters and, for a run
 // launched on its own, straight to the caller's coherent host copy.
 __device__ __forceinline__ void small_counts(const MeshDesc &d, MeshCounters *host, const MeshCounters &c) {
@@ -1667,280 +1691,66 @@ __device__ __forceinline__ void small_counts(const MeshDesc &d, MeshCounters *ho
     if (host) *host = c;
 }
 
-template <int IT>
-__device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host) {
-    constexpr int TI = IT / 3;
+// TI: triangles per thread (1, 2 or 4).
+template <int TI>
+__device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host, const SmallTris<TI> &tr) {
     extern __shared__ int4 lds_raw[];
     __shared__ int s_scan[72];
-    __shared__ int s_cnt[4];   // tied maxima, tips, new middle edges, frontier half-edges
-    const int nt = d.nt, nh = 3 * nt, tid = threadIdx.x;
-    if (nt <= 0 || nt > TI * kSmallBlock) {   // (uniform) an empty mesh; larger ones are never launched here
-        if (tid == 0) {
-            MeshCounters c{};
-            c.err = nt != 0 ? kErrCorrupt : 0;
-            small_counts(d, host, c);
-            if (nt == 0) d.loop_off[0] = 0;
-        }
-        return;
-    }
-    if (tid < 4) s_cnt[tid] = 0;
-    char *base = reinterpret_cast<char *>(lds_raw);
-    const size_t a16 = small_a16_bytes(nt);
-    uint16_t *s_e = reinterpret_cast<uint16_t *>(base);             // twin slot | frontier bits
-    uint16_t *s_p = s_e;                                             // then doubling pointer, loop offset
-    uint16_t *s_nx = reinterpret_cast<uint16_t *>(base + a16);      // next', then loop length at minima
-    uint32_t *s_mk = reinterpret_cast<uint32_t *>(base + 2 * a16);  // minimum | distance to it << 16
-    uint8_t *s_lab = reinterpret_cast<uint8_t *>(base + 4 * a16);   // local index of the longest edge
+    __shared__ int s_cnt[5];   // tied maxima, tips, new middle edges, frontier half-edges, seeds
+    const int nt = d.nt, nh = 3 * nt, tid = threadIdx.x, lane = __lane_id();
+    const uint32_t ns = 4u * (uint32_t)nt;
+    uint16_t *s_sl = reinterpret_cast<uint16_t *>(lds_raw);   // by slot: the twin's slot; 4t + 3: the triangle's word
+    uint16_t *s_nx = s_sl + ns;     // by slot: next'; 4t + 3: length, then place, of the loop with its minimum in t
+    uint16_t *s_pv = s_nx + ns;     // by slot: prev'; then the loops' half-edges in output order
+    uint16_t *s_list = s_pv + ns;   // seeds (label phase, then both sides of every middle edge), then minima
+    uint32_t *w32 = reinterpret_cast<uint32_t *>(s_sl);
     int bad = 0;
+    if (tid < 5) s_cnt[tid] = 0;
 
     // 1. longest edges; edge i of t runs from corner i to corner i + 1, and a
-    //    tie at the maximum goes to the lower edge id min(h, twin h).  All the
-    //    corner and twin loads first, then the coordinates.
+    //    tie at the maximum goes to the lower edge id min(h, twin h)
+    uint32_t L[TI];
     {
         const gcv2i xy = (gcv2i)(d.xy);
-        const TwinView twin = twin_view(d);
-        int v[TI][3], g[TI][3];
-#pragma unroll
-        for (int j = 0; j < TI; j++) {
-            const int t = tid + j * kSmallBlock, tt = t < nt ? t : 0;
-            if (!d.org8) {
-                const gcint org = (gcint)(d.org);
-#pragma unroll
-                for (int i = 0; i < 3; i++) v[j][i] = org[3 * tt + i];
-            } else {
-                const v2i r = ((GLOBAL const v2i *)d.org8)[tt];
-                const int d1 = (int)(int16_t)(r.y & 0xffff), d2 = r.y >> 16;
-                v[j][0] = r.x;
-                v[j][1] = d1 != kEsc16 ? r.x + d1 : esc_lookup(d.esc, d.esc_mask, ~(3 * tt + 1));
-                v[j][2] = d2 != kEsc16 ? r.x + d2 : esc_lookup(d.esc, d.esc_mask, ~(3 * tt + 2));
-            }
-#pragma unroll
-            for (int i = 0; i < 3; i++) g[j][i] = twin[3 * tt + i];
-        }
         int2 p[TI][3];
 #pragma unroll
         for (int j = 0; j < TI; j++) {
             const bool in = tid + j * kSmallBlock < nt;
 #pragma unroll
             for (int i = 0; i < 3; i++) {
-                const bool ok = v[j][i] >= 0 && v[j][i] < d.nv;
+                const bool ok = tr.v[j][i] >= 0 && tr.v[j][i] < d.nv;
                 bad |= in && !ok;
-                const v2i q = xy[ok ? v[j][i] : 0];
+                const v2i q = xy[ok ? tr.v[j][i] : 0];
                 p[j][i] = make_int2(q.x, q.y);
             }
         }
+        __syncthreads();   // (s_cnt; and, after a build, its table)
         int ties = 0;
 #pragma unroll
         for (int j = 0; j < TI; j++) {
             const int t = tid + j * kSmallBlock;
+            L[j] = 0;
             if (t >= nt) continue;
             const long long l[3] = {sq_len(p[j][0], p[j][1]), sq_len(p[j][1], p[j][2]), sq_len(p[j][2], p[j][0])};
-            int best = 0;
             long long bl = l[0];
-            int bid = (g[j][0] >= 0 && g[j][0] < 3 * t) ? g[j][0] : 3 * t;
+            uint32_t bid = min(tr.s[j][0], 4u * t);
 #pragma unroll
             for (int i = 1; i < 3; i++) {
-                const int h = 3 * t + i, id = (g[j][i] >= 0 && g[j][i] < h) ? g[j][i] : h;
+                const uint32_t id = min(tr.s[j][i], 4u * t + i);
                 if (l[i] > bl || (l[i] == bl && id < bid)) {
-                    best = i;
+                    L[j] = i;
                     bl = l[i];
                     bid = id;
                 }
             }
             ties += (l[0] == bl) + (l[1] == bl) + (l[2] == bl) > 1;
-            s_lab[t] = (uint8_t)best;
 #pragma unroll
-            for (int i = 0; i < 3; i++) {
-                const int gi = g[j][i];
-                const bool ok = gi >= 0 && gi < nh;
-                bad |= gi >= nh || gi < -1;
-                s_e[4 * t + i] = (uint16_t)(ok ? 4 * tri_of(gi) + (gi - 3 * tri_of(gi)) : kSlotNone);
-            }
+            for (int i = 0; i < 3; i++) bad |= tr.s[j][i] != kNoSlot && tr.s[j][i] >= ns;
+            reinterpret_cast<ushort4 *>(s_sl)[t] = make_ushort4((uint16_t)tr.s[j][0], (uint16_t)tr.s[j][1], (uint16_t)tr.s[j][2], (uint16_t)L[j]);
         }
         if (ties) atomicAdd(&s_cnt[0], ties);
     }
-    __syncthreads();
-
-    // the half-edges this thread owns: h = tid + j * kSmallBlock, slot q[j]
-    int q[IT];
-#pragma unroll
-    for (int j = 0; j < IT; j++) {
-        const int h = tid + j * kSmallBlock;
-        q[j] = h < nh ? 4 * tri_of(h) + (h - 3 * tri_of(h)) : -1;
-    }
-
-    // 2. frontier half-edges: on the boundary, or the longest edge of neither
-    //    triangle (both bits; the repair adds to the second)
-    uint32_t front = 0;   // bit j: q[j] is a frontier half-edge (label phase, then repaired)
-    {
-        uint32_t e[IT];
-#pragma unroll
-        for (int j = 0; j < IT; j++) e[j] = q[j] >= 0 ? s_e[q[j]] : kSlotNone;
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            if (q[j] < 0) continue;
-            const int g = (int)(e[j] & kSlotNone);
-            const bool lh = s_lab[q[j] >> 2] == (q[j] & 3);
-            const bool lg = g != (int)kSlotNone && s_lab[g >> 2] == (g & 3);
-            const bool f = g == (int)kSlotNone || (!lh && !lg);
-            if (f) {
-                s_e[q[j]] = (uint16_t)(e[j] | kSlotF1 | kSlotF2);
-                front |= 1u << j;
-            }
-        }
-    }
-    __syncthreads();
-
-    // 3. turns: next'(h) = the first frontier slot clockwise around the target
-    //    of h from next(h); a turn that ends at twin(h) found a tip
-    int nx[IT], deg[IT];
-    uint32_t tip = 0;
-    {
-        uint32_t act = front;
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            nx[j] = (front >> j) & 1u ? slot_next(q[j]) : 0;
-            deg[j] = 1;
-        }
-        for (int it = 0; act && it <= 4 * nt; it++) {
-            uint32_t e[IT];
-#pragma unroll
-            for (int j = 0; j < IT; j++) e[j] = ((act >> j) & 1u) ? s_e[nx[j]] : kSlotF1;
-#pragma unroll
-            for (int j = 0; j < IT; j++) {
-                if (!((act >> j) & 1u)) continue;
-                if (e[j] & kSlotF1) {
-                    act &= ~(1u << j);
-                } else if ((e[j] & kSlotNone) == kSlotNone) {   // a non-frontier edge on the boundary: not a valid mesh
-                    act &= ~(1u << j);
-                    bad = 1;
-                } else {
-                    nx[j] = slot_next((int)(e[j] & kSlotNone));
-                    deg[j]++;
-                }
-            }
-        }
-        bad |= act != 0;
-        int tips = 0, fresh = 0;
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            if (!((front >> j) & 1u)) continue;
-            s_nx[q[j]] = (uint16_t)nx[j];
-            const int tw = (int)(s_e[q[j]] & kSlotNone);
-            if (tw == (int)kSlotNone || nx[j] != tw) continue;
-            // a tip: its frontier half-edge is tw; the middle edge deg / 2
-            // clockwise steps further
-            int m = tw;
-            for (int k = 0; k < deg[j] / 2; k++) m = slot_next((int)(s_e[m] & kSlotNone));
-            const int mt = (int)(s_e[m] & kSlotNone);
-            if (mt == (int)kSlotNone) {
-                bad = 1;
-                continue;
-            }
-            tip |= 1u << j;
-            deg[j] = m;   // from here on: the tip's middle slot
-            const int lo = min(m, mt), hi = max(m, mt);
-            uint32_t *w32 = reinterpret_cast<uint32_t *>(s_e);
-            const uint32_t blo = kSlotF2 << (16 * (lo & 1));
-            const uint32_t old = atomicOr(&w32[lo >> 1], blo);
-            atomicOr(&w32[hi >> 1], kSlotF2 << (16 * (hi & 1)));
-            tips++;
-            fresh += !(old & blo);   // the edge's first tip counts it
-        }
-        if (tips) {
-            atomicAdd(&s_cnt[1], tips);
-            atomicAdd(&s_cnt[2], fresh);
-        }
-    }
-    __syncthreads();
-
-    // 3b. the turns around both ends of every middle edge again, over the
-    //     repaired frontier: every slot entering such a vertex.  (Two tips may
-    //     share a vertex; they write the same values.)
-    if (s_cnt[1] > 0) {   // (uniform)
-        auto turn2 = [&](int c) {
-            for (int k = 0; k <= 4 * nt; k++) {
-                const uint32_t e = s_e[c];
-                if (e & kSlotF2) return c;
-                if ((e & kSlotNone) == kSlotNone) return -1;
-                c = slot_next((int)(e & kSlotNone));
-            }
-            return -1;
-        };
-        auto fix_vertex = [&](int o0) {   // o0 leaves the vertex
-            bool open = false;
-            int o = o0;
-            for (int k = 0; k <= 4 * nt; k++) {   // clockwise
-                const int pin = slot_prev(o);
-                if (s_e[pin] & kSlotF2) {
-                    const int c = turn2(slot_next(pin));
-                    bad |= c < 0;
-                    s_nx[pin] = (uint16_t)(c < 0 ? 0 : c);
-                }
-                const int g = (int)(s_e[o] & kSlotNone);
-                if (g == (int)kSlotNone) {
-                    open = true;
-                    break;
-                }
-                o = slot_next(g);
-                if (o == o0) break;
-            }
-            if (!open) return;
-            o = o0;
-            for (int k = 0; k <= 4 * nt; k++) {   // counter-clockwise, to the other boundary edge
-                const int g = (int)(s_e[slot_prev(o)] & kSlotNone);
-                if (g == (int)kSlotNone) break;
-                o = g;
-                const int pin = slot_prev(o);
-                if (s_e[pin] & kSlotF2) {
-                    const int c = turn2(slot_next(pin));
-                    bad |= c < 0;
-                    s_nx[pin] = (uint16_t)(c < 0 ? 0 : c);
-                }
-            }
-        };
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            if (!((tip >> j) & 1u)) continue;
-            const int m = deg[j], mt = (int)(s_e[m] & kSlotNone);
-            fix_vertex(m);    // m leaves the tip
-            fix_vertex(mt);   // mt leaves the middle edge's other end
-        }
-        __syncthreads();
-    }
-
-    // 4. next' and prev' out (prev' is next' inverted); the doubling's first
-    //    window: m = min(q, n1), distance 1 when n1 is the smaller, p =
-    //    next'(n1).  A thread keeps its own items' values in registers.
-    int m[IT], k[IT], p[IT];
-    {
-        const gint nxo = (gint)d.next_o, pvo = (gint)d.prev_o;
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            if (q[j] < 0) continue;
-            if (s_e[q[j]] & kSlotF2) front |= 1u << j;   // the repair's middle edges
-        }
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            const int h = tid + j * kSmallBlock;
-            m[j] = kNone16;
-            k[j] = 0;
-            p[j] = q[j] >= 0 ? q[j] : 0;
-            if (q[j] < 0) continue;
-            if ((front >> j) & 1u) {
-                const int n1 = s_nx[q[j]], hn = slot_he(n1);
-                nxo[h] = hn;
-                pvo[hn] = h;
-                m[j] = min(q[j], n1);
-                k[j] = n1 < q[j] ? 1 : 0;
-                p[j] = s_nx[n1];
-            } else {
-                nxo[h] = -1;
-                pvo[h] = -1;
-            }
-        }
-    }
-    if (__syncthreads_or(bad)) {   // (uniform) no loop structure to follow; every read of s_e is done
+    if (__syncthreads_or(bad)) {   // (uniform) a slot or corner out of range
         if (tid == 0) {
             MeshCounters c{};
             c.err = kErrCorrupt;
@@ -1948,75 +1758,258 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host
         }
         return;
     }
+
+    // 2. frontier edges: on the boundary, or the longest edge of neither
+    //    triangle; seeds: the lower half-edge of a terminal edge
+    uint32_t F[TI];
 #pragma unroll
-    for (int j = 0; j < IT; j++) {
-        if (q[j] < 0) continue;
-        s_mk[q[j]] = (uint32_t)m[j] | ((uint32_t)k[j] << 16);
-        s_p[q[j]] = (uint16_t)p[j];
+    for (int j = 0; j < TI; j++) {
+        const int t = tid + j * kSmallBlock;
+        F[j] = 0;
+        bool seed = false;
+        if (t < nt) {
+            const uint32_t lbit = 1u << L[j], sL = pick3(L[j], tr.s[j][0], tr.s[j][1], tr.s[j][2]);
+            uint32_t E = 0, bnd = 0;   // bit i: the twin of edge i is not its triangle's longest edge; is missing
+#pragma unroll
+            for (int i = 0; i < 3; i++) {
+                const uint32_t q = tr.s[j][i], lab = s_sl[4 * min(q >> 2, (uint32_t)nt - 1u) + 3];
+                E |= min((lab ^ q) & 3u, 1u) << i;
+                bnd |= q == kNoSlot ? 1u << i : 0u;
+            }
+            F[j] = (E & ~lbit) | bnd;
+            seed = (bnd & lbit) || (!(E & lbit) && 4u * t + L[j] < sL);
+            s_sl[4 * t + 3] = (uint16_t)(L[j] | (F[j] << 2));   // (its longest edge as it was, for others' reads)
+        }
+        const unsigned long long m = __ballot(seed);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(&s_cnt[4], __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
+        if (seed) s_list[at] = (uint16_t)(4 * t + L[j]);
     }
     __syncthreads();
 
-    // 5. doubling: each round reads its operands before any thread writes
-    bool done = false;
-    for (int round = 0, w = 2; round < 16 && !done; round++, w *= 2) {
-        uint32_t mkq[IT];
-        int pq[IT];
+    // 3. next': the next edge of the triangle, or the turn across it
+    uint32_t mid[TI];   // the middle slot of a tip found here, or kNoSlot
+    {
+        uint32_t x[TI], c[TI], deg[TI];
+        bool act[TI];
+        bool any = false;
 #pragma unroll
-        for (int j = 0; j < IT; j++) {
-            mkq[j] = s_mk[p[j]];
-            pq[j] = s_p[p[j]];
+        for (int j = 0; j < TI; j++) {
+            x[j] = (kCrossNext >> (2 * F[j])) & 3u;
+            const uint32_t sx = pick3(x[j], tr.s[j][0], tr.s[j][1], tr.s[j][2]);
+            act[j] = x[j] != 3u;   // (then the edge is no frontier edge: sx is a slot)
+            c[j] = act[j] ? next_slot(sx) : 0u;
+            deg[j] = 2;   // half-edges at the target seen so far
+            mid[j] = kNoSlot;
+            any |= act[j];
+        }
+        for (int it = 0; any && it <= 4 * nt; it++) {
+            any = false;
+            uint32_t f[TI], g[TI];
+#pragma unroll
+            for (int j = 0; j < TI; j++) {
+                f[j] = act[j] ? s_sl[c[j] | 3u] : 0u;
+                g[j] = act[j] ? s_sl[c[j]] : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < TI; j++) {
+                if (!act[j]) continue;
+                if (fbit(f[j], (int)(c[j] & 3u))) {
+                    act[j] = false;
+                } else if (g[j] == kNo16) {   // a non-frontier edge on the boundary: not a valid mesh
+                    act[j] = false;
+                    bad = 1;
+                } else {
+                    c[j] = next_slot(g[j]);
+                    deg[j]++;
+                    any = true;
+                }
+            }
+        }
+        bad |= any;
+#pragma unroll
+        for (int j = 0; j < TI; j++) {
+            const int t = tid + j * kSmallBlock;
+            if (t >= nt) continue;
+            const uint32_t q = 4u * (uint32_t)t;
+            reinterpret_cast<ushort4 *>(s_nx)[t] = make_ushort4((uint16_t)(x[j] == 1u ? c[j] : q + 1), (uint16_t)(x[j] == 2u ? c[j] : q + 2),
+                                                                (uint16_t)(x[j] == 0u ? c[j] : q), 0);
+            const uint32_t tw = x[j] == 3u ? kNoSlot : pick3(x[j], tr.s[j][2], tr.s[j][0], tr.s[j][1]);
+            if (tw == kNoSlot || c[j] != tw) continue;
+            // a tip: its frontier half-edge is tw; the middle edge deg / 2
+            // clockwise steps further
+            uint32_t m = tw;
+            for (uint32_t k = 0; k < deg[j] / 2 && m != kNo16; k++) {
+                const uint32_t g = s_sl[m];
+                m = g == kNo16 ? g : next_slot(g);
+            }
+            const uint32_t mt = m == kNo16 ? m : s_sl[m];
+            if (mt == kNo16) {
+                bad = 1;
+                continue;
+            }
+            mid[j] = m;
+            const uint32_t lo = min(m, mt), hi = max(m, mt);
+            const uint32_t blo = 1u << (16 + 5 + (lo & 3u)), bhi = 1u << (16 + 5 + (hi & 3u));
+            const uint32_t old = atomicOr(&w32[2 * (lo >> 2) + 1], blo);
+            atomicOr(&w32[2 * (hi >> 2) + 1], bhi);
+            atomicAdd(&s_cnt[1], 1);
+            if (!(old & blo)) atomicAdd(&s_cnt[2], 1);   // the edge's first tip counts it
+            const int at = atomicAdd(&s_cnt[4], 2);      // both sides seed a loop
+            if (at + 1 >= 2 * nt + 8) {                  // more than a valid mesh can have
+                bad = 1;
+                continue;
+            }
+            s_list[at] = (uint16_t)m;
+            s_list[at + 1] = (uint16_t)mt;
+        }
+    }
+    __syncthreads();
+
+    // 3b. the turns around both ends of every middle edge again, over the
+    //     repaired frontier: every slot entering such a vertex.  (Two tips may
+    //     share a vertex; they write the same values.)
+    auto frontier2 = [&](uint32_t q) { return (repaired_bits(s_sl[q | 3u]) >> (q & 3u)) & 1u; };
+    if (s_cnt[1] > 0) {   // (uniform)
+        auto turn2 = [&](uint32_t c) {
+            for (int k = 0; k <= 4 * nt; k++) {
+                if (frontier2(c)) return c;
+                const uint32_t g = s_sl[c];
+                if (g == kNo16) break;
+                c = next_slot(g);
+            }
+            return kNoSlot;
+        };
+        auto fix_vertex = [&](uint32_t o0) {   // o0 leaves the vertex
+            bool open = false;
+            uint32_t o = o0;
+            for (int k = 0; k <= 4 * nt; k++) {   // clockwise
+                const uint32_t pin = prev_slot(o);
+                if (frontier2(pin)) {
+                    const uint32_t c = turn2(next_slot(pin));
+                    bad |= c == kNoSlot;
+                    s_nx[pin] = (uint16_t)(c == kNoSlot ? 0u : c);
+                }
+                const uint32_t g = s_sl[o];
+                if (g == kNo16) {
+                    open = true;
+                    break;
+                }
+                o = next_slot(g);
+                if (o == o0) break;
+            }
+            if (!open) return;
+            o = o0;
+            for (int k = 0; k <= 4 * nt; k++) {   // counter-clockwise, to the other boundary edge
+                const uint32_t g = s_sl[prev_slot(o)];
+                if (g == kNo16) break;
+                o = g;
+                const uint32_t pin = prev_slot(o);
+                if (frontier2(pin)) {
+                    const uint32_t c = turn2(next_slot(pin));
+                    bad |= c == kNoSlot;
+                    s_nx[pin] = (uint16_t)(c == kNoSlot ? 0u : c);
+                }
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < TI; j++) {
+            if (mid[j] == kNoSlot) continue;
+            fix_vertex(mid[j]);         // leaves the tip
+            fix_vertex(s_sl[mid[j]]);   // leaves the middle edge's other end
         }
         __syncthreads();
-        int lowered = 0;
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            if (!((front >> j) & 1u)) continue;
-            const int mq = (int)(mkq[j] & 0xffffu);
-            if (mq < m[j]) {   // the minimum lies beyond this window: w + its distance from p
-                m[j] = mq;
-                k[j] = w + (int)(mkq[j] >> 16);
-                s_mk[q[j]] = (uint32_t)m[j] | ((uint32_t)k[j] << 16);
-                lowered = 1;
-            }
-            p[j] = pq[j];
-            s_p[q[j]] = (uint16_t)pq[j];
-        }
-        done = !__syncthreads_or(lowered);
     }
-    bad |= !done;
 
-    // 6. loops in the order of their minima: each thread scans a contiguous
-    //    run of slots; a minimum's loop is one longer than the distance from
-    //    its successor back to it
-    constexpr int QT = 4 * TI;   // slots per thread
-    const int q0 = tid * QT;
-    int len[QT];
-    int cnt = 0, sum = 0;
+    // 4. prev' inverts next'; then both go out, and every seed's loop is walked
 #pragma unroll
-    for (int r = 0; r < QT; r++) {
-        const int s = q0 + r;
-        len[r] = 0;
-        if ((r & 3) != 3 && (s >> 2) < nt && (int)(s_mk[s] & 0xffffu) == s) {
-            len[r] = (int)(s_mk[s_nx[s]] >> 16) + 1;
-            cnt++;
-            sum += len[r];
+    for (int j = 0; j < TI; j++) {
+        const int t = tid + j * kSmallBlock;
+        if (t >= nt) continue;
+        F[j] = repaired_bits(s_sl[4 * t + 3]);
+        const ushort4 n = reinterpret_cast<const ushort4 *>(s_nx)[t];
+        if (F[j] & 1u) s_pv[n.x] = (uint16_t)(4 * t);
+        if (F[j] & 2u) s_pv[n.y] = (uint16_t)(4 * t + 1);
+        if (F[j] & 4u) s_pv[n.z] = (uint16_t)(4 * t + 2);
+    }
+    if (__syncthreads_or(bad)) {   // (uniform) no loop structure to follow
+        if (tid == 0) {
+            MeshCounters c{};
+            c.err = kErrCorrupt;
+            small_counts(d, host, c);
         }
+        return;
+    }
+    int nfront = 0;
+#pragma unroll
+    for (int j = 0; j < TI; j++) {
+        const int t = tid + j * kSmallBlock;
+        const bool in = t < nt;
+#pragma unroll
+        for (int i = 0; i < 3; i++) nfront += __popcll(__ballot(in && ((F[j] >> i) & 1u)));
+        if (!in) continue;
+        const ushort4 n = reinterpret_cast<const ushort4 *>(s_nx)[t], p = reinterpret_cast<const ushort4 *>(s_pv)[t];
+        const int none[3] = {(F[j] & 1u) ? 0 : -1, (F[j] & 2u) ? 0 : -1, (F[j] & 4u) ? 0 : -1};
+        *(GLOBAL v3i_a4 *)((gint)d.next_o + 3 * t) =
+            v3i_a4{he_of_slot(n.x) | none[0], he_of_slot(n.y) | none[1], he_of_slot(n.z) | none[2]};
+        *(GLOBAL v3i_a4 *)((gint)d.prev_o + 3 * t) =
+            v3i_a4{he_of_slot(p.x) | none[0], he_of_slot(p.y) | none[1], he_of_slot(p.z) | none[2]};
+    }
+    if (lane == 0 && nfront) atomicAdd(&s_cnt[3], nfront);
+    const int nlist = s_cnt[4];   // (within s_list: checked as it grew)
+    for (int k = tid; k < nlist; k += kSmallBlock) {
+        const uint32_t s0 = s_list[k], f = repaired_bits(s_sl[s0 | 3u]);
+        uint32_t st = ((f >> (s0 & 3u)) & 1u) ? s0 : (s0 & ~3u) + (uint32_t)__builtin_ctz(f | 8u);
+        if (!f) {   // clockwise around the seed's origin to a frontier half-edge
+            st = s0;
+            for (int r = 0; !frontier2(st); r++) {
+                const uint32_t g = s_sl[st];
+                if (g == kNo16 || r > 4 * nt) {
+                    bad = 1;
+                    break;
+                }
+                st = next_slot(g);
+            }
+        }
+        uint32_t cur = s_nx[st], mn = st;
+        int len = 1;
+        for (; cur != st && len <= nh; len++) {
+            mn = min(mn, cur);
+            cur = s_nx[cur];
+        }
+        bad |= len > nh;
+        const uint32_t old = atomicOr(&w32[2 * (mn >> 2) + 1], kRecorded << 16);
+        const bool won = !(old & (kRecorded << 16));
+        if (won) s_nx[mn | 3u] = (uint16_t)len;
+        s_list[k] = (uint16_t)(won ? mn : kNo16);
+    }
+    bad = __syncthreads_or(bad);
+
+    // 5. loops in the order of their minima: each thread scans a few
+    //    consecutive triangles (a loop's minimum is the first frontier
+    //    half-edge of its triangle, and no triangle has two loops)
+    int cnt = 0, sum = 0, len[TI];
+#pragma unroll
+    for (int r = 0; r < TI; r++) {
+        const int t = tid * TI + r;
+        len[r] = t < nt ? s_nx[4 * t + 3] : 0;
+        cnt += len[r] != 0;
+        sum += len[r];
     }
     int ec, es, tc, ts;
     block_excl_scan2(cnt, sum, ec, es, tc, ts, s_scan);
-    // a loop has at least three half-edges, and each half-edge one loop
-    const bool fits = tc <= nt && ts <= nh;
-    bad |= !fits;
+    // every frontier half-edge lies on exactly one loop
+    const bool fits = !bad && tc <= nt && ts <= nh && ts == s_cnt[3];
     if (fits) {
         const gint seeds = (gint)d.seeds, loff = (gint)d.loop_off;
 #pragma unroll
-        for (int r = 0; r < QT; r++) {
+        for (int r = 0; r < TI; r++) {
             if (!len[r]) continue;
-            const int s = q0 + r;
-            seeds[ec] = slot_he(s);
+            const uint32_t q = 4u * (uint32_t)(tid * TI + r);
+            seeds[ec] = he_of_slot(q + (uint32_t)__builtin_ctz(repaired_bits(s_sl[q + 3]) | 8u));
             loff[ec] = es;
-            s_p[s] = (uint16_t)es;       // the loop's first slot
-            s_nx[s] = (uint16_t)len[r];  // and its length, for step 7
+            s_nx[q + 3] = (uint16_t)es;   // the loop's first place
             ec++;
             es += len[r];
         }
@@ -2024,36 +2017,24 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host
     }
     __syncthreads();
 
-    // 7. every frontier half-edge into its loop's slot: the minimum first,
-    //    then the others in next' order
+    // 6. every loop from its minimum into its place (prev' is out), then out
     if (fits) {
+        for (int k = tid; k < nlist; k += kSmallBlock) {
+            const uint32_t mn = s_list[k];
+            if (mn == kNo16) continue;
+            uint32_t at = s_nx[mn | 3u], cur = mn;
+            do {
+                s_pv[at++] = (uint16_t)cur;
+                cur = s_nx[cur];
+            } while (cur != mn);
+        }
+        __syncthreads();
         const gint lhe = (gint)d.loop_he;
-        int off[IT], ln[IT];
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            const int mc = ((front >> j) & 1u) ? m[j] : 0;
-            off[j] = s_p[mc];
-            ln[j] = s_nx[mc];
-        }
-        int nfront = 0;
-#pragma unroll
-        for (int j = 0; j < IT; j++) {
-            if (!((front >> j) & 1u)) continue;
-            nfront++;
-            const int pos = k[j] == 0 ? 0 : ln[j] - k[j];
-            if (pos < 0 || pos >= ln[j] || off[j] + pos >= ts) {
-                bad = 1;
-                continue;
-            }
-            lhe[off[j] + pos] = tid + j * kSmallBlock;
-        }
-        if (nfront) atomicAdd(&s_cnt[3], nfront);
+        for (int k = tid; k < ts; k += kSmallBlock) lhe[k] = he_of_slot(s_pv[k]);
     }
-    const int anybad = __syncthreads_or(bad);
     if (tid == 0) {
         MeshCounters c{};
-        // every frontier half-edge lies on exactly one loop
-        c.err = (anybad || s_cnt[3] != ts) ? kErrCorrupt : 0;
+        c.err = fits ? 0 : kErrCorrupt;
         c.nties = s_cnt[0];
         c.ntips = s_cnt[1];
         c.nmiddle = s_cnt[2];
@@ -2063,69 +2044,102 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host
     }
 }
 
+template <int TI>
+__device__ __forceinline__ void small_mesh(const MeshDesc &d, MeshCounters *host) {
+    if (d.nt <= 0 || d.nt > TI * kSmallBlock) {   // (uniform) an empty mesh; larger ones are never launched here
+        if (threadIdx.x == 0) {
+            MeshCounters c{};
+            c.err = d.nt != 0 ? kErrCorrupt : 0;
+            small_counts(d, host, c);
+            if (d.nt == 0) d.loop_off[0] = 0;
+        }
+        return;
+    }
+    SmallTris<TI> tr;
+    small_load(d, tr);
+    small_body(d, host, tr);
+}
+
 // a batch of small meshes: one workgroup per descriptor
-template <int IT>
+template <int TI>
 __global__ void __launch_bounds__(kSmallBlock) k_small(const MeshDesc *__restrict__ descs) {
-    small_body<IT>(descs[blockIdx.x], nullptr);
+    small_mesh<TI>(descs[blockIdx.x], nullptr);
 }
 
 // one small mesh, its descriptor passed by value and its counts written to
 // host memory: a call that needs nothing staged before it or copied after it
-template <int IT>
+template <int TI>
 __global__ void __launch_bounds__(kSmallBlock) k_small_one(const MeshDesc d, MeshCounters *host) {
-    small_body<IT>(d, host);
+    small_mesh<TI>(d, host);
 }
 
 // ---------------------------------------------------------------------------
 // k_small_jobs: build and mesh one small job per workgroup
 //
-// The half-edge build of Section 4.1-4.2 for a job small enough for LDS, in
-// the order and with the error reports of the staged build kernels: every
-// coordinate in [0, 2^30]; every corner index in [0, nv) and no zero-area
-// triangle (exact int64 orientation test), clockwise triangles reordered
-// counter-clockwise; then twins by bucketing the half-edges by origin and
-// searching the target's bucket for the reverse edge, where two reverse
-// edges, or a repeated directed edge without one, is non-manifold.  Errors
-// keep the lowest (rank << 8 | code): coordinates first, then the lowest bad
-// triangle, then the lowest non-manifold half-edge; the twins are matched
-// only when the first checks pass.  The built structure goes to device
-// scratch and the workgroup then meshes it as k_small does.
+// The half-edge build of Section 4.1-4.2 for a job small enough for LDS, with
+// the error reports of the staged build kernels: every coordinate in [0,
+// 2^30]; every corner index in [0, nv) and no zero-area triangle (exact int64
+// orientation test), clockwise triangles reordered counter-clockwise; then
+// twins by a hash table of the edges in LDS, where a third half-edge of one
+// edge, or a second in the same direction, is non-manifold.  Errors keep the
+// lowest (rank << 8 | code): coordinates first, then the lowest bad triangle,
+// then non-manifold; the twins are matched only when the first checks pass.
+// A thread keeps its triangles in registers from their loads to the labels of
+// the meshing that follows (as k_small does it), so a job's structure goes to
+// memory only for a build on its own.
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ unsigned long long job_key(unsigned long long rank, int code) {
     return (rank << 8) | (unsigned long long)(-code);
 }
 
+// Slots of the build's edge table: more than the 3 nt edges a job can have.
+template <int TI>
+struct JobTable {
+    static constexpr int kBits = TI == 1 ? 12 : (TI == 2 ? 13 : 14), kSlots = 1 << kBits;
+    static_assert(kSlots > 3 * TI * kSmallBlock, "every edge finds a slot");
+};
+
 size_t small_job_lds_bytes(int max_nv, int max_nt) {
-    // corners (3 nt), bucket starts (nv + 1), fill cursors (nv), bucket (3 nt)
-    const size_t build = 4 * (3 * (size_t)max_nt + (size_t)max_nv + 1 + (size_t)max_nv + 3 * (size_t)max_nt) + 64;
-    const size_t mesh = small_lds_bytes(max_nt);
+    (void)max_nv;
+    const int slots = max_nt <= kSmallBlock       ? JobTable<1>::kSlots
+                      : max_nt <= 2 * kSmallBlock ? JobTable<2>::kSlots
+                                                  : JobTable<4>::kSlots;
+    const size_t build = 8 * (size_t)slots, mesh = small_lds_bytes(max_nt);
     return build > mesh ? build : mesh;
 }
 
-template <int IT>
-__global__ void __launch_bounds__(kSmallBlock) k_small_jobs(const SmallJob *__restrict__ jobs) {
+template <int TI>
+__device__ __forceinline__ void small_job(const SmallJob &jd) {
     extern __shared__ int4 lds_raw[];
     __shared__ unsigned long long s_key;
     __shared__ int s_flip;
-    __shared__ int s_scan[72];
-    const SmallJob &jd = jobs[blockIdx.x];
-    const int nv = jd.nv, nt = jd.nt, nh = 3 * nt, tid = threadIdx.x;
-    if (tid == 0) {
-        s_key = ~0ull;
-        s_flip = 0;
-    }
-    if (nv < 0 || nt < 0 || nv > kJobSmallV || nt > (IT / 3) * kSmallBlock) {   // (uniform) never launched so
+    constexpr int kBits = JobTable<TI>::kBits, kSlots = JobTable<TI>::kSlots;
+    const int nv = jd.nv, nt = jd.nt, tid = threadIdx.x;
+    if (nv < 0 || nt < 0 || nv > kJobSmallV || nt > TI * kSmallBlock) {   // (uniform) never launched so
         if (tid == 0) {
             jd.counts[8] = (int)(uint32_t)job_key(0, -1);
             jd.counts[9] = 0;
         }
         return;
     }
-    int *s_org = reinterpret_cast<int *>(lds_raw);   // 3 nt corners, counter-clockwise
-    int *s_vst = s_org + nh;                          // nv + 1 bucket starts
-    int *s_cur = s_vst + nv + 1;                      // nv fill cursors
-    int *s_bkt = s_cur + nv;                          // nh half-edges grouped by origin
+    if (tid == 0) {
+        s_key = ~0ull;
+        s_flip = 0;
+    }
+    // an edge's slot: bits 0-11 and 12-23 its ends (the lower first), bit 24 a
+    // 1; bits 32-45 the first half-edge's slot, bit 46 it runs from the lower
+    // end, bits 48-62 the second's slot + 1 (0 before it comes)
+    unsigned long long *s_table = reinterpret_cast<unsigned long long *>(lds_raw);
+    for (int k = tid; k < kSlots / 2; k += kSmallBlock) reinterpret_cast<ulonglong2 *>(lds_raw)[k] = ulonglong2{0ull, 0ull};
+    // corners: indices, orientation, counter-clockwise order
+    SmallTris<TI> tr;
+#pragma unroll
+    for (int j = 0; j < TI; j++) {
+        const int t = tid + j * kSmallBlock, tt = t < nt ? t : 0;
+#pragma unroll
+        for (int i = 0; i < 3; i++) tr.v[j][i] = nt > 0 ? jd.tri[3 * tt + i] : 0;
+    }
     __syncthreads();
     // coordinates (and the mesh's own copy of them)
     for (int v = tid; v < nv; v += kSmallBlock) {
@@ -2133,32 +2147,28 @@ __global__ void __launch_bounds__(kSmallBlock) k_small_jobs(const SmallJob *__re
         if (jd.xy_out) jd.xy_out[v] = p;
         if (p.x < 0 || p.x > (1 << 30) || p.y < 0 || p.y > (1 << 30)) atomicMin(&s_key, job_key(0, -2));
     }
-    // corners: indices, orientation, counter-clockwise order
     int flips = 0;
-    for (int t = tid; t < nt; t += kSmallBlock) {
-        int a = jd.tri[3 * t], b = jd.tri[3 * t + 1], c = jd.tri[3 * t + 2];
+#pragma unroll
+    for (int j = 0; j < TI; j++) {
+        const int t = tid + j * kSmallBlock;
+        if (t >= nt) continue;
+        const int a = tr.v[j][0], b = tr.v[j][1], c = tr.v[j][2];
         if ((unsigned)a >= (unsigned)nv || (unsigned)b >= (unsigned)nv || (unsigned)c >= (unsigned)nv) {
             atomicMin(&s_key, job_key(1ull + t, -1));
-            a = b = c = 0;
-        } else {
-            const int2 pa = jd.xy[a], pb = jd.xy[b], pc = jd.xy[c];
-            const long long o = ((long long)pb.x - pa.x) * ((long long)pc.y - pa.y) -
-                                ((long long)pb.y - pa.y) * ((long long)pc.x - pa.x);
-            if (o == 0) {
-                atomicMin(&s_key, job_key(1ull + t, -3));
-            } else if (o < 0) {
-                const int sw = b;
-                b = c;
-                c = sw;
-                flips++;
-            }
+            continue;
         }
-        s_org[3 * t] = a;
-        s_org[3 * t + 1] = b;
-        s_org[3 * t + 2] = c;
+        const int2 pa = jd.xy[a], pb = jd.xy[b], pc = jd.xy[c];
+        const long long o = ((long long)pb.x - pa.x) * ((long long)pc.y - pa.y) -
+                            ((long long)pb.y - pa.y) * ((long long)pc.x - pa.x);
+        if (o == 0) {
+            atomicMin(&s_key, job_key(1ull + t, -3));
+        } else if (o < 0) {
+            tr.v[j][1] = c;
+            tr.v[j][2] = b;
+            flips++;
+        }
     }
     if (flips) atomicAdd(&s_flip, flips);
-    for (int v = tid; v <= nv; v += kSmallBlock) s_vst[v] = 0;
     __syncthreads();
     if (s_key != ~0ull) {   // (uniform) the inputs failed their checks: no twins
         if (tid == 0) {
@@ -2167,65 +2177,68 @@ __global__ void __launch_bounds__(kSmallBlock) k_small_jobs(const SmallJob *__re
         }
         return;
     }
-    // out-degrees, their exclusive scan (four vertices per thread), buckets
-    for (int h = tid; h < nh; h += kSmallBlock) atomicAdd(&s_vst[s_org[h]], 1);
-    __syncthreads();
-    {
-        constexpr int VP = (kJobSmallV + kSmallBlock - 1) / kSmallBlock;
-        const int v0 = tid * VP;
-        int dv[VP], sum = 0;
+    // every half-edge into its edge's slot, then its twin from there
+    uint32_t q[TI][3];
+    bool dup = false;
 #pragma unroll
-        for (int k = 0; k < VP; k++) {
-            dv[k] = v0 + k < nv ? s_vst[v0 + k] : 0;
-            sum += dv[k];
-        }
-        int ex, ex2, tot, tot2;
-        block_excl_scan2(sum, 0, ex, ex2, tot, tot2, s_scan);
+    for (int j = 0; j < TI; j++) {
+        const int t = tid + j * kSmallBlock;
 #pragma unroll
-        for (int k = 0; k < VP; k++) {
-            if (v0 + k < nv) {
-                s_vst[v0 + k] = ex;
-                s_cur[v0 + k] = ex;
+        for (int i = 0; i < 3; i++) {
+            q[j][i] = 0;
+            if (t >= nt) continue;
+            const uint32_t u = (uint32_t)tr.v[j][i], v = (uint32_t)tr.v[j][i == 2 ? 0 : i + 1], slot = 4u * t + i;
+            const uint32_t key = min(u, v) | (max(u, v) << 12) | (1u << 24);
+            const unsigned long long word = (unsigned long long)(slot | (u < v ? 1u << 14 : 0u)) << 32 | key;
+            uint32_t at = (key * 0x9E3779B1u) >> (32 - kBits);
+            while (true) {
+                const unsigned long long was = atomicCAS(&s_table[at], 0ull, word);
+                if (was == 0ull) break;
+                if ((uint32_t)was == key) {
+                    atomicOr(reinterpret_cast<unsigned *>(&s_table[at]) + 1, (slot + 1u) << 16);
+                    dup |= ((uint32_t)((was ^ word) >> 32) & (1u << 14)) == 0;
+                    break;
+                }
+                at = (at + 1) & (kSlots - 1);
             }
-            ex += dv[k];
+            q[j][i] = at;
         }
-        if (tid == 0) s_vst[nv] = tot;
     }
     __syncthreads();
-    for (int h = tid; h < nh; h += kSmallBlock) s_bkt[atomicAdd(&s_cur[s_org[h]], 1)] = h;
-    __syncthreads();
-    // twins: h = u->v pairs with the one v->u in v's bucket
-    for (int h = tid; h < nh; h += kSmallBlock) {
-        const int u = s_org[h], v = s_org[he_next(h)];
-        int found = -1, nrev = 0, ndup = 0;
-        for (int k = s_vst[v], e = s_vst[v + 1]; k < e; k++) {
-            const int g = s_bkt[k];
-            if (s_org[he_next(g)] == u) {
-                found = g;
-                ++nrev;
-            }
+#pragma unroll
+    for (int j = 0; j < TI; j++) {
+        const int t = tid + j * kSmallBlock;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            tr.s[j][i] = kNoSlot;
+            if (t >= nt) continue;
+            const uint32_t w = (uint32_t)(s_table[q[j][i]] >> 32), slot = 4u * t + i, first = w & 0x3fffu, second = w >> 16;
+            const bool lead = first == slot;
+            dup |= !lead && second != slot + 1u;   // (a third half-edge's slot has run together with the second's)
+            tr.s[j][i] = !lead ? first : (second ? second - 1u : kNoSlot);
         }
-        if (nrev == 0)
-            for (int k = s_vst[u], e = s_vst[u + 1]; k < e; k++) {
-                const int g = s_bkt[k];
-                if (g != h && s_org[he_next(g)] == v) ++ndup;
-            }
-        if (nrev > 1 || ndup > 0) atomicMin(&s_key, job_key(1ull + nt + h, -4));
-        jd.org[h] = u;
-        jd.twin[h] = nrev == 1 ? found : -1;
     }
+    if (dup) atomicMin(&s_key, job_key(1ull + nt, -4));
     __syncthreads();
     if (tid == 0) {
         jd.counts[8] = (int)(uint32_t)s_key;
         jd.counts[9] = (int)(uint32_t)(s_key >> 32);
         jd.counts[10] = s_flip;
     }
-    if (s_key != ~0ull || jd.build_only) return;   // (uniform)
-    __threadfence_block();   // the structure in global memory, for the meshing that follows
+    if (s_key != ~0ull) return;   // (uniform)
+    if (jd.build_only) {          // (uniform)
+#pragma unroll
+        for (int j = 0; j < TI; j++) {
+            const int t = tid + j * kSmallBlock;
+            if (t >= nt) continue;
+            *(GLOBAL v3i_a4 *)((gint)jd.org + 3 * t) = v3i_a4{tr.v[j][0], tr.v[j][1], tr.v[j][2]};
+            const auto he = [](uint32_t s) { return s == kNoSlot ? -1 : he_of_slot(s); };
+            *(GLOBAL v3i_a4 *)((gint)jd.twin + 3 * t) = v3i_a4{he(tr.s[j][0]), he(tr.s[j][1]), he(tr.s[j][2])};
+        }
+        return;
+    }
     MeshDesc d{};
     d.xy = jd.xy;
-    d.org = jd.org;
-    d.twin = jd.twin;
     d.next_o = jd.next_o;
     d.prev_o = jd.prev_o;
     d.seeds = jd.seeds;
@@ -2234,7 +2247,37 @@ __global__ void __launch_bounds__(kSmallBlock) k_small_jobs(const SmallJob *__re
     d.ctr = reinterpret_cast<MeshCounters *>(jd.counts);
     d.nt = nt;
     d.nv = nv;
-    small_body<IT>(d, nullptr);
+    if (nt == 0) {   // (uniform)
+        if (tid == 0) {
+            *d.ctr = MeshCounters{};
+            d.loop_off[0] = 0;
+        }
+        return;
+    }
+    small_body(d, nullptr, tr);
+}
+
+template <int TI>
+__global__ void __launch_bounds__(kSmallBlock) k_small_jobs(const SmallJob *__restrict__ jobs) {
+    small_job<TI>(jobs[blockIdx.x]);
+}
+
+// one job, its description passed by value
+template <int TI>
+__global__ void __launch_bounds__(kSmallBlock) k_small_job_one(const SmallJob job) {
+    small_job<TI>(job);
+}
+
+hipError_t launch_small_job_one(const SmallJob &job, hipStream_t s) {
+    const dim3 grid(1), block(kSmallBlock);
+    const size_t lds = small_job_lds_bytes(job.nv, job.nt);
+    if (job.nt <= kSmallBlock)
+        hipLaunchKernelGGL(k_small_job_one<1>, grid, block, lds, s, job);
+    else if (job.nt <= 2 * kSmallBlock)
+        hipLaunchKernelGGL(k_small_job_one<2>, grid, block, lds, s, job);
+    else
+        hipLaunchKernelGGL(k_small_job_one<4>, grid, block, lds, s, job);
+    return hipGetLastError();
 }
 
 hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nv, int max_nt, hipStream_t s) {
@@ -2242,11 +2285,11 @@ hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nv, int max_nt
     const dim3 grid(n), block(kSmallBlock);
     const size_t lds = small_job_lds_bytes(max_nv, max_nt);
     if (max_nt <= kSmallBlock)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_jobs<3>), grid, block, lds, s, jobs);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_jobs<1>), grid, block, lds, s, jobs);
     else if (max_nt <= 2 * kSmallBlock)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_jobs<6>), grid, block, lds, s, jobs);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_jobs<2>), grid, block, lds, s, jobs);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_jobs<12>), grid, block, lds, s, jobs);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_jobs<4>), grid, block, lds, s, jobs);
     return hipGetLastError();
 }
 
@@ -2351,24 +2394,27 @@ hipError_t launch_small_one(const MeshDesc &d, MeshCounters *host, hipStream_t s
     const dim3 grid(1), block(kSmallBlock);
     const size_t lds = small_lds_bytes(d.nt);
     if (d.nt <= kSmallBlock)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<3>), grid, block, lds, s, d, host);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<1>), grid, block, lds, s, d, host);
     else if (d.nt <= 2 * kSmallBlock)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<6>), grid, block, lds, s, d, host);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<2>), grid, block, lds, s, d, host);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<12>), grid, block, lds, s, d, host);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<4>), grid, block, lds, s, d, host);
     return hipGetLastError();
 }
 
 int prepare_small(int lds_block) {
-    const void *const fns[9] = {reinterpret_cast<const void *>(&k_small<3>),
-                                reinterpret_cast<const void *>(&k_small<6>),
-                                reinterpret_cast<const void *>(&k_small<12>),
-                                reinterpret_cast<const void *>(&k_small_one<3>),
-                                reinterpret_cast<const void *>(&k_small_one<6>),
-                                reinterpret_cast<const void *>(&k_small_one<12>),
-                                reinterpret_cast<const void *>(&k_small_jobs<3>),
-                                reinterpret_cast<const void *>(&k_small_jobs<6>),
-                                reinterpret_cast<const void *>(&k_small_jobs<12>)};
+    const void *const fns[12] = {reinterpret_cast<const void *>(&k_small_job_one<1>),
+                                reinterpret_cast<const void *>(&k_small_job_one<2>),
+                                reinterpret_cast<const void *>(&k_small_job_one<4>),
+                                reinterpret_cast<const void *>(&k_small<1>),
+                                reinterpret_cast<const void *>(&k_small<2>),
+                                reinterpret_cast<const void *>(&k_small<4>),
+                                reinterpret_cast<const void *>(&k_small_one<1>),
+                                reinterpret_cast<const void *>(&k_small_one<2>),
+                                reinterpret_cast<const void *>(&k_small_one<4>),
+                                reinterpret_cast<const void *>(&k_small_jobs<1>),
+                                reinterpret_cast<const void *>(&k_small_jobs<2>),
+                                reinterpret_cast<const void *>(&k_small_jobs<4>)};
     int fixed = 0;
     for (const void *f : fns) {
         hipFuncAttributes a{};
@@ -2400,11 +2446,11 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
         const size_t lds = small_lds_bytes(rb.max_nt);
         H(K_SMALL, 0);
         if (rb.max_nt <= kSmallBlock)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<3>), grid, block, lds, s, rb.descs);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<1>), grid, block, lds, s, rb.descs);
         else if (rb.max_nt <= 2 * kSmallBlock)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<6>), grid, block, lds, s, rb.descs);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<2>), grid, block, lds, s, rb.descs);
         else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<12>), grid, block, lds, s, rb.descs);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<4>), grid, block, lds, s, rb.descs);
         H(K_SMALL, 1);
         return hipGetLastError();
     }

@@ -634,7 +634,9 @@ int renumber_input(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri,
 // Builds meshes that each fit one workgroup with one launch of the small-job
 // kernel in build-only mode: host inputs packed into one upload, the checks,
 // orientation and twin matching in LDS (with the staged build's error codes
-// and ranking), and one download of every mesh's error key and flip count.
+// and ranking); every mesh's error key and flip count go straight to pinned
+// host memory.  A mesh on its own has its description passed by value, so
+// with inputs on the device nothing is copied in either direction.
 int build_small_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, const int32_t *const *tri,
                      const int32_t *nt, uint32_t flags, gp_mesh **out, int *status) {
     const bool in_dev = (flags & GP_IN_DEVICE) != 0;
@@ -655,9 +657,9 @@ int build_small_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *
         in_bytes += align_up(12 * (size_t)nt[i], 16);
     }
     const size_t desc_off = align_up(in_bytes, 256), up_bytes = desc_off + sizeof(gp::SmallJob) * (size_t)n;
-    const size_t cnt_off = align_up(up_bytes, 256), cnt_bytes = 4 * (size_t)gp::kJobCounts * (size_t)n;
+    const size_t copied = n == 1 ? in_bytes : up_bytes, cnt_bytes = 4 * (size_t)gp::kJobCounts * (size_t)n;
     void *dev = nullptr;
-    int rc = c->pool.alloc(cnt_off + cnt_bytes, &dev);
+    int rc = copied ? c->pool.alloc(copied, &dev) : GP_OK;
     char *up = rc == GP_OK ? static_cast<char *>(pinned_take(c, up_bytes)) : nullptr;
     char *down = up ? static_cast<char *>(pinned_take(c, cnt_bytes)) : nullptr;
     if (rc == GP_OK && (!up || !down)) rc = GP_ENOMEM;
@@ -667,7 +669,7 @@ int build_small_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *
     for (int i = 0; i < n && rc == GP_OK; i++) {
         gp::SmallJob &sj = descs[i];
         sj = gp::SmallJob{};
-        sj.counts = reinterpret_cast<int32_t *>(d + cnt_off) + (size_t)gp::kJobCounts * i;
+        sj.counts = reinterpret_cast<int32_t *>(down) + (size_t)gp::kJobCounts * i;
         sj.build_only = 1;
         if (status[i] != GP_OK) continue;   // nothing to build: an empty job in the launch
         gp_mesh *m = new (std::nothrow) gp_mesh();
@@ -708,10 +710,10 @@ int build_small_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *
     }
     hipStream_t s = c->stream;
     if (rc == GP_OK &&
-        (hipMemcpyAsync(d, up, up_bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
-         gp::launch_small_jobs(reinterpret_cast<const gp::SmallJob *>(d + desc_off), n, max_nv, max_nt, s) !=
-             hipSuccess ||
-         hipMemcpyAsync(down, d + cnt_off, cnt_bytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        ((copied && hipMemcpyAsync(d, up, copied, hipMemcpyHostToDevice, s) != hipSuccess) ||
+         (n == 1 ? gp::launch_small_job_one(descs[0], s)
+                 : gp::launch_small_jobs(reinterpret_cast<const gp::SmallJob *>(d + desc_off), n, max_nv, max_nt,
+                                         s)) != hipSuccess ||
          hipStreamSynchronize(s) != hipSuccess)) {
         (void)hipGetLastError();
         (void)hipStreamSynchronize(s);
