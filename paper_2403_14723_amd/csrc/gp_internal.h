@@ -281,14 +281,27 @@ struct RenumberBuffers {
     int32_t *vperm;        // nv: new -> old vertex
     int32_t *tperm;        // nt: new -> old triangle
     int32_t *vinv;         // nv: old -> new vertex (scratch)
-    uint64_t *keys, *keys_alt;   // max(nv, nt) each (scratch)
-    int32_t *vals;               // max(nv, nt) (scratch)
-    void *sort_tmp;              // sort_bytes (scratch)
+    // the sort by sampling (arrays that are not too long for it)
+    void *sample_tmp;      // sample_bytes (scratch)
+    int32_t *overflow;     // a word of it: a bucket did not fit
+    int32_t *overflow_out; // the caller's pinned word, set to 1 then: the outputs are
+                           // not written, and the input goes to the library's sort
+    bool library;          // sort with the library whatever the lengths
+    // the library's sort of the others: `pairs` keys and values (scratch)
+    uint64_t *keys, *keys_alt;
+    int32_t *vals;
+    void *sort_tmp;        // sort_bytes (scratch)
     size_t sort_bytes;
 };
 
-// scratch bytes of the radix sort of n key-value pairs
-size_t renumber_sort_bytes(int32_t n);
+// Scratch of a renumbering: the sampling sort's bytes, and the pairs and bytes
+// of the library's sort (0 when neither array goes there).
+struct RenumberSizes {
+    size_t sample_bytes = 0, sort_bytes = 0;
+    int32_t pairs = 0;
+    bool ok = true;
+};
+RenumberSizes renumber_sizes(int32_t nv, int32_t nt, bool library);
 hipError_t launch_renumber(const RenumberBuffers &b, hipStream_t s);
 
 // ---- compact half-edge encoding (build_kernels.hip) ----------------------

@@ -575,21 +575,25 @@ void renumbered_free(gp_ctx *c, Renumbered &r, bool keep_maps) {
     r = Renumbered{};
 }
 
-// Queues the renumbering of one input on the context's stream.
+// Queues the renumbering of one input on the context's stream.  overflow: a
+// pinned word that is 1 after the stream has drained when the input has to be
+// renumbered again, with the library's sort.
 int renumber_input(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, int32_t nt, bool in_dev,
-                   Renumbered &r) {
+                   bool library, int32_t *overflow, Renumbered &r) {
     if (nv < 0 || nt < 0 || (nv > 0 && !xy) || (nt > 0 && !tri)) return GP_EINVAL;
     if (3ll * nt >= (1ll << 31)) return GP_ERANGE;
     hipStream_t s = c->stream;
     const size_t nxy = sizeof(int2) * (size_t)std::max(nv, 1), ntri = 12 * (size_t)std::max(nt, 1);
-    const int32_t nmax = std::max(std::max(nv, nt), 1);
-    const size_t sort = gp::renumber_sort_bytes(nmax);
-    if (!sort) return GP_EHIP;
+    *overflow = 0;
+    const gp::RenumberSizes z = gp::renumber_sizes(nv, nt, library);
+    if (!z.ok) return GP_EHIP;
     int rc = c->pool.alloc(nxy, &r.xy);
     if (rc == GP_OK) rc = c->pool.alloc(ntri, &r.tri);
     if (rc == GP_OK) rc = c->pool.alloc(4 * (size_t)std::max(nv, 1), &r.vperm);
     if (rc == GP_OK) rc = c->pool.alloc(4 * (size_t)std::max(nt, 1), &r.tperm);
-    const size_t tmp = arena_bytes<int32_t>(nmax) * 2 + arena_bytes<uint64_t>(nmax) * 2 + align_up(sort);
+    const size_t tmp = arena_bytes<int32_t>(std::max(nv, 1)) + arena_bytes<char>(z.sample_bytes) +
+                       arena_bytes<int32_t>(1) + arena_bytes<int32_t>(z.pairs) + 2 * arena_bytes<uint64_t>(z.pairs) +
+                       arena_bytes<char>(z.sort_bytes);
     if (rc == GP_OK) rc = c->pool.alloc(tmp, &r.tmp);
     const void *src_xy = xy, *src_tri = tri;
     if (rc == GP_OK && !in_dev) {   // the inputs are read several times: upload them once
@@ -616,12 +620,16 @@ int renumber_input(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri,
     b.tri_out = static_cast<int32_t *>(r.tri);
     b.vperm = static_cast<int32_t *>(r.vperm);
     b.tperm = static_cast<int32_t *>(r.tperm);
-    b.vinv = a.take<int32_t>(nmax);
-    b.vals = a.take<int32_t>(nmax);
-    b.keys = a.take<uint64_t>(nmax);
-    b.keys_alt = a.take<uint64_t>(nmax);
-    b.sort_tmp = a.take<char>(sort);
-    b.sort_bytes = sort;
+    b.vinv = a.take<int32_t>(std::max(nv, 1));
+    b.sample_tmp = a.take<char>(z.sample_bytes);
+    b.overflow = a.take<int32_t>(1);
+    b.overflow_out = overflow;
+    b.library = library;
+    b.vals = a.take<int32_t>(z.pairs);
+    b.keys = a.take<uint64_t>(z.pairs);
+    b.keys_alt = a.take<uint64_t>(z.pairs);
+    b.sort_tmp = a.take<char>(z.sort_bytes);
+    b.sort_bytes = z.sort_bytes;
     if (gp::launch_renumber(b, s) != hipSuccess) {
         (void)hipGetLastError();
         return GP_EHIP;
@@ -765,9 +773,10 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
             return build_small_many(c, n, xy, nv, tri, nt, flags, out, status);
     }
     std::vector<BuildJob> jobs(n);
-    const size_t hb = sizeof(BuildReport) * (size_t)std::max(n, 1);
+    const size_t hb = (sizeof(BuildReport) + sizeof(int32_t)) * (size_t)std::max(n, 1);
     BuildReport *host = static_cast<BuildReport *>(pinned_take(c, hb));
     if (!host) return GP_ENOMEM;
+    int32_t *overflow = reinterpret_cast<int32_t *>(host + std::max(n, 1));   // renumbering only
     for (int i = 0; i < n; i++) {
         jobs[i].report = host + i;
         out[i] = nullptr;
@@ -781,18 +790,41 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
     };
     // renumbered inputs (GP_RENUMBER): built from their device copies
     std::vector<Renumbered> rn((flags & GP_RENUMBER) ? n : 0);
+    auto renumber_queue = [&](int i, bool library) {
+        jobs[i].rc = renumber_input(c, xy[i], nv[i], tri[i], nt[i], (flags & GP_IN_DEVICE) != 0, library,
+                                    overflow + i, rn[i]);
+        if (jobs[i].rc == GP_OK)
+            jobs[i].rc = build_queue(c, static_cast<const int32_t *>(rn[i].xy), nv[i],
+                                     static_cast<const int32_t *>(rn[i].tri), nt[i], flags | GP_IN_DEVICE, jobs[i]);
+    };
+    auto renumber_reset = [&](int i) {
+        build_abort(c, jobs[i]);
+        renumbered_free(c, rn[i], false);
+    };
     for (int i = 0; i < n; i++) {
         if (flags & GP_RENUMBER) {
-            jobs[i].rc = renumber_input(c, xy[i], nv[i], tri[i], nt[i], (flags & GP_IN_DEVICE) != 0, rn[i]);
-            if (jobs[i].rc == GP_OK)
-                jobs[i].rc = build_queue(c, static_cast<const int32_t *>(rn[i].xy), nv[i],
-                                         static_cast<const int32_t *>(rn[i].tri), nt[i], flags | GP_IN_DEVICE,
-                                         jobs[i]);
+            renumber_queue(i, false);
+            if (jobs[i].rc == GP_ENOMEM) {   // the library's sort needs less scratch
+                renumber_reset(i);
+                renumber_queue(i, true);
+            }
         } else {
             jobs[i].rc = build_queue(c, xy[i], nv[i], tri[i], nt[i], flags, jobs[i]);
         }
     }
     drain();
+    bool again = false;
+    for (int i = 0; i < (int)rn.size(); i++) {
+        if (jobs[i].rc != GP_OK || !overflow[i]) continue;
+        renumber_reset(i);   // (built from arrays that were not written)
+        renumber_queue(i, true);
+        again = true;
+    }
+    if (again) drain();
+    for (Renumbered &r : rn) {   // (its work is done: room for what follows)
+        c->pool.release(r.tmp);
+        r.tmp = nullptr;
+    }
     bool large = false;
     for (BuildJob &j : jobs) {
         if (!j.large()) continue;
