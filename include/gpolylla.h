@@ -306,13 +306,15 @@ typedef struct {
  * group_triangles triangles (0: 8M; a larger job is a group of its own) and
  * each group is one batched run (gpolylla_mesh_batch); flags: 0 or GP_GRAPH.
  * A list whose jobs all have at most 4096 triangles and 4096 vertices (and
- * fit the device's LDS per workgroup) runs packed instead: per group one
- * upload of every job's inputs from a pinned staging block, one launch that
- * builds and meshes each job in a workgroup of its own (the same checks and
- * error codes as gpolylla_build_halfedges), and one download; flags are
- * then ignored.
- * Uses the context's stream for uploads, builds and runs, and a stream of its
- * own for the downloads; returns when every job's outputs are in host memory.
+ * fit the device's LDS per workgroup) runs packed instead, in groups of up to
+ * group_triangles triangles (0: 128K), of which up to five are in flight: per
+ * group one upload of every job's inputs from a pinned staging block, one
+ * launch that builds and meshes each job in a workgroup of its own (the same
+ * checks and error codes as gpolylla_build_halfedges), and one download; two
+ * threads that the context keeps help to hand out the results; flags are then
+ * ignored.
+ * Uses the context's stream and streams of its own (ordered after the work
+ * that is queued on the context's); returns when every job's outputs are in host memory.
  * Returns GP_OK when every job succeeded, else the first failed job's status
  * (every job's own status is set either way); GP_EINVAL for a null or
  * inconsistent argument (nothing run).  Not to be called concurrently with

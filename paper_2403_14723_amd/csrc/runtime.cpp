@@ -1175,6 +1175,7 @@ void gpolylla_ctx_destroy(gp_ctx *c) {
     if (!c) return;
     DeviceGuard g(c->device);
     (void)hipStreamSynchronize(c->stream);
+    job_crew_free(c);
     resolve_profile(c);
     reap_retired(c, true);
     if (c->graphs) {

@@ -139,6 +139,7 @@ size_t arena_bytes(size_t count) {
 
 struct RunState;
 struct GraphCache;
+struct JobCrew;
 
 struct DeviceGuard {
     int prev = -1;
@@ -162,6 +163,9 @@ void pinned_give(gp_ctx *c, void *p, size_t n);
 
 int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, const int32_t *const *tri,
                const int32_t *nt, uint32_t flags, gp_mesh **out, int *status);
+
+// gives back what packed lists of jobs keep with the context (jobs.cpp)
+void job_crew_free(gp_ctx *c);
 
 // device bytes gpolylla_build_halfedges takes from the pool
 size_t build_footprint(int64_t nv, int64_t nt, bool inputs_on_device);
@@ -201,6 +205,7 @@ struct gp_ctx {
     int ring_next = 0;
     std::vector<gprt::RunState *> retired;
     gprt::GraphCache *graphs = nullptr;
+    gprt::JobCrew *crew = nullptr;   // packed lists of jobs (jobs.cpp)
 };
 
 struct gp_mesh {
