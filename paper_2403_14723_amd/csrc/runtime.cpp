@@ -379,6 +379,7 @@ namespace {
 struct BuildReport {
     unsigned long long err;   // gp::BuildBuffers::err
     int32_t nflipped, nbig, total, ntasks;
+    int32_t nesc, pad;        // compact meshes: gp::CompactBuffers::nesc
 };
 
 // the report, then the flip counters; each vertex group's two counters follow
@@ -402,6 +403,7 @@ struct BuildJob {
     gp::BuildBuffers b{};
     BuildReport *report = nullptr;   // pinned
     const BuildReport *report_dev = nullptr;
+    bool encoded = false;     // the compact encoding was queued with the build
     int rc = GP_OK;
     bool large() const { return rc == GP_OK && report->err == 0 && report->nbig > 0; }
 };
@@ -413,7 +415,34 @@ void build_abort(gp_ctx *c, BuildJob &j) {
     j.m = nullptr;
 }
 
-// Allocation, input copies, the kernels and the readback, all queued.
+// A compact mesh's arrays (see gp::MeshDesc), held by the mesh.
+int compact_alloc(gp_ctx *c, gp_mesh *m) {
+    void *p8 = nullptr, *p16 = nullptr;
+    int rc = c->pool.alloc(sizeof(int2) * (size_t)std::max<int32_t>(m->nt, 1), &p8);
+    if (rc == GP_OK) rc = c->pool.alloc(sizeof(int16_t) * (size_t)std::max<int64_t>(3ll * m->nt, 1), &p16);
+    if (rc != GP_OK) {
+        c->pool.release(p8);
+        return rc;
+    }
+    m->org8 = static_cast<int2 *>(p8);
+    m->twin16 = static_cast<int16_t *>(p16);
+    return GP_OK;
+}
+
+gp::CompactBuffers compact_buffers(const gp_mesh *m, int32_t *nesc) {
+    gp::CompactBuffers cb{};
+    cb.org = m->org;
+    cb.twin = m->twin;
+    cb.nt = m->nt;
+    cb.org8 = m->org8;
+    cb.twin16 = m->twin16;
+    cb.nesc = nesc;
+    return cb;
+}
+
+// Allocation, input copies, the kernels and the readback, all queued; and the
+// compact encoding with them, when its arrays can be had before the scratch
+// goes back (the twins of large groups come later: then it is done again).
 int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, int32_t nt, uint32_t flags,
                 BuildJob &j) {
     if (nv < 0 || nt < 0) return GP_EINVAL;
@@ -471,6 +500,8 @@ int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, in
         (!in_dev && nt > 0 &&
          hipMemcpyAsync(tri_dev, tri, sizeof(int32_t) * (size_t)nh, hipMemcpyHostToDevice, s) != hipSuccess) ||
         hipMemsetAsync(zero, 0, zero_bytes, s) != hipSuccess || gp::launch_build(b, s) != hipSuccess ||
+        ((flags & GP_COMPACT) && (j.encoded = compact_alloc(c, m) == GP_OK) &&
+         gp::launch_compact_encode(compact_buffers(m, &rep->nesc), s) != hipSuccess) ||
         gp::launch_copy_words(j.report, rep, sizeof(BuildReport), s) != hipSuccess) {
         (void)hipGetLastError();
         return GP_EHIP;
@@ -500,56 +531,48 @@ int build_finish(gp_ctx *c, BuildJob &j) {
     return GP_OK;
 }
 
-// Re-encodes a built mesh compactly (see gp::MeshDesc) and frees its int32
-// corners and twins.  host: 4 bytes of pinned scratch.
-int compact_mesh(gp_ctx *c, gp_mesh *m, int32_t *host) {
-    const int64_t nt = m->nt, nh = 3 * nt;
-    void *p8 = nullptr, *p16 = nullptr, *pe = nullptr, *pn = nullptr;
-    int rc = c->pool.alloc(sizeof(int2) * (size_t)std::max<int64_t>(nt, 1), &p8);
-    if (rc == GP_OK) rc = c->pool.alloc(sizeof(int16_t) * (size_t)std::max<int64_t>(nh, 1), &p16);
+// Encodes a built mesh and waits for the number of escapes (host: 4 bytes of
+// pinned scratch).
+int compact_encode(gp_ctx *c, gp_mesh *m, int32_t *host) {
+    int rc = m->org8 ? GP_OK : compact_alloc(c, m);
+    void *pn = nullptr;
     if (rc == GP_OK) rc = c->pool.alloc(sizeof(int32_t), &pn);
-    gp::CompactBuffers cb{};
-    cb.org = m->org;
-    cb.twin = m->twin;
-    cb.nt = m->nt;
-    cb.org8 = static_cast<int2 *>(p8);
-    cb.twin16 = static_cast<int16_t *>(p16);
-    cb.nesc = static_cast<int32_t *>(pn);
+    if (rc != GP_OK) return rc;
     hipStream_t s = c->stream;
-    if (rc == GP_OK &&
-        (hipMemsetAsync(cb.nesc, 0, sizeof(int32_t), s) != hipSuccess ||
-         gp::launch_compact_encode(cb, s) != hipSuccess ||
-         hipMemcpyAsync(host, cb.nesc, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-         hipStreamSynchronize(s) != hipSuccess)) {
+    if (hipMemsetAsync(pn, 0, sizeof(int32_t), s) != hipSuccess ||
+        gp::launch_compact_encode(compact_buffers(m, static_cast<int32_t *>(pn)), s) != hipSuccess ||
+        hipMemcpyAsync(host, pn, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess) {
         (void)hipGetLastError();
-        rc = GP_EHIP;
-    }
-    int32_t slots = 2;   // a power of two at least twice the escapes
-    if (rc == GP_OK) {
-        while (slots < 2 * (int64_t)*host) slots *= 2;
-        rc = c->pool.alloc(2 * sizeof(int32_t) * (size_t)slots, &pe);
-    }
-    cb.esc = static_cast<int32_t *>(pe);
-    cb.esc_mask = slots - 1;
-    if (rc == GP_OK &&
-        (gp::launch_compact_escapes(cb, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)) {
-        (void)hipGetLastError();
+        (void)hipStreamSynchronize(s);
         rc = GP_EHIP;
     }
     c->pool.release(pn);
-    if (rc != GP_OK) {
+    return rc;
+}
+
+// The escape table of an encoded mesh; its int32 corners and twins are freed.
+int compact_finish(gp_ctx *c, gp_mesh *m, int32_t nesc) {
+    const int64_t nt = m->nt, nh = 3 * nt;
+    void *pe = nullptr;
+    int32_t slots = 2;   // a power of two at least twice the escapes
+    while (slots < 2 * (int64_t)nesc) slots *= 2;
+    const int rc = c->pool.alloc(2 * sizeof(int32_t) * (size_t)slots, &pe);
+    if (rc != GP_OK) return rc;
+    gp::CompactBuffers cb = compact_buffers(m, nullptr);
+    cb.esc = static_cast<int32_t *>(pe);
+    cb.esc_mask = slots - 1;
+    hipStream_t s = c->stream;
+    if (gp::launch_compact_escapes(cb, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+        (void)hipGetLastError();
         (void)hipStreamSynchronize(s);
-        c->pool.release(p8);
-        c->pool.release(p16);
         c->pool.release(pe);
-        return rc;
+        return GP_EHIP;
     }
-    m->nesc = *host;
+    m->nesc = nesc;
     c->pool.release(m->org);
     c->pool.release(m->twin);
     m->org = m->twin = nullptr;
-    m->org8 = cb.org8;
-    m->twin16 = cb.twin16;
     m->esc = cb.esc;
     m->esc_mask = cb.esc_mask;
     m->bytes = align_up(sizeof(int2) * (size_t)std::max(m->nv, 1)) +
@@ -743,7 +766,11 @@ int build_small_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *
                 m->nflipped = cnt[10];
                 m->bytes = align_up(sizeof(int2) * (size_t)std::max(m->nv, 1)) +
                            2 * align_up(sizeof(int32_t) * (size_t)std::max<int64_t>(3ll * m->nt, 1));
-                if (flags & GP_COMPACT) st = compact_mesh(c, m, reinterpret_cast<int32_t *>(down) + (size_t)gp::kJobCounts * i);
+                if (flags & GP_COMPACT) {
+                    int32_t *nesc = reinterpret_cast<int32_t *>(down) + (size_t)gp::kJobCounts * i;
+                    st = compact_encode(c, m, nesc);
+                    if (st == GP_OK) st = compact_finish(c, m, *nesc);
+                }
             }
         }
         status[i] = st;
@@ -836,7 +863,10 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
         if (j.rc == GP_OK) j.rc = build_finish(c, j);
     if (flags & GP_COMPACT)
         for (BuildJob &j : jobs)
-            if (j.rc == GP_OK) j.rc = compact_mesh(c, j.m, &j.report->nflipped);
+            if (j.rc == GP_OK) {
+                if (!j.encoded || j.report->nbig > 0) j.rc = compact_encode(c, j.m, &j.report->nesc);
+                if (j.rc == GP_OK) j.rc = compact_finish(c, j.m, j.report->nesc);
+            }
     // a failed job's memory goes back after the stream has drained its work
     // (as do the renumbered inputs, which the builds have finished reading)
     bool failed = false;
