@@ -62,6 +62,8 @@ struct MeshDesc {
     const int2 *org8;
     const int16_t *twin16;
     const int32_t *esc;  // (key, value) pairs: key h for a twin, ~h for corner h
+    MeshCounters *ctr_out;   // coherent host memory the counts are written to, or null.  The tiled
+                             // chain leaves err there alone unless it is set, so the host clears it first.
 };
 
 static_assert(sizeof(MeshDesc) % 4 == 0, "descriptor tables are copied in 4-byte words");
@@ -162,15 +164,17 @@ extern const char *const kKernelNames[K_COUNT];
 // Per-kernel hooks so the runtime can bracket launches with events.
 typedef void (*launch_hook)(void *user, int kernel_id, int after);
 
+// one: the descriptor of a run of one mesh, passed to the first kernel, which
+// writes it to rb.descs (null: the table is there already).
 hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream_t s,
-                           launch_hook hook, void *user);
+                           launch_hook hook, void *user, const MeshDesc *one);
 // Whether meshes of at most max_nt triangles fit k_small, and whether a run
 // of rb goes through it (one launch) instead of the chain.
 bool small_fits(const LaunchCfg &cfg, int max_nt);
 bool runs_small(const LaunchCfg &cfg, const RunBuffers &rb);
 // One small mesh on its own: its descriptor as a kernel argument (d.ctr may
-// be null) and its counts written to coherent host memory.
-hipError_t launch_small_one(const MeshDesc &d, MeshCounters *host, hipStream_t s);
+// be null).
+hipError_t launch_small_one(const MeshDesc &d, hipStream_t s);
 // Lets k_small use the current device's LDS per workgroup (lds_block bytes,
 // less its own static LDS); returns the dynamic LDS bytes it may then ask for
 // (0: none).  Once per device, before its first launch.
@@ -180,9 +184,6 @@ int prepare_small(int lds_block);
 // be coherent pinned host memory.
 hipError_t launch_copy_words(void *dst, const void *src, size_t bytes, hipStream_t s);
 
-// Writes one descriptor into device memory with a kernel (its value travels
-// as a kernel argument), so no host staging buffer is needed.
-hipError_t launch_put_desc(const MeshDesc &d, MeshDesc *dst, hipStream_t s);
 // Writes the counts of mesh counters c as 8 int32: status (0 or -10), npoly,
 // nloop, ntips, nmiddle, nties, 0, 0.
 hipError_t launch_export_counts(const MeshCounters *c, int32_t *out, hipStream_t s);

@@ -36,6 +36,8 @@
 //   bit  6    the repair split the polygon whose seed this triangle holds
 //   bit  7    from k_label to k_relink: the longest edge is tied; in k_walk: a
 //             loop of a split polygon whose minimum lies here has been counted
+#include <type_traits>
+
 #include "gp_internal.h"
 
 namespace gp {
@@ -302,8 +304,15 @@ struct ClearArgs {
 // sets it, k_relink counts it and writes the byte back without it).
 constexpr uint32_t kTieBit = 1u << 7;
 
-template <int ITEMS>
-__global__ void __launch_bounds__(1024) k_label(const MeshDesc *__restrict__ descs, int nmesh, ClearArgs ca) {
+//
+// VALUE: one mesh, its descriptor passed by value; the first thread writes it
+// where the kernels that follow read it.  (Staged by a launch of its own it cost
+// a call 4 us.)
+struct NoDesc {};
+template <int ITEMS, bool VALUE>
+__global__ void __launch_bounds__(1024) k_label(const MeshDesc *__restrict__ descs, int nmesh, ClearArgs ca,
+                                                MeshDesc *desc_out,
+                                                const std::conditional_t<VALUE, MeshDesc, NoDesc> one) {
     // the run's counters, list sizes and per-tile totals start at zero for
     // the kernels that follow (nothing in this kernel counts into them)
     {
@@ -316,13 +325,19 @@ __global__ void __launch_bounds__(1024) k_label(const MeshDesc *__restrict__ des
             ca.emit_counts[gid * kStripePad] = 0;
             ca.wbuf_counts[gid * kStripePad] = 0;
         }
+        if constexpr (VALUE)
+            if (gid == 0) *desc_out = one;
     }
     extern __shared__ int4 lds_raw[];
     int *s_org = reinterpret_cast<int *>(lds_raw);
     const int B = blockDim.x, tid = threadIdx.x;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int mi = find_mesh<0>(descs, nmesh, tile);
-    const MeshDesc &d = descs[mi];
+    const MeshDesc &d = [&]() -> const MeshDesc & {
+        if constexpr (VALUE)
+            return one;
+        else
+            return descs[find_mesh<0>(descs, nmesh, tile)];
+    }();
     const int nt = d.nt;
     const int base = (tile - d.tri_tile0) * B * ITEMS;
     const gcv2i xy = (gcv2i)(d.xy);
@@ -1229,7 +1244,24 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
 // a loop of len half-edges takes about len / 2 dependent steps.
 template <int ITEMS, bool ONE>
 __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs, const EmitEntry *emit,
-                                              const int32_t *emit_counts, int emit_cap) {
+                                              const int32_t *emit_counts, int emit_cap, int nmesh) {
+    // the counts are complete but for errors found here
+    if (blockIdx.x == 0)
+        for (int m = threadIdx.x; m < nmesh; m += blockDim.x) {
+            const MeshDesc &d = descs[m];
+            if (!d.ctr_out) continue;
+            const MeshCounters c = *d.ctr;
+            d.ctr_out->ntips = c.ntips;
+            d.ctr_out->nmiddle = c.nmiddle;
+            d.ctr_out->nties = c.nties;
+            d.ctr_out->npoly = c.npoly;
+            d.ctr_out->nloop = c.nloop;
+            if (c.err) d.ctr_out->err = c.err;
+        }
+    const auto corrupt = [](const MeshDesc &d) {
+        atomicOr(&d.ctr->err, kErrCorrupt);
+        if (d.ctr_out) d.ctr_out->err = kErrCorrupt;
+    };
     __shared__ int s_pref[kStripes + 1];
     const int total = striped_prefix(emit_counts, emit_cap, s_pref);
     const int nthreads = gridDim.x * blockDim.x;
@@ -1252,7 +1284,7 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
             // k_compact left the loop's length in its first slot
             const int L = (e.off >= 0 && e.off < 3 * d.nt) ? ((gcint)d.loop_he)[e.off] : -1;
             if (L < 1 || (long long)e.off + L > 3ll * d.nt) {
-                atomicOr(&d.ctr->err, kErrCorrupt);
+                corrupt(d);
                 continue;
             }
             nx[j] = (gcint)d.next_o;
@@ -1275,7 +1307,7 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
                 }
                 const int nf = nx[j][f[j]], nb = pv[j][b[j]];   // both in flight together
                 if (nf < 0 || nb < 0) {
-                    atomicOr(&descs[ONE ? 0 : mesh[j]].ctr->err, kErrCorrupt);
+                    corrupt(descs[ONE ? 0 : mesh[j]]);
                     live[j] = false;
                     continue;
                 }
@@ -1684,16 +1716,16 @@ __device__ __forceinline__ void small_load(const MeshDesc &d, SmallTris<TI> &tr)
     }
 }
 
-// The counts of a run go to the mesh's device counters and, for a run
-// launched on its own, straight to the caller's coherent host copy.
-__device__ __forceinline__ void small_counts(const MeshDesc &d, MeshCounters *host, const MeshCounters &c) {
+// The counts of a run go to the mesh's device counters and to the host's
+// coherent copy, where there are such.
+__device__ __forceinline__ void small_counts(const MeshDesc &d, const MeshCounters &c) {
     if (d.ctr) *d.ctr = c;
-    if (host) *host = c;
+    if (d.ctr_out) *d.ctr_out = c;
 }
 
 // TI: triangles per thread (1, 2 or 4).
 template <int TI>
-__device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host, const SmallTris<TI> &tr) {
+__device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI> &tr) {
     extern __shared__ int4 lds_raw[];
     __shared__ int s_scan[72];
     __shared__ int s_cnt[5];   // tied maxima, tips, new middle edges, frontier half-edges, seeds
@@ -1754,7 +1786,7 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host
         if (tid == 0) {
             MeshCounters c{};
             c.err = kErrCorrupt;
-            small_counts(d, host, c);
+            small_counts(d, c);
         }
         return;
     }
@@ -1937,7 +1969,7 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host
         if (tid == 0) {
             MeshCounters c{};
             c.err = kErrCorrupt;
-            small_counts(d, host, c);
+            small_counts(d, c);
         }
         return;
     }
@@ -2040,37 +2072,37 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, MeshCounters *host
         c.nmiddle = s_cnt[2];
         c.npoly = tc;
         c.nloop = ts;
-        small_counts(d, host, c);
+        small_counts(d, c);
     }
 }
 
 template <int TI>
-__device__ __forceinline__ void small_mesh(const MeshDesc &d, MeshCounters *host) {
+__device__ __forceinline__ void small_mesh(const MeshDesc &d) {
     if (d.nt <= 0 || d.nt > TI * kSmallBlock) {   // (uniform) an empty mesh; larger ones are never launched here
         if (threadIdx.x == 0) {
             MeshCounters c{};
             c.err = d.nt != 0 ? kErrCorrupt : 0;
-            small_counts(d, host, c);
+            small_counts(d, c);
             if (d.nt == 0) d.loop_off[0] = 0;
         }
         return;
     }
     SmallTris<TI> tr;
     small_load(d, tr);
-    small_body(d, host, tr);
+    small_body(d, tr);
 }
 
 // a batch of small meshes: one workgroup per descriptor
 template <int TI>
 __global__ void __launch_bounds__(kSmallBlock) k_small(const MeshDesc *__restrict__ descs) {
-    small_mesh<TI>(descs[blockIdx.x], nullptr);
+    small_mesh<TI>(descs[blockIdx.x]);
 }
 
 // one small mesh, its descriptor passed by value and its counts written to
 // host memory: a call that needs nothing staged before it or copied after it
 template <int TI>
-__global__ void __launch_bounds__(kSmallBlock) k_small_one(const MeshDesc d, MeshCounters *host) {
-    small_mesh<TI>(d, host);
+__global__ void __launch_bounds__(kSmallBlock) k_small_one(const MeshDesc d) {
+    small_mesh<TI>(d);
 }
 
 // ---------------------------------------------------------------------------
@@ -2257,7 +2289,7 @@ __device__ __forceinline__ void small_job(const SmallJob &jd) {
         }
         return;
     }
-    small_body(d, nullptr, tr);
+    small_body(d, tr);
 }
 
 template <int TI>
@@ -2316,15 +2348,6 @@ hipError_t launch_copy_words(void *dst, const void *src, size_t bytes, hipStream
     return hipGetLastError();
 }
 
-__global__ void k_put_desc(MeshDesc d, MeshDesc *dst) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = d;
-}
-
-hipError_t launch_put_desc(const MeshDesc &d, MeshDesc *dst, hipStream_t s) {
-    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, d, dst);
-    return hipGetLastError();
-}
-
 __global__ void k_export_counts(const MeshCounters *c, int32_t *out) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         const MeshCounters k = *c;
@@ -2348,16 +2371,19 @@ hipError_t launch_export_counts(const MeshCounters *c, int32_t *out, hipStream_t
 // host launch of the whole chain
 // ---------------------------------------------------------------------------
 
-#define GP_LAUNCH_ITEMS(KER, ITEMS_RT, GRID, BLOCK, LDS, STREAM, ...)                            \
-    do {                                                                                      \
-        switch (ITEMS_RT) {                                                                   \
-            case 1: hipLaunchKernelGGL(KER<1>, GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break; \
-            case 2: hipLaunchKernelGGL(KER<2>, GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break; \
-            case 4: hipLaunchKernelGGL(KER<4>, GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break; \
-            case 8: hipLaunchKernelGGL(KER<8>, GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break; \
-            default: return hipErrorInvalidValue;                                             \
-        }                                                                                     \
+#define GP_LAUNCH_ITEMS(KER, ITEMS_RT, GRID, BLOCK, LDS, STREAM, ...)                          \
+    do {                                                                                       \
+        switch (ITEMS_RT) {                                                                    \
+            case 1: hipLaunchKernelGGL(KER(1), GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break;  \
+            case 2: hipLaunchKernelGGL(KER(2), GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break;  \
+            case 4: hipLaunchKernelGGL(KER(4), GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break;  \
+            case 8: hipLaunchKernelGGL(KER(8), GRID, BLOCK, LDS, STREAM, __VA_ARGS__); break;  \
+            default: return hipErrorInvalidValue;                                              \
+        }                                                                                      \
     } while (0)
+#define GP_LABEL(I) HIP_KERNEL_NAME(k_label<I, false>)
+#define GP_LABEL_ONE(I) HIP_KERNEL_NAME(k_label<I, true>)
+#define GP_COMPACT(I) HIP_KERNEL_NAME(k_compact<I>)
 
 template <bool CM, bool NT>
 hipError_t launch_relink_nt(const LaunchCfg &cfg, const RunBuffers &rb, hipStream_t s, size_t lds, int cmp_tb) {
@@ -2393,15 +2419,15 @@ bool small_fits(const LaunchCfg &cfg, int max_nt) {
 
 bool runs_small(const LaunchCfg &cfg, const RunBuffers &rb) { return !rb.chain_only && small_fits(cfg, rb.max_nt); }
 
-hipError_t launch_small_one(const MeshDesc &d, MeshCounters *host, hipStream_t s) {
+hipError_t launch_small_one(const MeshDesc &d, hipStream_t s) {
     const dim3 grid(1), block(kSmallBlock);
     const size_t lds = small_lds_bytes(d.nt);
     if (d.nt <= kSmallBlock)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<1>), grid, block, lds, s, d, host);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<1>), grid, block, lds, s, d);
     else if (d.nt <= 2 * kSmallBlock)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<2>), grid, block, lds, s, d, host);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<2>), grid, block, lds, s, d);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<4>), grid, block, lds, s, d, host);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_one<4>), grid, block, lds, s, d);
     return hipGetLastError();
 }
 
@@ -2439,7 +2465,7 @@ int prepare_small(int lds_block) {
 }
 
 hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream_t s, launch_hook hook,
-                           void *user) {
+                           void *user, const MeshDesc *one_desc) {
     auto H = [&](int k, int after) {
         if (hook) hook(user, k, after);
     };
@@ -2448,7 +2474,10 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
         const dim3 grid(rb.nmesh), block(kSmallBlock);
         const size_t lds = small_lds_bytes(rb.max_nt);
         H(K_SMALL, 0);
-        if (rb.max_nt <= kSmallBlock)
+        if (one_desc) {
+            const hipError_t e = launch_small_one(*one_desc, s);
+            if (e != hipSuccess) return e;
+        } else if (rb.max_nt <= kSmallBlock)
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<1>), grid, block, lds, s, rb.descs);
         else if (rb.max_nt <= 2 * kSmallBlock)
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small<2>), grid, block, lds, s, rb.descs);
@@ -2467,8 +2496,13 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
     {
         const ClearArgs ca = {rb.ctrs, rb.status, rb.cmp_tiles, rb.tip_counts, rb.walk_counts, rb.emit_counts,
                               rb.wbuf_counts};
-        GP_LAUNCH_ITEMS(k_label, cfg.items_label, dim3(rb.tri_tiles), dim3(cfg.block_label),
-                        sizeof(int) * 3 * (size_t)cfg.block_label * cfg.items_label, s, rb.descs, rb.nmesh, ca);
+        const dim3 grid(rb.tri_tiles), block(cfg.block_label);
+        const size_t lds = sizeof(int) * 3 * (size_t)cfg.block_label * cfg.items_label;
+        MeshDesc *const out = const_cast<MeshDesc *>(rb.descs);
+        if (one_desc)
+            GP_LAUNCH_ITEMS(GP_LABEL_ONE, cfg.items_label, grid, block, lds, s, rb.descs, rb.nmesh, ca, out, *one_desc);
+        else
+            GP_LAUNCH_ITEMS(GP_LABEL, cfg.items_label, grid, block, lds, s, rb.descs, rb.nmesh, ca, out, NoDesc{});
     }
     H(K_LABEL, 1);
 
@@ -2502,13 +2536,14 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
     H(K_TSCAN, 1);
 
     H(K_COMPACT, 0);
-    GP_LAUNCH_ITEMS(k_compact, cfg.items_compact, dim3(rb.cmp_tiles), dim3(cfg.block_compact),
+    GP_LAUNCH_ITEMS(GP_COMPACT, cfg.items_compact, dim3(rb.cmp_tiles), dim3(cfg.block_compact),
                     compact_lds_bytes(cmp_tb), s, rb.descs, rb.nmesh,
                     rb.status, rb.cpre, rb.emit, rb.emit_counts, rb.emit_cap, rb.wbuf);
     H(K_COMPACT, 1);
 
     H(K_EMIT, 0);
-    hipLaunchKernelGGL((one ? k_emit<4, true> : k_emit<4, false>), dim3(pb), dim3(256), 0, s, rb.descs, rb.emit, rb.emit_counts, rb.emit_cap);
+    hipLaunchKernelGGL((one ? k_emit<4, true> : k_emit<4, false>), dim3(pb), dim3(256), 0, s, rb.descs, rb.emit,
+                       rb.emit_counts, rb.emit_cap, rb.nmesh);
     H(K_EMIT, 1);
     return hipGetLastError();
 }

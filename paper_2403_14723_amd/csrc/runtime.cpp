@@ -983,7 +983,7 @@ int graph_entry(gp_ctx *c, const Plan &plan, GraphEntry **out) {
         c->pool.release(e.scratch);
         return GP_EHIP;
     }
-    hipError_t le = gp::launch_pipeline(c->cfg, e.rb, s, nullptr, nullptr);
+    hipError_t le = gp::launch_pipeline(c->cfg, e.rb, s, nullptr, nullptr, nullptr);
     hipError_t ce = hipStreamEndCapture(s, &graph);
     if (le != hipSuccess || ce != hipSuccess || !graph ||
         hipGraphInstantiate(&e.exec, graph, nullptr, nullptr, 0) != hipSuccess) {
@@ -1520,6 +1520,8 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
         d.pl = pl[i];
         d.lpos = lpos[i];
         d.ctr = small_one ? nullptr : rb.ctrs + i;
+        d.ctr_out = r->host_ctrs + i;
+        r->host_ctrs[i].err = 0;
     }
     hipStream_t s = c->stream;
     int err = GP_OK;
@@ -1529,7 +1531,8 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
     const size_t dbytes = sizeof(gp::MeshDesc) * n;
     const bool same = ge && ge->staged.size() == descs.size() &&
                       std::memcmp(ge->staged.data(), descs.data(), dbytes) == 0;
-    if (!same && !small_one) {
+    const bool by_value = n == 1 && !ge;   // one mesh: its descriptor is a kernel argument
+    if (!same && !by_value) {
         if (stage_to_device(c, const_cast<gp::MeshDesc *>(rb.descs), descs.data(), dbytes) != hipSuccess)
             err = GP_EHIP;
         else if (ge)
@@ -1565,15 +1568,13 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
         }
     }
     if (err == GP_OK) {
-        hipError_t e = small_one ? gp::launch_small_one(descs[0], r->host_ctrs, s)
+        const gp::MeshDesc *one = by_value ? descs.data() : nullptr;
+        hipError_t e = small_one ? gp::launch_small_one(descs[0], s)
                        : ge      ? hipGraphLaunch(ge->exec, s)
-                       : c->debug ? gp::launch_pipeline(c->cfg, rb, s, debug_hook, &dh)
-                                  : gp::launch_pipeline(c->cfg, rb, s, c->profile ? profile_hook : nullptr, c);
+                       : c->debug ? gp::launch_pipeline(c->cfg, rb, s, debug_hook, &dh, one)
+                                  : gp::launch_pipeline(c->cfg, rb, s, c->profile ? profile_hook : nullptr, c, one);
         if (e != hipSuccess) err = GP_EHIP;
     }
-    if (err == GP_OK && !small_one &&
-        gp::launch_copy_words(r->host_ctrs, rb.ctrs, sizeof(gp::MeshCounters) * n, s) != hipSuccess)
-        err = GP_EHIP;
     if (err == GP_OK && hipEventRecord(r->done, s) != hipSuccess) err = GP_EHIP;
     // per-call temporaries go back to the pool; later users are ordered after
     // this run on the same stream
@@ -1646,8 +1647,8 @@ int gpolylla_mesh_noalloc(gp_ctx *c, const gp_mesh *m, const gp_result_dev *out,
     hipStream_t s = c->stream;
     // every counter and list the kernels use is cleared by the chain itself
     // (no memset node, so the call can be captured into a graph)
-    if (gp::launch_put_desc(d, const_cast<gp::MeshDesc *>(rb.descs), s) != hipSuccess ||
-        gp::launch_pipeline(c->cfg, rb, s, nullptr, nullptr) != hipSuccess ||
+    d.ctr_out = nullptr;
+    if (gp::launch_pipeline(c->cfg, rb, s, nullptr, nullptr, &d) != hipSuccess ||
         gp::launch_export_counts(rb.ctrs, reinterpret_cast<int32_t *>(counts), s) != hipSuccess) {
         (void)hipGetLastError();
         return GP_EHIP;
