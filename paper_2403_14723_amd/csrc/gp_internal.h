@@ -73,7 +73,8 @@ struct ListEntry {
     int32_t he;
 };
 
-// a loop whose half-edges k_emit writes: minimum mn, first output slot off
+// a loop whose half-edges k_emit writes: minimum mn (complemented when k_walk
+// kept them in its pool), first output slot off
 struct EmitEntry {
     int32_t mesh;
     int32_t mn;

@@ -1104,7 +1104,13 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // visits to an LDS buffer (forward ones from the front, backward ones from
 // the back), so a loop of at most BUF half-edges is copied to the scratch pool
 // (rotation index of the minimum, then the half-edges in loop order from the
-// first backward one) and k_compact places it without walking it again.
+// first backward one) and k_compact places it without walking it again.  A
+// chain that outgrows the buffer takes kLongWords of the pool and goes on
+// there, forward half-edges from the front and backward ones from the back, so
+// that k_emit copies a loop of fewer than kPlMax half-edges instead of walking
+// it again (its chain of dependent steps took 22 us for the longest loops of
+// the 1M-point Delaunay mesh; the copies take 6, and this kernel 37 instead of
+// 33).
 //
 // Whole waves iterate together, with nothing but the two loads in a step.  What
 // bounds the kernel is its device-scope atomics: one per wave for the pool, one
@@ -1113,6 +1119,8 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // settled in the step in which it closed, the 1M-point Delaunay mesh (280,000
 // loops) took 61 us.
 constexpr int kWalkBoth = 8;
+constexpr int kLongHead = 4, kLongMax = 64, kLongWords = kLongHead + kLongMax, kNotTried = -2;
+static_assert(kPlMax <= kLongMax, "every loop whose code holds its length fits");
 
 // ONE (here and in the other list-driven kernels): a run of one mesh, whose
 // descriptor is read once, uniformly, and not per entry.
@@ -1137,6 +1145,7 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
         // end bc (bb taken before the start; the start itself while bb == 0);
         // the minimum so far and where: forward index, or ~backward index
         int mesh = 0, fc = -1, bc = -1, fa = 0, bb = 0, mn = -1, mpos = 0, lim = 0;
+        int far = kNotTried;   // the chain's place in the pool, or -1
         bool live = false, closed = false, repair = false;
         if (b0 + tid < total) {
             const ListEntry e = walk[striped_index(s_pref, walk_cap, b0 + tid)];
@@ -1163,12 +1172,23 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
         }
         while (__any(live)) {
             if (!live) continue;
-            const bool two = fa >= both;
+            if (far == kNotTried && fa + bb > BUF - 2) {   // the buffer may be full after this step
+                const int at = atomicAdd(&wbuf_counts[wstripe * kStripePad], kLongWords);
+                far = at + kLongWords <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
+                if (far >= 0) {
+                    const gint out = (gint)wbuf + far + kLongHead;
+                    for (int k = 0; k < fa; k++) out[k] = s_buf[k * kSlots + tid];
+                    for (int k = 0; k < bb; k++) out[kLongMax - 1 - k] = s_buf[(BUF - 1 - k) * kSlots + tid];
+                }
+            }
+            const bool two = fa >= both, keep = far >= 0 && fa + bb < kLongMax - 1;
+            const gint out = (gint)wbuf + (keep ? far + kLongHead : 0);
             const int nf = nx[fc], nb = two ? pv[bc] : 0;
             bool done = nf == bc;   // the forward end reached the backward one
             if (!done && nf >= 0) {
                 fc = nf;
                 if (fa < BUF) s_buf[fa * kSlots + tid] = nf;
+                if (keep) out[fa] = nf;
                 if (nf < mn) {
                     mn = nf;
                     mpos = fa;
@@ -1178,6 +1198,7 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
                 if (two && !done && nb >= 0) {
                     bc = nb;
                     if (bb < BUF) s_buf[(BUF - 1 - bb) * kSlots + tid] = nb;
+                    if (keep) out[kLongMax - 1 - bb] = nb;
                     if (nb < mn) {
                         mn = nb;
                         mpos = ~bb;
@@ -1209,7 +1230,12 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
             ((gu8)d.pl)[tm] = loop_code(mn, len);
             // where the loop is stored (-1: nowhere), or its length when the
             // code does not hold it
-            if (len <= BUF || len >= kPlMax) ((gint)d.lpos)[tm] = len >= kPlMax ? len : pos;
+            ((gint)d.lpos)[tm] = len >= kPlMax ? len : len <= BUF ? pos : far;
+            if (len > BUF && len < kPlMax && far >= 0) {
+                // forward half-edges, and the minimum's position from the start
+                ((gint)wbuf)[far] = fa;
+                ((gint)wbuf)[far + 1] = mpos >= 0 ? mpos : len - 1 - ~mpos;
+            }
             if (need && pos >= 0) {
                 // position of the minimum in loop order from the first backward
                 // half-edge; then the backward half-edges (from the back of the
@@ -1244,7 +1270,8 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
 // a loop of len half-edges takes about len / 2 dependent steps.
 template <int ITEMS, bool ONE>
 __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs, const EmitEntry *emit,
-                                              const int32_t *emit_counts, int emit_cap, int nmesh) {
+                                              const int32_t *emit_counts, int emit_cap, const int32_t *wbuf,
+                                              int wbuf_cap, int nmesh) {
     // the counts are complete but for errors found here
     if (blockIdx.x == 0)
         for (int m = threadIdx.x; m < nmesh; m += blockDim.x) {
@@ -1265,6 +1292,40 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
     __shared__ int s_pref[kStripes + 1];
     const int total = striped_prefix(emit_counts, emit_cap, s_pref);
     const int nthreads = gridDim.x * blockDim.x;
+    // loops that k_walk kept: kCopyLanes lanes copy one, from its minimum on
+    constexpr int kCopyLanes = 16;
+    const int sub = threadIdx.x % kCopyLanes;
+    for (int g = (blockIdx.x * blockDim.x + threadIdx.x) / kCopyLanes; g < total; g += nthreads / kCopyLanes) {
+        const EmitEntry e = emit[striped_index(s_pref, emit_cap, g)];
+        if (e.mn >= 0) continue;
+        const MeshDesc &d = descs[ONE ? 0 : e.mesh];
+        // (its lanes, all of one wave, read these before any of them writes)
+        const bool in = e.off >= 0 && e.off < 3 * d.nt - 1;
+        const int L = in ? ((gcint)d.loop_he)[e.off] : -1, pos = in ? ((gcint)d.loop_he)[e.off + 1] : -1;
+        const bool ok = L > 0 && L < kPlMax && (long long)e.off + L <= 3ll * d.nt && pos >= 0 &&
+                        pos <= kStripes * wbuf_cap - kLongWords;
+        const gcint src = (gcint)wbuf + (ok ? pos : 0);
+        const int fore = src[0], rot = src[1];
+        if (!ok || fore < 1 || fore > L || rot < 0 || rot >= L) {
+            if (sub == 0) corrupt(d);
+            continue;
+        }
+        int v[kLongMax / kCopyLanes];
+#pragma unroll
+        for (int j = 0; j < kLongMax / kCopyLanes; j++) {
+            const int k = sub + j * kCopyLanes;
+            v[j] = src[kLongHead + (k < fore ? k : min(k + kLongMax - L, kLongMax - 1))];
+        }
+        const gint out = (gint)d.loop_he + e.off;
+#pragma unroll
+        for (int j = 0; j < kLongMax / kCopyLanes; j++) {
+            const int k = sub + j * kCopyLanes;
+            if (k >= L) continue;
+            if (k == rot && v[j] != ~e.mn) corrupt(d);
+            out[k >= rot ? k - rot : k - rot + L] = v[j];
+        }
+    }
+    // the others: walked again, from both ends
     for (int g0 = blockIdx.x * blockDim.x + threadIdx.x; g0 < total; g0 += nthreads * ITEMS) {
         gcint nx[ITEMS], pv[ITEMS];
         gint out[ITEMS];
@@ -1279,6 +1340,7 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
             const int g = g0 + j * nthreads;
             if (g >= total) continue;
             const EmitEntry e = emit[striped_index(s_pref, emit_cap, g)];
+            if (e.mn < 0) continue;
             const MeshDesc &d = descs[ONE ? 0 : e.mesh];
             mesh[j] = ONE ? 0 : e.mesh;
             // k_compact left the loop's length in its first slot
@@ -1593,12 +1655,13 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
             } else if (defer[j]) {
                 if (e < elim) {
                     emit[e].mesh = mi;
-                    emit[e].mn = mn;
+                    emit[e].mn = lens[j] > kWalkBuf && lens[j] < kPlMax && lp[j] >= 0 ? ~mn : mn;
                     emit[e].off = ps + off;
                 }
-                // the loop's length in its own first slot, which k_emit reads
-                // and then overwrites with the minimum
+                // the loop's length and place in the walk pool in its own
+                // first slots, which k_emit reads and then overwrites
                 he_out[off] = lens[j];
+                if (lens[j] > 1) he_out[off + 1] = lp[j];
                 ++e;
             }
         }
@@ -2543,7 +2606,7 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
 
     H(K_EMIT, 0);
     hipLaunchKernelGGL((one ? k_emit<4, true> : k_emit<4, false>), dim3(pb), dim3(256), 0, s, rb.descs, rb.emit,
-                       rb.emit_counts, rb.emit_cap, rb.nmesh);
+                       rb.emit_counts, rb.emit_cap, rb.wbuf, rb.wbuf_cap, rb.nmesh);
     H(K_EMIT, 1);
     return hipGetLastError();
 }
