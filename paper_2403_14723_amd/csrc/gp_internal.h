@@ -266,6 +266,8 @@ struct BuildBuffers {
     int32_t *nflipped;
     int32_t *nbig;          // large groups, left to launch_build_large
     int32_t *total, *ntasks;   // its list entries and classes
+    uint64_t *zero;         // all of these counters and the groups', cleared first
+    size_t zero_bytes;      // (a multiple of 8)
 };
 
 hipError_t launch_build(const BuildBuffers &b, hipStream_t s);

@@ -488,6 +488,8 @@ int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, in
     b.flips = reinterpret_cast<int32_t *>(zero + kBuildFlipsAt);
     b.count = reinterpret_cast<int32_t *>(zero + kBuildZeroBytes);
     b.cursor = b.count + b.nparts;
+    b.zero = reinterpret_cast<uint64_t *>(zero);
+    b.zero_bytes = zero_bytes;
     b.list = a.take<uint32_t>(z.list);
     b.tasks = a.take<gp::ClassTask>(z.tasks);
     int32_t *tri_dev = in_dev ? nullptr : a.take<int32_t>(nh);
@@ -499,7 +501,7 @@ int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, in
          hipMemcpyAsync(m->xy, xy, sizeof(int2) * (size_t)nv, hipMemcpyHostToDevice, s) != hipSuccess) ||
         (!in_dev && nt > 0 &&
          hipMemcpyAsync(tri_dev, tri, sizeof(int32_t) * (size_t)nh, hipMemcpyHostToDevice, s) != hipSuccess) ||
-        hipMemsetAsync(zero, 0, zero_bytes, s) != hipSuccess || gp::launch_build(b, s) != hipSuccess ||
+        gp::launch_build(b, s) != hipSuccess ||
         ((flags & GP_COMPACT) && (j.encoded = compact_alloc(c, m) == GP_OK) &&
          gp::launch_compact_encode(compact_buffers(m, &rep->nesc), s) != hipSuccess) ||
         gp::launch_copy_words(j.report, rep, sizeof(BuildReport), s) != hipSuccess) {
