@@ -300,6 +300,7 @@ struct gprt::JobCrew {
     std::mutex mu;
     std::condition_variable cv;
     bool quit = false;
+    bool alone = false;   // the caller's thread unpacks every group, in order
     gp_job *jobs = nullptr;
     std::deque<SmallGroup> live;   // started groups, oldest first (its elements stay where they are)
     size_t started = 0, taken = 0, done = 0, freed = 0;   // groups so far, in order
@@ -318,8 +319,8 @@ struct gprt::JobCrew {
         (void)hipSetDevice(device);
         std::unique_lock<std::mutex> lk(mu);
         while (true) {
-            cv.wait(lk, [&]() { return taken < started || quit; });
-            if (taken == started) return;
+            cv.wait(lk, [&]() { return (taken < started && !alone) || quit; });
+            if (quit) return;
             unpack_one(lk);
         }
     }
@@ -361,7 +362,37 @@ void gprt::job_crew_free(gp_ctx *c) {
 
 namespace {
 
-// Runs a list of small jobs in groups of up to `budget` triangles.
+// Whether no two jobs share an output array (by what each may write).
+bool outputs_apart(const gp_job *jobs, int n) {
+    struct Range {
+        const int32_t *at;
+        size_t ints;
+    };
+    std::vector<Range> r;
+    const auto apart = [&](auto range) {
+        r.clear();
+        bool sorted = true;
+        for (int k = 0; k < n; k++) {
+            const Range x = range(jobs[k]);
+            if (!x.at || !x.ints) continue;
+            sorted &= r.empty() || r.back().at < x.at;
+            r.push_back(x);
+        }
+        if (!sorted) std::sort(r.begin(), r.end(), [](const Range &a, const Range &b) { return a.at < b.at; });
+        for (size_t k = 1; k < r.size(); k++)
+            if (r[k - 1].at + r[k - 1].ints > r[k].at) return false;
+        return true;
+    };
+    return apart([](const gp_job &j) { return Range{j.next, 3 * (size_t)j.nt}; }) &&
+           apart([](const gp_job &j) { return Range{j.prev, 3 * (size_t)j.nt}; }) &&
+           apart([](const gp_job &j) { return Range{j.seeds, (size_t)j.nt}; }) &&
+           apart([](const gp_job &j) { return Range{j.loop_off, (size_t)j.nt + 1}; }) &&
+           apart([](const gp_job &j) { return Range{j.loop_he, 3 * (size_t)j.nt}; });
+}
+
+// Runs a list of small jobs in groups of up to `budget` triangles.  Jobs that
+// share an output array (a caller may want only the last one's) are unpacked
+// in order, by one thread.
 void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
     JobCrew *crew = c->crew;
     // Every second group goes to a stream of its own, so that one group's inputs
@@ -378,6 +409,11 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
         j0 = g.j1;
         if (k == 0 && j0 < n) {
             if (!crew) crew = c->crew = new (std::nothrow) JobCrew(c->device);
+            if (crew) {
+                const bool alone = !outputs_apart(jobs, n);
+                std::lock_guard<std::mutex> lk(crew->mu);
+                crew->alone = alone;
+            }
             if (crew && crew->second) {
                 if (hipEventRecord(crew->before, c->stream) == hipSuccess &&
                     hipStreamWaitEvent(crew->second, crew->before, 0) == hipSuccess)
@@ -399,7 +435,7 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
         crew->cv.notify_all();
         while (crew->started - crew->done >= kGroupsInFlight) {
             if (crew->taken < crew->started &&
-                (crew->helpers.empty() || crew->started - crew->taken >= kGroupsInFlight - 1))
+                (crew->alone || crew->helpers.empty() || crew->started - crew->taken >= kGroupsInFlight - 1))
                 crew->unpack_one(lk);
             else
                 crew->cv.wait(lk);
