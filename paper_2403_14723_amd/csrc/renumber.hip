@@ -14,14 +14,14 @@
 // puts every key and index into its bucket's list, and one workgroup per
 // bucket sorts its list in LDS and writes the permuted arrays.  Those are five
 // launches for the vertices and triangles together, and the data moves twice:
-// 300,000 vertices and 594,000 triangles take 88 us, where the library's sort
+// 300,000 vertices and 594,000 triangles take 79 us, where the library's sort
 // (block sorts, then merges of pairs of ever longer runs: 38 launches of 4 to
 // 8 us each at these sizes) with separate key and gather passes took 370 us.
 // Larger arrays go to the library, which above a million elements sorts by
 // digits in a fixed number of passes: a sample that cut them into buckets of
 // the size that a workgroup sorts would take longer to rank than it saves.
-// Whole builds with this sort and with the library's: 153 and 399 us with
-// 594,000 triangles, 364 and 801 us with 1,980,000 (the lists then take 250 MB
+// Whole builds with this sort and with the library's: 140 and 399 us with
+// 594,000 triangles, 331 and 801 us with 1,980,000 (the lists then take 250 MB
 // of scratch; when that cannot be had, the library sorts).
 #include <hipcub/hipcub.hpp>
 
@@ -387,9 +387,9 @@ __device__ __forceinline__ bool sort_words(const uint64_t (&key)[E], uint64_t lo
 // words (m + 1 rounds always suffice).  There is no room for those in a bucket
 // of more than kBucketCap: it is reported like a list that overflowed.
 template <bool TRI, int E>
-__device__ __forceinline__ void sort_bucket(const RenumberBuffers &b, const SortPart &p, int m, int first,
-                                            uint64_t *s, uint64_t *s_range) {
-    const int tid = threadIdx.x, bucket = blockIdx.x;
+__device__ __forceinline__ void sort_bucket(const RenumberBuffers &b, const SortPart &p, int bucket, int m,
+                                            int first, uint64_t *s, uint64_t *s_range) {
+    const int tid = threadIdx.x;
     const ListEntryOf<TRI> *list = static_cast<const ListEntryOf<TRI> *>(p.list) + (size_t)bucket * p.cap;
     uint64_t x[E], lo = ~0ull, hi = 0;
 #pragma unroll
@@ -431,8 +431,7 @@ __device__ __forceinline__ void sort_bucket(const RenumberBuffers &b, const Sort
         if constexpr (TRI) {
             b.tperm[k] = e.old;
 #pragma unroll
-            for (int c = 0; c < 3; c++)
-                b.tri_out[3 * (size_t)k + c] = (e.v[c] >= 0 && e.v[c] < b.nv) ? b.vinv[e.v[c]] : e.v[c];
+            for (int c = 0; c < 3; c++) b.tri_out[3 * (size_t)k + c] = e.v[c];   // (renamed by k_rename_corners)
         } else {
             b.vperm[k] = e.old;
             b.vinv[e.old] = k;
@@ -441,39 +440,63 @@ __device__ __forceinline__ void sort_bucket(const RenumberBuffers &b, const Sort
     }
 }
 
-// One workgroup per bucket; it starts where the buckets before it end.  BIG:
-// lists of more than kBucketCap (which need more registers).
+// A workgroup's bucket starts where the buckets before it end.
 template <bool TRI, bool BIG>
-__global__ void __launch_bounds__(kBucketBlock) k_sort_bucket(const RenumberBuffers b, const SortPart p) {
+__device__ __forceinline__ void place_bucket(const RenumberBuffers &b, const SortPart &p, int bucket, uint64_t *s,
+                                             uint64_t *s_range, int *s_first) {
+    const int tid = threadIdx.x;
+    if (tid == 0) *s_first = 0;
+    __syncthreads();
+    int sum = 0;
+    for (int k = tid; k < bucket; k += kBucketBlock) sum += p.cursor[k];
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((tid & 63) == 0 && sum) atomicAdd(s_first, sum);
+    const int m = min(p.cursor[bucket], p.cap);
+    __syncthreads();
+    const int first = *s_first;
+    if (m <= kBucketBlock)
+        sort_bucket<TRI, 1>(b, p, bucket, m, first, s, s_range);
+    else if (m <= 2 * kBucketBlock)
+        sort_bucket<TRI, 2>(b, p, bucket, m, first, s, s_range);
+    else if (m <= 4 * kBucketBlock)
+        sort_bucket<TRI, 4>(b, p, bucket, m, first, s, s_range);
+    else if (m <= 8 * kBucketBlock)
+        sort_bucket<TRI, 8>(b, p, bucket, m, first, s, s_range);
+    else if (!BIG || m <= 16 * kBucketBlock)
+        sort_bucket<TRI, 16>(b, p, bucket, m, first, s, s_range);
+    else if constexpr (BIG)
+        sort_bucket<TRI, 32>(b, p, bucket, m, first, s, s_range);
+}
+
+// One workgroup per bucket, the triangles' first (they are more), the vertices'
+// beside them: the new corner names, which need both, are a pass of their own
+// (7 us for 594,000 triangles; the buckets of both then take 30, where the
+// vertices' took 20 before the triangles' 25).  BIG: lists of more than kBucketCap (which need more
+// registers).
+template <bool BIG>
+__global__ void __launch_bounds__(kBucketBlock) k_sort_bucket(const RenumberBuffers b, const SortPart pv,
+                                                             const SortPart pt) {
     __shared__ uint64_t s[kBucketCap];
     __shared__ uint64_t s_range[2 * (kBucketBlock / 64)];
     __shared__ int s_first;
-    const int tid = threadIdx.x;
     if (*b.overflow) {   // (uniform) a list overflowed: the caller sorts in another way
-        if (blockIdx.x == 0 && tid == 0) *b.overflow_out = 1;
+        if (blockIdx.x == 0 && threadIdx.x == 0) *b.overflow_out = 1;
         return;
     }
-    if (tid == 0) s_first = 0;
-    __syncthreads();
-    int sum = 0;
-    for (int k = tid; k < (int)blockIdx.x; k += kBucketBlock) sum += p.cursor[k];
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if ((tid & 63) == 0 && sum) atomicAdd(&s_first, sum);
-    const int m = min(p.cursor[blockIdx.x], p.cap);
-    __syncthreads();
-    const int first = s_first;
-    if (m <= kBucketBlock)
-        sort_bucket<TRI, 1>(b, p, m, first, s, s_range);
-    else if (m <= 2 * kBucketBlock)
-        sort_bucket<TRI, 2>(b, p, m, first, s, s_range);
-    else if (m <= 4 * kBucketBlock)
-        sort_bucket<TRI, 4>(b, p, m, first, s, s_range);
-    else if (m <= 8 * kBucketBlock)
-        sort_bucket<TRI, 8>(b, p, m, first, s, s_range);
-    else if (!BIG || m <= 16 * kBucketBlock)
-        sort_bucket<TRI, 16>(b, p, m, first, s, s_range);
-    else if constexpr (BIG)
-        sort_bucket<TRI, 32>(b, p, m, first, s, s_range);
+    if ((int)blockIdx.x < pt.buckets)
+        place_bucket<true, BIG>(b, pt, blockIdx.x, s, s_range, &s_first);
+    else
+        place_bucket<false, BIG>(b, pv, blockIdx.x - pt.buckets, s, s_range, &s_first);
+}
+
+// The sorted triangles' corners by their new names (an index outside [0, nv)
+// stays).
+__global__ void __launch_bounds__(256) k_rename_corners(const RenumberBuffers b) {
+    const long long n = 3ll * b.nt;
+    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) {
+        const int w = b.tri_out[i];
+        if (w >= 0 && w < b.nv) b.tri_out[i] = b.vinv[w];
+    }
 }
 
 // The buckets of n elements (0: not sorted here).
@@ -539,10 +562,11 @@ hipError_t launch_renumber(const RenumberBuffers &b, hipStream_t s) {
         hipLaunchKernelGGL(k_sort_rank, dim3(2 * kMaxSamples / 64), dim3(64 * kRankWaves), 0, s, pv, pt);
         hipLaunchKernelGGL(k_sort_place, dim3(vblocks + tblocks), dim3(kPlaceBlock), 0, s, b, pv, pt, vblocks);
     }
-    if (pv.n > 0) {
-        const auto kernel = pv.cap > kBucketCap ? &k_sort_bucket<false, true> : &k_sort_bucket<false, false>;
-        hipLaunchKernelGGL(kernel, dim3(pv.buckets), dim3(kBucketBlock), 0, s, b, pv);
-    } else if (b.nv > 0) {
+    if (pv.n + pt.n > 0) {
+        const auto kernel = pv.cap > kBucketCap || pt.cap > kBucketCap ? &k_sort_bucket<true> : &k_sort_bucket<false>;
+        hipLaunchKernelGGL(kernel, dim3(pv.buckets + pt.buckets), dim3(kBucketBlock), 0, s, b, pv, pt);
+    }
+    if (!own_v && b.nv > 0) {
         hipLaunchKernelGGL(k_vertex_keys, dim3(blocks_for(b.nv)), dim3(256), 0, s, b.xy_in, b.nv, b.keys, b.vals);
         e = hipcub::DeviceRadixSort::SortPairs(b.sort_tmp, tb, b.keys, b.keys_alt, b.vals, b.vperm, b.nv, 0, 62, s);
         if (e != hipSuccess) return e;
@@ -550,8 +574,7 @@ hipError_t launch_renumber(const RenumberBuffers &b, hipStream_t s) {
                            b.xy_out);
     }
     if (pt.n > 0) {
-        const auto kernel = pt.cap > kBucketCap ? &k_sort_bucket<true, true> : &k_sort_bucket<true, false>;
-        hipLaunchKernelGGL(kernel, dim3(pt.buckets), dim3(kBucketBlock), 0, s, b, pt);
+        hipLaunchKernelGGL(k_rename_corners, dim3(blocks_for(3 * b.nt)), dim3(256), 0, s, b);
     } else if (b.nt > 0) {
         hipLaunchKernelGGL(k_triangle_keys, dim3(blocks_for(b.nt)), dim3(256), 0, s, b.xy_in, b.tri_in, b.nv, b.nt,
                            b.keys, b.vals);
