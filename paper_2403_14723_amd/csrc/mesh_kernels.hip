@@ -15,7 +15,8 @@
 //               then next/prev of every frontier half-edge by turning around
 //               its target / origin (Section 6.5, Algorithm 12); barrier tips
 //   k_repair    middle edge at every barrier tip (Section 6.4, Algorithm 11)
-//   k_fixup     next/prev again around both ends of every new frontier edge
+//   k_fixup     next/prev again around both ends of every new frontier edge;
+//               marks the seeds of the polygons that the repair split
 //   k_walk      for every seed k_relink left open and every seed made by the
 //               repair: move to a frontier half-edge of its polygon
 //               (Section 6.5.1, Algorithm 13), walk the loop, and record its
@@ -24,7 +25,7 @@
 //               by k_relink itself.
 //   k_tile_scan exclusive scan of the per-tile loop totals that k_relink and
 //               k_walk accumulate (Section 6.7)
-//   k_compact   writes seeds, loop offsets and the loops of up to four
+//   k_compact   writes seeds, loop offsets and the loops of up to sixteen
 //               half-edges of every tile from its prefix (Section 6.7)
 //   k_emit      writes the longer loops at the offsets k_compact reserved
 //
@@ -1085,7 +1086,10 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // ends from then on: forward along next' and backward along prev' from the
 // start, the two loads of a step in flight together, until the ends meet, so
 // a long loop of len half-edges takes about len / 2 dependent steps (short
-// loops, the most, read no prev').  Each chain also writes the half-edges it
+// loops, the most, read no prev').  A step loads the three links of its triangle
+// and follows the loop until it leaves it, one or two half-edges on (loading one
+// link a step, the kernel took 100 us on the 33.5M grid, this 88; 37 and 35 on
+// the 1M-point Delaunay mesh).  Each chain also writes the half-edges it
 // visits to an LDS buffer (forward ones from the front, backward ones from
 // the back), so a loop of at most BUF half-edges is copied to the scratch pool
 // (rotation index of the minimum, then the half-edges in loop order from the
@@ -1104,18 +1108,19 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // settled in the step in which it closed, the 1M-point Delaunay mesh (280,000
 // loops) took 61 us.
 constexpr int kWalkBoth = 8;
-constexpr int kLongHead = 4, kLongMax = 64, kLongWords = kLongHead + kLongMax, kNotTried = -2;
-static_assert(kPlMax <= kLongMax, "every loop whose code holds its length fits");
+constexpr int kLongHead = 4, kLongMax = 68, kLongWords = kLongHead + kLongMax, kNotTried = -2;
+static_assert(kPlMax - 1 <= kLongMax - 4, "every loop whose code holds its length fits, whatever its last step takes");
 
 // ONE (here and in the other list-driven kernels): a run of one mesh, whose
 // descriptor is read once, uniformly, and not per entry.
 template <int BUF, bool ONE>
-__global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs, const ListEntry *walk,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k_walk(const MeshDesc *__restrict__ descs, const ListEntry *walk,
                                               const int32_t *walk_counts, int walk_cap, uint64_t *agg,
                                               int cmp_tb, int32_t *wbuf, int32_t *wbuf_counts, int wbuf_cap) {
     constexpr int kSlots = 256;
+    constexpr int kHeld = BUF + 3;   // a step takes up to four half-edges
     __shared__ int s_pref[kStripes + 1];
-    __shared__ int s_buf[BUF * kSlots];   // element k of thread q's chain at k * kSlots + q
+    __shared__ int s_buf[kHeld * kSlots];   // element k of thread q's chain at k * kSlots + q
     const int total = striped_prefix(walk_counts, walk_cap, s_pref);
     const int nthreads = gridDim.x * blockDim.x;
     const int lane = __lane_id(), tid = threadIdx.x;
@@ -1155,43 +1160,59 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
                 s_buf[tid] = st;
             }
         }
+        const auto go_on_in_pool = [&]() {
+            const int at = atomicAdd(&wbuf_counts[wstripe * kStripePad], kLongWords);
+            far = at + kLongWords <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
+            if (far >= 0) {
+                const gint out = (gint)wbuf + far + kLongHead;
+                for (int k = 0; k < fa; k++) out[k] = s_buf[k * kSlots + tid];
+                for (int k = 0; k < bb; k++) out[kLongMax - 1 - k] = s_buf[(kHeld - 1 - k) * kSlots + tid];
+            }
+        };
         while (__any(live)) {
             if (!live) continue;
-            if (far == kNotTried && fa + bb > BUF - 2) {   // the buffer may be full after this step
-                const int at = atomicAdd(&wbuf_counts[wstripe * kStripePad], kLongWords);
-                far = at + kLongWords <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
-                if (far >= 0) {
-                    const gint out = (gint)wbuf + far + kLongHead;
-                    for (int k = 0; k < fa; k++) out[k] = s_buf[k * kSlots + tid];
-                    for (int k = 0; k < bb; k++) out[kLongMax - 1 - k] = s_buf[(BUF - 1 - k) * kSlots + tid];
-                }
-            }
-            const bool two = fa >= both, keep = far >= 0 && fa + bb < kLongMax - 1;
+            if (far == kNotTried && fa + bb >= BUF) go_on_in_pool();   // the buffer may be full after this step
+            const bool two = fa >= both, held = fa + bb < BUF, keep = far >= 0 && fa + bb <= kLongMax - 4;
             const gint out = (gint)wbuf + (keep ? far + kLongHead : 0);
-            const int nf = nx[fc], nb = two ? pv[bc] : 0;
-            bool done = nf == bc;   // the forward end reached the backward one
-            if (!done && nf >= 0) {
+            const int tf = tri_of(fc), tb = tri_of(bc);
+            const v3i nn = *(GLOBAL const v3i_a4 *)(nx + 3 * tf);
+            const v3i pp = two ? *(GLOBAL const v3i_a4 *)(pv + 3 * tb) : v3i{0, 0, 0};
+            bool done = false, bad = false;
+            const auto forward = [&]() {
+                const int i = fc - 3 * tf, nf = i == 0 ? nn.x : i == 1 ? nn.y : nn.z;
+                done = nf == bc;   // the forward end reached the backward one
+                bad = nf < 0;
+                if (done || bad) return;
                 fc = nf;
-                if (fa < BUF) s_buf[fa * kSlots + tid] = nf;
+                if (held) s_buf[fa * kSlots + tid] = nf;
                 if (keep) out[fa] = nf;
                 if (nf < mn) {
                     mn = nf;
                     mpos = fa;
                 }
                 ++fa;
-                done = two && nb == nf;   // the backward end reached the forward one
-                if (two && !done && nb >= 0) {
-                    bc = nb;
-                    if (bb < BUF) s_buf[(BUF - 1 - bb) * kSlots + tid] = nb;
-                    if (keep) out[kLongMax - 1 - bb] = nb;
-                    if (nb < mn) {
-                        mn = nb;
-                        mpos = ~bb;
-                    }
-                    ++bb;
+            };
+            const auto backward = [&]() {
+                const int i = bc - 3 * tb, nb = i == 0 ? pp.x : i == 1 ? pp.y : pp.z;
+                done = nb == fc;   // the backward end reached the forward one
+                bad = nb < 0;
+                if (done || bad) return;
+                bc = nb;
+                if (held) s_buf[(kHeld - 1 - bb) * kSlots + tid] = nb;
+                if (keep) out[kLongMax - 1 - bb] = nb;
+                if (nb < mn) {
+                    mn = nb;
+                    mpos = ~bb;
                 }
+                ++bb;
+            };
+            forward();
+            if (!done && !bad && (unsigned)(fc - 3 * tf) < 3u) forward();   // (in the same triangle still)
+            if (two && !done && !bad) {
+                backward();
+                if (!done && !bad && (unsigned)(bc - 3 * tb) < 3u) backward();
             }
-            const bool bad = nf < 0 || nb < 0 || fa + bb > lim;
+            bad |= fa + bb > lim;
             if (bad) atomicOr(&descs[ONE ? 0 : mesh].ctr->err, kErrCorrupt);
             closed = done && !bad;
             live = !done && !bad;
@@ -1201,6 +1222,7 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
         // loses its claim leaves its space unused)
         const MeshDesc &d = descs[ONE ? 0 : mesh];
         const int len = fa + bb, tm = closed ? tri_of(mn) : 0;
+        if (closed && len > BUF && far == kNotTried) go_on_in_pool();   // (it closed in the step that outgrew the buffer)
         const bool taken = closed && repair && set_label_bit(d, tm, kCountedBit);
         // whole 16-byte groups, so k_compact reads a loop with vector loads
         const int need = closed && len <= BUF ? (len + 4) & ~3 : 0;
@@ -1227,7 +1249,7 @@ __global__ void __launch_bounds__(256) k_walk(const MeshDesc *__restrict__ descs
                 // buffer) and the forward ones, in 16-byte groups
                 GLOBAL v4i *out = (GLOBAL v4i *)((gint)wbuf + pos);
                 const int rot = mpos >= 0 ? bb + mpos : bb - 1 - ~mpos;
-                const int back = (BUF - bb) * kSlots + tid, fore = -bb * kSlots + tid;
+                const int back = (kHeld - bb) * kSlots + tid, fore = -bb * kSlots + tid;
                 const auto at = [&](int k) { return s_buf[(k < bb ? back : fore) + min(k, len - 1) * kSlots]; };
                 for (int k = -1; k < len; k += 4) *out++ = v4i{k < 0 ? rot : at(k), at(k + 1), at(k + 2), at(k + 3)};
             }
@@ -1295,15 +1317,16 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
             if (sub == 0) corrupt(d);
             continue;
         }
-        int v[kLongMax / kCopyLanes];
+        constexpr int kCopies = (kPlMax - 2) / kCopyLanes + 1;   // L < kPlMax
+        int v[kCopies];
 #pragma unroll
-        for (int j = 0; j < kLongMax / kCopyLanes; j++) {
+        for (int j = 0; j < kCopies; j++) {
             const int k = sub + j * kCopyLanes;
             v[j] = src[kLongHead + (k < fore ? k : min(k + kLongMax - L, kLongMax - 1))];
         }
         const gint out = (gint)d.loop_he + e.off;
 #pragma unroll
-        for (int j = 0; j < kLongMax / kCopyLanes; j++) {
+        for (int j = 0; j < kCopies; j++) {
             const int k = sub + j * kCopyLanes;
             if (k >= L) continue;
             if (k == rot && v[j] != ~e.mn) corrupt(d);
