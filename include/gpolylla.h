@@ -153,8 +153,8 @@ int gpolylla_ctx_get_launch(const gp_ctx *ctx, char *buf, int32_t cap);
 /*
  * Builds the half-edge structure of a triangulation on the device
  * (Section 4.1-4.2): validation, counter-clockwise orientation (exact int64
- * orientation test) and twin matching (bucket half-edges by origin, then look
- * for the reverse edge in the target's bucket).
+ * orientation test) and twin matching (a table of the edges of each group of
+ * consecutive vertices).
  *   xy:  2*nv int32, interleaved (x0, y0, x1, y1, ...)
  *   tri: 3*nt int32 vertex indices
  * Host pointers unless flags has GP_IN_DEVICE.  The inputs are copied; the
