@@ -330,6 +330,13 @@ struct gprt::JobCrew {
             live.pop_front();
         }
     }
+    // Until every started group has been unpacked and its memory given back.
+    void drain(gp_ctx *c) {
+        std::unique_lock<std::mutex> lk(mu);
+        while (taken < started) unpack_one(lk);
+        cv.wait(lk, [&]() { return done == started; });
+        free_done(c);
+    }
     explicit JobCrew(int dev) : device(dev) {
         if (hipStreamCreateWithFlags(&second, hipStreamNonBlocking) != hipSuccess ||
             hipEventCreateWithFlags(&before, hipEventDisableTiming) != hipSuccess) {
@@ -423,6 +430,14 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
             }
         }
         small_group_start(c, jobs, g, streams[k % 2]);
+        if (g.rc == GP_ENOMEM && crew && k > 0) {   // no room beside the groups in flight: alone, then
+            const int first = g.j0, end = g.j1;
+            small_group_free(c, g);
+            crew->drain(c);
+            g.j0 = first;
+            g.j1 = end;
+            small_group_start(c, jobs, g, streams[k % 2]);
+        }
         if (!crew || (k == 0 && j0 == n)) {   // a list of one group, or no memory for the crew
             small_group_unpack(jobs, g);
             small_group_free(c, g);
@@ -442,11 +457,7 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
         }
         crew->free_done(c);
     }
-    if (!crew) return;
-    std::unique_lock<std::mutex> lk(crew->mu);
-    while (crew->taken < crew->started) crew->unpack_one(lk);
-    crew->cv.wait(lk, [&]() { return crew->done == crew->started; });
-    crew->free_done(c);
+    if (crew) crew->drain(c);
 }
 
 }  // namespace

@@ -35,3 +35,15 @@ def test_groups(shared, count, group):
                 else:
                     o = oracle.polylla(m.xy, m.tri)
                     assert (arr[k].npoly, arr[k].nloop_he) == (len(o.seeds), len(o.loop_he))
+
+
+def test_groups_in_a_capped_pool():
+    """room for one group at a time: the others wait for it"""
+    ms = [W.jittered_grid(20 + k % 5, seed=930 + k) for k in range(40)]
+    print("[gpu] job groups: capped pool", flush=True)
+    with gp.Context(0, pool_bytes=800 << 10) as c:
+        built = [_job(m) for m in ms]
+        arr = (gp.gp_job * len(ms))(*[b[0] for b in built])
+        assert gp.gpolylla_mesh_jobs(c.handle, arr, 8000) == gp.GP_OK
+        for k, m in enumerate(ms):
+            _check(arr[k], built[k][1], m, f"job {k}")
