@@ -48,7 +48,7 @@ struct MeshDesc {
     int32_t *loop_off;
     int32_t *loop_he;
     int32_t *lpos;       // per triangle: where k_walk stored the loop whose minimum it holds (-1: nowhere;
-                         // or that loop's length, when it is kPlMax or longer)
+                         // when it is kPlMax or longer, its length, or length and place packed)
     MeshCounters *ctr;
     int32_t nt;
     int32_t nv;

@@ -1095,11 +1095,11 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // (rotation index of the minimum, then the half-edges in loop order from the
 // first backward one) and k_compact places it without walking it again.  A
 // chain that outgrows the buffer takes kLongWords of the pool and goes on
-// there, forward half-edges from the front and backward ones from the back, so
-// that k_emit copies a loop of fewer than kPlMax half-edges instead of walking
-// it again (its chain of dependent steps took 22 us for the longest loops of
-// the 1M-point Delaunay mesh; the copies take 6, and this kernel 37 instead of
-// 33).
+// there, forward half-edges from the front and backward ones from the back (and
+// from there to a larger place), so that k_emit copies a loop of up to kHugeMax
+// half-edges instead of walking it again (its chain of dependent steps took 22
+// us for the longest loops of the 1M-point Delaunay mesh, 65 half-edges; the
+// copies take 6 to 9, and this kernel 37 instead of 33).
 //
 // Whole waves iterate together, with nothing but the two loads in a step.  What
 // bounds the kernel is its device-scope atomics: one per wave for the pool, one
@@ -1108,7 +1108,17 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // settled in the step in which it closed, the 1M-point Delaunay mesh (280,000
 // loops) took 61 us.
 constexpr int kWalkBoth = 8;
-constexpr int kLongHead = 4, kLongMax = 68, kLongWords = kLongHead + kLongMax, kNotTried = -2;
+// lpos of a loop of kPlMax or more that is stored: the sign bit, its length and
+// its place in the pool in 16-byte groups.  (With the place alone, and the length
+// read from the pool, k_compact took 183 us on the 33.5M grid, not 170.)
+__device__ __forceinline__ bool packs_long(int len, int pos) { return pos >= 0 && pos < 1 << 26 && len - kPlMax < 128; }
+__device__ __forceinline__ int pack_long(int len, int pos) {
+    return (int)(0x80000000u | (uint32_t)(len - kPlMax) << 24 | (uint32_t)pos >> 2);
+}
+__device__ __forceinline__ int packed_len(int lp) { return ((lp >> 24) & 127) + kPlMax; }
+__device__ __forceinline__ int packed_pos(int lp) { return (lp & 0xffffff) << 2; }
+constexpr int kLongHead = 4, kLongMax = 68, kLongWords = kLongHead + kLongMax, kHugeMax = 188, kNotTried = -2;
+static_assert(kHugeMax - kPlMax < 128, "a stored loop's length packs");
 static_assert(kPlMax - 1 <= kLongMax - 4, "every loop whose code holds its length fits, whatever its last step takes");
 
 // ONE (here and in the other list-driven kernels): a run of one mesh, whose
@@ -1135,7 +1145,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
         // end bc (bb taken before the start; the start itself while bb == 0);
         // the minimum so far and where: forward index, or ~backward index
         int mesh = 0, fc = -1, bc = -1, fa = 0, bb = 0, mn = -1, mpos = 0, lim = 0;
-        int far = kNotTried;   // the chain's place in the pool, or -1
+        int far = kNotTried, room = kLongMax;   // the chain's place in the pool, or -1; its half-edges there
         bool live = false, closed = false, repair = false;
         if (b0 + tid < total) {
             const ListEntry e = walk[striped_index(s_pref, walk_cap, b0 + tid)];
@@ -1169,10 +1179,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                 for (int k = 0; k < bb; k++) out[kLongMax - 1 - k] = s_buf[(kHeld - 1 - k) * kSlots + tid];
             }
         };
+        // from there to a place for the longest loops
+        const auto go_on_in_larger = [&]() {
+            const int at = room == kLongMax ? atomicAdd(&wbuf_counts[wstripe * kStripePad], kLongHead + kHugeMax) : wbuf_cap;
+            const int to = at + kLongHead + kHugeMax <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
+            if (to >= 0) {
+                const gint in = (gint)wbuf + far + kLongHead, out = (gint)wbuf + to + kLongHead;
+                for (int k = 0; k < fa; k++) out[k] = in[k];
+                for (int k = 0; k < bb; k++) out[kHugeMax - 1 - k] = in[kLongMax - 1 - k];
+            }
+            far = to;
+            room = kHugeMax;
+        };
         while (__any(live)) {
             if (!live) continue;
             if (far == kNotTried && fa + bb >= BUF) go_on_in_pool();   // the buffer may be full after this step
-            const bool two = fa >= both, held = fa + bb < BUF, keep = far >= 0 && fa + bb <= kLongMax - 4;
+            if (far >= 0 && fa + bb > room - 4) go_on_in_larger();
+            const bool two = fa >= both, held = fa + bb < BUF, keep = far >= 0;
             const gint out = (gint)wbuf + (keep ? far + kLongHead : 0);
             const int tf = tri_of(fc), tb = tri_of(bc);
             const v3i nn = *(GLOBAL const v3i_a4 *)(nx + 3 * tf);
@@ -1199,7 +1222,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                 if (done || bad) return;
                 bc = nb;
                 if (held) s_buf[(kHeld - 1 - bb) * kSlots + tid] = nb;
-                if (keep) out[kLongMax - 1 - bb] = nb;
+                if (keep) out[room - 1 - bb] = nb;
                 if (nb < mn) {
                     mn = nb;
                     mpos = ~bb;
@@ -1237,12 +1260,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
             ((gu8)d.pl)[tm] = loop_code(mn, len);
             // where the loop is stored (-1: nowhere), or its length when the
             // code does not hold it
-            ((gint)d.lpos)[tm] = len >= kPlMax ? len : len <= BUF ? pos : far;
-            if (len > BUF && len < kPlMax && far >= 0) {
-                // forward half-edges, and the minimum's position from the start
-                ((gint)wbuf)[far] = fa;
-                ((gint)wbuf)[far + 1] = mpos >= 0 ? mpos : len - 1 - ~mpos;
-            }
+            // (both for a stored one, packed: k_compact needs the length at once)
+            ((gint)d.lpos)[tm] = len <= BUF ? pos : len < kPlMax ? far : packs_long(len, far) ? pack_long(len, far) : len;
+            if (len > BUF && far >= 0)   // a record's head:
+                // forward half-edges, the minimum's position from the start
+                *(GLOBAL v4i *)((gint)wbuf + far) = v4i{fa, mpos >= 0 ? mpos : len - 1 - ~mpos, len, room};
             if (need && pos >= 0) {
                 // position of the minimum in loop order from the first backward
                 // half-edge; then the backward half-edges (from the back of the
@@ -1308,29 +1330,33 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
         const MeshDesc &d = descs[ONE ? 0 : e.mesh];
         // (its lanes, all of one wave, read these before any of them writes)
         const bool in = e.off >= 0 && e.off < 3 * d.nt - 1;
-        const int L = in ? ((gcint)d.loop_he)[e.off] : -1, pos = in ? ((gcint)d.loop_he)[e.off + 1] : -1;
-        const bool ok = L > 0 && L < kPlMax && (long long)e.off + L <= 3ll * d.nt && pos >= 0 &&
+        const int L = in ? ((gcint)d.loop_he)[e.off] : -1, at = in ? ((gcint)d.loop_he)[e.off + 1] : -1;
+        const int pos = L < kPlMax ? at : packed_pos(at);
+        const bool ok = L > 0 && (long long)e.off + L <= 3ll * d.nt && pos >= 0 &&
                         pos <= kStripes * wbuf_cap - kLongWords;
         const gcint src = (gcint)wbuf + (ok ? pos : 0);
-        const int fore = src[0], rot = src[1];
-        if (!ok || fore < 1 || fore > L || rot < 0 || rot >= L) {
+        const int fore = src[0], rot = src[1], room = src[3];
+        if (!ok || L != src[2] || L > room || (room != kLongMax && room != kHugeMax) ||
+            pos > kStripes * wbuf_cap - kLongHead - room || fore < 1 || fore > L || rot < 0 || rot >= L) {
             if (sub == 0) corrupt(d);
             continue;
         }
-        constexpr int kCopies = (kPlMax - 2) / kCopyLanes + 1;   // L < kPlMax
-        int v[kCopies];
-#pragma unroll
-        for (int j = 0; j < kCopies; j++) {
-            const int k = sub + j * kCopyLanes;
-            v[j] = src[kLongHead + (k < fore ? k : min(k + kLongMax - L, kLongMax - 1))];
-        }
         const gint out = (gint)d.loop_he + e.off;
+        constexpr int kCopies = 4;
+        for (int k0 = sub; k0 < L; k0 += kCopies * kCopyLanes) {
+            int v[kCopies];
 #pragma unroll
-        for (int j = 0; j < kCopies; j++) {
-            const int k = sub + j * kCopyLanes;
-            if (k >= L) continue;
-            if (k == rot && v[j] != ~e.mn) corrupt(d);
-            out[k >= rot ? k - rot : k - rot + L] = v[j];
+            for (int j = 0; j < kCopies; j++) {
+                const int k = k0 + j * kCopyLanes;
+                v[j] = src[kLongHead + (k < fore ? k : min(k + room - L, room - 1))];
+            }
+#pragma unroll
+            for (int j = 0; j < kCopies; j++) {
+                const int k = k0 + j * kCopyLanes;
+                if (k >= L) continue;
+                if (k == rot && v[j] != ~e.mn) corrupt(d);
+                out[k >= rot ? k - rot : k - rot + L] = v[j];
+            }
         }
     }
     // the others: walked again, from both ends
@@ -1551,7 +1577,10 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
         int len = code[j] >> 2;
         if (len == kPlQuadNext) len = 4;
         // longer than the code holds: k_walk left the length in lpos
-        if (len >= kPlMax) len = lp[j] >= kPlMax && lp[j] <= nh ? lp[j] : -1;
+        if (len >= kPlMax) {
+            len = lp[j] < 0 ? packed_len(lp[j]) : lp[j];
+            len = len >= kPlMax && len <= nh ? len : -1;
+        }
         if (len <= 0) {
             bad = true;
             len = 0;
@@ -1663,7 +1692,7 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
             } else if (defer[j]) {
                 if (e < elim) {
                     emit[e].mesh = mi;
-                    emit[e].mn = lens[j] > kWalkBuf && lens[j] < kPlMax && lp[j] >= 0 ? ~mn : mn;
+                    emit[e].mn = lens[j] > kWalkBuf && (lens[j] < kPlMax) == (lp[j] >= 0) ? ~mn : mn;
                     emit[e].off = ps + off;
                 }
                 // the loop's length and place in the walk pool in its own

@@ -1,5 +1,5 @@
 """Loops longer than k_walk's LDS buffer through the tiled chain: lengths from
-below the buffer to above what a loop's code holds, with room for them in the
+below the buffer to above what a loop's code and its longest record hold, with room for them in the
 walk pool and without, their minima anywhere (numbered at random), one mesh and
 a batch; against the oracle element by element."""
 import numpy as np
@@ -24,13 +24,15 @@ def ctx():
 
 def case(name):
     every = [(n, top) for n in range(6, 36) for top in (False, True)]   # loops of 13 to 72 half-edges
-    strips = {"every": every * 3, "short": [(8, False), (9, True)] * 400, "long": [(30, False), (30, True)] * 60}[name]
+    strips = {"every": every * 3, "short": [(8, False), (9, True)] * 400, "long": [(30, False), (30, True)] * 60,
+              "longest": [(3, False)] * 900 + [(n, top) for n in (31, 32, 33, 50, 92, 93, 94, 95, 200) for top in (False, True)]
+              }[name]
     xy, tri, _, lens = pc.rising_strips(strips)
     m = W.scrambled(W.Mesh(xy, tri, name), 5)
     return np.ascontiguousarray(m.xy), np.ascontiguousarray(m.tri)
 
 
-CASES = ("every", "short", "long")
+CASES = ("every", "short", "long", "longest")
 
 
 @pytest.fixture(scope="module")
