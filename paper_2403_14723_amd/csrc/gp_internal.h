@@ -91,6 +91,7 @@ constexpr int kStripePad = 32;   // counters 128 bytes apart: one cache line eac
 // mesh) the 3,867 tiles of a 1M-point Delaunay mesh, nearly all with a tip, cost
 // k_relink 20 of 62 us.
 constexpr int kTipStripes = 8;
+constexpr int kUnmarked = 1;   // beside the first stripe's counter: some split polygon's seed was left unmarked
 
 // ---- launch plumbing (host side, defined in mesh_kernels.hip) ------------
 

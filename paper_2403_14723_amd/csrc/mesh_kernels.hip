@@ -324,6 +324,7 @@ __global__ void __launch_bounds__(1024) k_label(const MeshDesc *__restrict__ des
         for (int k = gid; k < ca.nstatus; k += stride) ca.status[k] = 0ull;
         for (int k = gid; k < nmesh; k += stride) ca.ctrs[k] = MeshCounters{};
         if (gid < kTipStripes) ca.tip_counts[gid * kStripePad] = 0;
+        if (gid == 0) ca.tip_counts[kUnmarked] = 0;
         if (gid < kStripes) {
             ca.walk_counts[gid * kStripePad] = 0;
             ca.emit_counts[gid * kStripePad] = 0;
@@ -1011,12 +1012,19 @@ __device__ __forceinline__ bool fix_around(const MeshDesc &d, int o) {
 // Marks the seed of triangle t's polygon as split: up the longest edges from t
 // (Lepp, Definition 1) to the terminal edge, whose lower half-edge is the seed.
 // A triangle's label and its three twins are loaded together, so a step is one
-// dependent load (two where a compact mesh's twin has escaped).  Returns false when the structure is inconsistent.
+// dependent load (two where a compact mesh's twin has escaped).  A path may
+// run through every triangle of the mesh, and then takes longer than the walk
+// that the mark saves: past kClimb steps it is given up, and k_walk told so.
+// (The longest path of a 1M-point Delaunay mesh takes 31 steps.  A run over a
+// strip of 200,000 triangles with a tip at its low end: 156 ms with the whole
+// path climbed, 102 so; of 200 triangles, 241 us and 208.)  Returns whether
+// the seed was marked.
+constexpr int kClimb = 64;
 __device__ __forceinline__ bool mark_split(const MeshDesc &d, int t) {
     const TwinView twin = twin_view(d);
     const gcu8 tfl = (gcu8)d.tflag;
     int L = (int)(tfl[t] & 3u), g0 = twin.raw(3 * t), g1 = twin.raw(3 * t + 1), g2 = twin.raw(3 * t + 2);
-    for (int k = 0; k < kRotGuard; k++) {   // (a longer edge each time)
+    for (int k = 0; k < kClimb; k++) {
         const int g = twin.value(3 * t + L, L == 0 ? g0 : (L == 1 ? g1 : g2));
         if (g < 0) {   // a boundary terminal edge
             set_label_bit(d, t, kSplitBit);
@@ -1040,7 +1048,7 @@ __device__ __forceinline__ bool mark_split(const MeshDesc &d, int t) {
 // those of the anchors, since both are chains of dependent loads.
 template <bool ONE>
 __global__ void __launch_bounds__(256) k_fixup(const MeshDesc *__restrict__ descs, const ListEntry *tips,
-                                               const int32_t *tip_counts, int tip_cap, int cap_tips,
+                                               int32_t *tip_counts, int tip_cap, int cap_tips,
                                                const ListEntry *fixes) {
     const TipStripes stripes(tip_counts, tip_cap);
     const int ntips = min(stripes.total(), cap_tips), nfix = 2 * ntips, mark0 = (nfix + kWave - 1) & ~(kWave - 1);
@@ -1050,7 +1058,7 @@ __global__ void __launch_bounds__(256) k_fixup(const MeshDesc *__restrict__ desc
             if (q < mark0) continue;
             const ListEntry tip = tips[stripes.index(q - mark0, tip_cap)];
             const MeshDesc &d = descs[ONE ? 0 : tip.mesh];
-            if (!mark_split(d, tri_of(tip.he))) atomicOr(&d.ctr->err, kErrCorrupt);
+            if (!mark_split(d, tri_of(tip.he))) tip_counts[kUnmarked] = 1;
             continue;
         }
         const ListEntry en = fixes[q];
@@ -1125,14 +1133,16 @@ static_assert(kPlMax - 1 <= kLongMax - 4, "every loop whose code holds its lengt
 // descriptor is read once, uniformly, and not per entry.
 template <int BUF, bool ONE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k_walk(const MeshDesc *__restrict__ descs, const ListEntry *walk,
-                                              const int32_t *walk_counts, int walk_cap, uint64_t *agg,
-                                              int cmp_tb, int32_t *wbuf, int32_t *wbuf_counts, int wbuf_cap) {
+                                              const int32_t *walk_counts, int walk_cap, const int32_t *tip_counts,
+                                              uint64_t *agg, int cmp_tb, int32_t *wbuf, int32_t *wbuf_counts,
+                                              int wbuf_cap) {
     constexpr int kSlots = 256;
     constexpr int kHeld = BUF + 3;   // a step takes up to four half-edges
     __shared__ int s_pref[kStripes + 1];
     __shared__ int s_buf[kHeld * kSlots];   // element k of thread q's chain at k * kSlots + q
     const int total = striped_prefix(walk_counts, walk_cap, s_pref);
     const int nthreads = gridDim.x * blockDim.x;
+    const bool claim_all = tip_counts[kUnmarked] != 0;   // (uniform)
     const int lane = __lane_id(), tid = threadIdx.x;
     const int wstripe = ((blockIdx.x * blockDim.x + tid) >> 6) % kStripes;   // this wave's pool stripe
     // few loops (a quarter of the threads or fewer): every walk is its own
@@ -1246,7 +1256,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
         const MeshDesc &d = descs[ONE ? 0 : mesh];
         const int len = fa + bb, tm = closed ? tri_of(mn) : 0;
         if (closed && len > BUF && far == kNotTried) go_on_in_pool();   // (it closed in the step that outgrew the buffer)
-        const bool taken = closed && repair && set_label_bit(d, tm, kCountedBit);
+        const bool taken = closed && (repair || claim_all) && set_label_bit(d, tm, kCountedBit);
         // whole 16-byte groups, so k_compact reads a loop with vector loads
         const int need = closed && len <= BUF ? (len + 4) & ~3 : 0;
         const int incl = wave_incl_scan(need), wtot = __builtin_amdgcn_readlane(incl, kWave - 1);
@@ -2627,7 +2637,7 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
 
     H(K_WALK, 0);
     hipLaunchKernelGGL((one ? k_walk<kWalkBuf, true> : k_walk<kWalkBuf, false>), dim3(pb), dim3(256), 0, s, rb.descs, rb.walk,
-                       rb.walk_counts, rb.walk_cap, rb.status, cmp_tb, rb.wbuf, rb.wbuf_counts, rb.wbuf_cap);
+                       rb.walk_counts, rb.walk_cap, rb.tip_counts, rb.status, cmp_tb, rb.wbuf, rb.wbuf_counts, rb.wbuf_cap);
     H(K_WALK, 1);
 
     H(K_TSCAN, 0);
