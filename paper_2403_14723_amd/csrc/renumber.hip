@@ -113,13 +113,13 @@ inline int blocks_for(int n) { return n > 0 ? (n + 255) / 256 : 1; }
 
 // ---- sorting by sampling ---------------------------------------------------
 
-constexpr int kSortMax = 1 << 21;
+constexpr int kSortBits = 21, kSortMax = 1 << kSortBits;
 // A bucket's list has room for seven times the mean (and a bucket spans at
 // least four samples), or for at least four times the mean beyond kBucketMean
 // elements to each of the largest number of buckets (eight samples): fewer than
 // one random input in a thousand has a bucket that does not fit.
 constexpr int kBucketMean = 600, kMaxBuckets = 1024, kMaxSamples = 8192;
-constexpr int kBucketCap = 4096, kBigCap = 2 * kBucketCap;   // (the latter: k_sort_bucket<TRI, true>)
+constexpr int kBucketCap = 4096, kBigCap = 2 * kBucketCap;   // (the latter: k_sort_bucket<true>)
 static_assert(kSortMax / kMaxBuckets * 4 == kBigCap, "buckets fit");
 
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v, int m) { return (uint32_t)__shfl_xor((int)v, m); }
@@ -130,15 +130,15 @@ __device__ __forceinline__ uint64_t lane_xor(uint64_t v, int m) {
 // Sorts TPB * E words, E per thread: in increasing order of tid * E + r when it
 // returns.  A bitonic network: partners within a thread are registers, within
 // a wave lanes, and only the others meet in LDS (s, TPB * E words).
-template <int TPB, int E, class Word>
-__device__ __forceinline__ void block_sort(Word (&x)[E], Word *s) {
+template <int TPB, int E>
+__device__ __forceinline__ void block_sort(uint32_t (&x)[E], uint32_t *s) {
     const int tid = threadIdx.x;
     auto in_thread = [&](int j, int k) {   // (j, E: constants once unrolled)
 #pragma unroll
         for (int r = 0; r < E; r++) {
             if (r & j) continue;
             const bool up = ((tid * E + r) & k) == 0;
-            const Word a = min(x[r], x[r | j]), b = max(x[r], x[r | j]);
+            const uint32_t a = min(x[r], x[r | j]), b = max(x[r], x[r | j]);
             x[r] = up ? a : b;
             x[r | j] = up ? b : a;
         }
@@ -151,7 +151,7 @@ __device__ __forceinline__ void block_sort(Word (&x)[E], Word *s) {
         const bool up = ((tid * E) & k) == 0;
         for (int m = k / (2 * E); m > 0; m >>= 1) {   // partner thread: tid ^ m
             const bool low = ((tid & m) == 0) == up;
-            Word y[E];
+            uint32_t y[E];
             if (m >= 64) {
                 __syncthreads();
 #pragma unroll
@@ -172,12 +172,14 @@ __device__ __forceinline__ void block_sort(Word (&x)[E], Word *s) {
 }
 
 // One array's sort (vertices, or triangles): n elements in `buckets` buckets,
-// whose lists hold cap entries each.
+// whose lists hold cap entries each.  A bucket begins at a sample's key and
+// place in the input, so that equal keys, however many, spread over buckets too.
 struct SortPart {
     int n, samples, buckets, cap;
-    uint64_t *sample;   // samples: their keys
-    uint64_t *split;    // buckets: the lowest key of each (the first: none)
-    int32_t *cursor;    // buckets: elements of each
+    uint64_t *sample;    // samples: their keys
+    uint64_t *split;     // buckets: the lowest key of each (the first: none)
+    int32_t *split_at;   // buckets: of that key, the first place in the input
+    int32_t *cursor;     // buckets: elements of each
     void *list;         // buckets * cap entries
 };
 
@@ -215,17 +217,22 @@ __device__ __forceinline__ uint64_t load_entry(const RenumberBuffers &b, int k, 
     return key;
 }
 
-// Samples the keys, one from each of `samples` equal stretches of the input at
-// a place that a hash picks, and clears the lists.  grid: kMaxSamples / 256
-// blocks for the vertices, as many for the triangles.
+// Sample i's place in the input: in the i-th of `samples` equal stretches, where
+// a hash picks.
+__device__ __forceinline__ int sample_place(const SortPart &p, uint32_t i) {
+    const uint64_t at = (uint64_t)i * (uint32_t)p.n + ((uint64_t)(i * 0x9E3779B1u) * (uint32_t)p.n >> 32);
+    return (int)(at / (uint32_t)p.samples);
+}
+
+// Samples the keys, and clears the lists.  grid: kMaxSamples / 256 blocks for
+// the vertices, as many for the triangles.
 __global__ void __launch_bounds__(256) k_sort_sample(const RenumberBuffers b, const SortPart pv, const SortPart pt) {
     const bool tri = blockIdx.x >= kMaxSamples / 256;
     const SortPart &p = tri ? pt : pv;
     const uint32_t i = (blockIdx.x % (kMaxSamples / 256)) * 256 + threadIdx.x;
     if (!tri && i == 0) *b.overflow = 0;
     if (i >= (uint32_t)p.samples) return;
-    const uint64_t at = (uint64_t)i * (uint32_t)p.n + ((uint64_t)(i * 0x9E3779B1u) * (uint32_t)p.n >> 32);
-    const int k = (int)(at / (uint32_t)p.samples);
+    const int k = sample_place(p, i);
     VertexEntry ev;
     TriangleEntry et;
     p.sample[i] = tri ? load_entry(b, k, et) : load_entry(b, k, ev);
@@ -268,7 +275,10 @@ __global__ void __launch_bounds__(64 * kRankWaves) k_sort_rank(const SortPart pv
     atomicAdd(&s_rank[lane], rank);
     __syncthreads();
     const int span = p.samples / p.buckets;
-    if (threadIdx.x < 64 && s_rank[lane] % span == 0) p.split[s_rank[lane] / span] = x;
+    if (threadIdx.x < 64 && s_rank[lane] % span == 0) {
+        p.split[s_rank[lane] / span] = x;
+        p.split_at[s_rank[lane] / span] = sample_place(p, 64 * group + lane);
+    }
 }
 
 // Puts 2 elements per thread into their buckets' lists.  The block counts its
@@ -277,10 +287,11 @@ __global__ void __launch_bounds__(64 * kRankWaves) k_sort_rank(const SortPart pv
 constexpr int kPlaceItems = 2, kPlaceBlock = 1024;
 template <bool TRI>
 __device__ __forceinline__ void place(const RenumberBuffers &b, const SortPart &p, int block, uint64_t *s_split,
-                                      int *s_count) {
+                                      int *s_at, int *s_count) {
     const int tid = threadIdx.x;
     if (tid < p.buckets) {
         s_split[tid] = p.split[tid];
+        s_at[tid] = p.split_at[tid];
         s_count[tid] = 0;
     }
     ListEntryOf<TRI> e[kPlaceItems];
@@ -295,8 +306,13 @@ __device__ __forceinline__ void place(const RenumberBuffers &b, const SortPart &
     __syncthreads();
     for (int step = p.buckets / 2; step > 0; step /= 2)
 #pragma unroll
-        for (int j = 0; j < kPlaceItems; j++)
-            if (key[j] >= s_split[at[j] + step]) at[j] += step;
+        for (int j = 0; j < kPlaceItems; j++) {
+            // (without branches: hipcc 7.2 drops the step of equal keys from
+            // the form with && and ||)
+            const uint64_t first = s_split[at[j] + step];
+            const bool up = (key[j] > first) | ((key[j] == first) & (k[j] >= s_at[at[j] + step]));
+            at[j] += up ? step : 0;
+        }
 #pragma unroll
     for (int j = 0; j < kPlaceItems; j++)
         if (k[j] < p.n) rank[j] = atomicAdd(&s_count[at[j]], 1);
@@ -321,11 +337,11 @@ __device__ __forceinline__ void place(const RenumberBuffers &b, const SortPart &
 __global__ void __launch_bounds__(kPlaceBlock) k_sort_place(const RenumberBuffers b, const SortPart pv,
                                                            const SortPart pt, int vblocks) {
     __shared__ uint64_t s_split[kMaxBuckets];
-    __shared__ int s_count[kMaxBuckets];
+    __shared__ int s_at[kMaxBuckets], s_count[kMaxBuckets];
     if ((int)blockIdx.x < vblocks)
-        place<false>(b, pv, blockIdx.x, s_split, s_count);
+        place<false>(b, pv, blockIdx.x, s_split, s_at, s_count);
     else
-        place<true>(b, pt, blockIdx.x - vblocks, s_split, s_count);
+        place<true>(b, pt, blockIdx.x - vblocks, s_split, s_at, s_count);
 }
 
 // Sorts a bucket's m <= 256 * E elements by (key, index), E elements per
@@ -334,20 +350,26 @@ __global__ void __launch_bounds__(kPlaceBlock) k_sort_place(const RenumberBuffer
 // many leading bits as the bucket's range and the word leave room for, over
 // the place in the list; elements that agree in these bits are neighbours
 // afterwards, and swap by whole keys until they are in order.  Returns whether
-// they are, within `rounds`.
+// they are, within a few rounds.
 constexpr int kBucketBlock = 256;
-template <int E, class Word, class Entry>
-__device__ __forceinline__ bool sort_words(const uint64_t (&key)[E], uint64_t lo, uint64_t hi,
-                                           const Entry *__restrict__ list, int m, int rounds, Word *s) {
-    constexpr int kLocal = 8 + __builtin_ctz(E), kBits = 8 * sizeof(Word) - kLocal;
-    constexpr Word kPlace = ((Word)1 << kLocal) - 1;
+template <int E>
+struct BucketWord {
+    static constexpr int kLocal = 8 + __builtin_ctz(E), kBits = 32 - kLocal;
+    static constexpr uint32_t kPlace = (1u << kLocal) - 1;
+};
+
+template <int E, class Entry>
+__device__ __forceinline__ bool sort_words(const uint64_t (&key)[E], uint64_t lo, int bits,
+                                           const Entry *__restrict__ list, int m, uint32_t *s) {
+    constexpr int kLocal = BucketWord<E>::kLocal, kRounds = 4;
+    constexpr uint32_t kPlace = BucketWord<E>::kPlace;
     const int tid = threadIdx.x;
-    const int shift = max(0, (hi > lo ? 64 - __clzll((long long)(hi - lo)) : 0) - kBits);
-    Word x[E];
+    const int shift = max(0, bits - BucketWord<E>::kBits);
+    uint32_t x[E];
 #pragma unroll
     for (int r = 0; r < E; r++) {
         const int i = r * kBucketBlock + tid;
-        x[r] = i < m ? (Word)((key[r] - lo) >> shift) << kLocal | (Word)i : ~(Word)0;
+        x[r] = i < m ? (uint32_t)((key[r] - lo) >> shift) << kLocal | (uint32_t)i : ~0u;
     }
     block_sort<kBucketBlock, E>(x, s);
     __syncthreads();
@@ -361,11 +383,11 @@ __device__ __forceinline__ bool sort_words(const uint64_t (&key)[E], uint64_t lo
         tie |= i > 0 && i < m && (s[i] ^ s[i - 1]) >> kLocal == 0;
     }
     if (!__syncthreads_or(tie)) return true;
-    for (int round = 0; round < rounds; round++) {
+    for (int round = 0; round < kRounds; round++) {
         bool swapped = false;
         for (int par = 0; par < 2; par++) {
             for (int i = 2 * tid + par; i + 1 < m; i += 2 * kBucketBlock) {
-                const Word u = s[i], v = s[i + 1];
+                const uint32_t u = s[i], v = s[i + 1];
                 if ((u ^ v) >> kLocal) continue;
                 const Entry eu = list[u & kPlace], ev = list[v & kPlace];
                 const uint64_t ku = eu.key(), kv = ev.key();
@@ -381,14 +403,57 @@ __device__ __forceinline__ bool sort_words(const uint64_t (&key)[E], uint64_t lo
     return false;
 }
 
+// The same order whatever the keys: by the digits of the index in the input,
+// then those of the key's distance from the bucket's lowest, the least digit
+// first, each by a sort of words that hold the digit over the place in the
+// order so far.  For buckets where many keys agree in the bits above: equal
+// ones, or a cluster far smaller than the bucket's range (swapping neighbours
+// until they were in order, a build of 594,000 triangles with 3,500 vertices in
+// one place took 13.8 ms; now 0.14).
+template <int E, class Entry>
+__device__ __forceinline__ void sort_digits(uint64_t lo, int bits, const Entry *__restrict__ list, int m, uint32_t *s) {
+    constexpr int kLocal = BucketWord<E>::kLocal, kBits = BucketWord<E>::kBits;
+    constexpr int kOldDigits = (kSortBits + kBits - 1) / kBits;
+    const int tid = threadIdx.x, digits = kOldDigits + (bits + kBits - 1) / kBits;
+    uint32_t at[E];   // the element in place r * 256 + tid of the order so far
+#pragma unroll
+    for (int r = 0; r < E; r++) at[r] = r * kBucketBlock + tid;
+    for (int d = 0; d < digits; d++) {
+        uint32_t x[E];
+#pragma unroll
+        for (int r = 0; r < E; r++) {
+            const int i = r * kBucketBlock + tid;
+            x[r] = ~0u;
+            if (i >= m) continue;
+            const Entry e = list[at[r]];
+            const uint64_t from = d < kOldDigits ? (uint64_t)e.old >> (d * kBits) : (e.key() - lo) >> ((d - kOldDigits) * kBits);
+            x[r] = (uint32_t)from << kLocal | (uint32_t)i;
+        }
+        block_sort<kBucketBlock, E>(x, s);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < E; r++) s[tid * E + r] = x[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < E; r++) x[r] = s[r * kBucketBlock + tid] & BucketWord<E>::kPlace;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < E; r++) s[r * kBucketBlock + tid] = at[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < E; r++) at[r] = s[x[r]];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < E; r++) s[r * kBucketBlock + tid] = at[r];
+    __syncthreads();
+}
+
 // Sorts the bucket and writes its part of the permuted arrays, from `first`
-// on.  32-bit words order all but a few neighbours unless the keys lie in
-// clusters far smaller than the bucket's range, or many are equal: then 64-bit
-// words (m + 1 rounds always suffice).  There is no room for those in a bucket
-// of more than kBucketCap: it is reported like a list that overflowed.
+// on.
 template <bool TRI, int E>
 __device__ __forceinline__ void sort_bucket(const RenumberBuffers &b, const SortPart &p, int bucket, int m,
-                                            int first, uint64_t *s, uint64_t *s_range) {
+                                            int first, uint32_t *s, uint64_t *s_range) {
     const int tid = threadIdx.x;
     const ListEntryOf<TRI> *list = static_cast<const ListEntryOf<TRI> *>(p.list) + (size_t)bucket * p.cap;
     uint64_t x[E], lo = ~0ull, hi = 0;
@@ -413,21 +478,13 @@ __device__ __forceinline__ void sort_bucket(const RenumberBuffers &b, const Sort
         lo = min(lo, s_range[2 * w]);
         hi = max(hi, s_range[2 * w + 1]);
     }
-    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(s);
-    const bool wide = !sort_words<E, uint32_t>(x, lo, hi, list, m, 4, reinterpret_cast<uint32_t *>(s));
-    if (wide) {   // (uniform)
-        if constexpr (kBucketBlock * E <= kBucketCap) {
-            sort_words<E, uint64_t>(x, lo, hi, list, m, m + 1, s);
-        } else {
-            if (tid == 0) *b.overflow_out = 1;
-            return;
-        }
-    }
+    const int bits = hi > lo ? 64 - __clzll((long long)(hi - lo)) : 0;
+    if (!sort_words<E>(x, lo, bits, list, m, s)) sort_digits<E>(lo, bits, list, m, s);   // (uniform)
 #pragma unroll
     for (int r = 0; r < E; r++) {
         const int i = r * kBucketBlock + tid, k = first + i;
         if (i >= m) continue;
-        const ListEntryOf<TRI> e = list[(wide ? (uint32_t)s[i] : s32[i]) & (kBucketBlock * E - 1)];
+        const ListEntryOf<TRI> e = list[s[i] & BucketWord<E>::kPlace];
         if constexpr (TRI) {
             b.tperm[k] = e.old;
 #pragma unroll
@@ -442,7 +499,7 @@ __device__ __forceinline__ void sort_bucket(const RenumberBuffers &b, const Sort
 
 // A workgroup's bucket starts where the buckets before it end.
 template <bool TRI, bool BIG>
-__device__ __forceinline__ void place_bucket(const RenumberBuffers &b, const SortPart &p, int bucket, uint64_t *s,
+__device__ __forceinline__ void place_bucket(const RenumberBuffers &b, const SortPart &p, int bucket, uint32_t *s,
                                              uint64_t *s_range, int *s_first) {
     const int tid = threadIdx.x;
     if (tid == 0) *s_first = 0;
@@ -476,7 +533,7 @@ __device__ __forceinline__ void place_bucket(const RenumberBuffers &b, const Sor
 template <bool BIG>
 __global__ void __launch_bounds__(kBucketBlock) k_sort_bucket(const RenumberBuffers b, const SortPart pv,
                                                              const SortPart pt) {
-    __shared__ uint64_t s[kBucketCap];
+    __shared__ uint32_t s[BIG ? kBigCap : kBucketCap];
     __shared__ uint64_t s_range[2 * (kBucketBlock / 64)];
     __shared__ int s_first;
     if (*b.overflow) {   // (uniform) a list overflowed: the caller sorts in another way
@@ -515,7 +572,7 @@ SortPart sort_part(int n) {
 template <bool TRI>
 size_t part_bytes(const SortPart &p) {
     const size_t lists = sizeof(ListEntryOf<TRI>) * (size_t)p.buckets * (size_t)p.cap;
-    return (sizeof(uint64_t) * (size_t)(p.samples + p.buckets) + lists + sizeof(int32_t) * (size_t)p.buckets + 63) / 64 * 64;
+    return (sizeof(uint64_t) * (size_t)(p.samples + p.buckets) + lists + 2 * sizeof(int32_t) * (size_t)p.buckets + 63) / 64 * 64;
 }
 
 template <bool TRI>
@@ -525,6 +582,7 @@ char *part_layout(SortPart &p, char *at) {
     p.split = p.sample + p.samples;
     p.list = p.split + p.buckets;
     p.cursor = reinterpret_cast<int32_t *>(static_cast<ListEntryOf<TRI> *>(p.list) + (size_t)p.buckets * p.cap);
+    p.split_at = p.cursor + p.buckets;
     return at + part_bytes<TRI>(p);
 }
 
