@@ -1775,10 +1775,11 @@ __global__ void __launch_bounds__(1024) k_compact(const MeshDesc *__restrict__ d
 //      repaired frontier;
 //   4. prev' as the inverse of next'; every seed's loop walked once for its
 //      minimum and length (Section 6.6, Algorithm 14; the first walker of a
-//      loop that several seeds reach records it);
+//      loop that several seeds reach records it), or, when some loop is long,
+//      all loops ranked by pointer doubling;
 //   5. seeds and loop offsets from a block scan over the triangles that hold a
 //      minimum (Section 6.7);
-//   6. every loop walked again from its minimum into its place.
+//   6. every loop walked again from its minimum into its place, or by its ranks.
 // In LDS a half-edge 3t + i is slot 4t + i, so next and the triangle of a
 // slot are bit operations (the order of slots is the order of half-edges),
 // and slot 4t + 3 holds what belongs to the triangle.  The vector instructions
@@ -1833,12 +1834,88 @@ __device__ __forceinline__ void small_counts(const MeshDesc &d, const MeshCounte
     if (d.ctr_out) *d.ctr_out = c;
 }
 
+// Loops longer than this are not walked by one thread.
+template <int TI>
+constexpr int kSmallWalk = 16 * (TI + 1);
+
+// The minimum of every loop, its length, and every half-edge's place in its
+// loop, by pointer doubling along prev': for meshes with a long loop, which one
+// thread would walk twice, 55 ns a step (a strip of 4,079 triangles, one loop:
+// 474 us for a run with the walks, 64 so; 599 triangles, 89 and 29).  First each
+// half-edge's minimum over ever longer stretches (most: half-edges on the long
+// loops together), then its distance from that minimum.  Value and link of a half-edge are one word, so
+// a round needs no barrier between its reads and its writes: a word that has
+// moved on already only makes the stretch longer.  A round follows two links.
+// Leaves by slot: minimum | place << 16; and 4t + 3: the length of the loop with its
+// minimum in t, or 0.
+template <int TI>
+__device__ __forceinline__ void small_rank(uint32_t *s_pk, const uint16_t *s_pv, const uint32_t (&F)[TI], int nt,
+                                           int most) {
+    uint32_t p[TI][3], m[TI][3], n[TI][3];
+    bool on[TI][3];
+    // every frontier half-edge of the thread: f(its slot, j, i)
+    const auto each = [&](auto f) {
+#pragma unroll
+        for (int j = 0; j < TI; j++)
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+                if (on[j][i]) f(4u * (threadIdx.x + j * kSmallBlock) + i, j, i);
+    };
+#pragma unroll
+    for (int j = 0; j < TI; j++)
+#pragma unroll
+        for (int i = 0; i < 3; i++) on[j][i] = (int)threadIdx.x + j * kSmallBlock < nt && ((F[j] >> i) & 1u);
+    each([&](uint32_t q, int j, int i) { p[j][i] = s_pv[q]; });
+    __syncthreads();   // (s_pk lies over s_pv)
+    each([&](uint32_t q, int j, int i) {
+        m[j][i] = q;
+        n[j][i] = p[j][i];
+        s_pk[q] = q | p[j][i] << 16;
+    });
+#pragma unroll
+    for (int j = 0; j < TI; j++)
+        if ((int)threadIdx.x + j * kSmallBlock < nt) s_pk[4 * (threadIdx.x + j * kSmallBlock) + 3] = 0;
+    __syncthreads();
+    for (int w = 1; w < most; w *= 3) {   // stretches of w at least
+        each([&](uint32_t, int j, int i) {
+            const uint32_t a = s_pk[n[j][i]], b = s_pk[a >> 16];
+            m[j][i] = min(m[j][i], min(a & 0xffffu, b & 0xffffu));
+            n[j][i] = b >> 16;
+        });
+        each([&](uint32_t q, int j, int i) { s_pk[q] = m[j][i] | n[j][i] << 16; });
+        __syncthreads();
+    }
+    uint32_t d[TI][3];
+    each([&](uint32_t q, int j, int i) {
+        d[j][i] = m[j][i] != q;
+        n[j][i] = m[j][i] != q ? p[j][i] : q;
+        s_pk[q] = d[j][i] | n[j][i] << 16;
+    });
+    __syncthreads();
+    for (int w = 1; w < 4 * nt; w *= 3) {   // (a valid mesh's loops end it sooner)
+        bool open = false;
+        each([&](uint32_t, int j, int i) {
+            const uint32_t a = s_pk[n[j][i]], b = s_pk[a >> 16];
+            d[j][i] += (a & 0xffffu) + (b & 0xffffu);
+            n[j][i] = b >> 16;
+            open |= n[j][i] != m[j][i];
+        });
+        each([&](uint32_t q, int j, int i) { s_pk[q] = (d[j][i] & 0xffffu) | n[j][i] << 16; });
+        if (!__syncthreads_or(open)) break;   // (uniform)
+    }
+    each([&](uint32_t q, int j, int i) {
+        if (m[j][i] == q) s_pk[q | 3u] = (s_pk[p[j][i]] & 0xffffu) + 1u;
+    });
+    __syncthreads();
+    each([&](uint32_t q, int j, int i) { s_pk[q] = m[j][i] | d[j][i] << 16; });
+}
+
 // TI: triangles per thread (1, 2 or 4).
 template <int TI>
 __device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI> &tr) {
     extern __shared__ int4 lds_raw[];
     __shared__ int s_scan[72];
-    __shared__ int s_cnt[5];   // tied maxima, tips, new middle edges, frontier half-edges, seeds
+    __shared__ int s_cnt[6];   // tied maxima, tips, new middle edges, frontier half-edges, seeds, half-edges of walked loops
     const int nt = d.nt, nh = 3 * nt, tid = threadIdx.x, lane = __lane_id();
     const uint32_t ns = 4u * (uint32_t)nt;
     uint16_t *s_sl = reinterpret_cast<uint16_t *>(lds_raw);   // by slot: the twin's slot; 4t + 3: the triangle's word
@@ -1847,7 +1924,9 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI
     uint16_t *s_list = s_pv + ns;   // seeds (label phase, then both sides of every middle edge), then minima
     uint32_t *w32 = reinterpret_cast<uint32_t *>(s_sl);
     int bad = 0;
-    if (tid < 5) s_cnt[tid] = 0;
+    __shared__ int s_longer;   // some loop was not walked to its end
+    if (tid < 6) s_cnt[tid] = 0;
+    if (tid == 0) s_longer = 0;
 
     // 1. longest edges; edge i of t runs from corner i to corner i + 1, and a
     //    tie at the maximum goes to the lower edge id min(h, twin h)
@@ -2100,6 +2179,8 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI
     }
     if (lane == 0 && nfront) atomicAdd(&s_cnt[3], nfront);
     const int nlist = s_cnt[4];   // (within s_list: checked as it grew)
+    bool longer = false;
+    int walked = 0;
     for (int k = tid; k < nlist; k += kSmallBlock) {
         const uint32_t s0 = s_list[k], f = repaired_bits(s_sl[s0 | 3u]);
         uint32_t st = ((f >> (s0 & 3u)) & 1u) ? s0 : (s0 & ~3u) + (uint32_t)__builtin_ctz(f | 8u);
@@ -2116,17 +2197,30 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI
         }
         uint32_t cur = s_nx[st], mn = st;
         int len = 1;
-        for (; cur != st && len <= nh; len++) {
+        for (; cur != st && len < kSmallWalk<TI>; len++) {
             mn = min(mn, cur);
             cur = s_nx[cur];
         }
-        bad |= len > nh;
+        if (cur != st) {
+            longer = true;
+            continue;
+        }
         const uint32_t old = atomicOr(&w32[2 * (mn >> 2) + 1], kRecorded << 16);
         const bool won = !(old & (kRecorded << 16));
         if (won) s_nx[mn | 3u] = (uint16_t)len;
+        walked += won ? len : 0;
         s_list[k] = (uint16_t)(won ? mn : kNo16);
     }
+    if (longer) s_longer = 1;
     bad = __syncthreads_or(bad);
+    const bool ranked = __builtin_expect(s_longer, 0);
+    uint32_t *s_pk = reinterpret_cast<uint32_t *>(s_nx);   // (over s_nx and s_pv)
+    if (ranked) {   // (uniform)
+        if (walked) atomicAdd(&s_cnt[5], walked);
+        __syncthreads();
+        small_rank<TI>(s_pk, s_pv, F, nt, s_cnt[3] - s_cnt[5]);
+        __syncthreads();
+    }
 
     // 5. loops in the order of their minima: each thread scans a few
     //    consecutive triangles (a loop's minimum is the first frontier
@@ -2135,7 +2229,7 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI
 #pragma unroll
     for (int r = 0; r < TI; r++) {
         const int t = tid * TI + r;
-        len[r] = t < nt ? s_nx[4 * t + 3] : 0;
+        len[r] = t >= nt ? 0 : ranked ? (int)s_pk[4 * t + 3] : s_nx[4 * t + 3];
         cnt += len[r] != 0;
         sum += len[r];
     }
@@ -2151,7 +2245,11 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI
             const uint32_t q = 4u * (uint32_t)(tid * TI + r);
             seeds[ec] = he_of_slot(q + (uint32_t)__builtin_ctz(repaired_bits(s_sl[q + 3]) | 8u));
             loff[ec] = es;
-            s_nx[q + 3] = (uint16_t)es;   // the loop's first place
+            // the loop's first place
+            if (ranked)
+                s_pk[q + 3] = es;
+            else
+                s_nx[q + 3] = (uint16_t)es;
             ec++;
             es += len[r];
         }
@@ -2159,20 +2257,34 @@ __device__ __forceinline__ void small_body(const MeshDesc &d, const SmallTris<TI
     }
     __syncthreads();
 
-    // 6. every loop from its minimum into its place (prev' is out), then out
+    // 6. every loop from its minimum into its place (prev' is out; by the ranks:
+    //    the labels are done with), then out
     if (fits) {
-        for (int k = tid; k < nlist; k += kSmallBlock) {
-            const uint32_t mn = s_list[k];
-            if (mn == kNo16) continue;
-            uint32_t at = s_nx[mn | 3u], cur = mn;
-            do {
-                s_pv[at++] = (uint16_t)cur;
-                cur = s_nx[cur];
-            } while (cur != mn);
+        uint16_t *s_out = ranked ? s_sl : s_pv;
+        if (ranked) {   // (uniform)
+#pragma unroll
+            for (int j = 0; j < TI; j++)
+#pragma unroll
+                for (int i = 0; i < 3; i++) {
+                    const uint32_t t = tid + j * kSmallBlock, q = 4u * t + i;
+                    if ((int)t >= nt || !((F[j] >> i) & 1u)) continue;
+                    const uint32_t w = s_pk[q], at = s_pk[(w & 0xffffu) | 3u] + (w >> 16);
+                    if (at < (uint32_t)nh) s_out[at] = (uint16_t)q;   // (always, in a valid mesh)
+                }
+        } else {
+            for (int k = tid; k < nlist; k += kSmallBlock) {
+                const uint32_t mn = s_list[k];
+                if (mn == kNo16) continue;
+                uint32_t at = s_nx[mn | 3u], cur = mn;
+                do {
+                    s_out[at++] = (uint16_t)cur;
+                    cur = s_nx[cur];
+                } while (cur != mn);
+            }
         }
         __syncthreads();
         const gint lhe = (gint)d.loop_he;
-        for (int k = tid; k < ts; k += kSmallBlock) lhe[k] = he_of_slot(s_pv[k]);
+        for (int k = tid; k < ts; k += kSmallBlock) lhe[k] = he_of_slot(s_out[k]);
     }
     if (tid == 0) {
         MeshCounters c{};
