@@ -1102,19 +1102,24 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // the back), so a loop of at most BUF half-edges is copied to the scratch pool
 // (rotation index of the minimum, then the half-edges in loop order from the
 // first backward one) and k_compact places it without walking it again.  A
-// chain that outgrows the buffer takes kLongWords of the pool and goes on
-// there, forward half-edges from the front and backward ones from the back (and
-// from there to a larger place), so that k_emit copies a loop of up to kHugeMax
-// half-edges instead of walking it again (its chain of dependent steps took 22
-// us for the longest loops of the 1M-point Delaunay mesh, 65 half-edges; the
-// copies take 6 to 9, and this kernel 37 instead of 33).
+// chain that fills the buffer takes kLongWords of the pool and empties the buffer
+// there each time it is full, forward half-edges from the front and backward ones
+// from the back (and from there to a larger place), so that k_emit copies a loop
+// of up to kHugeMax half-edges instead of walking it again (its chain of
+// dependent steps took 22 us for the longest loops of the 1M-point Delaunay
+// mesh, 65 half-edges; the copies take 6 to 9, and this kernel 37 instead of
+// 33).  Such chains go on in a loop of their own, one link of either end at a
+// step: few lanes are left then, and a wave's time is the instructions of its
+// steps (one loop of 200 half-edges: 71 us with the steps of the short ones, 46
+// so).
 //
 // Whole waves iterate together, with nothing but the two loads in a step.  What
 // bounds the kernel is its device-scope atomics: one per wave for the pool, one
 // per wave and compaction tile for the totals (a wave's loops end in a few
 // tiles), one per repair seed.  With a claim, a total and a mark per loop,
 // settled in the step in which it closed, the 1M-point Delaunay mesh (280,000
-// loops) took 61 us.
+// loops) took 61 us; with an atomic per lane for the larger places, 60,000
+// loops of 17 half-edges took 44 us, now 20.
 constexpr int kWalkBoth = 8;
 // lpos of a loop of kPlMax or more that is stored: the sign bit, its length and
 // its place in the pool in 16-byte groups.  (With the place alone, and the length
@@ -1127,7 +1132,7 @@ __device__ __forceinline__ int packed_len(int lp) { return ((lp >> 24) & 127) + 
 __device__ __forceinline__ int packed_pos(int lp) { return (lp & 0xffffff) << 2; }
 constexpr int kLongHead = 4, kLongMax = 68, kLongWords = kLongHead + kLongMax, kHugeMax = 188, kNotTried = -2;
 static_assert(kHugeMax - kPlMax < 128, "a stored loop's length packs");
-static_assert(kPlMax - 1 <= kLongMax - 4, "every loop whose code holds its length fits, whatever its last step takes");
+static_assert(kPlMax - 1 <= kLongMax, "every loop whose code holds its length fits");
 
 // ONE (here and in the other list-driven kernels): a run of one mesh, whose
 // descriptor is read once, uniformly, and not per entry.
@@ -1155,8 +1160,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
         // end bc (bb taken before the start; the start itself while bb == 0);
         // the minimum so far and where: forward index, or ~backward index
         int mesh = 0, fc = -1, bc = -1, fa = 0, bb = 0, mn = -1, mpos = 0, lim = 0;
-        int far = kNotTried, room = kLongMax;   // the chain's place in the pool, or -1; its half-edges there
-        bool live = false, closed = false, repair = false;
+        // the chain's place in the pool, or -1; what it holds; the half-edges that are there already
+        int far = kNotTried, room = kLongMax, f0 = 0, k0 = 0;
+        bool live = false, closed = false, repair = false, more = false;
         if (b0 + tid < total) {
             const ListEntry e = walk[striped_index(s_pref, walk_cap, b0 + tid)];
             mesh = ONE ? 0 : e.mesh;
@@ -1180,33 +1186,58 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                 s_buf[tid] = st;
             }
         }
-        const auto go_on_in_pool = [&]() {
-            const int at = atomicAdd(&wbuf_counts[wstripe * kStripePad], kLongWords);
-            far = at + kLongWords <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
+        // words of the pool for each lane that is here: one atomic for all
+        const auto take = [&](int words) {
+            const unsigned long long here = __ballot(true);
+            const int leader = __ffsll((long long)here) - 1;
+            int at = 0;
+            if (lane == leader) at = atomicAdd(&wbuf_counts[wstripe * kStripePad], words * __popcll(here));
+            return __builtin_amdgcn_readlane(at, leader) + words * __popcll(here & ((1ull << lane) - 1ull));
+        };
+        // the buffered half-edges go to the chain's place in the pool, if there is one
+        const auto flush = [&]() {
+            if (far == kNotTried) {
+                const int at = take(kLongWords);
+                far = at + kLongWords <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
+            }
+            if (far >= 0 && fa + bb > room) {
+                int at = wbuf_cap;
+                if (room == kLongMax) at = take(kLongHead + kHugeMax);
+                const int to = at + kLongHead + kHugeMax <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
+                if (to >= 0) {
+                    // the whole place to both ends of the larger one, four
+                    // 16-byte groups in flight
+                    const GLOBAL v4i *in = (const GLOBAL v4i *)((gcint)wbuf + far + kLongHead);
+                    GLOBAL v4i *out = (GLOBAL v4i *)((gint)wbuf + to + kLongHead);
+                    constexpr int kGroups = kLongMax / 4, kBack = (kHugeMax - kLongMax) / 4;
+                    static_assert(kLongMax % 4 == 0 && kHugeMax % 4 == 0 && kHugeMax >= 2 * kLongMax, "16-byte groups, apart");
+                    for (int k = 0; k < kGroups; k += 4) {
+                        v4i v[4];
+#pragma unroll
+                        for (int g = 0; g < 4; g++) v[g] = in[min(k + g, kGroups - 1)];
+#pragma unroll
+                        for (int g = 0; g < 4; g++) out[min(k + g, kGroups - 1)] = out[kBack + min(k + g, kGroups - 1)] = v[g];
+                    }
+                }
+                far = to;
+                room = kHugeMax;
+            }
             if (far >= 0) {
                 const gint out = (gint)wbuf + far + kLongHead;
-                for (int k = 0; k < fa; k++) out[k] = s_buf[k * kSlots + tid];
-                for (int k = 0; k < bb; k++) out[kLongMax - 1 - k] = s_buf[(kHeld - 1 - k) * kSlots + tid];
+                for (int k = f0; k < fa; k++) out[k] = s_buf[(k - f0) * kSlots + tid];
+                for (int k = k0; k < bb; k++) out[room - 1 - k] = s_buf[(kHeld - 1 - (k - k0)) * kSlots + tid];
             }
-        };
-        // from there to a place for the longest loops
-        const auto go_on_in_larger = [&]() {
-            const int at = room == kLongMax ? atomicAdd(&wbuf_counts[wstripe * kStripePad], kLongHead + kHugeMax) : wbuf_cap;
-            const int to = at + kLongHead + kHugeMax <= wbuf_cap ? wstripe * wbuf_cap + at : -1;
-            if (to >= 0) {
-                const gint in = (gint)wbuf + far + kLongHead, out = (gint)wbuf + to + kLongHead;
-                for (int k = 0; k < fa; k++) out[k] = in[k];
-                for (int k = 0; k < bb; k++) out[kHugeMax - 1 - k] = in[kLongMax - 1 - k];
-            }
-            far = to;
-            room = kHugeMax;
+            f0 = fa;
+            k0 = bb;
         };
         while (__any(live)) {
             if (!live) continue;
-            if (far == kNotTried && fa + bb >= BUF) go_on_in_pool();   // the buffer may be full after this step
-            if (far >= 0 && fa + bb > room - 4) go_on_in_larger();
-            const bool two = fa >= both, held = fa + bb < BUF, keep = far >= 0;
-            const gint out = (gint)wbuf + (keep ? far + kLongHead : 0);
+            if (fa + bb >= BUF) {   // the buffer may be full after this step
+                more = true;
+                live = false;
+                continue;
+            }
+            const bool two = fa >= both;
             const int tf = tri_of(fc), tb = tri_of(bc);
             const v3i nn = *(GLOBAL const v3i_a4 *)(nx + 3 * tf);
             const v3i pp = two ? *(GLOBAL const v3i_a4 *)(pv + 3 * tb) : v3i{0, 0, 0};
@@ -1217,8 +1248,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                 bad = nf < 0;
                 if (done || bad) return;
                 fc = nf;
-                if (held) s_buf[fa * kSlots + tid] = nf;
-                if (keep) out[fa] = nf;
+                s_buf[fa * kSlots + tid] = nf;
                 if (nf < mn) {
                     mn = nf;
                     mpos = fa;
@@ -1231,8 +1261,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                 bad = nb < 0;
                 if (done || bad) return;
                 bc = nb;
-                if (held) s_buf[(kHeld - 1 - bb) * kSlots + tid] = nb;
-                if (keep) out[room - 1 - bb] = nb;
+                s_buf[(kHeld - 1 - bb) * kSlots + tid] = nb;
                 if (nb < mn) {
                     mn = nb;
                     mpos = ~bb;
@@ -1250,12 +1279,42 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
             closed = done && !bad;
             live = !done && !bad;
         }
+        // the longer loops: both ways, one link of each at a step
+        while (__any(more)) {
+            if (!more) continue;
+            const int nf = nx[fc], nb = pv[bc];
+            if (fa - f0 + bb - k0 >= BUF) flush();
+            bool done = nf == bc;
+            const bool bad = nf < 0 || nb < 0 || fa + bb > lim;
+            if (!done) {
+                fc = nf;
+                s_buf[(fa - f0) * kSlots + tid] = nf;
+                if (nf < mn) {
+                    mn = nf;
+                    mpos = fa;
+                }
+                ++fa;
+                done = nb == nf;
+                if (!done) {
+                    bc = nb;
+                    s_buf[(kHeld - 1 - (bb - k0)) * kSlots + tid] = nb;
+                    if (nb < mn) {
+                        mn = nb;
+                        mpos = ~bb;
+                    }
+                    ++bb;
+                }
+            }
+            if (bad) atomicOr(&descs[ONE ? 0 : mesh].ctr->err, kErrCorrupt);
+            closed = done && !bad;
+            more = !done && !bad;
+        }
         // every loop of the wave has closed: the claims of the repair seeds,
         // in flight with one atomic for the wave's pool space (a walker that
         // loses its claim leaves its space unused)
         const MeshDesc &d = descs[ONE ? 0 : mesh];
         const int len = fa + bb, tm = closed ? tri_of(mn) : 0;
-        if (closed && len > BUF && far == kNotTried) go_on_in_pool();   // (it closed in the step that outgrew the buffer)
+        if (closed && len > BUF && far != -1) flush();
         const bool taken = closed && (repair || claim_all) && set_label_bit(d, tm, kCountedBit);
         // whole 16-byte groups, so k_compact reads a loop with vector loads
         const int need = closed && len <= BUF ? (len + 4) & ~3 : 0;
