@@ -91,6 +91,13 @@ constexpr int kStripePad = 32;   // counters 128 bytes apart: one cache line eac
 // mesh) the 3,867 tiles of a 1M-point Delaunay mesh, nearly all with a tip, cost
 // k_relink 20 of 62 us.
 constexpr int kTipStripes = 8;
+// Stripe s of the tip list holds entries [at[s], at[s + 1]): one for each triangle
+// of its tiles (tile % kTipStripes == s), of which each has one tip at most.  (With
+// a whole tile's room for each mesh's last one, 1,000 meshes of 50 triangles and a
+// run over them took 22.5 MB; so they take 18.7.)
+struct TipSpan {
+    int32_t at[kTipStripes + 1];
+};
 constexpr int kUnmarked = 1;   // beside the first stripe's counter: some split polygon's seed was left unmarked
 
 // ---- launch plumbing (host side, defined in mesh_kernels.hip) ------------
@@ -123,7 +130,7 @@ struct RunBuffers {
     int32_t cmp_tiles;       // total compaction tiles
     ListEntry *tips;         // striped: barrier tips
     int32_t *tip_counts;     // kTipStripes counters, kStripePad ints apart
-    int32_t tip_cap;         // per stripe
+    TipSpan tip_span;        // its stripes
     int32_t cap_tips;        // most tips in all
     ListEntry *fixes;        // 2 cap_tips
     uint64_t *status;        // per compaction tile: (loops << 32 | half-edges), then its prefix within its chunk

@@ -255,17 +255,18 @@ __device__ __forceinline__ int striped_index(const int *s_pref, int cap, int g) 
 // The tip list's stripes: how many tips come before each (uniform loads).
 struct TipStripes {
     int first[kTipStripes + 1];
-    __device__ __forceinline__ TipStripes(const int32_t *counts, int cap) {
+    __device__ __forceinline__ TipStripes(const int32_t *counts, const TipSpan &span) {
         first[0] = 0;
 #pragma unroll
-        for (int s = 0; s < kTipStripes; s++) first[s + 1] = first[s] + max(0, min(counts[s * kStripePad], cap));
+        for (int s = 0; s < kTipStripes; s++)
+            first[s + 1] = first[s] + max(0, min(counts[s * kStripePad], span.at[s + 1] - span.at[s]));
     }
     __device__ __forceinline__ int total() const { return first[kTipStripes]; }
     // place in the list of the g-th tip
-    __device__ __forceinline__ int index(int g, int cap) const {
+    __device__ __forceinline__ int index(int g, const TipSpan &span) const {
         int at = g;
 #pragma unroll
-        for (int s = 1; s < kTipStripes; s++) at = g >= first[s] ? s * cap + g - first[s] : at;
+        for (int s = 1; s < kTipStripes; s++) at = g >= first[s] ? span.at[s] + g - first[s] : at;
         return at;
     }
 };
@@ -556,7 +557,7 @@ __host__ __device__ inline size_t relink_lds_bytes(int tile) {
 // (nontemporal) stores.
 template <int ITEMS, bool CM, bool NT>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) k_relink(const MeshDesc *__restrict__ descs, int nmesh,
-                                                  ListEntry *tips, int32_t *tip_counts, int tip_cap,
+                                                  ListEntry *tips, int32_t *tip_counts, const TipSpan tip_span,
                                                   ListEntry *walk, int32_t *walk_counts, int walk_cap,
                                                   uint64_t *agg, int cmp_tb) {
     extern __shared__ int4 lds_raw[];
@@ -789,8 +790,9 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
             cn[j] = w.x;
             if (w.y != kNoSlot) {
                 const int k = s_tbase + (int)w.y, x = (int)(xy[j] & 3u);
-                if (k < tip_cap)
-                    tips[tile % kTipStripes * tip_cap + k] = {mi, h0 + (x == 0 ? 2 : x - 1)};
+                const int first = tip_span.at[tile % kTipStripes];
+                if (k < tip_span.at[tile % kTipStripes + 1] - first)
+                    tips[first + k] = {mi, h0 + (x == 0 ? 2 : x - 1)};
                 else
                     err = true;
             }
@@ -848,9 +850,9 @@ __device__ __forceinline__ int wave_reserve2(int32_t *counter, bool pred) {
 // anchors for k_fixup go to entries 2k and 2k + 1 (half-edge -1: none).
 template <bool ONE>
 __global__ void k_repair(const MeshDesc *__restrict__ descs, const ListEntry *tips, const int32_t *tip_counts,
-                         int tip_cap, int cap_tips, ListEntry *walk, int32_t *walk_counts, int walk_cap,
+                         const TipSpan tip_span, int cap_tips, ListEntry *walk, int32_t *walk_counts, int walk_cap,
                          ListEntry *fixes) {
-    const TipStripes stripes(tip_counts, tip_cap);
+    const TipStripes stripes(tip_counts, tip_span);
     const int all = stripes.total(), ntips = min(all, cap_tips);
     const int lane = __lane_id();
     const int stride = gridDim.x * blockDim.x;
@@ -864,7 +866,7 @@ __global__ void k_repair(const MeshDesc *__restrict__ descs, const ListEntry *ti
         int mesh = 0, a = -1, m = -1, mt = -1;
         bool newmid = false;
         if (ok) {
-            const ListEntry e = tips[stripes.index(k, tip_cap)];
+            const ListEntry e = tips[stripes.index(k, tip_span)];
             mesh = ONE ? 0 : e.mesh;
             const MeshDesc &d = descs[ONE ? 0 : mesh];
             const TwinView twin = twin_view(d);
@@ -1048,15 +1050,15 @@ __device__ __forceinline__ bool mark_split(const MeshDesc &d, int t) {
 // those of the anchors, since both are chains of dependent loads.
 template <bool ONE>
 __global__ void __launch_bounds__(256) k_fixup(const MeshDesc *__restrict__ descs, const ListEntry *tips,
-                                               int32_t *tip_counts, int tip_cap, int cap_tips,
+                                               int32_t *tip_counts, const TipSpan tip_span, int cap_tips,
                                                const ListEntry *fixes) {
-    const TipStripes stripes(tip_counts, tip_cap);
+    const TipStripes stripes(tip_counts, tip_span);
     const int ntips = min(stripes.total(), cap_tips), nfix = 2 * ntips, mark0 = (nfix + kWave - 1) & ~(kWave - 1);
     const int stride = gridDim.x * blockDim.x;
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < mark0 + ntips; q += stride) {
         if (q >= nfix) {
             if (q < mark0) continue;
-            const ListEntry tip = tips[stripes.index(q - mark0, tip_cap)];
+            const ListEntry tip = tips[stripes.index(q - mark0, tip_span)];
             const MeshDesc &d = descs[ONE ? 0 : tip.mesh];
             if (!mark_split(d, tri_of(tip.he))) tip_counts[kUnmarked] = 1;
             continue;
@@ -2669,7 +2671,7 @@ hipError_t launch_export_counts(const MeshCounters *c, int32_t *out, hipStream_t
 template <bool CM, bool NT>
 hipError_t launch_relink_nt(const LaunchCfg &cfg, const RunBuffers &rb, hipStream_t s, size_t lds, int cmp_tb) {
     const dim3 grid(rb.he_tiles), block(cfg.block_relink);
-#define GP_RELINK_ARGS rb.descs, rb.nmesh, rb.tips, rb.tip_counts, rb.tip_cap, rb.walk, rb.walk_counts, rb.walk_cap, \
+#define GP_RELINK_ARGS rb.descs, rb.nmesh, rb.tips, rb.tip_counts, rb.tip_span, rb.walk, rb.walk_counts, rb.walk_cap, \
                        rb.status, cmp_tb
     switch (cfg.items_relink) {
         case 1: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_relink<1, CM, NT>), grid, block, lds, s, GP_RELINK_ARGS); break;
@@ -2797,13 +2799,13 @@ hipError_t launch_pipeline(const LaunchCfg &cfg, const RunBuffers &rb, hipStream
     H(K_RELINK, 1);
 
     H(K_REPAIR, 0);
-    hipLaunchKernelGGL(one ? k_repair<true> : k_repair<false>, dim3(pq), dim3(pt), 0, s, rb.descs, rb.tips, rb.tip_counts, rb.tip_cap, rb.cap_tips,
+    hipLaunchKernelGGL(one ? k_repair<true> : k_repair<false>, dim3(pq), dim3(pt), 0, s, rb.descs, rb.tips, rb.tip_counts, rb.tip_span, rb.cap_tips,
                        rb.walk, rb.walk_counts, rb.walk_cap, rb.fixes);
     H(K_REPAIR, 1);
 
     H(K_FIXUP, 0);
     hipLaunchKernelGGL(one ? k_fixup<true> : k_fixup<false>, dim3(pq), dim3(256), 0, s, rb.descs, rb.tips, rb.tip_counts,
-                       rb.tip_cap, rb.cap_tips, rb.fixes);
+                       rb.tip_span, rb.cap_tips, rb.fixes);
     H(K_FIXUP, 1);
 
     H(K_WALK, 0);

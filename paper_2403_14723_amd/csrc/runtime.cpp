@@ -106,7 +106,7 @@ void debug_hook(void *user, int kernel, int after) {
                 (void)hipMemcpyAsync(h->d->prev_relink[i], x->prev_o, 4 * nh, hipMemcpyDeviceToDevice, s);
             }
         }
-        (void)hipMemcpyAsync(h->d->tips, h->rb->tips, sizeof(gp::ListEntry) * (size_t)h->d->tip_cap * gp::kTipStripes,
+        (void)hipMemcpyAsync(h->d->tips, h->rb->tips, sizeof(gp::ListEntry) * (size_t)h->d->tip_span.at[gp::kTipStripes],
                              hipMemcpyDeviceToDevice, s);
         (void)hipMemcpyAsync(h->d->tip_counts, h->rb->tip_counts, sizeof(int32_t) * gp::kTipStripes * gp::kStripePad,
                              hipMemcpyDeviceToDevice, s);
@@ -247,7 +247,8 @@ namespace {
 // Sizes of one run over meshes of nts[0..n) triangles.  No allocation: the
 // no-allocation entry point plans its single mesh with this directly.
 struct PlanSizes {
-    int64_t tri_tiles = 0, he_tiles = 0, cmp_tiles = 0, cap_tips = 0, tip_cap = 0;
+    int64_t tri_tiles = 0, he_tiles = 0, cmp_tiles = 0, cap_tips = 0;
+    gp::TipSpan tip_span{};
     int64_t walk_cap = 0, emit_cap = 0, wbuf_cap = 0;
     size_t out_bytes = 0, tmp_bytes = 0, tmp_mesh = 0;
 };
@@ -259,7 +260,7 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
     const int64_t th = (int64_t)cfg.block_relink * cfg.items_relink;
     const int64_t tc = (int64_t)cfg.block_compact * cfg.items_compact;
     *p = PlanSizes{};
-    int64_t total_nt = 0;
+    int64_t total_nt = 0, stripe_nt[gp::kTipStripes] = {};   // triangles, in all and of the tip list's stripes
     for (int i = 0; i < n; i++) {
         const int32_t nt = nts[i];
         gp::MeshDesc &d = descs[i];
@@ -270,6 +271,10 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
         d.he_tile0 = (int32_t)p->he_tiles;
         d.cmp_tile0 = (int32_t)p->cmp_tiles;
         p->tri_tiles += gp::tiles_for(nt, tt);
+        const int64_t whole = nt / th, each = whole / gp::kTipStripes;
+        for (int k = 0; k < gp::kTipStripes; k++)   // tile k of the mesh and every eighth after it, then the last one
+            stripe_nt[(p->he_tiles + k) % gp::kTipStripes] += (each + (k < whole % gp::kTipStripes)) * th;
+        stripe_nt[(p->he_tiles + whole) % gp::kTipStripes] += nt % th;
         p->he_tiles += gp::tiles_for(nt, th);
         p->cmp_tiles += gp::tiles_for(nt, tc);
         p->cap_tips += nt / 2 + 2;   // tips are interior vertices: at most T/2 + 1
@@ -283,7 +288,7 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
     // striped lists, sized for the worst case: every triangle of a tile holds
     // a tip, a seed (walk) or a loop minimum (emit); repair seeds spread evenly
     const int64_t S = gp::kStripes;
-    p->tip_cap = (p->he_tiles + gp::kTipStripes - 1) / gp::kTipStripes * th;
+    for (int k = 0; k < gp::kTipStripes; k++) p->tip_span.at[k + 1] = p->tip_span.at[k] + (int32_t)stripe_nt[k];
     p->walk_cap = (p->he_tiles + S - 1) / S * th + (2 * p->cap_tips + S - 1) / S + 2;
     p->emit_cap = (p->cmp_tiles + S - 1) / S * tc;
     // walked loops: a general-position mesh takes about 1.7 ints a triangle
@@ -293,7 +298,7 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
     if (p->walk_cap * S > 0x7fffffff || p->emit_cap * S > 0x7fffffff || p->wbuf_cap * S > 0x7fffffff)
         return GP_ERANGE;
     p->tmp_bytes = p->tmp_mesh + arena_bytes<gp::MeshDesc>(n) +
-                   arena_bytes<gp::MeshCounters>(n) + arena_bytes<gp::ListEntry>(p->tip_cap * gp::kTipStripes) +
+                   arena_bytes<gp::MeshCounters>(n) + arena_bytes<gp::ListEntry>(total_nt) +
                    arena_bytes<gp::ListEntry>(2 * p->cap_tips) + 2 * arena_bytes<uint64_t>(p->cmp_tiles) +
                    arena_bytes<gp::ListEntry>(p->walk_cap * S) + arena_bytes<gp::EmitEntry>(p->emit_cap * S) +
                    arena_bytes<int32_t>(p->wbuf_cap * S + 32) + 3 * arena_bytes<int32_t>(S * gp::kStripePad) +
@@ -334,9 +339,9 @@ void layout_scratch(const PlanSizes &p, const gp::MeshDesc *descs, int n, void *
     rb->he_tiles = (int32_t)p.he_tiles;
     rb->cmp_tiles = (int32_t)p.cmp_tiles;
     rb->ctrs = at.take<gp::MeshCounters>(n);
-    rb->tips = at.take<gp::ListEntry>(p.tip_cap * gp::kTipStripes);
+    rb->tips = at.take<gp::ListEntry>(p.tip_span.at[gp::kTipStripes]);
     rb->tip_counts = at.take<int32_t>(gp::kTipStripes * gp::kStripePad);
-    rb->tip_cap = (int32_t)p.tip_cap;
+    rb->tip_span = p.tip_span;
     rb->cap_tips = (int32_t)p.cap_tips;
     rb->fixes = at.take<gp::ListEntry>(2 * p.cap_tips);
     rb->status = at.take<uint64_t>(p.cmp_tiles);
@@ -1279,9 +1284,9 @@ int gpolylla_result_debug(gp_result *x, gp_result_debug *out) {
     std::vector<gp::ListEntry> part;
     int32_t k = 0;
     for (int s = 0; s < gp::kTipStripes; s++) {
-        part.resize((size_t)std::max(0, std::min(counts[s * gp::kStripePad], d.tip_cap)));
+        part.resize((size_t)std::max(0, std::min(counts[s * gp::kStripePad], d.tip_span.at[s + 1] - d.tip_span.at[s])));
         if (!part.empty())
-            HIP_OK(hipMemcpy(part.data(), d.tips + (size_t)s * d.tip_cap, sizeof(gp::ListEntry) * part.size(),
+            HIP_OK(hipMemcpy(part.data(), d.tips + d.tip_span.at[s], sizeof(gp::ListEntry) * part.size(),
                              hipMemcpyDeviceToHost));
         for (const gp::ListEntry &e : part) {
             if (e.mesh != i) continue;
@@ -1544,7 +1549,7 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
     if (err == GP_OK && c->debug) {
         // the snapshots' memory: per mesh two label arrays and next', prev'
         DebugSnap *d = new (std::nothrow) DebugSnap();
-        const size_t ntips = (size_t)rb.tip_cap * gp::kTipStripes,
+        const size_t ntips = (size_t)rb.tip_span.at[gp::kTipStripes],
                      ncounts = (size_t)gp::kTipStripes * gp::kStripePad;
         size_t bytes = arena_bytes<gp::ListEntry>(ntips) + arena_bytes<int32_t>(ncounts);
         for (int i = 0; i < n; i++)
@@ -1555,7 +1560,7 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
             err = GP_ENOMEM;
         } else {
             Arena ad{static_cast<char *>(d->block), bytes, 0};
-            d->tip_cap = rb.tip_cap;
+            d->tip_span = rb.tip_span;
             d->tips = ad.take<gp::ListEntry>(ntips);
             d->tip_counts = ad.take<int32_t>(ncounts);
             for (int i = 0; i < n; i++) {

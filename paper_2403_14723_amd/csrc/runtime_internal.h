@@ -246,9 +246,9 @@ struct DebugSnap {
     void *block = nullptr;
     std::vector<uint8_t *> tflag_relink, tflag_final;
     std::vector<int32_t *> next_relink, prev_relink;
-    gp::ListEntry *tips = nullptr;    // the striped list: tip_cap entries per stripe
+    gp::ListEntry *tips = nullptr;    // the striped list
     int32_t *tip_counts = nullptr;    // its counters
-    int32_t tip_cap = 0;
+    gp::TipSpan tip_span{};
 };
 
 struct RunState {

@@ -1,0 +1,54 @@
+"""Batches of small meshes through the tiled chain in pools that just hold them:
+the lists of a run take room by triangles, not by tiles."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2403_14723_amd as gp
+from paper_2403_14723_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# (meshes of 50 triangles, one of 7,200 beside them, launch shapes, pool).  The
+# pools: what the runs took when the tip list had an entry per possible tip
+# (half the triangles) and no stripes, 19.27, 7.49 and 7.18 MB.
+CASES = [(1000, False, "small=0", 19_350_000), (300, True, "", 7_530_000),
+         (300, True, "relink=1024x1,compact=64x1,label=64x1", 7_220_000)]
+
+
+@pytest.mark.parametrize("count,large,launch,pool", CASES, ids=["1000", "300", "300_tiles"])
+def test_batch_in_a_capped_pool(count, large, launch, pool):
+    ms = [W.jittered_grid(5, seed=40 + k % 7) for k in range(count)] + ([W.jittered_grid(60, seed=47)] if large else [])
+    os_ = {}
+    print(f"[gpu] scratch: batch of {len(ms)} in {pool} bytes, {launch}", flush=True)
+    with gp.Context(0, pool_bytes=pool) as ctx:
+        if launch:
+            ctx.set_launch(launch)
+        hs = [ctx.build_halfedges(m.xy, m.tri) for m in ms]
+        for m, r in zip(ms, ctx.mesh_batch(hs)):
+            g = r.copy()
+            r.free()
+            if m.name not in os_:
+                os_[m.name] = oracle.polylla(m.xy, m.tri)
+            for key in ("next", "prev", "seeds", "loop_off", "loop_he"):
+                assert np.array_equal(g[key], getattr(os_[m.name], key)), key
+        for h in hs:
+            h.free()
+
+
+def test_tips_of_many_small_meshes():
+    """tips of meshes of every size about a tile, whose stripes end unevenly"""
+    ms = [W.random_delaunay(n, 50 + k) for k, n in enumerate([20, 255, 258, 300, 40, 517, 600, 1100, 30, 25, 260] * 4)]
+    print(f"[gpu] scratch: tips of {len(ms)} meshes", flush=True)
+    with gp.Context(0) as ctx:
+        for launch in ("small=0", "relink=64x1", "relink=512x2"):
+            ctx.set_launch(launch)
+            hs = [ctx.build_halfedges(m.xy, m.tri) for m in ms]
+            for m, r in zip(ms, ctx.mesh_batch(hs)):
+                g, o = r.copy(), oracle.polylla(m.xy, m.tri)
+                r.free()
+                assert g["info"]["ntips"] == o.stats["ntips"]
+                for key in ("next", "prev", "seeds", "loop_off", "loop_he"):
+                    assert np.array_equal(g[key], getattr(o, key)), key
+            for h in hs:
+                h.free()
