@@ -128,11 +128,11 @@ struct RunBuffers {
     int32_t tri_tiles;       // total triangle tiles (label)
     int32_t he_tiles;        // total relink tiles
     int32_t cmp_tiles;       // total compaction tiles
-    ListEntry *tips;         // striped: barrier tips
+    ListEntry *tips;         // striped: barrier tips (where wbuf is, from k_walk on)
     int32_t *tip_counts;     // kTipStripes counters, kStripePad ints apart
     TipSpan tip_span;        // its stripes
     int32_t cap_tips;        // most tips in all
-    ListEntry *fixes;        // 2 cap_tips
+    ListEntry *fixes;        // 2 cap_tips (likewise)
     uint64_t *status;        // per compaction tile: (loops << 32 | half-edges), then its prefix within its chunk
     uint64_t *cpre;          // per compaction tile; at each chunk's first tile: the chunk's prefix
     int32_t max_chunks;      // most chunks (of kScanChunk tiles) in one mesh
@@ -151,8 +151,11 @@ struct RunBuffers {
 };
 
 // k_walk records each chain's half-edges in LDS, up to this many; longer
-// loops are left to k_emit
+// loops go to larger places in the pool
 constexpr int kWalkBuf = 16;
+// Ints that pool space is taken in (the common measure of the larger places), so
+// that a place packs into few bits.
+constexpr int kPoolUnit = 24;
 constexpr long long kStreamOutBytes = 256ll << 20;   // MI355X's last-level cache (Infinity Cache)
 constexpr int kTileScanItems = 4;                   // compaction tiles per k_tile_scan thread
 constexpr int kScanChunk = 1024 * kTileScanItems;   // compaction tiles per k_tile_scan block

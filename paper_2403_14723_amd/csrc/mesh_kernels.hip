@@ -1124,16 +1124,21 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // loops of 17 half-edges took 44 us, now 20.
 constexpr int kWalkBoth = 8;
 // lpos of a loop of kPlMax or more that is stored: the sign bit, its length and
-// its place in the pool in 16-byte groups.  (With the place alone, and the length
-// read from the pool, k_compact took 183 us on the 33.5M grid, not 170.)
-__device__ __forceinline__ bool packs_long(int len, int pos) { return pos >= 0 && pos < 1 << 26 && len - kPlMax < 128; }
+// its place in the pool in units of kPoolUnit.  (With the place alone, and the
+// length read from the pool, k_compact took 183 us on the 33.5M grid, not 170.)
+// Places from 2^24 units on do not pack, and their loops are walked again: some
+// of a run's from 57 million triangles on.
+__device__ __forceinline__ bool packs_long(int len, int pos) {
+    return pos >= 0 && pos < kPoolUnit << 24 && len - kPlMax < 128;
+}
 __device__ __forceinline__ int pack_long(int len, int pos) {
-    return (int)(0x80000000u | (uint32_t)(len - kPlMax) << 24 | (uint32_t)pos >> 2);
+    return (int)(0x80000000u | (uint32_t)(len - kPlMax) << 24 | (uint32_t)pos / kPoolUnit);
 }
 __device__ __forceinline__ int packed_len(int lp) { return ((lp >> 24) & 127) + kPlMax; }
-__device__ __forceinline__ int packed_pos(int lp) { return (lp & 0xffffff) << 2; }
+__device__ __forceinline__ int packed_pos(int lp) { return (lp & 0xffffff) * kPoolUnit; }
 constexpr int kLongHead = 4, kLongMax = 68, kLongWords = kLongHead + kLongMax, kHugeMax = 188, kNotTried = -2;
 static_assert(kHugeMax - kPlMax < 128, "a stored loop's length packs");
+static_assert(kLongWords % kPoolUnit == 0 && (kLongHead + kHugeMax) % kPoolUnit == 0 && kPoolUnit % 4 == 0, "its place packs");
 static_assert(kPlMax - 1 <= kLongMax, "every loop whose code holds its length fits");
 
 // ONE (here and in the other list-driven kernels): a run of one mesh, whose
@@ -1320,7 +1325,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
         const bool taken = closed && (repair || claim_all) && set_label_bit(d, tm, kCountedBit);
         // whole 16-byte groups, so k_compact reads a loop with vector loads
         const int need = closed && len <= BUF ? (len + 4) & ~3 : 0;
-        const int incl = wave_incl_scan(need), wtot = __builtin_amdgcn_readlane(incl, kWave - 1);
+        const int incl = wave_incl_scan(need);
+        const int wtot = (__builtin_amdgcn_readlane(incl, kWave - 1) + kPoolUnit - 1) / kPoolUnit * kPoolUnit;
         int wbase = 0;
         if (lane == 0 && wtot > 0) wbase = atomicAdd(&wbuf_counts[wstripe * kStripePad], wtot);
         wbase = __builtin_amdgcn_readlane(wbase, 0);

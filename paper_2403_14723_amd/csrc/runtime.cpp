@@ -250,7 +250,7 @@ struct PlanSizes {
     int64_t tri_tiles = 0, he_tiles = 0, cmp_tiles = 0, cap_tips = 0;
     gp::TipSpan tip_span{};
     int64_t walk_cap = 0, emit_cap = 0, wbuf_cap = 0;
-    size_t out_bytes = 0, tmp_bytes = 0, tmp_mesh = 0;
+    size_t out_bytes = 0, tmp_bytes = 0, tmp_mesh = 0, pool_bytes = 0;
 };
 
 // Fills the sizes and tile offsets of descs[0..n) (nt, nv, *_tile0) and *p.
@@ -291,17 +291,24 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
     for (int k = 0; k < gp::kTipStripes; k++) p->tip_span.at[k + 1] = p->tip_span.at[k] + (int32_t)stripe_nt[k];
     p->walk_cap = (p->he_tiles + S - 1) / S * th + (2 * p->cap_tips + S - 1) / S + 2;
     p->emit_cap = (p->cmp_tiles + S - 1) / S * tc;
-    // walked loops: a general-position mesh takes about 1.7 ints a triangle
-    // (a stripe that fills up leaves its loops to k_emit); slack for uneven
-    // stripes
-    p->wbuf_cap = align_up((3 * total_nt + S - 1) / S + 2048, 4);
-    if (p->walk_cap * S > 0x7fffffff || p->emit_cap * S > 0x7fffffff || p->wbuf_cap * S > 0x7fffffff)
+    if (p->walk_cap * S > 0x7fffffff || p->emit_cap * S > 0x7fffffff ||
+        4 * total_nt + (S << 12) > 0x7fffffff)
         return GP_ERANGE;
+    // the pool of walked loops, over the tips and their anchors, whose last
+    // readers run before k_walk.  A loop of up to 16 half-edges takes at most 4
+    // ints a triangle (the walkers that reach a loop second take theirs too), a
+    // longer one that is kept at most 5.4; this is 7 where the tips may be many,
+    // so a stripe fills up only where the loops spread unevenly.  (At 3, a mesh of
+    // 60,000 loops of 17 half-edges kept two thirds of them, and short loops lost their
+    // place to long ones.)
+    p->wbuf_cap = (4 * total_nt + 6 * p->cap_tips) / S + 4096 - 32;
+    p->wbuf_cap = std::min<int64_t>(p->wbuf_cap, 0x7fffffff / S) / gp::kPoolUnit * gp::kPoolUnit;
+    p->pool_bytes = std::max(arena_bytes<gp::ListEntry>(total_nt) + arena_bytes<gp::ListEntry>(2 * p->cap_tips),
+                             arena_bytes<int32_t>(p->wbuf_cap * S + 32));
     p->tmp_bytes = p->tmp_mesh + arena_bytes<gp::MeshDesc>(n) +
-                   arena_bytes<gp::MeshCounters>(n) + arena_bytes<gp::ListEntry>(total_nt) +
-                   arena_bytes<gp::ListEntry>(2 * p->cap_tips) + 2 * arena_bytes<uint64_t>(p->cmp_tiles) +
+                   arena_bytes<gp::MeshCounters>(n) + 2 * arena_bytes<uint64_t>(p->cmp_tiles) +
                    arena_bytes<gp::ListEntry>(p->walk_cap * S) + arena_bytes<gp::EmitEntry>(p->emit_cap * S) +
-                   arena_bytes<int32_t>(p->wbuf_cap * S + 32) + 3 * arena_bytes<int32_t>(S * gp::kStripePad) +
+                   arena_bytes<char>(p->pool_bytes) + 3 * arena_bytes<int32_t>(S * gp::kStripePad) +
                    arena_bytes<int32_t>(gp::kTipStripes * gp::kStripePad);
     return GP_OK;
 }
@@ -339,11 +346,9 @@ void layout_scratch(const PlanSizes &p, const gp::MeshDesc *descs, int n, void *
     rb->he_tiles = (int32_t)p.he_tiles;
     rb->cmp_tiles = (int32_t)p.cmp_tiles;
     rb->ctrs = at.take<gp::MeshCounters>(n);
-    rb->tips = at.take<gp::ListEntry>(p.tip_span.at[gp::kTipStripes]);
     rb->tip_counts = at.take<int32_t>(gp::kTipStripes * gp::kStripePad);
     rb->tip_span = p.tip_span;
     rb->cap_tips = (int32_t)p.cap_tips;
-    rb->fixes = at.take<gp::ListEntry>(2 * p.cap_tips);
     rb->status = at.take<uint64_t>(p.cmp_tiles);
     rb->cpre = at.take<uint64_t>(p.cmp_tiles);
     {
@@ -361,7 +366,10 @@ void layout_scratch(const PlanSizes &p, const gp::MeshDesc *descs, int n, void *
     rb->emit = at.take<gp::EmitEntry>(p.emit_cap * S);
     rb->emit_counts = at.take<int32_t>(S * gp::kStripePad);
     rb->emit_cap = (int32_t)p.emit_cap;
-    rb->wbuf = at.take<int32_t>(p.wbuf_cap * S + 32);   // + a 16-byte-group overread at the end
+    char *const pool = at.take<char>(p.pool_bytes);
+    rb->tips = reinterpret_cast<gp::ListEntry *>(pool);
+    rb->fixes = reinterpret_cast<gp::ListEntry *>(pool + arena_bytes<gp::ListEntry>(p.tip_span.at[gp::kTipStripes]));
+    rb->wbuf = reinterpret_cast<int32_t *>(pool);   // 32 ints over: a 16-byte-group overread at the end
     rb->wbuf_counts = at.take<int32_t>(S * gp::kStripePad);
     rb->wbuf_cap = (int32_t)p.wbuf_cap;
     rb->max_nt = 0;
