@@ -200,6 +200,9 @@ hipError_t launch_copy_words(void *dst, const void *src, size_t bytes, hipStream
 // nloop, ntips, nmiddle, nties, 0, 0.
 hipError_t launch_export_counts(const MeshCounters *c, int32_t *out, hipStream_t s);
 
+// The run's tips so far into out (cap_tips entries), their number into *ntips.
+hipError_t launch_gather_tips(const RunBuffers &rb, ListEntry *out, int32_t *ntips, hipStream_t s);
+
 // tiles of one mesh for a given tile size; every mesh has at least one tile
 // so that an empty mesh still gets its loop_off[0] written
 inline int32_t tiles_for(int64_t n, int64_t tile) {

@@ -944,6 +944,21 @@ __global__ void k_repair(const MeshDesc *__restrict__ descs, const ListEntry *ti
     }
 }
 
+// The tip list in one piece (debug runs).
+__global__ void k_gather_tips(const ListEntry *tips, const int32_t *tip_counts, const TipSpan tip_span, int cap,
+                              ListEntry *out, int32_t *ntips) {
+    const TipStripes stripes(tip_counts, tip_span);
+    const int n = min(stripes.total(), cap), first = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int k = first; k < n; k += gridDim.x * blockDim.x) out[k] = tips[stripes.index(k, tip_span)];
+    if (first == 0) *ntips = n;
+}
+
+hipError_t launch_gather_tips(const RunBuffers &rb, ListEntry *out, int32_t *ntips, hipStream_t s) {
+    hipLaunchKernelGGL(k_gather_tips, dim3(64), dim3(256), 0, s, rb.tips, rb.tip_counts, rb.tip_span, rb.cap_tips, out,
+                       ntips);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // k_fixup: recompute next/prev of every frontier half-edge at a vertex
 // ---------------------------------------------------------------------------

@@ -106,10 +106,7 @@ void debug_hook(void *user, int kernel, int after) {
                 (void)hipMemcpyAsync(h->d->prev_relink[i], x->prev_o, 4 * nh, hipMemcpyDeviceToDevice, s);
             }
         }
-        (void)hipMemcpyAsync(h->d->tips, h->rb->tips, sizeof(gp::ListEntry) * (size_t)h->d->tip_span.at[gp::kTipStripes],
-                             hipMemcpyDeviceToDevice, s);
-        (void)hipMemcpyAsync(h->d->tip_counts, h->rb->tip_counts, sizeof(int32_t) * gp::kTipStripes * gp::kStripePad,
-                             hipMemcpyDeviceToDevice, s);
+        (void)gp::launch_gather_tips(*h->rb, h->d->tips, h->d->ntips, s);
     } else if (kernel == gp::K_EMIT) {
         for (int i = 0; i < n; i++) {
             const size_t nt = (size_t)(*h->res)[i]->nt;
@@ -1287,20 +1284,16 @@ int gpolylla_result_debug(gp_result *x, gp_result_debug *out) {
     if (nt && out->tflag_final) HIP_OK(hipMemcpy(out->tflag_final, d.tflag_final[i], nt, hipMemcpyDeviceToHost));
     if (nh && out->next_relink) HIP_OK(hipMemcpy(out->next_relink, d.next_relink[i], 4 * nh, hipMemcpyDeviceToHost));
     if (nh && out->prev_relink) HIP_OK(hipMemcpy(out->prev_relink, d.prev_relink[i], 4 * nh, hipMemcpyDeviceToHost));
-    std::vector<int32_t> counts(gp::kTipStripes * gp::kStripePad);
-    HIP_OK(hipMemcpy(counts.data(), d.tip_counts, sizeof(int32_t) * counts.size(), hipMemcpyDeviceToHost));
-    std::vector<gp::ListEntry> part;
+    int32_t total = 0;
+    HIP_OK(hipMemcpy(&total, d.ntips, sizeof total, hipMemcpyDeviceToHost));
+    total = std::max(0, std::min(total, d.cap_tips));
+    std::vector<gp::ListEntry> all((size_t)total);
+    if (total) HIP_OK(hipMemcpy(all.data(), d.tips, sizeof(gp::ListEntry) * (size_t)total, hipMemcpyDeviceToHost));
     int32_t k = 0;
-    for (int s = 0; s < gp::kTipStripes; s++) {
-        part.resize((size_t)std::max(0, std::min(counts[s * gp::kStripePad], d.tip_span.at[s + 1] - d.tip_span.at[s])));
-        if (!part.empty())
-            HIP_OK(hipMemcpy(part.data(), d.tips + d.tip_span.at[s], sizeof(gp::ListEntry) * part.size(),
-                             hipMemcpyDeviceToHost));
-        for (const gp::ListEntry &e : part) {
-            if (e.mesh != i) continue;
-            if (out->tips && k < out->tips_cap) out->tips[k] = e.he;
-            k++;
-        }
+    for (const gp::ListEntry &e : all) {
+        if (e.mesh != i) continue;
+        if (out->tips && k < out->tips_cap) out->tips[k] = e.he;
+        k++;
     }
     out->ntips = k;
     return st;
@@ -1557,9 +1550,7 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
     if (err == GP_OK && c->debug) {
         // the snapshots' memory: per mesh two label arrays and next', prev'
         DebugSnap *d = new (std::nothrow) DebugSnap();
-        const size_t ntips = (size_t)rb.tip_span.at[gp::kTipStripes],
-                     ncounts = (size_t)gp::kTipStripes * gp::kStripePad;
-        size_t bytes = arena_bytes<gp::ListEntry>(ntips) + arena_bytes<int32_t>(ncounts);
+        size_t bytes = arena_bytes<gp::ListEntry>((size_t)std::max(rb.cap_tips, 1)) + arena_bytes<int32_t>(1);
         for (int i = 0; i < n; i++)
             bytes += 2 * align_up((size_t)std::max(res[i]->nt, 1)) +
                      2 * align_up(sizeof(int32_t) * 3 * (size_t)std::max(res[i]->nt, 1));
@@ -1568,9 +1559,9 @@ int gpolylla_mesh_batch(gp_ctx *c, const gp_mesh *const *meshes, int32_t n, uint
             err = GP_ENOMEM;
         } else {
             Arena ad{static_cast<char *>(d->block), bytes, 0};
-            d->tip_span = rb.tip_span;
-            d->tips = ad.take<gp::ListEntry>(ntips);
-            d->tip_counts = ad.take<int32_t>(ncounts);
+            d->cap_tips = rb.cap_tips;
+            d->tips = ad.take<gp::ListEntry>((size_t)std::max(rb.cap_tips, 1));
+            d->ntips = ad.take<int32_t>(1);
             for (int i = 0; i < n; i++) {
                 const size_t nt = (size_t)std::max(res[i]->nt, 1);
                 d->tflag_relink.push_back(ad.take<uint8_t>(nt));

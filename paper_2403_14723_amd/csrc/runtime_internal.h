@@ -246,9 +246,9 @@ struct DebugSnap {
     void *block = nullptr;
     std::vector<uint8_t *> tflag_relink, tflag_final;
     std::vector<int32_t *> next_relink, prev_relink;
-    gp::ListEntry *tips = nullptr;    // the striped list
-    int32_t *tip_counts = nullptr;    // its counters
-    gp::TipSpan tip_span{};
+    gp::ListEntry *tips = nullptr;    // cap_tips entries
+    int32_t *ntips = nullptr;         // the run's tip count
+    int32_t cap_tips = 0;
 };
 
 struct RunState {

@@ -36,6 +36,21 @@ def test_batch_in_a_capped_pool(count, large, launch, pool):
             h.free()
 
 
+def test_debug_run_in_a_capped_pool():
+    """a debug run over 20,000 triangles takes 4.62 MB with its mesh: a tip
+    snapshot of an entry per possible tip"""
+    m = W.jittered_grid(100, seed=100)
+    print("[gpu] scratch: debug run", flush=True)
+    with gp.Context(0, pool_bytes=4_640_000) as ctx:
+        ctx.set_debug(True)
+        h = ctx.build_halfedges(m.xy, m.tri)
+        r = ctx.mesh(h)
+        o, g, d = oracle.polylla(m.xy, m.tri), r.copy(), r.debug()
+        assert np.array_equal(g["next"], o.next) and len(d["tips"]) == o.stats["ntips"]
+        r.free()
+        h.free()
+
+
 def test_tips_of_many_small_meshes():
     """tips of meshes of every size about a tile, whose stripes end unevenly"""
     ms = [W.random_delaunay(n, 50 + k) for k, n in enumerate([20, 255, 258, 300, 40, 517, 600, 1100, 30, 25, 260] * 4)]
