@@ -726,14 +726,17 @@ inline int grid_for(long long n, int block, int cap = 1 << 16) {
 
 }  // namespace
 
-BuildSizes build_sizes(int64_t nv, int64_t nt) {
+BuildSizes build_sizes(int64_t nv, int64_t nt, bool roomy) {
     BuildSizes z;
     z.parts = (nv + kBuildGroup - 1) / kBuildGroup;
     z.tasks = 3 * nt / kClassSplit + z.parts + 1;
     // 12 bytes a vertex and 24 a triangle are enough for full lists unless
-    // most vertices are in no triangle; lists then are shorter
+    // most vertices are in no triangle.  Lists then are shorter, or, roomy, as
+    // many times longer in all: with 600,000 triangles numbered at random in the
+    // last tenth of the vertices, all groups that have any outgrow the short
+    // lists (a build took 940 us, 366 with the long ones).
     const int64_t bytes = 12 * nv + 24 * nt + 65536 - 8 * z.parts - (int64_t)sizeof(ClassTask) * z.tasks;
-    z.cap = z.parts > 0 ? bytes / (4 * z.parts) : kGroupCap;
+    z.cap = z.parts > 0 && !roomy ? bytes / (4 * z.parts) : kGroupCap;
     if (z.cap > kGroupCap) z.cap = kGroupCap;
     z.list = z.parts * z.cap > 3 * nt ? z.parts * z.cap : 3 * nt;   // large groups' lists: 3 nt at most
     return z;

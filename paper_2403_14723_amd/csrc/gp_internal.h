@@ -249,11 +249,12 @@ struct ClassTask {
 };
 
 // Scratch of a build: vertex groups, triangles a group's list has room for,
-// ints of all lists, classes of large groups.
+// ints of all lists, classes of large groups.  roomy: full lists, whatever memory
+// they take.
 struct BuildSizes {
     int64_t parts, cap, list, tasks;
 };
-BuildSizes build_sizes(int64_t nv, int64_t nt);
+BuildSizes build_sizes(int64_t nv, int64_t nt, bool roomy);
 // Ends of an edge are near below 8,192 or an eighth of the vertices: a grid's
 // rows (up to that wide) are, most edges of a random numbering are not.  Two
 // ends in one group always are.

@@ -397,8 +397,7 @@ constexpr size_t kBuildFlipsAt = 256;
 constexpr size_t kBuildZeroBytes = kBuildFlipsAt + sizeof(int32_t) * gp::kFlipStripes * gp::kFlipPad;
 
 // Device scratch of one build.
-size_t build_scratch_bytes(int64_t nv, int64_t nt, bool inputs_on_device) {
-    const gp::BuildSizes z = gp::build_sizes(nv, nt);
+size_t build_scratch_bytes(const gp::BuildSizes &z, int64_t nt, bool inputs_on_device) {
     return align_up(kBuildZeroBytes + 2 * sizeof(int32_t) * (size_t)z.parts) + arena_bytes<uint32_t>(z.list) +
            arena_bytes<gp::ClassTask>(z.tasks) + (inputs_on_device ? 0 : arena_bytes<int32_t>(3 * nt));
 }
@@ -473,11 +472,15 @@ int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, in
     m->org = static_cast<int32_t *>(p_org);
     if (rc == GP_OK) rc = c->pool.alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(nh, 1), &p_twin);
     m->twin = static_cast<int32_t *>(p_twin);
-    const size_t tmp_bytes = build_scratch_bytes(nv, nt, in_dev);
-    if (rc == GP_OK) rc = c->pool.alloc(tmp_bytes, &j.p_tmp);
+    // full lists where nothing limits the pool, if they can be had
+    gp::BuildSizes z = gp::build_sizes(nv, nt, c->pool.cap == 0 && !c->pool.is_arena());
+    if (rc == GP_OK) rc = c->pool.alloc(build_scratch_bytes(z, nt, in_dev), &j.p_tmp);
+    if (rc == GP_ENOMEM && m->twin) {
+        z = gp::build_sizes(nv, nt, false);
+        rc = c->pool.alloc(build_scratch_bytes(z, nt, in_dev), &j.p_tmp);
+    }
     if (rc != GP_OK) return rc;
-    Arena a{static_cast<char *>(j.p_tmp), tmp_bytes, 0};
-    const gp::BuildSizes z = gp::build_sizes(nv, nt);
+    Arena a{static_cast<char *>(j.p_tmp), build_scratch_bytes(z, nt, in_dev), 0};
     gp::BuildBuffers &b = j.b;
     b.nv = nv;
     b.nt = nt;
@@ -907,7 +910,7 @@ size_t build_footprint(int64_t nv, int64_t nt, bool inputs_on_device) {
     const int64_t nh = 3 * nt;
     const size_t keep = align_up(sizeof(int2) * (size_t)std::max<int64_t>(nv, 1)) +
                         2 * align_up(sizeof(int32_t) * (size_t)std::max<int64_t>(nh, 1));
-    return keep + align_up(build_scratch_bytes(nv, nt, inputs_on_device));
+    return keep + align_up(build_scratch_bytes(gp::build_sizes(nv, nt, false), nt, inputs_on_device));
 }
 
 size_t batch_footprint(const gp::LaunchCfg &cfg, const int32_t *nts, int n) {
