@@ -735,7 +735,8 @@ BuildSizes build_sizes(int64_t nv, int64_t nt, bool roomy) {
     // many times longer in all: with 600,000 triangles numbered at random in the
     // last tenth of the vertices, all groups that have any outgrow the short
     // lists (a build took 940 us, 366 with the long ones).
-    const int64_t bytes = 12 * nv + 24 * nt + 65536 - 8 * z.parts - (int64_t)sizeof(ClassTask) * z.tasks;
+    int64_t bytes = 12 * nv + 24 * nt - 8 * z.parts - (int64_t)sizeof(ClassTask) * z.tasks - 9216;   // (the counters)
+    if (bytes < 65536) bytes = 65536;   // sixteen full lists
     z.cap = z.parts > 0 && !roomy ? bytes / (4 * z.parts) : kGroupCap;
     if (z.cap > kGroupCap) z.cap = kGroupCap;
     z.list = z.parts * z.cap > 3 * nt ? z.parts * z.cap : 3 * nt;   // large groups' lists: 3 nt at most

@@ -36,6 +36,26 @@ def test_batch_in_a_capped_pool(count, large, launch, pool):
             h.free()
 
 
+def test_build_in_a_capped_pool():
+    """a build of a mesh most of whose vertices are in no triangle: its scratch
+    is 12 bytes a vertex and 24 a triangle"""
+    import torch
+    m = W.scrambled(W.random_delaunay(20_000, 3, order="morton"), 4)
+    xy = np.concatenate([np.zeros((10 * m.nv, 2), np.int32), m.xy])
+    tri = (m.tri + 10 * m.nv).astype(np.int32)
+    up = lambda n: (n + 255) // 256 * 256
+    pool = up(8 * len(xy)) + 2 * up(12 * m.nt) + up(12 * len(xy) + 24 * m.nt)
+    print(f"[gpu] scratch: build in {pool} bytes", flush=True)
+    d = torch.from_numpy(xy).cuda(), torch.from_numpy(tri).cuda()
+    torch.cuda.synchronize()
+    o = oracle.polylla(xy, tri)
+    with gp.Context(0, pool_bytes=pool) as ctx:
+        h = ctx.build_halfedges(*d)
+        org, twin, _ = h.copy()
+        h.free()
+    assert np.array_equal(org, o.org) and np.array_equal(twin, o.twin)
+
+
 def test_debug_run_in_a_capped_pool():
     """a debug run over 20,000 triangles takes 4.62 MB with its mesh: a tip
     snapshot of an entry per possible tip"""
