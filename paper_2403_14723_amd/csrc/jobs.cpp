@@ -14,8 +14,10 @@
 //      most two meshed groups hold memory at once).
 // Memory goes back to the context's pool only after the host has seen the
 // downloads that read it complete, so the pool's reuse stays ordered.
+#include <semaphore.h>
+
 #include <algorithm>
-#include <condition_variable>
+#include <chrono>
 #include <cstring>
 #include <deque>
 #include <mutex>
@@ -291,20 +293,30 @@ constexpr int64_t kPackedTriangles = 128 << 10;
 // A helper that the system has not scheduled yet holds nothing up: the
 // caller's thread takes the groups that no helper has.  (Threads and a stream
 // made by each call cost it 250 us, and up to 2 ms when the joins had to wait
-// for threads that had not run.)
+// for threads that had not run.)  Nor does the caller's thread sleep while helpers
+// work: after work that had kept every CPU busy, others of which still spin (a
+// parallel loop's workers), a thread that slept waits 3 to 4 ms for its turn.  So
+// it took 4 to 5 ms for every other such list that it waited for on a condition
+// variable (whose notification, too, may wait for a thread that was notified
+// before and has not run), all groups unpacked within 1.4; a semaphore polled
+// for a while takes 1.5 to 2.4 (3.5 with one thread and one group).
 struct gprt::JobCrew {
     int device = 0;
     hipStream_t second = nullptr;
     hipEvent_t before = nullptr;
     std::vector<std::thread> helpers;
     std::mutex mu;
-    std::condition_variable cv;
+    sem_t work, finished;   // posted for each group started, and for each that a helper has unpacked
     bool quit = false;
     bool alone = false;   // the caller's thread unpacks every group, in order
     gp_job *jobs = nullptr;
     std::deque<SmallGroup> live;   // started groups, oldest first (its elements stay where they are)
     size_t started = 0, taken = 0, done = 0, freed = 0;   // groups so far, in order
 
+    static void wait(sem_t &s) {
+        while (sem_wait(&s) != 0) {
+        }   // (a signal)
+    }
     // Unpacks the oldest group that no thread has taken.
     void unpack_one(std::unique_lock<std::mutex> &lk) {
         SmallGroup &g = live[taken++ - freed];
@@ -313,16 +325,30 @@ struct gprt::JobCrew {
         lk.lock();
         g.unpacked = true;
         while (done < started && live[done - freed].unpacked) done++;
-        cv.notify_all();
     }
     void help() {
         (void)hipSetDevice(device);
-        std::unique_lock<std::mutex> lk(mu);
         while (true) {
-            cv.wait(lk, [&]() { return (taken < started && !alone) || quit; });
+            wait(work);
+            std::unique_lock<std::mutex> lk(mu);
             if (quit) return;
+            if (taken == started || alone) continue;
             unpack_one(lk);
+            lk.unlock();
+            sem_post(&finished);
         }
+    }
+    // Until a helper has unpacked a group, now or since the caller last waited.
+    // The caller's thread stays awake for as long as that takes with helpers
+    // that run (as it does in the runtime's own waits).
+    void wait_finished(std::unique_lock<std::mutex> &lk) {
+        lk.unlock();
+        const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(5);
+        bool got = false;
+        do got = sem_trywait(&finished) == 0;
+        while (!got && std::chrono::steady_clock::now() < until);
+        if (!got) wait(finished);
+        lk.lock();
     }
     void free_done(gp_ctx *c) {
         for (; freed < done; freed++) {
@@ -334,7 +360,7 @@ struct gprt::JobCrew {
     void drain(gp_ctx *c) {
         std::unique_lock<std::mutex> lk(mu);
         while (taken < started) unpack_one(lk);
-        cv.wait(lk, [&]() { return done == started; });
+        while (done < started) wait_finished(lk);
         free_done(c);
     }
     explicit JobCrew(int dev) : device(dev) {
@@ -344,6 +370,8 @@ struct gprt::JobCrew {
             if (second) (void)hipStreamDestroy(second);
             second = nullptr;
         }
+        sem_init(&work, 0, 0);
+        sem_init(&finished, 0, 0);
         helpers.reserve(kHelpers);
         try {
             for (int k = 0; k < kHelpers; k++) helpers.emplace_back([this]() { help(); });
@@ -355,8 +383,10 @@ struct gprt::JobCrew {
             std::lock_guard<std::mutex> lk(mu);
             quit = true;
         }
-        cv.notify_all();
+        for (size_t k = 0; k < helpers.size(); k++) sem_post(&work);
         for (std::thread &t : helpers) t.join();
+        sem_destroy(&work);
+        sem_destroy(&finished);
         if (before) (void)hipEventDestroy(before);
         if (second) (void)hipStreamDestroy(second);
     }
@@ -447,13 +477,13 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
         crew->jobs = jobs;
         crew->live.push_back(std::move(g));
         crew->started++;
-        crew->cv.notify_all();
+        if (!crew->alone) sem_post(&crew->work);
         while (crew->started - crew->done >= kGroupsInFlight) {
             if (crew->taken < crew->started &&
                 (crew->alone || crew->helpers.empty() || crew->started - crew->taken >= kGroupsInFlight - 1))
                 crew->unpack_one(lk);
             else
-                crew->cv.wait(lk);
+                crew->wait_finished(lk);
         }
         crew->free_done(c);
     }
