@@ -312,7 +312,10 @@ typedef struct {
  * launch that builds and meshes each job in a workgroup of its own (the same
  * checks and error codes as gpolylla_build_halfedges), and one download; two
  * threads that the context keeps help to hand out the results; flags are then
- * ignored.
+ * ignored.  Jobs may share output arrays, which are then written in the order of
+ * the jobs (by the calling thread alone).  Where one job's outputs lie over
+ * another's inputs, the inputs of a group and of the next are read before the
+ * group's outputs are written, and a group is 8M triangles unless given.
  * Uses the context's stream and streams of its own (ordered after the work
  * that is queued on the context's); returns when every job's outputs are in host memory.
  * Returns GP_OK when every job succeeded, else the first failed job's status

@@ -283,7 +283,7 @@ void small_group_free(gp_ctx *c, SmallGroup &g) {
 // helpers, 1,360 us with threads and stream kept between calls.  Half the triangles to a group is as fast, twice as many is slower
 // (1,900 us: too few groups to overlap).
 constexpr int kGroupsInFlight = 5, kHelpers = 2;
-constexpr int64_t kPackedTriangles = 128 << 10;
+constexpr int64_t kPackedTriangles = 128 << 10, kLargeGroup = 8 << 20;
 
 }  // namespace
 
@@ -399,38 +399,89 @@ void gprt::job_crew_free(gp_ctx *c) {
 
 namespace {
 
-// Whether no two jobs share an output array (by what each may write).
-bool outputs_apart(const gp_job *jobs, int n) {
+// Arrays that jobs of a list share, by what each job may read or write.
+enum class Shared {
+    nothing,
+    outputs,   // an output array of one and an output array of another, of whatever kind
+    inputs     // an output array of one and an input array of another
+};
+
+Shared shared_arrays(const gp_job *jobs, int n) {
     struct Range {
-        const int32_t *at;
-        size_t ints;
+        uintptr_t at, end;
+        bool operator<(const Range &o) const { return at < o.at; }
     };
-    std::vector<Range> r;
-    const auto apart = [&](auto range) {
-        r.clear();
-        bool sorted = true;
+    constexpr int kKinds = 5;
+    std::vector<Range> kind[kKinds];
+    Range span[kKinds] = {};   // of all ranges of a kind
+    for (int q = 0; q < kKinds; q++) {
+        std::vector<Range> &r = kind[q];
+        r.reserve(n);
         for (int k = 0; k < n; k++) {
-            const Range x = range(jobs[k]);
-            if (!x.at || !x.ints) continue;
-            sorted &= r.empty() || r.back().at < x.at;
-            r.push_back(x);
+            const gp_job &j = jobs[k];
+            const int32_t *const at[kKinds] = {j.next, j.prev, j.loop_he, j.seeds, j.loop_off};
+            const size_t nt = (size_t)j.nt, ints = q < 3 ? 3 * nt : q == 3 ? nt : nt + 1;
+            if (at[q] && ints) r.push_back({(uintptr_t)at[q], (uintptr_t)(at[q] + ints)});
         }
-        if (!sorted) std::sort(r.begin(), r.end(), [](const Range &a, const Range &b) { return a.at < b.at; });
+        if (!std::is_sorted(r.begin(), r.end())) std::sort(r.begin(), r.end());
+        for (const Range &x : r) span[q] = span[q].end ? Range{span[q].at, std::max(span[q].end, x.end)} : x;
+    }
+    const auto meet = [](const Range &a, const Range &b) { return a.at < b.end && b.at < a.end; };
+    const auto overlap = [](const std::vector<Range> &r) {
         for (size_t k = 1; k < r.size(); k++)
-            if (r[k - 1].at + r[k - 1].ints > r[k].at) return false;
-        return true;
+            if (r[k - 1].end > r[k].at) return true;
+        return false;
     };
-    return apart([](const gp_job &j) { return Range{j.next, 3 * (size_t)j.nt}; }) &&
-           apart([](const gp_job &j) { return Range{j.prev, 3 * (size_t)j.nt}; }) &&
-           apart([](const gp_job &j) { return Range{j.seeds, (size_t)j.nt}; }) &&
-           apart([](const gp_job &j) { return Range{j.loop_off, (size_t)j.nt + 1}; }) &&
-           apart([](const gp_job &j) { return Range{j.loop_he, 3 * (size_t)j.nt}; });
+    // every kind by itself; all together only if their spans meet (arrays of the
+    // kinds are often apart, or one array per kind cut up for the jobs)
+    bool outputs = false, mixed = false;
+    for (int q = 0; q < kKinds; q++) {
+        outputs |= overlap(kind[q]);
+        for (int p = 0; p < q; p++) mixed |= meet(span[p], span[q]);
+    }
+    const auto in_a_span = [&](const Range &x) {
+        return std::any_of(span, span + kKinds, [&](const Range &s) { return meet(s, x); });
+    };
+    std::vector<Range> all;
+    const auto merge = [&]() {
+        for (const std::vector<Range> &r : kind) {
+            const size_t m = all.size();
+            all.insert(all.end(), r.begin(), r.end());
+            std::inplace_merge(all.begin(), all.begin() + m, all.end());
+        }
+    };
+    if (!outputs && mixed) {
+        merge();
+        outputs = overlap(all);
+    }
+    for (int k = 0; k < n; k++) {
+        const gp_job &j = jobs[k];
+        for (const Range &x : {Range{(uintptr_t)j.xy, (uintptr_t)(j.xy + 2 * (size_t)j.nv)},
+                               Range{(uintptr_t)j.tri, (uintptr_t)(j.tri + 3 * (size_t)j.nt)}}) {
+            if (x.at == x.end || !in_a_span(x)) continue;
+            if (outputs) return Shared::inputs;   // (as far as is known)
+            if (all.empty()) merge();
+            auto after = std::upper_bound(all.begin(), all.end(), x);
+            if ((after != all.end() && meet(*after, x)) || (after != all.begin() && meet(after[-1], x)))
+                return Shared::inputs;
+        }
+    }
+    return outputs ? Shared::outputs : Shared::nothing;
 }
 
-// Runs a list of small jobs in groups of up to `budget` triangles.  Jobs that
-// share an output array (a caller may want only the last one's) are unpacked
-// in order, by one thread.
-void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
+// Runs a list of small jobs in groups of up to `triangles` triangles (0: as the
+// library sees fit).  Jobs that share output arrays (a caller may want only the
+// last one's) are unpacked in order, by one thread.  Where one job's outputs lie
+// over another's inputs, groups are large and two at most are in flight, so that
+// a job's inputs are read before the outputs of the others of its group and of
+// the group before are written.
+void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t triangles) {
+    int64_t budget = triangles > 0 ? triangles : kPackedTriangles, total = 0;
+    for (int k = 0; k < n && total <= budget; k++) total += jobs[k].nt;
+    Shared shared = Shared::nothing;
+    if (total > budget || n >= 65536) shared = shared_arrays(jobs, n);   // (more than one group)
+    if (shared == Shared::inputs && triangles <= 0) budget = kLargeGroup;
+    const size_t in_flight = shared == Shared::inputs ? 2 : kGroupsInFlight;
     JobCrew *crew = c->crew;
     // Every second group goes to a stream of its own, so that one group's inputs
     // go up while another's outputs come down.  Its blocks may still be in use
@@ -447,9 +498,8 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
         if (k == 0 && j0 < n) {
             if (!crew) crew = c->crew = new (std::nothrow) JobCrew(c->device);
             if (crew) {
-                const bool alone = !outputs_apart(jobs, n);
                 std::lock_guard<std::mutex> lk(crew->mu);
-                crew->alone = alone;
+                crew->alone = shared != Shared::nothing;
             }
             if (crew && crew->second) {
                 if (hipEventRecord(crew->before, c->stream) == hipSuccess &&
@@ -478,9 +528,9 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t budget) {
         crew->live.push_back(std::move(g));
         crew->started++;
         if (!crew->alone) sem_post(&crew->work);
-        while (crew->started - crew->done >= kGroupsInFlight) {
+        while (crew->started - crew->done >= in_flight) {
             if (crew->taken < crew->started &&
-                (crew->alone || crew->helpers.empty() || crew->started - crew->taken >= kGroupsInFlight - 1))
+                (crew->alone || crew->helpers.empty() || crew->started - crew->taken >= in_flight - 1))
                 crew->unpack_one(lk);
             else
                 crew->wait_finished(lk);
@@ -509,10 +559,10 @@ int gpolylla_mesh_jobs(gp_ctx *c, gp_job *jobs, int32_t n, int64_t group_triangl
         jobs[i].status = GP_OK;
     }
     if (n == 0) return GP_OK;
-    const int64_t budget = group_triangles > 0 ? group_triangles : ((int64_t)8 << 20);
+    const int64_t budget = group_triangles > 0 ? group_triangles : kLargeGroup;
     DeviceGuard dg(c->device);
     if (small_jobs_fit(c, jobs, n)) {   // every job builds and meshes in one workgroup
-        small_jobs_run(c, jobs, n, group_triangles > 0 ? group_triangles : kPackedTriangles);
+        small_jobs_run(c, jobs, n, group_triangles);
         int rc_all = GP_OK;
         for (int i = 0; i < n; i++)
             if (jobs[i].status != GP_OK && rc_all == GP_OK) rc_all = jobs[i].status;
