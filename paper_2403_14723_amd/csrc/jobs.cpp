@@ -20,9 +20,9 @@
 #include <chrono>
 #include <cstring>
 #include <deque>
+#include <exception>
 #include <mutex>
 #include <new>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -147,7 +147,12 @@ struct SmallGroup {
 void small_group_start(gp_ctx *c, gp_job *jobs, SmallGroup &g, hipStream_t s) {
     g.stream = s;
     const int n = g.j1 - g.j0;
-    g.lay.assign(n, SmallLayout{});
+    try {
+        g.lay.assign(n, SmallLayout{});
+    } catch (const std::bad_alloc &) {
+        g.rc = GP_ENOMEM;
+        return;
+    }
     size_t in_bytes = 0, out_bytes = 0;
     bool links = false;   // a job asks for next and prev
     int max_nv = 0, max_nt = 0;
@@ -372,11 +377,11 @@ struct gprt::JobCrew {
         }
         sem_init(&work, 0, 0);
         sem_init(&finished, 0, 0);
-        helpers.reserve(kHelpers);
         try {
+            helpers.reserve(kHelpers);
             for (int k = 0; k < kHelpers; k++) helpers.emplace_back([this]() { help(); });
-        } catch (const std::system_error &) {
-        }   // (no thread to be had: the caller's does all)
+        } catch (const std::exception &) {
+        }   // (no thread to be had, or no memory for it: the caller's does all)
     }
     ~JobCrew() {
         {
@@ -479,7 +484,13 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t triangles) {
     int64_t budget = triangles > 0 ? triangles : kPackedTriangles, total = 0;
     for (int k = 0; k < n && total <= budget; k++) total += jobs[k].nt;
     Shared shared = Shared::nothing;
-    if (total > budget || n >= 65536) shared = shared_arrays(jobs, n);   // (more than one group)
+    if (total > budget || n >= 65536) {   // more than one group
+        try {
+            shared = shared_arrays(jobs, n);
+        } catch (const std::bad_alloc &) {
+            shared = Shared::inputs;   // (not known)
+        }
+    }
     if (shared == Shared::inputs && triangles <= 0) budget = kLargeGroup;
     const size_t in_flight = shared == Shared::inputs ? 2 : kGroupsInFlight;
     JobCrew *crew = c->crew;
@@ -525,7 +536,15 @@ void small_jobs_run(gp_ctx *c, gp_job *jobs, int n, int64_t triangles) {
         }
         std::unique_lock<std::mutex> lk(crew->mu);
         crew->jobs = jobs;
-        crew->live.push_back(std::move(g));
+        try {
+            crew->live.push_back(std::move(g));
+        } catch (const std::bad_alloc &) {   // (g is as it was) in its turn, by this thread
+            lk.unlock();
+            crew->drain(c);
+            small_group_unpack(jobs, g);
+            small_group_free(c, g);
+            continue;
+        }
         crew->started++;
         if (!crew->alone) sem_post(&crew->work);
         while (crew->started - crew->done >= in_flight) {
