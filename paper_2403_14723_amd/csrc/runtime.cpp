@@ -832,7 +832,9 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
     };
     // renumbered inputs (GP_RENUMBER): built from their device copies
     std::vector<Renumbered> rn((flags & GP_RENUMBER) ? n : 0);
+    std::vector<char> by_library(rn.size(), 0);   // (its overflow word may still be written by the try before)
     auto renumber_queue = [&](int i, bool library) {
+        by_library[i] = library;
         jobs[i].rc = renumber_input(c, xy[i], nv[i], tri[i], nt[i], (flags & GP_IN_DEVICE) != 0, library,
                                     overflow + i, rn[i]);
         if (jobs[i].rc == GP_OK)
@@ -857,7 +859,7 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
     drain();
     bool again = false;
     for (int i = 0; i < (int)rn.size(); i++) {
-        if (jobs[i].rc != GP_OK || !overflow[i]) continue;
+        if (jobs[i].rc != GP_OK || by_library[i] || !overflow[i]) continue;
         renumber_reset(i);   // (built from arrays that were not written)
         renumber_queue(i, true);
         again = true;

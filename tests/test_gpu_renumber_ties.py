@@ -63,6 +63,43 @@ def test_order(ctx, mesh, name):
     assert np.array_equal(tp, order(c[:, 0], c[:, 1]))
 
 
+def unsampled(n=60_000, samples=2048):
+    """n vertices of which those that the sort samples (sample_place in
+    renumber.hip) lie far apart, a mesh's among them, and all others in one
+    place's neighbourhood: a bucket that no list holds"""
+    m = W.random_delaunay(1500, 27)
+    i = np.arange(samples, dtype=np.uint64)
+    h = (i * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)
+    at = ((i * np.uint64(n) + (h * np.uint64(n) >> np.uint64(32))) // np.uint64(samples)).astype(np.int64)
+    rng = np.random.default_rng(28)
+    q = rng.permutation(300 * 300)[:n]
+    xy = np.stack([q % 300, q // 300], -1).astype(np.int32) + (1 << 29)
+    xy[at] = rng.integers(0, 1 << 30, (samples, 2))
+    xy[at[:m.nv]] = m.xy
+    return xy, at[m.tri].astype(np.int32)
+
+
+def test_overflow():
+    """the library's sort in its place, in pools with room for the lists and
+    without: where there is none at all the error, else the same order"""
+    xy, tri = unsampled()
+    c = xy.astype(np.int64)[tri].sum(axis=1) // 3
+    want, fits = (order(xy[:, 0], xy[:, 1]), order(c[:, 0], c[:, 1])), 0
+    for pool in [0] + [k << 18 for k in range(4, 60, 3)]:
+        with gp.Context(0, pool_bytes=pool) as ctx:
+            print(f"[gpu] renumber overflow: pool {pool}", flush=True)
+            try:
+                h = ctx.build_halfedges(xy, tri, gp.GP_RENUMBER)
+            except gp.GPolyllaError as e:
+                assert e.code == gp.GP_ENOMEM and pool
+                continue
+            tp, vp = h.permutation()
+            h.free()
+            fits += 1
+            assert np.array_equal(vp, want[0]) and np.array_equal(tp, want[1])
+    assert fits > 3
+
+
 def test_triangle_ties(ctx):
     """a unit grid, where neighbours' centroids round to one code, and 5,000
     triangles of their own vertices in one place"""
