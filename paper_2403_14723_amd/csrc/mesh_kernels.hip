@@ -1420,9 +1420,11 @@ __global__ void __launch_bounds__(256) k_emit(const MeshDesc *__restrict__ descs
         const EmitEntry e = emit[striped_index(s_pref, emit_cap, g)];
         if (e.mn >= 0) continue;
         const MeshDesc &d = descs[ONE ? 0 : e.mesh];
-        // (its lanes, all of one wave, read these before any of them writes)
+        // its lanes, all of one wave, read these before any of them writes
         const bool in = e.off >= 0 && e.off < 3 * d.nt - 1;
         const int L = in ? ((gcint)d.loop_he)[e.off] : -1, at = in ? ((gcint)d.loop_he)[e.off + 1] : -1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         const int pos = L < kPlMax ? at : packed_pos(at);
         const bool ok = L > 0 && (long long)e.off + L <= 3ll * d.nt && pos >= 0 &&
                         pos <= kStripes * wbuf_cap - kLongWords;
