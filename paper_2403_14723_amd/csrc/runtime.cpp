@@ -288,9 +288,7 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
     for (int k = 0; k < gp::kTipStripes; k++) p->tip_span.at[k + 1] = p->tip_span.at[k] + (int32_t)stripe_nt[k];
     p->walk_cap = (p->he_tiles + S - 1) / S * th + (2 * p->cap_tips + S - 1) / S + 2;
     p->emit_cap = (p->cmp_tiles + S - 1) / S * tc;
-    if (p->walk_cap * S > 0x7fffffff || p->emit_cap * S > 0x7fffffff ||
-        4 * total_nt + (S << 12) > 0x7fffffff)
-        return GP_ERANGE;
+    if (p->walk_cap * S > 0x7fffffff || p->emit_cap * S > 0x7fffffff) return GP_ERANGE;
     // the pool of walked loops, over the tips and their anchors, whose last
     // readers run before k_walk.  A loop of up to 16 half-edges takes at most 4
     // ints a triangle (the walkers that reach a loop second take theirs too), a
@@ -299,6 +297,7 @@ int plan_core(const gp::LaunchCfg &cfg, const int32_t *nts, const int32_t *nvs, 
     // 60,000 loops of 17 half-edges kept two thirds of them, and short loops lost their
     // place to long ones.)
     p->wbuf_cap = (4 * total_nt + 6 * p->cap_tips) / S + 4096 - 32;
+    // (Places are ints: from 306 million triangles on it is less.)
     p->wbuf_cap = std::min<int64_t>(p->wbuf_cap, 0x7fffffff / S) / gp::kPoolUnit * gp::kPoolUnit;
     p->pool_bytes = std::max(arena_bytes<gp::ListEntry>(total_nt) + arena_bytes<gp::ListEntry>(2 * p->cap_tips),
                              arena_bytes<int32_t>(p->wbuf_cap * S + 32));
