@@ -150,11 +150,12 @@ __device__ __forceinline__ void place_items(WaveGroups &w, int e[kTileItems], in
 // Every wave works alone: it finds the groups of its triangles (three to five
 // in an ordered numbering), takes their places in the groups' lists with one
 // atomic instruction, a lane to a group, and writes the entries, consecutive
-// lanes to consecutive places.  33.5M-triangle grid: 0.325 ms for 1.24 GB
-// (12 bytes a triangle in and out, 8 a vertex in and out, 1.3 entries of 4
-// bytes), 3.8 TB/s of the 4.7 a large copy reaches; 647 vector instructions a
-// wave, which take half of that time.  With a tile's counts in LDS, two
-// barriers and an atomic per workgroup and group it took 0.39 ms and 1,043.
+// lanes to consecutive places.  33.5M-triangle grid: 0.288 ms for 1.43 GB
+// moved (12 bytes a triangle in and out, 8 a vertex in and out, 1.3 entries of
+// 4 bytes), 5.0 TB/s, which is what bounds it: a large copy reaches 4.7.  Its 537
+// vector instructions a wave take 55% of that time.  With a tile's counts in
+// LDS, two barriers and an atomic per workgroup and group it took 0.39 ms and
+// 1,043.
 template <bool WIDE>
 __global__ void __launch_bounds__(256) k_orient(BuildBuffers b, int tiles) {
     const int tid = threadIdx.x, lane = __lane_id();
@@ -343,9 +344,10 @@ __device__ __forceinline__ uint32_t edge_slot(uint32_t own, uint32_t d) {
 }
 
 // One workgroup per group: the triangles of its list, their edges into the
-// table, then each half-edge's twin from its slot.  33.5M-triangle grid: 0.39
+// table, then each half-edge's twin from its slot.  33.5M-triangle grid: 0.37
 // ms for 1.0 GB (the list, 1.2 x 12 bytes a triangle of corners, 12 of twins);
-// bound by its 367 vector instructions a wave (three quarters of the time).
+// bound by its 347 vector instructions a wave, which keep the SIMDs busy for 87%
+// of that time.  The LDS is in use for 51% of it, bank conflicts half of that.
 // The three edges' first tries go out together, without branches: one loop per
 // edge took 0.53 ms, 430 vector and 474 scalar instructions.
 template <bool WIDE>
@@ -494,7 +496,7 @@ __global__ void __launch_bounds__(256) k_part_alloc(BuildBuffers b) {
     const int n = b.count[g], k = (n + kClassSplit - 1) / kClassSplit;
     b.cursor[g] = atomicAdd(b.total, n) + 1;
     const int at = atomicAdd(b.ntasks, k);
-    for (int r = 0; r < k; r++) b.tasks[at + r] = {g, r, k};   // at most build_tasks() in all
+    for (int r = 0; r < k; r++) b.tasks[at + r] = {g, r, k};   // at most BuildSizes::tasks in all
 }
 
 __global__ void __launch_bounds__(256) k_scatter(BuildBuffers b) {

@@ -88,7 +88,7 @@ constexpr int kStripes = 64;
 constexpr int kStripePad = 32;   // counters 128 bytes apart: one cache line each
 // The tip list has fewer: one append per tile with a tip, and its readers take
 // all the counters in uniform loads.  With one counter for all (and another per
-// mesh) the 3,867 tiles of a 1M-point Delaunay mesh, nearly all with a tip, cost
+// mesh) the 3,867 tiles of a Delaunay mesh of 1M points, nearly all with a tip, cost
 // k_relink 20 of 62 us.
 constexpr int kTipStripes = 8;
 // Stripe s of the tip list holds entries [at[s], at[s + 1]): one for each triangle
@@ -233,8 +233,8 @@ struct SmallJob {
     int32_t pad;
 };
 // dynamic LDS of one such workgroup
-size_t small_job_lds_bytes(int max_nv, int max_nt);
-hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nv, int max_nt, hipStream_t s);
+size_t small_job_lds_bytes(int max_nt);
+hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nt, hipStream_t s);
 // one such job; counts may be coherent host memory
 hipError_t launch_small_job_one(const SmallJob &job, hipStream_t s);
 

@@ -113,13 +113,12 @@ void group_finish(Group &g, hipStream_t cs) {
 // overlap (small_jobs_run).
 
 bool small_jobs_fit(const gp_ctx *c, const gp_job *jobs, int n) {
-    int max_nv = 0, max_nt = 0;
+    int max_nt = 0;
     for (int i = 0; i < n; i++) {
         if (jobs[i].nt > gp::kJobSmallTri || jobs[i].nv > gp::kJobSmallV) return false;
-        max_nv = std::max(max_nv, jobs[i].nv);
         max_nt = std::max(max_nt, jobs[i].nt);
     }
-    return c->cfg.small_max >= max_nt && gp::small_job_lds_bytes(max_nv, max_nt) <= (size_t)c->cfg.lds_max;
+    return c->cfg.small_max >= max_nt && gp::small_job_lds_bytes(max_nt) <= (size_t)c->cfg.lds_max;
 }
 
 // Byte offsets of one job's parts: inputs (xy, tri) in the upload block,
@@ -155,7 +154,7 @@ void small_group_start(gp_ctx *c, gp_job *jobs, SmallGroup &g, hipStream_t s) {
     }
     size_t in_bytes = 0, out_bytes = 0;
     bool links = false;   // a job asks for next and prev
-    int max_nv = 0, max_nt = 0;
+    int max_nt = 0;
     for (int k = 0; k < n; k++) {
         const gp_job &jb = jobs[g.j0 + k];
         const size_t nh = 3 * (size_t)jb.nt;
@@ -172,7 +171,6 @@ void small_group_start(gp_ctx *c, gp_job *jobs, SmallGroup &g, hipStream_t s) {
         out_bytes += align_up(4 * (size_t)jb.nt + 8, 16);
         L.loop_he = out_bytes;
         out_bytes += align_up(4 * nh + 4, 16);
-        max_nv = std::max(max_nv, jb.nv);
         max_nt = std::max(max_nt, jb.nt);
         links |= jb.next != nullptr;
     }
@@ -221,7 +219,7 @@ void small_group_start(gp_ctx *c, gp_job *jobs, SmallGroup &g, hipStream_t s) {
         sj.pad = 0;
     }
     if (hipMemcpyAsync(d, g.up, g.up_bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
-        gp::launch_small_jobs(reinterpret_cast<const gp::SmallJob *>(d + desc_off), n, max_nv, max_nt, s) !=
+        gp::launch_small_jobs(reinterpret_cast<const gp::SmallJob *>(d + desc_off), n, max_nt, s) !=
             hipSuccess ||
         hipMemcpyAsync(g.down, d + out_off, g.out_bytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipEventRecord(g.done, s) != hipSuccess) {

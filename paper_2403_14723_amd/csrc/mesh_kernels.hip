@@ -27,7 +27,8 @@
 //               k_walk accumulate (Section 6.7)
 //   k_compact   writes seeds, loop offsets and the loops of up to sixteen
 //               half-edges of every tile from its prefix (Section 6.7)
-//   k_emit      writes the longer loops at the offsets k_compact reserved
+//   k_emit      copies the longer loops that k_walk kept to the offsets that
+//               k_compact reserved, and walks those it did not keep
 //
 // Label byte per triangle (tflag):
 //   bits 0-1  local index of the longest edge
@@ -1032,7 +1033,7 @@ __device__ __forceinline__ bool fix_around(const MeshDesc &d, int o) {
 // dependent load (two where a compact mesh's twin has escaped).  A path may
 // run through every triangle of the mesh, and then takes longer than the walk
 // that the mark saves: past kClimb steps it is given up, and k_walk told so.
-// (The longest path of a 1M-point Delaunay mesh takes 31 steps.  A run over a
+// (The longest path of a Delaunay mesh of 1M points takes 31 steps.  A run over a
 // strip of 200,000 triangles with a tip at its low end: 156 ms with the whole
 // path climbed, 102 so; of 200 triangles, 241 us and 208.)  Returns whether
 // the seed was marked.
@@ -1113,8 +1114,8 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // a long loop of len half-edges takes about len / 2 dependent steps (short
 // loops, the most, read no prev').  A step loads the three links of its triangle
 // and follows the loop until it leaves it, one or two half-edges on (loading one
-// link a step, the kernel took 100 us on the 33.5M grid, this 88; 37 and 35 on
-// the 1M-point Delaunay mesh).  Each chain also writes the half-edges it
+// link a step, the kernel took 100 us on the 33.5M grid, this 91; 37 and 35 on
+// 64 mirrored Delaunay patches of 16,384 points).  Each chain also writes the half-edges it
 // visits to an LDS buffer (forward ones from the front, backward ones from
 // the back), so a loop of at most BUF half-edges is copied to the scratch pool
 // (rotation index of the minimum, then the half-edges in loop order from the
@@ -1123,9 +1124,9 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // there each time it is full, forward half-edges from the front and backward ones
 // from the back (and from there to a larger place), so that k_emit copies a loop
 // of up to kHugeMax half-edges instead of walking it again (its chain of
-// dependent steps took 22 us for the longest loops of the 1M-point Delaunay
-// mesh, 65 half-edges; the copies take 6 to 9, and this kernel 37 instead of
-// 33).  Such chains go on in a loop of their own, one link of either end at a
+// dependent steps took 22 us for the longest loops of those patches, some 65
+// half-edges; the copies take 6, and this kernel 37 instead of 33).  Such
+// chains go on in a loop of their own, one link of either end at a
 // step: few lanes are left then, and a wave's time is the instructions of its
 // steps (one loop of 200 half-edges: 71 us with the steps of the short ones, 46
 // so).
@@ -1134,8 +1135,9 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // bounds the kernel is its device-scope atomics: one per wave for the pool, one
 // per wave and compaction tile for the totals (a wave's loops end in a few
 // tiles), one per repair seed.  With a claim, a total and a mark per loop,
-// settled in the step in which it closed, the 1M-point Delaunay mesh (280,000
-// loops) took 61 us; with an atomic per lane for the larger places, 60,000
+// settled in the step in which it closed, the patches (280,000 loops) took 61
+// us.  One triangulation of 1M points takes 40, its loops being longer (45 with
+// an atomic per lane for the larger places); with an atomic per lane for the larger places, 60,000
 // loops of 17 half-edges took 44 us, now 20.
 constexpr int kWalkBoth = 8;
 // lpos of a loop of kPlMax or more that is stored: the sign bit, its length and
@@ -2441,8 +2443,7 @@ struct JobTable {
     static_assert(kSlots > 3 * TI * kSmallBlock, "every edge finds a slot");
 };
 
-size_t small_job_lds_bytes(int max_nv, int max_nt) {
-    (void)max_nv;
+size_t small_job_lds_bytes(int max_nt) {
     const int slots = max_nt <= kSmallBlock       ? JobTable<1>::kSlots
                       : max_nt <= 2 * kSmallBlock ? JobTable<2>::kSlots
                                                   : JobTable<4>::kSlots;
@@ -2611,7 +2612,7 @@ __global__ void __launch_bounds__(kSmallBlock) k_small_job_one(const SmallJob jo
 
 hipError_t launch_small_job_one(const SmallJob &job, hipStream_t s) {
     const dim3 grid(1), block(kSmallBlock);
-    const size_t lds = small_job_lds_bytes(job.nv, job.nt);
+    const size_t lds = small_job_lds_bytes(job.nt);
     if (job.nt <= kSmallBlock)
         hipLaunchKernelGGL(k_small_job_one<1>, grid, block, lds, s, job);
     else if (job.nt <= 2 * kSmallBlock)
@@ -2621,10 +2622,10 @@ hipError_t launch_small_job_one(const SmallJob &job, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nv, int max_nt, hipStream_t s) {
+hipError_t launch_small_jobs(const SmallJob *jobs, int n, int max_nt, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const dim3 grid(n), block(kSmallBlock);
-    const size_t lds = small_job_lds_bytes(max_nv, max_nt);
+    const size_t lds = small_job_lds_bytes(max_nt);
     if (max_nt <= kSmallBlock)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_small_jobs<1>), grid, block, lds, s, jobs);
     else if (max_nt <= 2 * kSmallBlock)

@@ -18,8 +18,9 @@
 // (block sorts, then merges of pairs of ever longer runs: 38 launches of 4 to
 // 8 us each at these sizes) with separate key and gather passes took 370 us.
 // Larger arrays go to the library, which above a million elements sorts by
-// digits in a fixed number of passes: a sample that cut them into buckets of
-// the size that a workgroup sorts would take longer to rank than it saves.
+// digits in a fixed number of passes.  kSortMax is where 1,024 buckets, the most
+// that k_sort_place keeps, hold a quarter at the mean of the 8,192 elements that a
+// workgroup sorts, and not where the library would be as fast.
 // Whole builds with this sort and with the library's: 140 and 399 us with
 // 594,000 triangles, 331 and 801 us with 1,980,000 (the lists then take 250 MB
 // of scratch; when that cannot be had, the library sorts).
@@ -619,8 +620,6 @@ hipError_t launch_renumber(const RenumberBuffers &b, hipStream_t s) {
         hipLaunchKernelGGL(k_sort_sample, dim3(2 * kMaxSamples / 256), dim3(256), 0, s, b, pv, pt);
         hipLaunchKernelGGL(k_sort_rank, dim3(2 * kMaxSamples / 64), dim3(64 * kRankWaves), 0, s, pv, pt);
         hipLaunchKernelGGL(k_sort_place, dim3(vblocks + tblocks), dim3(kPlaceBlock), 0, s, b, pv, pt, vblocks);
-    }
-    if (pv.n + pt.n > 0) {
         const auto kernel = pv.cap > kBucketCap || pt.cap > kBucketCap ? &k_sort_bucket<true> : &k_sort_bucket<false>;
         hipLaunchKernelGGL(kernel, dim3(pv.buckets + pt.buckets), dim3(kBucketBlock), 0, s, b, pv, pt);
     }

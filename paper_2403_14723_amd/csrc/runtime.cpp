@@ -378,7 +378,7 @@ void layout_scratch(const PlanSizes &p, const gp::MeshDesc *descs, int n, void *
     for (int i = 0; i < n; i++) {
         rb->max_nt = std::max(rb->max_nt, descs[i].nt);
         tflag[i] = at.take<uint8_t>(align_up(descs[i].nt + 4, 4));
-        pl[i] = at.take<uint8_t>(align_up(descs[i].nt + 4, 4));   // whole words: k_walk claims by OR
+        pl[i] = at.take<uint8_t>(align_up(descs[i].nt + 4, 4));
         lpos[i] = at.take<int32_t>(descs[i].nt + 1);
     }
 }
@@ -692,13 +692,12 @@ int build_small_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *
     const bool in_dev = (flags & GP_IN_DEVICE) != 0;
     std::vector<size_t> in_xy(n, 0), in_tri(n, 0);
     size_t in_bytes = 0;
-    int max_nv = 0, max_nt = 0;
+    int max_nt = 0;
     for (int i = 0; i < n; i++) {
         out[i] = nullptr;
         status[i] = GP_OK;
         if (nv[i] < 0 || nt[i] < 0 || (nv[i] > 0 && !xy[i]) || (nt[i] > 0 && !tri[i])) status[i] = GP_EINVAL;
         if (status[i] != GP_OK) continue;
-        max_nv = std::max(max_nv, nv[i]);
         max_nt = std::max(max_nt, nt[i]);
         if (in_dev) continue;
         in_xy[i] = in_bytes;
@@ -762,8 +761,8 @@ int build_small_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *
     if (rc == GP_OK &&
         ((copied && hipMemcpyAsync(d, up, copied, hipMemcpyHostToDevice, s) != hipSuccess) ||
          (n == 1 ? gp::launch_small_job_one(descs[0], s)
-                 : gp::launch_small_jobs(reinterpret_cast<const gp::SmallJob *>(d + desc_off), n, max_nv, max_nt,
-                                         s)) != hipSuccess ||
+                 : gp::launch_small_jobs(reinterpret_cast<const gp::SmallJob *>(d + desc_off), n, max_nt, s)) !=
+              hipSuccess ||
          hipStreamSynchronize(s) != hipSuccess)) {
         (void)hipGetLastError();
         (void)hipStreamSynchronize(s);
@@ -809,13 +808,12 @@ int build_many(gp_ctx *c, int n, const int32_t *const *xy, const int32_t *nv, co
                const int32_t *nt, uint32_t flags, gp_mesh **out, int *status) {
     if (!(flags & GP_RENUMBER) && n > 0 && n < 65536 && c->cfg.small_max > 0) {
         bool small = true;
-        int max_nv = 0, max_nt = 0;
+        int max_nt = 0;
         for (int i = 0; i < n && small; i++) {
             small = nv[i] >= 0 && nt[i] >= 0 && nv[i] <= gp::kJobSmallV && nt[i] <= std::min(gp::kJobSmallTri, c->cfg.small_max);
-            max_nv = std::max(max_nv, nv[i]);
             max_nt = std::max(max_nt, nt[i]);
         }
-        if (small && gp::small_job_lds_bytes(max_nv, max_nt) <= (size_t)c->cfg.lds_max)
+        if (small && gp::small_job_lds_bytes(max_nt) <= (size_t)c->cfg.lds_max)
             return build_small_many(c, n, xy, nv, tri, nt, flags, out, status);
     }
     std::vector<BuildJob> jobs(n);
