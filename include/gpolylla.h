@@ -306,8 +306,9 @@ typedef struct {
  * group_triangles triangles (0: 8M; a larger job is a group of its own) and
  * each group is one batched run (gpolylla_mesh_batch); flags: 0 or GP_GRAPH.
  * A list whose jobs all have at most 4096 triangles and 4096 vertices (and
- * fit the device's LDS per workgroup) runs packed instead, in groups of up to
- * group_triangles triangles (0: 128K), of which up to five are in flight: per
+ * fit the device's LDS per workgroup) runs packed instead: as one group, if it
+ * has at most group_triangles triangles (0: 128K), or in groups of as many, but of
+ * 128K at most, of which up to five are in flight: per
  * group one upload of every job's inputs from a pinned staging block, one
  * launch that builds and meshes each job in a workgroup of its own (the same
  * checks and error codes as gpolylla_build_halfedges), and one download; two
@@ -315,7 +316,8 @@ typedef struct {
  * ignored.  Jobs may share output arrays, which are then written in the order of
  * the jobs (by the calling thread alone).  Where one job's outputs lie over
  * another's inputs, the inputs of a group and of the next are read before the
- * group's outputs are written, and a group is 8M triangles unless given.
+ * group's outputs are written, and a group is of up to group_triangles triangles
+ * (0: 8M).
  * Uses the context's stream and streams of its own (ordered after the work
  * that is queued on the context's); returns when every job's outputs are in host memory.
  * Returns GP_OK when every job succeeded, else the first failed job's status
