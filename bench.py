@@ -627,9 +627,9 @@ def main():
     dom_rec = chain_rec.get(dom.split("<")[0])
     traffic = dom_rec["fetch_bytes"] + dom_rec["write_bytes"] if dom_rec else None
     chain_traffic = None
-    if chain_rec and all(k.split("<")[0] in chain_rec for k in kms):
-        chain_traffic = sum(chain_rec[k.split("<")[0]]["fetch_bytes"] + chain_rec[k.split("<")[0]]["write_bytes"]
-                            for k in kms)
+    ran = [k.split("<")[0] for k, (_, launches) in kms.items() if launches]   # (the one-workgroup form did not)
+    if chain_rec and all(k in chain_rec for k in ran):
+        chain_traffic = sum(chain_rec[k]["fetch_bytes"] + chain_rec[k]["write_bytes"] for k in ran)
 
     batched = served = served_loops = delaunay = transfers = band = pipeline = compact = None
     if not args.no_forms:
