@@ -1115,8 +1115,8 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // loops, the most, read no prev').  A step loads the three links of its triangle
 // and follows the loop until it leaves it, one or two half-edges on (loading one
 // link a step, the kernel took 100 us on the 33.5M grid, this 91; 37 and 35 on
-// 64 mirrored Delaunay patches of 16,384 points).  Each chain also writes the half-edges it
-// visits to an LDS buffer (forward ones from the front, backward ones from
+// 64 mirrored Delaunay patches of 16,384 points).  Each chain also writes the
+// half-edges it visits to an LDS buffer (forward ones from the front, backward ones from
 // the back), so a loop of at most BUF half-edges is copied to the scratch pool
 // (rotation index of the minimum, then the half-edges in loop order from the
 // first backward one) and k_compact places it without walking it again.  A
@@ -1136,9 +1136,9 @@ __device__ __forceinline__ int seek_frontier(const MeshDesc &d, int s) {
 // per wave and compaction tile for the totals (a wave's loops end in a few
 // tiles), one per repair seed.  With a claim, a total and a mark per loop,
 // settled in the step in which it closed, the patches (280,000 loops) took 61
-// us.  One triangulation of 1M points takes 40, its loops being longer (45 with
-// an atomic per lane for the larger places); with an atomic per lane for the larger places, 60,000
-// loops of 17 half-edges took 44 us, now 20.
+// us.  With an atomic per lane for the larger places, one triangulation of 1M
+// points, whose loops are longer, took 46, now 40, and 60,000 loops of 17
+// half-edges 44, now 20.
 constexpr int kWalkBoth = 8;
 // lpos of a loop of kPlMax or more that is stored: the sign bit, its length and
 // its place in the pool in units of kPoolUnit.  (With the place alone, and the
