@@ -245,12 +245,14 @@ def bench_transfers(gp, W, stream, reps=5):
     return out
 
 
-def _pipelined(gp, ctx, meshes, group, loops_only, reps=2):
+def _pipelined(gp, ctx, meshes, group, loops_only, reps=5):
     """Host-to-host rate of gpolylla_mesh_jobs over `meshes` (one job each):
     inputs in pinned host memory (one buffer per distinct mesh), outputs into
     one pinned set of buffers of the largest job's size that every job
     overwrites in turn (the downloads of one call run one after another on one
-    stream).  Best of reps timed calls after an untimed one."""
+    stream).  Best of reps timed calls after an untimed one: the runtime takes a
+    further copy engine when copies of one direction meet, two or three times in a
+    process and in whichever call, and each time holds that call for 6 ms."""
     import torch
     distinct = {id(m): m for m in meshes}
     pin = {k: (torch.from_numpy(m.xy.reshape(-1)).pin_memory(), torch.from_numpy(m.tri.reshape(-1)).pin_memory())
