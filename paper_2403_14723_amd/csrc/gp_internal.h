@@ -249,10 +249,11 @@ struct ClassTask {
 };
 
 // Scratch of a build: vertex groups, triangles a group's list has room for,
-// ints of all lists, classes of large groups.  roomy: full lists, whatever memory
-// they take.
+// ints of all lists, where among them large groups' counters begin, classes of large
+// groups.  roomy: full lists, whatever memory they take.
+constexpr int kPlacePad = 16;
 struct BuildSizes {
-    int64_t parts, cap, list, tasks;
+    int64_t parts, cap, list, places, tasks;
 };
 BuildSizes build_sizes(int64_t nv, int64_t nt, bool roomy);
 // Ends of an edge are near below 8,192 or an eighth of the vertices: a grid's
@@ -277,6 +278,7 @@ struct BuildBuffers {
     int32_t *flips;         // kFlipStripes, kFlipPad apart
     int32_t *count;         // nparts: triangles per group
     int32_t *cursor;        // nparts: not 0 for a large group (then its place in list + 1)
+    int32_t *place;         // nparts, kPlacePad apart: of a large group, the next place in its list
     unsigned long long *err;   // 0, or the highest ~(rank << 8 | -code) seen
     int32_t *nflipped;
     int32_t *nbig;          // large groups, left to launch_build_large

@@ -508,6 +508,7 @@ int build_queue(gp_ctx *c, const int32_t *xy, int32_t nv, const int32_t *tri, in
     b.zero = reinterpret_cast<uint64_t *>(zero);
     b.zero_bytes = zero_bytes;
     b.list = a.take<uint32_t>(z.list);
+    b.place = reinterpret_cast<int32_t *>(b.list + z.places);
     b.tasks = a.take<gp::ClassTask>(z.tasks);
     int32_t *tri_dev = in_dev ? nullptr : a.take<int32_t>(nh);
     b.tri = in_dev ? tri : tri_dev;
